@@ -17,6 +17,7 @@
 // are constants.  With learned sketches (Algorithm 2) the last step goes through the networks
 // instead and can also return the gradient with respect to their parameters.
 #include "psf_internal.h"
+#include "psf_f32.h"
 
 namespace psf {
 namespace {
@@ -1112,6 +1113,37 @@ BwdWs carve_bwd(const Problem &pb, void *ws)
     return w;
 }
 
+// the same steps on the fp32 matrix-core kernels
+template <typename T>
+psf_status bwd_launch_f32(const Problem &pb, const BwdWs &w, const void *Q, const void *K, const void *V,
+                          const void *G, const void *dO, void *dQ, void *dK, void *dV, hipStream_t s, StageTimer *tm)
+{
+    const size_t rows = (size_t)pb.units * pb.n;
+    const F32Plan pl = f32_plan(pb, (size_t)pb.units * pb.t * (size_t)pb.F * (pb.dv + 1), false, true);
+    float *GV = w.GC, *gden = w.GC + rows * pb.dv;
+    psf_status st = general_sketch_pair_f32(pb, Q, K, G, w.MQ, w.MK, s);
+    if (st != PSF_OK) return st;
+    if (tm) tm->mark();                                   // stage: sketches
+    if (pl.states) {
+        st = f32_key_states(pb, pl, w.MK, V, w.Z, s);
+        if (st != PSF_OK) return st;
+    }
+    st = f32_rows_grad(pb, pl, w.MQ, w.MK, Q, K, V, w.Z, dO, GV, gden, s);
+    if (st != PSF_OK) return st;
+    if (tm) tm->mark();                                   // stage: forward rows
+    if (pl.states) {
+        st = f32_mirror_states(pb, pl, w.MQ, GV, gden, w.RB, s);
+        if (st != PSF_OK) return st;
+    }
+    if (tm) tm->mark();                                   // stage: reverse states
+    st = f32_bwd_side(pb, pl, false, w.MQ, w.MK, Q, K, V, GV, gden, w.Z, w.dMQ, w.dQd, nullptr, s);
+    if (st != PSF_OK) return st;
+    if (tm) tm->mark();                                   // stage: query side
+    st = f32_bwd_side(pb, pl, true, w.MQ, w.MK, Q, K, V, GV, gden, w.RB, w.dMK, w.dKd, dV, s);
+    if (tm) tm->mark();                                   // stage: key side
+    return st;
+}
+
 template <typename T>
 psf_status bwd_launch(const Problem &pb, const void *Q, const void *K, const void *V, const void *G,
                       const void *dO, void *dQ, void *dK, void *dV, float *dG, void *ws, hipStream_t s,
@@ -1119,68 +1151,74 @@ psf_status bwd_launch(const Problem &pb, const void *Q, const void *K, const voi
 {
     BwdWs w = carve_bwd(pb, ws);
     const size_t rows = (size_t)pb.units * pb.n;
-    const int kc = pb.dv + 1;
-    const int le = pb.local_exact ? 1 : 0;
-    psf_status st = general_sketch_f32(pb, Q, G, w.MQ, s);
-    if (st != PSF_OK) return st;
-    st = general_sketch_f32(pb, K, G, w.MK, s);
-    if (st != PSF_OK) return st;
-    hipLaunchKernelGGL(bwd_cv_kernel<T>, dim3((unsigned)((rows * kc + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, s, (const T *)V, w.CV, rows, pb.dv);
-    PSF_LAUNCH_CHECK();
-    if (tm) tm->mark();                                   // stage: sketches
+    psf_status st;
+    if (f32_supported(pb)) {
+        st = bwd_launch_f32<T>(pb, w, Q, K, V, G, dO, dQ, dK, dV, s, tm);
+        if (st != PSF_OK) return st;
+    } else {
+        const int kc = pb.dv + 1;
+        const int le = pb.local_exact ? 1 : 0;
+        st = general_sketch_f32(pb, Q, G, w.MQ, s);
+        if (st != PSF_OK) return st;
+        st = general_sketch_f32(pb, K, G, w.MK, s);
+        if (st != PSF_OK) return st;
+        hipLaunchKernelGGL(bwd_cv_kernel<T>, dim3((unsigned)((rows * kc + kThreads - 1) / kThreads)),
+                           dim3(kThreads), 0, s, (const T *)V, w.CV, rows, pb.dv);
+        PSF_LAUNCH_CHECK();
+        if (tm) tm->mark();                                   // stage: sketches
 
-    const dim3 sgrid((unsigned)((pb.F + kStateFeat - 1) / kStateFeat), (unsigned)pb.t, (unsigned)pb.units);
-    const size_t per_block = (size_t)pb.F * kc;
-    const unsigned scan_grid = (unsigned)(((size_t)pb.units * per_block + kThreads - 1) / kThreads);
-    if (pb.t > 1) {
-        hipLaunchKernelGGL(bwd_state_kernel, sgrid, dim3(kThreads), 0, s, w.MK, w.CV, w.Z, pb.n, kc, pb.b,
-                           pb.t, pb.mcols, pb.F);
+        const dim3 sgrid((unsigned)((pb.F + kStateFeat - 1) / kStateFeat), (unsigned)pb.t, (unsigned)pb.units);
+        const size_t per_block = (size_t)pb.F * kc;
+        const unsigned scan_grid = (unsigned)(((size_t)pb.units * per_block + kThreads - 1) / kThreads);
+        if (pb.t > 1) {
+            hipLaunchKernelGGL(bwd_state_kernel, sgrid, dim3(kThreads), 0, s, w.MK, w.CV, w.Z, pb.n, kc, pb.b,
+                               pb.t, pb.mcols, pb.F);
+            PSF_LAUNCH_CHECK();
+            hipLaunchKernelGGL(bwd_scan_kernel, dim3(scan_grid), dim3(kThreads), 0, s, w.Z, pb.units, pb.t,
+                               per_block, 0);
+            PSF_LAUNCH_CHECK();
+        }
+        int RT = kRows;                                       // tokens per workgroup, all in one block
+        while (pb.b % RT != 0) RT /= 2;
+        const dim3 rgrid((unsigned)(pb.n / RT), (unsigned)pb.units);
+        const int wa = pb.local_exact ? pb.d : pb.mcols;
+        const size_t lds_rows = rows_lds(nullptr, pb.d, kc, pb.mcols, wa, nullptr, nullptr, nullptr, nullptr, nullptr);
+        const size_t lds_q = q_lds(nullptr, pb.d, kc, pb.mcols, wa, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+        const size_t lds_k = k_lds(nullptr, pb.d, kc, pb.mcols, wa, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+                                   nullptr);
+        // the largest admitted sizes (d = dv = r = 256) need more than the default dynamic LDS limit
+        PSF_HIP_TRY(hipFuncSetAttribute((const void *)bwd_rows_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)lds_rows));
+        PSF_HIP_TRY(hipFuncSetAttribute((const void *)bwd_q_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)lds_q));
+        PSF_HIP_TRY(hipFuncSetAttribute((const void *)bwd_k_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)lds_k));
+        hipLaunchKernelGGL(bwd_rows_kernel<T>, rgrid, dim3(kThreads), lds_rows, s, w.MQ, w.MK, (const T *)Q,
+                           (const T *)K, w.CV, w.Z, (const T *)dO, w.GC, pb.n, pb.d, pb.dv, pb.p, pb.b, pb.t,
+                           pb.mcols, pb.F, le, RT);
         PSF_LAUNCH_CHECK();
-        hipLaunchKernelGGL(bwd_scan_kernel, dim3(scan_grid), dim3(kThreads), 0, s, w.Z, pb.units, pb.t,
-                           per_block, 0);
+        if (tm) tm->mark();                                   // stage: forward rows
+
+        if (pb.t > 1) {
+            hipLaunchKernelGGL(bwd_state_kernel, sgrid, dim3(kThreads), 0, s, w.MQ, w.GC, w.RB, pb.n, kc, pb.b,
+                               pb.t, pb.mcols, pb.F);
+            PSF_LAUNCH_CHECK();
+            hipLaunchKernelGGL(bwd_scan_kernel, dim3(scan_grid), dim3(kThreads), 0, s, w.RB, pb.units, pb.t,
+                               per_block, 1);
+            PSF_LAUNCH_CHECK();
+        }
+        if (tm) tm->mark();                                   // stage: reverse states
+
+        hipLaunchKernelGGL(bwd_q_kernel<T>, rgrid, dim3(kThreads), lds_q, s, w.MQ, w.MK, (const T *)Q, (const T *)K,
+                           w.CV, w.GC, w.Z, w.dMQ, w.dQd, pb.n, pb.d, pb.dv, pb.p, pb.b, pb.t, pb.mcols, pb.F, le, RT);
         PSF_LAUNCH_CHECK();
+        if (tm) tm->mark();                                   // stage: query side
+        hipLaunchKernelGGL(bwd_k_kernel<T>, rgrid, dim3(kThreads), lds_k, s, w.MQ, w.MK, (const T *)Q, (const T *)K,
+                           w.CV, w.GC, w.RB, w.dMK, w.dKd, (T *)dV, pb.n, pb.d, pb.dv, pb.p, pb.b, pb.t,
+                           pb.mcols, pb.F, le, RT);
+        PSF_LAUNCH_CHECK();
+        if (tm) tm->mark();                                   // stage: key side
     }
-    int RT = kRows;                                       // tokens per workgroup, all in one block
-    while (pb.b % RT != 0) RT /= 2;
-    const dim3 rgrid((unsigned)(pb.n / RT), (unsigned)pb.units);
-    const int wa = pb.local_exact ? pb.d : pb.mcols;
-    const size_t lds_rows = rows_lds(nullptr, pb.d, kc, pb.mcols, wa, nullptr, nullptr, nullptr, nullptr, nullptr);
-    const size_t lds_q = q_lds(nullptr, pb.d, kc, pb.mcols, wa, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
-    const size_t lds_k = k_lds(nullptr, pb.d, kc, pb.mcols, wa, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                               nullptr);
-    // the largest admitted sizes (d = dv = r = 256) need more than the default dynamic LDS limit
-    PSF_HIP_TRY(hipFuncSetAttribute((const void *)bwd_rows_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)lds_rows));
-    PSF_HIP_TRY(hipFuncSetAttribute((const void *)bwd_q_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)lds_q));
-    PSF_HIP_TRY(hipFuncSetAttribute((const void *)bwd_k_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)lds_k));
-    hipLaunchKernelGGL(bwd_rows_kernel<T>, rgrid, dim3(kThreads), lds_rows, s, w.MQ, w.MK, (const T *)Q,
-                       (const T *)K, w.CV, w.Z, (const T *)dO, w.GC, pb.n, pb.d, pb.dv, pb.p, pb.b, pb.t,
-                       pb.mcols, pb.F, le, RT);
-    PSF_LAUNCH_CHECK();
-    if (tm) tm->mark();                                   // stage: forward rows
-
-    if (pb.t > 1) {
-        hipLaunchKernelGGL(bwd_state_kernel, sgrid, dim3(kThreads), 0, s, w.MQ, w.GC, w.RB, pb.n, kc, pb.b,
-                           pb.t, pb.mcols, pb.F);
-        PSF_LAUNCH_CHECK();
-        hipLaunchKernelGGL(bwd_scan_kernel, dim3(scan_grid), dim3(kThreads), 0, s, w.RB, pb.units, pb.t,
-                           per_block, 1);
-        PSF_LAUNCH_CHECK();
-    }
-    if (tm) tm->mark();                                   // stage: reverse states
-
-    hipLaunchKernelGGL(bwd_q_kernel<T>, rgrid, dim3(kThreads), lds_q, s, w.MQ, w.MK, (const T *)Q, (const T *)K,
-                       w.CV, w.GC, w.Z, w.dMQ, w.dQd, pb.n, pb.d, pb.dv, pb.p, pb.b, pb.t, pb.mcols, pb.F, le, RT);
-    PSF_LAUNCH_CHECK();
-    if (tm) tm->mark();                                   // stage: query side
-    hipLaunchKernelGGL(bwd_k_kernel<T>, rgrid, dim3(kThreads), lds_k, s, w.MQ, w.MK, (const T *)Q, (const T *)K,
-                       w.CV, w.GC, w.RB, w.dMK, w.dKd, (T *)dV, pb.n, pb.d, pb.dv, pb.p, pb.b, pb.t,
-                       pb.mcols, pb.F, le, RT);
-    PSF_LAUNCH_CHECK();
-    if (tm) tm->mark();                                   // stage: key side
 
     if (pb.learned) {
         if (dG) {
@@ -1196,6 +1234,11 @@ psf_status bwd_launch(const Problem &pb, const void *Q, const void *K, const voi
         if (tm) tm->mark();                               // stage: sketch gradient
         return PSF_OK;
     }
+    if (f32_sketch_bwd_supported(pb)) {
+        st = f32_sketch_bwd_pair(pb, Q, K, G, w.dMQ, w.dMK, w.dQd, w.dKd, dQ, dK, s);
+        if (tm) tm->mark();                               // stage: sketch gradient
+        return st;
+    }
     const int grid = (int)(rows < 65536 ? rows : 65536);
     hipLaunchKernelGGL(bwd_sketch_kernel<T>, dim3(grid), dim3(kThreads), 0, s, (const T *)Q, (const T *)G,
                        w.dMQ, w.dQd, (T *)dQ, (long long)rows, pb.n, pb.heads, pb.per_head ? 1 : 0, pb.d,
@@ -1210,25 +1253,6 @@ psf_status bwd_launch(const Problem &pb, const void *Q, const void *K, const voi
 }
 
 }  // namespace
-
-// Algorithm 1's reverse alone: dX = direct + J_m(X)^T dM for rows of X (storage type of pb), with
-// dM [rows][mcols] and direct [rows][d] fp32.
-psf_status general_sketch_bwd(const Problem &pb, const void *X, const void *G, const float *dM,
-                              const float *direct, void *dX, hipStream_t s)
-{
-    const size_t rows = (size_t)pb.units * pb.n;
-    const int grid = (int)(rows < 65536 ? rows : 65536);
-    if (pb.bf16)
-        hipLaunchKernelGGL(bwd_sketch_kernel<bf16_t>, dim3(grid), dim3(kThreads), 0, s, (const bf16_t *)X,
-                           (const bf16_t *)G, dM, direct, (bf16_t *)dX, (long long)rows, pb.n, pb.heads,
-                           pb.per_head ? 1 : 0, pb.d, pb.r, pb.p, pb.g_len);
-    else
-        hipLaunchKernelGGL(bwd_sketch_kernel<float>, dim3(grid), dim3(kThreads), 0, s, (const float *)X,
-                           (const float *)G, dM, direct, (float *)dX, (long long)rows, pb.n, pb.heads,
-                           pb.per_head ? 1 : 0, pb.d, pb.r, pb.p, pb.g_len);
-    PSF_LAUNCH_CHECK();
-    return PSF_OK;
-}
 
 bool general_bwd_supported(const Problem &pb)
 {

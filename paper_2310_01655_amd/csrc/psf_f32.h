@@ -1,0 +1,81 @@
+// Host interface of the fp32 matrix-core kernels (psf_f32_fwd.hip, psf_f32_bwd.hip).
+#ifndef PSF_F32_H
+#define PSF_F32_H
+
+#include <initializer_list>
+#include <type_traits>
+#include "psf_internal.h"
+
+namespace psf {
+
+struct F32Shape;
+
+// How a call cuts the sequence: a state per `span` tokens (whole blocks of a causal call).
+struct F32Plan {
+    int span, spans;
+    int pairs, states;       // weights of pairs inside a span taken directly; states across spans
+    int noncausal;
+};
+
+// rows of a staged tile: 64, or 32 where three tiles of 128 columns would leave a CU one workgroup
+constexpr int f32_tile_rows(int dt, int wr) { return dt == 8 && wr == 4 ? 32 : 64; }
+
+bool f32_supported(const Problem &pb);
+// z_floats: room for state records (the caller's workspace); grad: plan for the backward pass
+F32Plan f32_plan(const Problem &pb, size_t z_floats, bool noncausal, bool grad);
+F32Shape f32_shape(const Problem &pb, const F32Plan &pl);
+// 16 rows a workgroup instead of 64: fewer than two workgroups a CU otherwise
+bool f32_split_rows(const Problem &pb);
+
+// m(x) of all rows (X2, M2 may be null); Gaussian sketches only
+psf_status f32_sketch_pair(const Problem &pb, const void *X1, const void *X2, const void *G, float *M1, float *M2,
+                           hipStream_t s);
+psf_status f32_key_states(const Problem &pb, const F32Plan &pl, const float *MK, const void *V, float *Z, hipStream_t s);
+psf_status f32_rows(const Problem &pb, const F32Plan &pl, const float *MQ, const float *MK, const void *Q,
+                    const void *K, const void *V, const float *Z, void *O, hipStream_t s);
+
+// backward pass: G_i as GV [rows][dv] and gden [rows]
+psf_status f32_rows_grad(const Problem &pb, const F32Plan &pl, const float *MQ, const float *MK, const void *Q,
+                         const void *K, const void *V, const float *Z, const void *dO, float *GV, float *gden,
+                         hipStream_t s);
+psf_status f32_mirror_states(const Problem &pb, const F32Plan &pl, const float *MQ, const float *GV, const float *gden,
+                             float *R, hipStream_t s);
+
+// dM, direct gradients of Q or K and dV of a side; then Algorithm 1's reverse
+psf_status f32_bwd_side(const Problem &pb, const F32Plan &pl, bool key_side, const float *MQ, const float *MK,
+                        const void *Q, const void *K, const void *V, const float *GV, const float *gden,
+                        const float *Z, float *dM, float *dX, void *dV, hipStream_t s);
+bool f32_sketch_bwd_supported(const Problem &pb);
+psf_status f32_sketch_bwd_pair(const Problem &pb, const void *X1, const void *X2, const void *G, const float *dM1,
+                               const float *dM2, const float *direct1, const float *direct2, void *dX1, void *dX2,
+                               hipStream_t s);
+
+// rows of `width` columns may be moved four columns at a time
+template <typename T>
+static inline bool pieces_ok(int width, std::initializer_list<const void *> tensors)
+{
+    if (width % 4 != 0) return false;
+    for (const void *p : tensors)
+        if (((uintptr_t)p & (4 * sizeof(T) - 1)) != 0) return false;
+    return true;
+}
+
+static inline int tiles16(int w) { return (w + 15) / 16; }
+
+// calls f with <DT, RT> as integral constants; the sketch tiles of a 128-wide head are 32, 64 or 128 columns
+template <typename F>
+static inline psf_status with_tiles(const Problem &pb, F f)
+{
+    const bool wide = pb.d > 64 || pb.dv > 64 || pb.mcols > 64;
+    if (!wide) {
+        if (pb.mcols <= 16) return f(std::integral_constant<int, 4>{}, std::integral_constant<int, 1>{});
+        if (pb.mcols <= 32) return f(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
+        return f(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+    }
+    if (pb.mcols <= 32) return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{});
+    if (pb.mcols <= 64) return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 4>{});
+    return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 8>{});
+}
+
+}  // namespace psf
+#endif

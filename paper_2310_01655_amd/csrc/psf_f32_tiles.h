@@ -1,0 +1,289 @@
+// Device helpers of the fp32 matrix-core kernels (psf_f32_fwd.hip, psf_f32_bwd.hip).
+//
+// All products of these kernels are v_mfma_f32_16x16x4_f32: fp32 operands, fp32 accumulation.
+// One wave owns 16 rows of the sequence.  With li = lane & 15 and g = lane >> 4 a lane holds
+//   operand A (16 x 4): row li, column g;   operand B (4 x 16): row g, column li;
+//   result (16 x 16):   column li, rows 4 g + 0 .. 3.
+// The sum over k may visit k in any order as long as both operands agree, so step s of a group of
+// four steps takes k = 4 g + s.  A lane then reads the four k of a group as one 16-byte piece, and
+// a result (rows 4 g + s, column li) is the B operand of the next product as it stands.  Every
+// kernel computes its results transposed, with the wave's own rows as columns, so that scores,
+// weights, sketches and gradients of row li stay in the lanes li, li + 16, li + 32, li + 48 and no
+// intermediate goes through LDS.  A row x of w columns held that way ("fragments") is
+// f[4 q + s] = x[16 q + 4 g + s].
+#ifndef PSF_F32_TILES_H
+#define PSF_F32_TILES_H
+
+#include "psf_internal.h"
+
+namespace psf {
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+constexpr int kF32Threads = 256;
+
+__device__ __forceinline__ f4 mm(float a, float b, f4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f4 load4(const float *p) { return *(const f4 *)p; }
+__device__ __forceinline__ f4 load4(const bf16_t *p)
+{
+    const uint2 v = *(const uint2 *)p;
+    return f4{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
+              __uint_as_float(v.y & 0xffff0000u)};
+}
+__device__ __forceinline__ void store4(float *p, f4 v) { *(f4 *)p = v; }
+__device__ __forceinline__ void store4(bf16_t *p, f4 v)
+{
+    *(uint2 *)p = make_uint2((uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16),
+                             (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16));
+}
+
+template <int N>
+__device__ __forceinline__ void clear(f4 (&a)[N])
+{
+#pragma unroll
+    for (int k = 0; k < N; ++k) a[k] = f4{0.f, 0.f, 0.f, 0.f};
+}
+// Waits until the products issued before it can be read by other instructions.  The compiler
+// inserts these waits itself, but it can miss one where a product and its reader lie in different
+// basic blocks with a longer and a shorter way between them (seen: the last result of a state
+// piece read three instructions after its product); so results that leave a branch or a loop
+// are read after this.
+__device__ __forceinline__ void settle()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int N>
+__device__ __forceinline__ void add_to(f4 (&a)[N], const f4 (&x)[N])
+{
+    settle();
+#pragma unroll
+    for (int k = 0; k < N; ++k) a[k] += x[k];
+}
+
+// Columns c .. c + 3 of a row of `width` columns, zero beyond it.  vec: four columns may be moved
+// as one piece (width a multiple of 4 and the tensor's base aligned to the piece).
+template <typename S>
+__device__ __forceinline__ f4 row_piece(const S *row, int c, int width, int vec)
+{
+    f4 v = {0.f, 0.f, 0.f, 0.f};
+    if (vec) {
+        if (c < width) v = load4(row + c);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (c + k < width) v[k] = load_f(row, c + k);
+    }
+    return v;
+}
+
+template <typename S>
+__device__ __forceinline__ void store_piece(S *row, int c, int width, int vec, f4 v)
+{
+    if (vec) {
+        if (c < width) store4(row + c, v);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (c + k < width) store_f(row, c + k, v[k]);
+    }
+}
+
+// fragments of one row (see above); zeros when the row is not there
+template <int NT, typename S>
+__device__ __forceinline__ void load_frags(const S *row, int width, bool there, int vec, int g, float (&f)[4 * NT])
+{
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+        f4 v = {0.f, 0.f, 0.f, 0.f};
+        if (there) v = row_piece(row, 16 * q + 4 * g, width, vec);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) f[4 * q + s] = v[s];
+    }
+}
+
+// LDS rows are padded by four floats: the 16-byte reads of 8 consecutive rows fall into different
+// banks, and so do the 4-byte reads of 16 columns of rows 0, 4, 8, 12.
+template <int NT>
+constexpr int pitch_of() { return 16 * NT + 4; }
+
+// NR rows of 16 * NT columns into LDS; rows >= nvalid and columns >= width are zero.
+template <int NT, int NR, typename S>
+__device__ __forceinline__ void stage_tile(const S *src, size_t ld, int nvalid, int width, int vec, float *dst)
+{
+#pragma unroll
+    for (int it = 0; it < (NR * 4 * NT + kF32Threads - 1) / kF32Threads; ++it) {
+        const int idx = it * kF32Threads + threadIdx.x;
+        if (NR * 4 * NT % kF32Threads != 0 && idx >= NR * 4 * NT) break;
+        const int row = idx / (4 * NT), c = 4 * (idx % (4 * NT));
+        f4 v = {0.f, 0.f, 0.f, 0.f};
+        if (row < nvalid) v = row_piece(src + (size_t)row * ld, c, width, vec);
+        *(f4 *)&dst[row * pitch_of<NT>() + c] = v;
+    }
+}
+
+// acc^T += (rows of the LDS tile)^T w for one group of 16 tile rows: acc[ct] has rows
+// 16 ct + 4 g + s, column li; w[s] belongs to tile row row0 + 4 g + s.
+// GUARD: some of the 16 weights of a lane may be masked zeros whose tile row this lane's own row
+// must not see.  0 * inf would carry a later token's inf or NaN to an earlier row, so a group
+// that holds one is summed without the masked pairs; seen: bit k set when tile row row0 + k
+// counts for this lane's own row.
+template <int NT, bool GUARD>
+__device__ __forceinline__ void add_rows(const float *tile, int row0, const float (&w)[4], f4 (&acc)[NT], int lane,
+                                         unsigned seen)
+{
+    const int li = lane & 15, g = lane >> 4;
+    constexpr int P = pitch_of<NT>();
+    const float *at = tile + (row0 + 4 * g) * P + li;
+    if (GUARD) {
+        float probe = 0.f;
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int ct = 0; ct < NT; ++ct) probe = __builtin_fmaf(at[s * P + 16 * ct], 0.f, probe);
+        if (__any(probe != 0.f)) {
+            for (int k4 = 0; k4 < 4; ++k4) {
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const float wk = __shfl(w[s], li + 16 * k4);
+                    if ((seen >> (4 * k4 + s)) & 1u) {
+#pragma unroll
+                        for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+                            for (int k = 0; k < 4; ++k)
+                                acc[ct][k] += wk * tile[(row0 + 4 * k4 + s) * P + 16 * ct + 4 * g + k];
+                    }
+                }
+            }
+            return;
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) acc[ct] = mm(at[s * P + 16 * ct], w[s], acc[ct]);
+}
+
+// scores of 16 tile rows with the wave's own rows: result rows row0 + 4 g + s, column li
+template <int NT>
+__device__ __forceinline__ f4 score_rows(const float *tile, int row0, const float (&own)[4 * NT], int lane)
+{
+    const float *at = tile + (row0 + (lane & 15)) * pitch_of<NT>() + 4 * (lane >> 4);
+    f4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+        const f4 a = *(const f4 *)(at + 16 * q);
+        s0 = mm(a[0], own[4 * q], s0);
+        s1 = mm(a[1], own[4 * q + 1], s1);
+        s0 = mm(a[2], own[4 * q + 2], s0);
+        s1 = mm(a[3], own[4 * q + 3], s1);
+    }
+    return s0 + s1;
+}
+
+__device__ __forceinline__ float over_groups(float x)       // sum over the four lanes of a row
+{
+    x += __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
+}
+
+// x^p and x^(p-1) for p a power of two
+__device__ __forceinline__ void powers(float x, int p, float &pw, float &pm1)
+{
+    pw = x;
+    pm1 = 1.f;
+    for (int e = 1; e < p; e <<= 1) { pm1 *= pw; pw *= pw; }
+}
+
+// ---- projections of Algorithm 1 -----------------------------------------------------------
+// A wave takes 16 H rows.  The row vectors live in LDS, [rows][columns + 4], columns padded to 16
+// with zeros; result^T = G^T x^T for 16 columns from c0: A = G[e][c] from memory (lane row c,
+// k = e; the matrices stay in the caches), each value serving the H groups of 16 rows, B = x
+// from LDS in 16-byte pieces.
+template <int H, typename T>
+__device__ __forceinline__ void project(const T *G, int in, int r, int c0, const float *x, int pitch, f4 (&out)[H],
+                                        int lane)
+{
+    const int li = lane & 15, g = lane >> 4, c = c0 + li;
+    const float *xr = x + li * pitch + 4 * g;
+    const T *ga = G + (size_t)(4 * g) * r + (c < r ? c : 0);
+    f4 odd[H];                                              // two chains a result: shorter sums
+    clear(out);
+    clear(odd);
+    int e0 = 0;
+    if (c0 + 16 <= r)
+        for (; e0 + 32 <= in; e0 += 32)
+#pragma unroll
+            for (int e = 0; e < 32; e += 16) {
+                f4 xv[H];
+#pragma unroll
+                for (int h = 0; h < H; ++h) xv[h] = *(const f4 *)(xr + 16 * h * pitch + e0 + e);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const float a = load_f(ga, (size_t)(e0 + e + s) * r);
+#pragma unroll
+                    for (int h = 0; h < H; ++h) {
+                        if (e) odd[h] = mm(a, xv[h][s], odd[h]);
+                        else out[h] = mm(a, xv[h][s], out[h]);
+                    }
+                }
+            }
+    for (; e0 < in; e0 += 16) {
+        f4 xv[H];
+#pragma unroll
+        for (int h = 0; h < H; ++h) xv[h] = *(const f4 *)(xr + 16 * h * pitch + e0);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const float a = c < r && e0 + 4 * g + s < in ? load_f(ga, (size_t)(e0 + s) * r) : 0.f;
+#pragma unroll
+            for (int h = 0; h < H; ++h) out[h] = mm(a, xv[h][s], out[h]);
+        }
+    }
+    add_to(out, odd);
+}
+
+// the transposed product: acc^T (16 rows e from e0) += G y^T for y [rows][pitch] of r columns
+template <int H, typename T>
+__device__ __forceinline__ void back_project(const T *G, int in, int r, int e0, const float *y, int pitch, int vec,
+                                             f4 (&acc)[H], int lane)
+{
+    const int li = lane & 15, g = lane >> 4, e = e0 + li;
+    const T *ga = G + (size_t)(e < in ? e : 0) * r;
+    const float *yr = y + li * pitch + 4 * g;
+    for (int c0 = 0; c0 < r; c0 += 16) {
+        f4 a = {0.f, 0.f, 0.f, 0.f};
+        if (e < in) a = row_piece(ga, c0 + 4 * g, r, vec);
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            const f4 yv = *(const f4 *)(yr + 16 * h * pitch + c0);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) acc[h] = mm(a[s], yv[s], acc[h]);
+        }
+    }
+    settle();
+}
+
+// ---- states -----------------------------------------------------------------------------
+// phi' = m (x) m is symmetric in its two indices: only tiles of 16 x 16 index pairs (a, b') with
+// b' tile >= a tile are formed.  A state record is, for the RT (RT + 1) / 2 tile pairs in the
+// order (0,0) (0,1) .. (1,1) .., [a16][b16][16 VT columns] and then, for the same pairs,
+// [a16][b16] of the denominator column.  Tiles off the diagonal are stored doubled, for their mirror.
+__host__ __device__ constexpr int tile_pairs(int rt) { return rt * (rt + 1) / 2; }
+__host__ __device__ constexpr size_t record_floats(int rt, int vt) { return (size_t)tile_pairs(rt) * 256 * (16 * vt + 1); }
+
+// Everything the kernels need to know about the shape and how the sequence is cut.
+struct F32Shape {
+    int n, d, dv, mcols, p, b, heads;
+    int span, spans;          // tokens between two states; number of such spans
+    int local_exact, noncausal, pairs, states;
+    int vec_x, vec_v, vec_m, vec_g;   // 4-column pieces of Q, K (d), V, O (dv), m (mcols), G (r)
+};
+
+}  // namespace psf
+#endif

@@ -4,6 +4,7 @@
 // (arXiv 2310.01655, Sections 3.1 and 3.2) step by step; the tuned bf16 MFMA kernels for
 // the large shapes live in psf_mfma.hip.
 #include "psf_internal.h"
+#include "psf_f32.h"
 
 namespace psf {
 namespace {
@@ -418,12 +419,36 @@ psf_status sketch_launch(const Problem &pb, const void *X, const void *G, float 
     return PSF_OK;
 }
 
+// m(Q) and m(K): matrix cores for the Gaussian sketches they cover, the vector kernels otherwise
+template <typename T>
+psf_status sketches_f32(const Problem &pb, const void *X, const void *X2, const void *G, float *M, float *M2,
+                        hipStream_t s)
+{
+    if (f32_supported(pb) && !pb.learned) return f32_sketch_pair(pb, X, X2, G, M, M2, s);
+    return sketch_launch<T>(pb, X, G, M, nullptr, nullptr, s, X2, M2);
+}
+
 template <typename T>
 psf_status attn_launch(const Problem &pb, const void *Q, const void *K, const void *V, const void *G,
                        void *O, void *ws, hipStream_t s, StageTimer *tm, bool noncausal)
 {
     GeneralWs w = carve(pb, ws);
     psf_status st;
+    if (f32_supported(pb)) {
+        const size_t z_floats = (size_t)pb.units * pb.t * (size_t)pb.F * (pb.dv + 1);
+        const F32Plan pl = f32_plan(pb, z_floats, noncausal, false);
+        st = sketches_f32<T>(pb, Q, K, G, w.MQ, w.MK, s);
+        if (st != PSF_OK) return st;
+        if (tm) { tm->mark(); tm->mark(); }             // one launch for both
+        if (pl.states) {
+            st = f32_key_states(pb, pl, w.MK, V, w.Z, s);
+            if (st != PSF_OK) return st;
+        }
+        if (tm) { tm->mark(); tm->mark(); }             // states and their scan
+        st = f32_rows(pb, pl, w.MQ, w.MK, Q, K, V, w.Z, O, s);
+        if (tm) tm->mark();
+        return st;
+    }
     if (!pb.exact_feat) {
         st = sketch_launch<T>(pb, Q, G, w.MQ, nullptr, nullptr, s);
         if (st != PSF_OK) return st;
@@ -483,15 +508,14 @@ psf_status general_sketch(const Problem &pb, const void *X, const void *G, void 
 
 psf_status general_sketch_f32(const Problem &pb, const void *X, const void *G, float *M_f32, hipStream_t s)
 {
-    return pb.bf16 ? sketch_launch<bf16_t>(pb, X, G, M_f32, nullptr, nullptr, s)
-                   : sketch_launch<float>(pb, X, G, M_f32, nullptr, nullptr, s);
+    return general_sketch_pair_f32(pb, X, nullptr, G, M_f32, nullptr, s);
 }
 
 psf_status general_sketch_pair_f32(const Problem &pb, const void *X, const void *X2, const void *G, float *M_f32,
                                    float *M2_f32, hipStream_t s)
 {
-    return pb.bf16 ? sketch_launch<bf16_t>(pb, X, G, M_f32, nullptr, nullptr, s, X2, M2_f32)
-                   : sketch_launch<float>(pb, X, G, M_f32, nullptr, nullptr, s, X2, M2_f32);
+    return pb.bf16 ? sketches_f32<bf16_t>(pb, X, X2, G, M_f32, M2_f32, s)
+                   : sketches_f32<float>(pb, X, X2, G, M_f32, M2_f32, s);
 }
 
 psf_status general_attn(const Problem &pb, const void *Q, const void *K, const void *V, const void *G,

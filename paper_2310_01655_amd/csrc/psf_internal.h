@@ -61,9 +61,6 @@ psf_status general_attn_bwd(const Problem &pb, const void *Q, const void *K, con
                             const void *G, const void *dO, void *dQ, void *dK, void *dV, void *ws,
                             hipStream_t s, StageTimer *tm, float *dG = nullptr);
 
-psf_status general_sketch_bwd(const Problem &pb, const void *X, const void *G, const float *dM,
-                              const float *direct, void *dX, hipStream_t s);
-
 // Backward pass on MFMA (bf16, d = dv in {64, 128}, p in {4, 8}, r in {32, 64}, b % 256 == 0, exact
 // in-block weights; for d = 64 and p = 4 also Section 3.1's in-block rule (r = 64) and learned sketches).
 bool mfma_bwd_supported(const Problem &pb);

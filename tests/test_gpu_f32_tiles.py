@@ -1,0 +1,72 @@
+"""The fp32 matrix-core kernels of the general path at the edges of their tiles: sketch and head
+widths around multiples of 16 and 64, blocks around 16 and 64 tokens, last tiles with one row,
+spans with and without states, either split of the rows.  Against the float64 oracle with the
+bounds of parity.py (1e-4 for fp32 storage; sums of non-negative fp32 terms err by about 1e-6)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2310_01655_amd import binding as psf
+from paper_2310_01655_amd import inputs
+from parity import as_f64, assert_close, assert_close_scaled, gpu_attn, oracle_attn
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # batch, heads, n, d, dv, p, r, b, dtype, local
+    (1, 2, 2046, 64, 64, 4, 16, 66, "f32", psf.LOCAL_EXACT),       # many spans, 16 rows a workgroup
+    (2, 3, 1040, 64, 64, 4, 17, 65, "f32", psf.LOCAL_EXACT),       # a sketch tile with one column
+    (1, 1, 2400, 60, 62, 4, 33, 48, "bf16", psf.LOCAL_EXACT),      # widths that four does not divide
+    (1, 2, 2040, 65, 64, 4, 16, 120, "f32", psf.LOCAL_EXACT),      # wide tiles, one column over
+    (1, 1, 1530, 128, 128, 8, 32, 255, "f32", psf.LOCAL_SKETCH),
+    (1, 1, 2600, 100, 128, 2, 100, 100, "f32", psf.LOCAL_EXACT),     # m(x) = x, 100 columns
+    (1, 1, 390, 128, 128, 16, 128, 130, "bf16", psf.LOCAL_EXACT),  # largest sizes, three levels
+    (40, 14, 66, 16, 8, 4, 8, 33, "f32", psf.LOCAL_EXACT),         # 64 rows a workgroup, tiny sequences
+    (16, 34, 65, 128, 16, 4, 16, 65, "bf16", psf.LOCAL_EXACT),
+    (1, 1, 1, 64, 64, 4, 32, 1, "f32", psf.LOCAL_EXACT),
+    (1, 2, 1300, 64, 64, 4, 32, 13, "f32", psf.LOCAL_SKETCH),
+]
+
+
+def case_inputs(batch, heads, n, d, dv, p, r, b, dtype):
+    q, k, v = inputs.make_qkv(batch, heads, n, d, dv=dv, seed=7, dtype=dtype)
+    G = inputs.make_sketch_matrices(heads, d, r, p, per_head=True, seed=3, dtype=dtype) if p > 2 else None
+    return q, k, v, G
+
+
+@pytest.mark.parametrize("batch,heads,n,d,dv,p,r,b,dtype,local", CASES)
+def test_forward_and_backward_at_tile_edges(batch, heads, n, d, dv, p, r, b, dtype, local):
+    q, k, v, G = case_inputs(batch, heads, n, d, dv, p, r, b, dtype)
+    dO = inputs.make_dout(batch, heads, n, dv, seed=7, dtype=dtype)
+    desc = psf.make_desc(batch, heads, n, d, p, r, b, dtype, dv=dv, local=local, per_head=True)
+    assert psf.kernel_path(desc) == 0
+    args = [x.cuda() if x is not None else None for x in (q, k, v, G)]
+    O = psf.psf_causal_attn_fwd(desc, *args)
+    N = psf.psf_noncausal_attn_fwd(desc, *args)
+    grads = psf.psf_causal_attn_bwd(desc, *args, dO.cuda())
+    ol = oracle.LOCAL_EXACT if local == psf.LOCAL_EXACT else oracle.LOCAL_SKETCH
+    f = [as_f64(x) if x is not None else None for x in (q, k, v, G)]
+    want, _ = oracle.attn_def_batch(*f, p, r, b, local=ol)
+    assert_close(O.float().cpu().numpy(), want, dtype, "forward")
+    last = heads - 1
+    want = oracle.attn_noncausal(f[0][0, last], f[1][0, last], f[2][0, last],
+                                 f[3][last] if G is not None else None, p, r)
+    want = want[0] if isinstance(want, tuple) else want
+    assert_close(N[0, last].float().cpu().numpy(), want, dtype, "noncausal")
+    wants = oracle.attn_bwd_batch(*f, as_f64(dO), p, r, b, local=ol)
+    for name, got, w in zip(("dQ", "dK", "dV"), grads, wants):
+        assert_close_scaled(got.float().cpu().numpy(), w, dtype, name)
+
+
+@pytest.mark.parametrize("n,at", [(96, 37), (1300, 901)])
+def test_a_later_infinity_does_not_reach_earlier_rows(n, at):
+    cfg = dict(batch=1, heads=2, n=n, d=64, p=4, r=32, b=n // 4, dtype="f32", per_head=True)
+    q, k, v, G = case_inputs(1, 2, n, 64, 64, 4, 32, n // 4, "f32")
+    want, _ = gpu_attn(cfg, q, k, v, G)
+    v[:, :, at, 5] = float("inf")
+    v[:, :, at, 6] = float("nan")
+    got, _ = gpu_attn(cfg, q, k, v, G)
+    assert torch.isfinite(got[:, :, :at]).all()
+    torch.testing.assert_close(got[:, :, :at], want[:, :, :at], rtol=1e-5, atol=1e-6)   # fp32 sums in another order
+    assert not torch.isfinite(got[:, :, at:, 5:7]).any()
