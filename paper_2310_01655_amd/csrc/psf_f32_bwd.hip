@@ -58,15 +58,31 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? 2 : 1) void f32_bwd_kernel(
         const size_t row = urow + x0;
         const bool exact_g = KSIDE ? x0 < edge_g_last : x0 + KT > edge_g;
         const bool cross_g = KSIDE ? x0 + KT > edge_g : x0 < edge_g_last;
+        Tile<DT, KT, T> xt;
+        Tile<RT, KT, float> mt;
+        typedef std::conditional_t<KSIDE, float, T> C;
+        Tile<VT, KT, C> ct;
+        const T *xp = Xstr + row * sh.d;
+        const float *mp = Mstr + row * sh.mcols;
+        const C *cp;
+        if constexpr (KSIDE) cp = GV + row * sh.dv;
+        else cp = V + row * sh.dv;
+        const int vec_c = KSIDE ? sh.vec_g : sh.vec_v;
+        if (vec_c) ct.load(cp, sh.dv, nv, sh.dv);
+        if (exact_g && sh.vec_x) xt.load(xp, sh.d, nv, sh.d);
+        if (cross_g && sh.vec_m) mt.load(mp, sh.mcols, nv, sh.mcols);
         __syncthreads();
-        if (exact_g) stage_tile<DT, KT>(Xstr + row * sh.d, sh.d, nv, sh.d, sh.vec_x, xs);
-        if (cross_g) stage_tile<RT, KT>(Mstr + row * sh.mcols, sh.mcols, nv, sh.mcols, sh.vec_m, ms);
-        if constexpr (KSIDE) {
-            stage_tile<VT, KT>(GV + row * sh.dv, sh.dv, nv, sh.dv, sh.vec_g, cs);
-            if (threadIdx.x < KT) gs[threadIdx.x] = (int)threadIdx.x < nv ? gden[row + threadIdx.x] : 0.f;
-        } else {
-            stage_tile<VT, KT>(V + row * sh.dv, sh.dv, nv, sh.dv, sh.vec_v, cs);
+        if (exact_g) {
+            if (sh.vec_x) xt.store(xs, nv, sh.d);
+            else stage_scalar<DT, KT>(xp, sh.d, nv, sh.d, xs);
         }
+        if (cross_g) {
+            if (sh.vec_m) mt.store(ms, nv, sh.mcols);
+            else stage_scalar<RT, KT>(mp, sh.mcols, nv, sh.mcols, ms);
+        }
+        if (vec_c) ct.store(cs, nv, sh.dv);
+        else stage_scalar<VT, KT>(cp, sh.dv, nv, sh.dv, cs);
+        if (KSIDE && threadIdx.x < KT) gs[threadIdx.x] = (int)threadIdx.x < nv ? gden[row + threadIdx.x] : 0.f;
         __syncthreads();
         f4 px[DT], pm[RT], pc[VT];                          // this tile's sums: two levels of summation,
         clear(px);                                          // as long chains of one sign or both lose digits

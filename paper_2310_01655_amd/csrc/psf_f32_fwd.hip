@@ -10,8 +10,8 @@
 // f32_plan() chooses the span.
 //
 // Measured against the vector kernels (us a call, forward / forward and backward): 36 units of 3000
-// tokens, r = 32, b = 200, bf16 storage 8530 -> 516; 24 units of 1950, b = 150, forward and backward
-// 26950 -> 1060; one unit of 1024, r = 16, fp32 storage 248 -> 42.  Relative error against float64
+// tokens, r = 32, b = 200, bf16 storage 8530 -> 450; 24 units of 1950, b = 150, forward and backward
+// 26950 -> 870; one unit of 1024, r = 16, fp32 storage 248 -> 35.  Relative error against float64
 // (fp32 storage, 2048 tokens, r = 64): 1.6e-6 -> 4.5e-7, gradients 4e-7 to 5e-7 on either.
 #include "psf_f32_tiles.h"
 #include "psf_f32.h"
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(64) void f32_sketch_kernel(const T *__restrict__ X1
 // multiply for the products of four column tiles), B = C_j.  The denominator column is a running
 // sum of the A operands.  Wide values (VT = 8) are split over two workgroups, 64 columns each.
 template <int RT, int VT, typename S>
-__global__ __launch_bounds__(kF32Threads) void f32_state_kernel(const float *__restrict__ M, const S *__restrict__ C,
+__global__ __launch_bounds__(kF32Threads, RT <= 2 ? 3 : RT == 4 ? 2 : 1) void f32_state_kernel(const float *__restrict__ M, const S *__restrict__ C,
                                                                 const float *__restrict__ wts, float *__restrict__ Z,
                                                                 F32Shape sh, int span0)
 {
@@ -112,9 +112,16 @@ __global__ __launch_bounds__(kF32Threads) void f32_state_kernel(const float *__r
     for (int j0 = j_begin; j0 < j_end; j0 += KT) {
         const size_t row = (size_t)u * sh.n + j0;
         const int nv = j_end - j0;
+        const S *cp = C + row * sh.dv + c0;
+        Tile<RT, KT, float> mt;
+        Tile<4, KT, S> ct;
+        if (sh.vec_m) mt.load(M + row * sh.mcols, sh.mcols, nv, sh.mcols);
+        if (sh.vec_v) ct.load(cp, sh.dv, nv, sh.dv - c0);
         __syncthreads();
-        stage_tile<RT, KT>(M + row * sh.mcols, sh.mcols, nv, sh.mcols, sh.vec_m, ms);
-        stage_tile<4, KT>(C + row * sh.dv + c0, sh.dv, nv, sh.dv - c0, sh.vec_v, vs);
+        if (sh.vec_m) mt.store(ms, nv, sh.mcols);
+        else stage_scalar<RT, KT>(M + row * sh.mcols, sh.mcols, nv, sh.mcols, ms);
+        if (sh.vec_v) ct.store(vs, nv, sh.dv - c0);
+        else stage_scalar<4, KT>(cp, sh.dv, nv, sh.dv - c0, vs);
         if (threadIdx.x < KT) ws[threadIdx.x] = wts && (int)threadIdx.x < nv ? wts[row + threadIdx.x] : 1.f;
         __syncthreads();
         f4 part[RT][4];                                     // two levels of summation, as in psf_f32_bwd.hip
@@ -192,7 +199,7 @@ __global__ __launch_bounds__(kF32Threads) void f32_scan_kernel(float *__restrict
 // the end: four times the workgroups, for problems that would not fill the chip otherwise.
 // GRAD: instead of the output, G_i = [dO_i / D_i | -<dO_i, o_i> / D_i] for the backward pass.
 template <int DT, int RT, int VT, int WR, bool GRAD, typename T>
-__global__ __launch_bounds__(kF32Threads) void f32_rows_kernel(
+__global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void f32_rows_kernel(
     const float *__restrict__ MQ, const float *__restrict__ MK, const T *__restrict__ Q, const T *__restrict__ K,
     const T *__restrict__ V, const float *__restrict__ Z, T *__restrict__ O, const T *__restrict__ dO,
     float *__restrict__ GV, float *__restrict__ gden, F32Shape sh)
@@ -233,10 +240,26 @@ __global__ __launch_bounds__(kF32Threads) void f32_rows_kernel(
         const int j_end = sh.noncausal ? sh.n : i_last + 1;
         for (int j0 = sh.noncausal ? 0 : s_begin; j0 < j_end; j0 += KT) {
             const int nv = min(KT, j_end - j0);
+            const bool exact_g = j0 + KT > bs_wg, cross_g = j0 < bs_wg_last;
+            Tile<DT, KT, T> kt;
+            Tile<RT, KT, float> mt;
+            Tile<VT, KT, T> vt;
+            const T *vp = V + (urow + j0) * sh.dv, *kp = K + (urow + j0) * sh.d;
+            const float *mp = MK + (urow + j0) * sh.mcols;
+            if (sh.vec_v) vt.load(vp, sh.dv, nv, sh.dv);
+            if (exact_g && sh.vec_x) kt.load(kp, sh.d, nv, sh.d);
+            if (cross_g && sh.vec_m) mt.load(mp, sh.mcols, nv, sh.mcols);
             __syncthreads();
-            if (j0 + KT > bs_wg) stage_tile<DT, KT>(K + (urow + j0) * sh.d, sh.d, nv, sh.d, sh.vec_x, ks);
-            if (j0 < bs_wg_last) stage_tile<RT, KT>(MK + (urow + j0) * sh.mcols, sh.mcols, nv, sh.mcols, sh.vec_m, ms);
-            stage_tile<VT, KT>(V + (urow + j0) * sh.dv, sh.dv, nv, sh.dv, sh.vec_v, vs);
+            if (exact_g) {
+                if (sh.vec_x) kt.store(ks, nv, sh.d);
+                else stage_scalar<DT, KT>(kp, sh.d, nv, sh.d, ks);
+            }
+            if (cross_g) {
+                if (sh.vec_m) mt.store(ms, nv, sh.mcols);
+                else stage_scalar<RT, KT>(mp, sh.mcols, nv, sh.mcols, ms);
+            }
+            if (sh.vec_v) vt.store(vs, nv, sh.dv);
+            else stage_scalar<VT, KT>(vp, sh.dv, nv, sh.dv, vs);
             __syncthreads();
             for (int sub = (WR == 4 ? 0 : wave); sub < KT / 16; sub += (WR == 4 ? 1 : 4)) {
                 const int js = j0 + 16 * sub;
@@ -459,21 +482,24 @@ F32Shape f32_shape(const Problem &pb, const F32Plan &pl)
 }
 
 // Where the states lie.  Costs in seconds of the whole chip at the rates these kernels reach
-// (products 90 TFLOP/s, state traffic 4 TB/s, 5 us for the two further launches): forming a
-// record and applying it against the pairs that a longer span takes directly.
+// (states 90 TFLOP/s, pairs 65 TFLOP/s, state traffic 4 TB/s, 5 us for the two further
+// launches): forming a record and applying it against the pairs that a longer span takes directly.
+// Measured with every span forced (blocks a span: us): 36 units x 3000, r 32, b 200: 1: 475, 2: 452,
+// 4: 469, 8: 534, all 15: 558; 12 x 16384, r 32, b 64: 1: 855, 4: 668, 16: 934, all: 4267; 24 x 8000,
+// r 64, b 250: 1: 2061, 2: 2061, 8: 2646; 48 x 8192, r 16, b 256: 1: 697, 4: 1224.
 F32Plan f32_plan(const Problem &pb, size_t z_floats, bool noncausal, bool grad)
 {
     const bool wide = pb.d > 64 || pb.dv > 64 || pb.mcols > 64;
     int rt = 0, vt = wide ? 8 : 4;
     with_tiles(pb, [&](auto, auto r) -> psf_status { rt = decltype(r)::value; return PSF_OK; });
-    const double tokens = (double)pb.units * pb.n, rate = 90e12, bw = 4e12;
+    const double tokens = (double)pb.units * pb.n, rate = 90e12, pair_rate = 65e12, bw = 4e12;
     const size_t rec = record_floats(rt, vt);
     const double state_flops = tile_pairs(rt) * 256.0 * 16 * vt * 2 * (grad ? 6 : 2);
     const double pair_flops = 2.0 * 16 * (grad ? 5 * rt + 4 * vt : rt + vt);
     const double passes = grad ? 9 : 4;
     F32Plan best = {};
     if (noncausal) {
-        const double direct = tokens * pb.n * pair_flops / rate;
+        const double direct = tokens * pb.n * pair_flops / pair_rate;
         const double with_state = tokens * state_flops / rate + 10e-6;
         // spans only split the sum over the tokens: enough workgroups to fill the chip
         int spans = (int)((2048 + (long long)pb.units * 4 * rt - 1) / ((long long)pb.units * 4 * rt));
@@ -497,7 +523,7 @@ F32Plan f32_plan(const Problem &pb, size_t z_floats, bool noncausal, bool grad)
         const int spans = (pb.t + s - 1) / s;
         const double span = (double)s * pb.b;
         if (spans == 1 || (size_t)spans * pb.units * rec <= z_floats) {
-            double cost = tokens * (span < pb.n ? span : pb.n) / 2 * pair_flops / rate;
+            double cost = tokens * (span < pb.n ? span : pb.n) / 2 * pair_flops / pair_rate;
             if (spans > 1)
                 cost += tokens * (1.0 - 1.0 / spans) * state_flops / rate +
                         (double)pb.units * spans * rec * 4 * passes / bw + (grad ? 10e-6 : 5e-6);

@@ -27,12 +27,21 @@ __device__ __forceinline__ f4 mm(float a, float b, f4 c)
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// Four columns as stored, and as fp32.
+template <typename S> struct Raw4;
+template <> struct Raw4<float> { typedef f4 type; };
+template <> struct Raw4<bf16_t> { typedef uint2 type; };
+__device__ __forceinline__ f4 widen(f4 v) { return v; }
+__device__ __forceinline__ f4 widen(uint2 v)
+{
+    return f4{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
+              __uint_as_float(v.y & 0xffff0000u)};
+}
+
 __device__ __forceinline__ f4 load4(const float *p) { return *(const f4 *)p; }
 __device__ __forceinline__ f4 load4(const bf16_t *p)
 {
-    const uint2 v = *(const uint2 *)p;
-    return f4{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
-              __uint_as_float(v.y & 0xffff0000u)};
+    return widen(*(const uint2 *)p);
 }
 __device__ __forceinline__ void store4(float *p, f4 v) { *(f4 *)p = v; }
 __device__ __forceinline__ void store4(bf16_t *p, f4 v)
@@ -113,17 +122,45 @@ __device__ __forceinline__ void load_frags(const S *row, int width, bool there, 
 template <int NT>
 constexpr int pitch_of() { return 16 * NT + 4; }
 
-// NR rows of 16 * NT columns into LDS; rows >= nvalid and columns >= width are zero.
+// NR rows of 16 * NT columns on their way into LDS; rows >= nvalid (at least 1) and columns >=
+// width become zero.  All loads are issued before the first result is needed, and none of them
+// sits behind a branch: places that are not there load the first piece instead.  A thread
+// holds the same columns of kPieces rows, as stored.
 template <int NT, int NR, typename S>
-__device__ __forceinline__ void stage_tile(const S *src, size_t ld, int nvalid, int width, int vec, float *dst)
-{
+struct Tile {
+    static constexpr int kPieces = NR * 4 * NT / kF32Threads, kStep = kF32Threads / (4 * NT);
+    static_assert(NR * 4 * NT % kF32Threads == 0 && kF32Threads % (4 * NT) == 0, "whole pieces");
+    typedef typename Raw4<S>::type raw;
+    raw v[kPieces];
+    __device__ __forceinline__ void load(const S *src, int ld, int nvalid, int width)
+    {
+        const int row = threadIdx.x / (4 * NT), c = 4 * (threadIdx.x % (4 * NT));
+        const uint32_t at = ((uint32_t)row * ld + c) * sizeof(S), step = (uint32_t)kStep * ld * sizeof(S);
+        const int rows = c < width ? nvalid : 0;
 #pragma unroll
-    for (int it = 0; it < (NR * 4 * NT + kF32Threads - 1) / kF32Threads; ++it) {
-        const int idx = it * kF32Threads + threadIdx.x;
-        if (NR * 4 * NT % kF32Threads != 0 && idx >= NR * 4 * NT) break;
-        const int row = idx / (4 * NT), c = 4 * (idx % (4 * NT));
+        for (int it = 0; it < kPieces; ++it)
+            v[it] = *(const raw *)((const char *)src + (row + it * kStep < rows ? at + it * step : 0u));
+    }
+    __device__ __forceinline__ void store(float *dst, int nvalid, int width) const
+    {
+        const int row = threadIdx.x / (4 * NT), c = 4 * (threadIdx.x % (4 * NT));
+        const int rows = c < width ? nvalid : 0;
+#pragma unroll
+        for (int it = 0; it < kPieces; ++it)
+            *(f4 *)&dst[(row + it * kStep) * pitch_of<NT>() + c] =
+                row + it * kStep < rows ? widen(v[it]) : f4{0.f, 0.f, 0.f, 0.f};
+    }
+};
+
+// the same for tensors whose rows cannot be moved four columns at a time
+template <int NT, int NR, typename S>
+__device__ __forceinline__ void stage_scalar(const S *src, int ld, int nvalid, int width, float *dst)
+{
+    const int c = 4 * (threadIdx.x % (4 * NT));
+#pragma unroll 1
+    for (int row = threadIdx.x / (4 * NT); row < NR; row += kF32Threads / (4 * NT)) {
         f4 v = {0.f, 0.f, 0.f, 0.f};
-        if (row < nvalid) v = row_piece(src + (size_t)row * ld, c, width, vec);
+        if (row < nvalid) v = row_piece(src + (size_t)row * ld, c, width, 0);
         *(f4 *)&dst[row * pitch_of<NT>() + c] = v;
     }
 }
