@@ -28,6 +28,7 @@
 #include <type_traits>
 
 #include "psf_internal.h"
+#include "psf_f32.h"
 
 namespace psf {
 namespace {
@@ -601,9 +602,8 @@ __global__ __launch_bounds__(kThreads) void dec_finish_kernel(const T *__restric
                          : mq_new[(size_t)u * mcols + e] * mk_new[(size_t)u * mcols + e];
     red[tid] = a;
     __syncthreads();
+    const float sdot = sum256(red);
     if (tid == 0) {
-        float sdot = 0.f;
-        for (int q2 = 0; q2 < kThreads; ++q2) sdot += red[q2];
         float wv = sdot * sdot;
         if (local_exact) {
             wv = 1.f;
@@ -815,15 +815,26 @@ __global__ __launch_bounds__(kThreads, 2) void dec_fold_mfma_kernel(float *__res
         if (k >= rpw) break;
         const int a = a0 + row0 + k;
         const size_t rowbase = (size_t)tri_row(a, mcols);
+        // accumulator: lane x = column c, register v = row b' = 8 (v / 4) + 4 h + v % 4.  All rows
+        // are read before the first is written: the reads and writes go to one array, so that in
+        // one loop every read would wait for the write before it (768 units of r = d = 64:
+        // 1240 -> 875 us).
+        float old[TC][16];
+#pragma unroll
+        for (int ct = 0; ct < TC; ++ct)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int bp = max(a, 32 * bt + 8 * (v / 4) + 4 * h + (v % 4));
+                old[ct][v] = su[L.zv + (rowbase + bp - a) * dv + 32 * ct + x];
+            }
 #pragma unroll
         for (int ct = 0; ct < TC; ++ct) {
-            // accumulator: lane x = column c, register v = row b' = 8 (v / 4) + 4 h + v % 4
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int bp = 32 * bt + 8 * (v / 4) + 4 * h + (v % 4);
                 if (bp >= a) {
                     const size_t at = (rowbase + bp - a) * dv + 32 * ct + x;
-                    const float znew = su[L.zv + at] + (bp > a ? 2.f : 1.f) * acc[k][ct][v];
+                    const float znew = old[ct][v] + (bp > a ? 2.f : 1.f) * acc[k][ct][v];
                     su[L.zv + at] = znew;
                     if (L.shadow) ((bf16_t *)(su + L.zh))[at] = f32_to_bf16(znew);
                 }
@@ -881,6 +892,22 @@ __global__ __launch_bounds__(kThreads) void dec_prefill_kernel(const T *__restri
                 if (tid < mcols) su[L.cm + (size_t)(j0 + i) * mcols + tid] = fin[i][tid];
         }
     }
+}
+
+// Keys and values of prompt tokens pos0 .. pos0 + count - 1 into cache slots 0 .. count - 1, where
+// m(k) comes from elsewhere.  Rows of a unit are contiguous on both sides; PIECE elements at a
+// time (16 bytes where sizes and alignment allow it).
+template <typename T, int PIECE>
+__global__ __launch_bounds__(kThreads) void dec_cache_rows_kernel(const T *__restrict__ K, const T *__restrict__ V,
+                                                                  float *__restrict__ state, DecodeLayout L, int d,
+                                                                  int dv, int n_prompt, int pos0, int count)
+{
+    struct __attribute__((aligned(sizeof(T) * PIECE))) Piece { T v[PIECE]; };
+    const int u = blockIdx.y;
+    float *su = state + (size_t)u * L.per_unit;
+    const size_t i = ((size_t)blockIdx.x * kThreads + threadIdx.x) * PIECE, row0 = (size_t)u * n_prompt + pos0;
+    if (i < (size_t)count * d) *(Piece *)((T *)(su + L.ck) + i) = *(const Piece *)(K + row0 * d + i);
+    if (i < (size_t)count * dv) *(Piece *)((T *)(su + L.cv) + i) = *(const Piece *)(V + row0 * dv + i);
 }
 
 // The state after the complete blocks of a prompt, taken from the forward path's state kernel:
@@ -1088,7 +1115,8 @@ static psf_status prefill_launch(const Problem &pb, const void *K, const void *V
     if constexpr (std::is_same_v<T, bf16_t>) {
         if (first > 0) {
             const bf16_t *kc = (const bf16_t *)K, *vc = (const bf16_t *)V;
-            if (tail > 0) {
+            int src_n = n_prompt;
+            if (tail > 0 && pb.learned) {                  // the learned sketch kernel takes contiguous rows
                 const size_t pieces = (size_t)pb.units * first * pb.d / 8;
                 const unsigned grid = (unsigned)((pieces + kThreads - 1) / kThreads);
                 hipLaunchKernelGGL(dec_gather_rows_kernel, dim3(grid), dim3(kThreads), 0, s, (const bf16_t *)K,
@@ -1099,11 +1127,12 @@ static psf_status prefill_launch(const Problem &pb, const void *K, const void *V
                 PSF_LAUNCH_CHECK();
                 kc = (const bf16_t *)wsp;
                 vc = (const bf16_t *)(wsp + pl.copy_bytes);
+                src_n = first;
             }
             const void *zg = nullptr;
             const float *spart = nullptr;
             int parts = 0;
-            st = mfma_total_state(pb, first, kc, vc, G, wsp + 2 * pl.copy_bytes, s, &zg, &spart, &parts);
+            st = mfma_total_state(pb, first, src_n, kc, vc, G, wsp + 2 * pl.copy_bytes, s, &zg, &spart, &parts);
             if (st != PSF_OK) return st;
             const long long pairs = tri_count(pb.mcols);
             const long long pieces = (long long)pb.mcols * (pb.mcols / 8) * pb.dv;      // >= pairs
@@ -1136,7 +1165,25 @@ static psf_status prefill_launch(const Problem &pb, const void *K, const void *V
     for (int pos0 = first; pos0 < n_prompt; pos0 += pb.b) {
         const int count = n_prompt - pos0 < pb.b ? n_prompt - pos0 : pb.b;
         const dim3 grid((unsigned)((count + kPrefillTokens - 1) / kPrefillTokens), (unsigned)pb.units);
-        if (have_m)
+        if (!have_m && f32_supported(pb)) {
+            // sketches on the fp32 matrix cores, straight into the cache (768 units x 1012 tokens of
+            // d = r = 64: 347 us and 76 for the rows, against 1690 by two rows a workgroup)
+            Problem part = pb;
+            part.n = count;
+            st = f32_sketch_rows(part, (const T *)K + (size_t)pos0 * pb.d, (size_t)n_prompt * pb.d, G, state + L.cm,
+                                 L.per_unit, s);
+            if (st != PSF_OK) return st;
+            constexpr int kWide = 16 / sizeof(T);
+            const bool wide = pb.d % kWide == 0 && pb.dv % kWide == 0 && (((uintptr_t)K | (uintptr_t)V) & 15u) == 0;
+            const size_t pieces = (size_t)count * (pb.d > pb.dv ? pb.d : pb.dv) / (wide ? kWide : 1);
+            const dim3 cgrid((unsigned)((pieces + kThreads - 1) / kThreads), (unsigned)pb.units);
+            if (wide)
+                hipLaunchKernelGGL((dec_cache_rows_kernel<T, kWide>), cgrid, dim3(kThreads), 0, s, (const T *)K,
+                                   (const T *)V, state, L, pb.d, pb.dv, n_prompt, pos0, count);
+            else
+                hipLaunchKernelGGL((dec_cache_rows_kernel<T, 1>), cgrid, dim3(kThreads), 0, s, (const T *)K,
+                                   (const T *)V, state, L, pb.d, pb.dv, n_prompt, pos0, count);
+        } else if (have_m)
             hipLaunchKernelGGL((dec_prefill_kernel<T, true>), grid, dim3(kThreads), 0, s, (const T *)K, (const T *)V,
                                (const float *)m_tail, state, L, pb.d, pb.dv, pb.p, pb.mcols, n_prompt, pos0, count,
                                first, tail, ska);

@@ -30,6 +30,9 @@ bool f32_split_rows(const Problem &pb);
 // m(x) of all rows (X2, M2 may be null); Gaussian sketches only
 psf_status f32_sketch_pair(const Problem &pb, const void *X1, const void *X2, const void *G, float *M1, float *M2,
                            hipStream_t s);
+// the same for the n rows of every unit that start x_unit elements apart, results m_unit apart
+psf_status f32_sketch_rows(const Problem &pb, const void *X, size_t x_unit, const void *G, float *M, size_t m_unit,
+                           hipStream_t s);
 psf_status f32_key_states(const Problem &pb, const F32Plan &pl, const float *MK, const void *V, float *Z, hipStream_t s);
 psf_status f32_rows(const Problem &pb, const F32Plan &pl, const float *MQ, const float *MK, const void *Q,
                     const void *K, const void *V, const float *Z, void *O, hipStream_t s);

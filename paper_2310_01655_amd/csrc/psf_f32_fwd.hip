@@ -29,13 +29,15 @@ template <typename T>
 __global__ __launch_bounds__(64) void f32_sketch_kernel(const T *__restrict__ X1, const T *__restrict__ X2,
                                                         const T *__restrict__ G, float *__restrict__ M1,
                                                         float *__restrict__ M2, int n, int d, int r, int p, int heads,
-                                                        int per_head, size_t g_len, int vec_x, int vec_m)
+                                                        int per_head, size_t g_len, size_t x_unit, size_t m_unit,
+                                                        int vec_x, int vec_m)
 {
+    // x_unit, m_unit: elements from the rows of one unit to those of the next
     extern __shared__ __attribute__((aligned(16))) float smem[];
     const int lane = threadIdx.x, li = lane & 15, g = lane >> 4, u = blockIdx.y, i0 = blockIdx.x * kSketchRows;
     const int dp = (d + 15) / 16 * 16, rp = (r + 15) / 16 * 16, xp = dp + 4, mp = rp + 4;
-    const T *X = (blockIdx.z ? X2 : X1) + ((size_t)u * n + i0) * d;
-    float *M = (blockIdx.z ? M2 : M1) + ((size_t)u * n + i0) * (p == 2 ? d : r);
+    const T *X = (blockIdx.z ? X2 : X1) + u * x_unit + (size_t)i0 * d;
+    float *M = (blockIdx.z ? M2 : M1) + u * m_unit + (size_t)i0 * (p == 2 ? d : r);
     const int nv = min(kSketchRows, n - i0);
     const int quads = dp / 4;
     for (int idx = lane; idx < kSketchRows * quads; idx += 64) {
@@ -393,18 +395,18 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void 
 
 template <typename T>
 psf_status sketch_pair(const Problem &pb, const void *X1, const void *X2, const void *G, float *M1, float *M2,
-                       hipStream_t s)
+                       size_t x_unit, size_t m_unit, hipStream_t s)
 {
     const dim3 grid((unsigned)((pb.n + kSketchRows - 1) / kSketchRows), (unsigned)pb.units, X2 ? 2 : 1);
-    const int vx = X2 ? pieces_ok<T>(pb.d, {X1, X2}) : pieces_ok<T>(pb.d, {X1});
-    const int vm = pieces_ok<float>(pb.mcols, {M1, M2 ? M2 : M1});
+    const int vx = x_unit % 4 == 0 && (X2 ? pieces_ok<T>(pb.d, {X1, X2}) : pieces_ok<T>(pb.d, {X1}));
+    const int vm = m_unit % 4 == 0 && pieces_ok<float>(pb.mcols, {M1, M2 ? M2 : M1});
     const int dp = tiles16(pb.d) * 16, rp = tiles16(pb.r) * 16;
     const size_t lds = (size_t)kSketchRows * (dp + 4 + sketch_nodes(pb.p) * (rp + 4)) * sizeof(float);
     if (lds > (64u << 10))                               // p = 16 with wide sketches: up to 118 KB
         PSF_HIP_TRY(hipFuncSetAttribute((const void *)f32_sketch_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                         (int)lds));
     hipLaunchKernelGGL(f32_sketch_kernel<T>, grid, dim3(64), lds, s, (const T *)X1, (const T *)X2, (const T *)G, M1, M2,
-                       pb.n, pb.d, pb.r, pb.p, pb.heads, pb.per_head ? 1 : 0, pb.g_len, vx, vm);
+                       pb.n, pb.d, pb.r, pb.p, pb.heads, pb.per_head ? 1 : 0, pb.g_len, x_unit, m_unit, vx, vm);
     PSF_LAUNCH_CHECK();
     return PSF_OK;
 }
@@ -540,7 +542,16 @@ F32Plan f32_plan(const Problem &pb, size_t z_floats, bool noncausal, bool grad)
 psf_status f32_sketch_pair(const Problem &pb, const void *X1, const void *X2, const void *G, float *M1, float *M2,
                            hipStream_t s)
 {
-    return pb.bf16 ? sketch_pair<bf16_t>(pb, X1, X2, G, M1, M2, s) : sketch_pair<float>(pb, X1, X2, G, M1, M2, s);
+    const size_t x_unit = (size_t)pb.n * pb.d, m_unit = (size_t)pb.n * pb.mcols;
+    return pb.bf16 ? sketch_pair<bf16_t>(pb, X1, X2, G, M1, M2, x_unit, m_unit, s)
+                   : sketch_pair<float>(pb, X1, X2, G, M1, M2, x_unit, m_unit, s);
+}
+
+psf_status f32_sketch_rows(const Problem &pb, const void *X, size_t x_unit, const void *G, float *M, size_t m_unit,
+                           hipStream_t s)
+{
+    return pb.bf16 ? sketch_pair<bf16_t>(pb, X, nullptr, G, M, nullptr, x_unit, m_unit, s)
+                   : sketch_pair<float>(pb, X, nullptr, G, M, nullptr, x_unit, m_unit, s);
 }
 
 psf_status f32_key_states(const Problem &pb, const F32Plan &pl, const float *MK, const void *V, float *Z, hipStream_t s)

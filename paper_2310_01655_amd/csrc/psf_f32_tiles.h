@@ -293,6 +293,8 @@ __device__ __forceinline__ void back_project(const T *G, int in, int r, int e0, 
     const int li = lane & 15, g = lane >> 4, e = e0 + li;
     const T *ga = G + (size_t)(e < in ? e : 0) * r;
     const float *yr = y + li * pitch + 4 * g;
+    f4 part[H];                                             // two levels of summation
+    clear(part);
     for (int c0 = 0; c0 < r; c0 += 16) {
         f4 a = {0.f, 0.f, 0.f, 0.f};
         if (e < in) a = row_piece(ga, c0 + 4 * g, r, vec);
@@ -300,10 +302,10 @@ __device__ __forceinline__ void back_project(const T *G, int in, int r, int e0, 
         for (int h = 0; h < H; ++h) {
             const f4 yv = *(const f4 *)(yr + 16 * h * pitch + c0);
 #pragma unroll
-            for (int s = 0; s < 4; ++s) acc[h] = mm(a[s], yv[s], acc[h]);
+            for (int s = 0; s < 4; ++s) part[h] = mm(a[s], yv[s], part[h]);
         }
     }
-    settle();
+    add_to(acc, part);
 }
 
 // ---- states -----------------------------------------------------------------------------

@@ -240,8 +240,9 @@ __global__ __launch_bounds__(kWg) void k_sketch(const bf16_t *__restrict__ X,
                                                 const bf16_t *__restrict__ Gt, int n, int heads,
                                                 int per_head, size_t g_len, int tiles_per_wg,
                                                 bf16_t *__restrict__ M_rm, float *__restrict__ M8,
-                                                float *__restrict__ Spart)
+                                                float *__restrict__ Spart, int x_n)
 {
+    // x_n: rows of a unit in X, of which the first n are sketched
     __shared__ __attribute__((aligned(16))) SketchLds<D, R> lds;
     __shared__ float red[QSIDE ? 1 : 4][QSIDE ? 1 : 32][33];
     __shared__ __attribute__((aligned(16))) bf16_t qtile[QSIDE ? 4 : 1][QSIDE ? 32 : 1][R + 8];
@@ -249,6 +250,7 @@ __global__ __launch_bounds__(kWg) void k_sketch(const bf16_t *__restrict__ X,
     const int x = lane & 31, h = lane >> 5;
     const size_t tok_wg0 = (size_t)blockIdx.x * tiles_per_wg * 128;   // global token (row) index
     const int u = (int)(tok_wg0 / n);
+    X += (size_t)u * (x_n - n) * D;
     const bf16_t *g = Gt + (per_head ? (size_t)(u % heads) * g_len : 0);
     const float scale = sqrtf(1.0f / (float)R);
     constexpr int KS = D / 16, NT = R / 32;
@@ -385,15 +387,18 @@ __global__ __launch_bounds__(kWg) void k_sketch(const bf16_t *__restrict__ X,
 // V [rows][D] -> V8 [rows/8][D][8] (bf16 bits moved, not converted)
 template <int D>
 __global__ __launch_bounds__(kWg) void k_v_octets(const bf16_t *__restrict__ V,
-                                                  bf16_t *__restrict__ V8, size_t octets)
+                                                  bf16_t *__restrict__ V8, size_t octets,
+                                                  unsigned oct_per_unit, unsigned gap)
 {
+    // oct_per_unit != 0: `gap` more rows of V follow the ones taken of every unit
     const size_t idx = (size_t)blockIdx.x * kWg + threadIdx.x;
     if (idx >= octets * D) return;
     const size_t oct = idx / D;
     const int c = (int)(idx % D);
+    const size_t row = oct * 8 + (oct_per_unit ? (size_t)((unsigned)oct / oct_per_unit) * gap : 0);
     uint16_t tmp[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) tmp[j] = V[(oct * 8 + j) * D + c];
+    for (int j = 0; j < 8; ++j) tmp[j] = V[(row + j) * D + c];
     uint4 pk;
     pk.x = tmp[0] | ((uint32_t)tmp[1] << 16);
     pk.y = tmp[2] | ((uint32_t)tmp[3] << 16);
@@ -2624,15 +2629,16 @@ psf_status launch_transpose_g(const Problem &pb, const void *G, bf16_t *Gt, hipS
 
 template <int D, int R, int P>
 psf_status launch_sketch(const Problem &pb, const void *X, const bf16_t *Gt, bool qside, bf16_t *M_rm,
-                         float *M8, float *Spart, int tiles, hipStream_t s)
+                         float *M8, float *Spart, int tiles, hipStream_t s, int x_n = 0)
 {
+    if (x_n == 0) x_n = pb.n;
     const unsigned grid = (unsigned)((size_t)pb.units * pb.n / (128 * (size_t)tiles));
     if (qside)
         hipLaunchKernelGGL((k_sketch<D, R, P, true>), dim3(grid), dim3(kWg), 0, s, (const bf16_t *)X, Gt,
-                           pb.n, pb.heads, pb.per_head ? 1 : 0, pb.g_len, tiles, M_rm, M8, Spart);
+                           pb.n, pb.heads, pb.per_head ? 1 : 0, pb.g_len, tiles, M_rm, M8, Spart, x_n);
     else
         hipLaunchKernelGGL((k_sketch<D, R, P, false>), dim3(grid), dim3(kWg), 0, s, (const bf16_t *)X, Gt,
-                           pb.n, pb.heads, pb.per_head ? 1 : 0, pb.g_len, tiles, M_rm, M8, Spart);
+                           pb.n, pb.heads, pb.per_head ? 1 : 0, pb.g_len, tiles, M_rm, M8, Spart, x_n);
     PSF_LAUNCH_CHECK();
     return PSF_OK;
 }
@@ -2815,7 +2821,7 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
     if (!v_done) {
         const size_t octets = (size_t)pb.units * pb.n / 8;
         hipLaunchKernelGGL((k_v_octets<D>), dim3((unsigned)((octets * D + kWg - 1) / kWg)), dim3(kWg), 0,
-                           s, (const bf16_t *)V, w.V8, octets);
+                           s, (const bf16_t *)V, w.V8, octets, 0u, 0u);
         PSF_LAUNCH_CHECK();
     }
     if (tm) tm->mark();
@@ -3087,8 +3093,8 @@ size_t mfma_total_state_workspace_bytes(const Problem &pb, int n_tok)
 
 namespace {
 template <int D, int R, int P>
-psf_status total_state_impl(const Problem &pb, const void *K, const void *V, const void *G, const TotalWs &w,
-                            hipStream_t s)
+psf_status total_state_impl(const Problem &pb, int src_n, const void *K, const void *V, const void *G,
+                            const TotalWs &w, hipStream_t s)
 {
     psf_status st;
     if (pb.learned) {
@@ -3107,26 +3113,27 @@ psf_status total_state_impl(const Problem &pb, const void *K, const void *V, con
     } else {
         st = launch_transpose_g(pb, G, w.Gt, s);
         if (st != PSF_OK) return st;
-        st = launch_sketch<D, R, P>(pb, K, w.Gt, false, nullptr, w.MK8, w.Spart, sketch_tiles_per_wg(pb.b), s);
+        st = launch_sketch<D, R, P>(pb, K, w.Gt, false, nullptr, w.MK8, w.Spart, sketch_tiles_per_wg(pb.b), s, src_n);
         if (st != PSF_OK) return st;
     }
     const size_t octets = (size_t)pb.units * pb.n / 8;
     hipLaunchKernelGGL((k_v_octets<D>), dim3((unsigned)((octets * D + kWg - 1) / kWg)), dim3(kWg), 0, s,
-                       (const bf16_t *)V, w.V8, octets);
+                       (const bf16_t *)V, w.V8, octets, src_n > pb.n ? (unsigned)(pb.n / 8) : 0u,
+                       (unsigned)(src_n - pb.n));
     PSF_LAUNCH_CHECK();
     return launch_state<D, R>(pb, w.MK8, w.V8, w.Zg, s);
 }
 }  // namespace
 
-psf_status mfma_total_state(const Problem &pb0, int n_tok, const void *K, const void *V, const void *G, void *ws,
-                            hipStream_t s, const void **Zg, const float **Spart, int *parts_per_unit)
+psf_status mfma_total_state(const Problem &pb0, int n_tok, int src_n, const void *K, const void *V, const void *G,
+                            void *ws, hipStream_t s, const void **Zg, const float **Spart, int *parts_per_unit)
 {
     const Problem pb = total_problem(pb0, n_tok);
     const TotalWs w = carve_total(pb, ws);
     *Zg = w.Zg;
     *Spart = w.Spart;
     *parts_per_unit = pb.n / part_tokens(pb);
-#define PSF_AT(D_, R_, P_) (total_state_impl<D_, R_, P_>(pb, K, V, G, w, s))
+#define PSF_AT(D_, R_, P_) (total_state_impl<D_, R_, P_>(pb, src_n, K, V, G, w, s))
     if (pb.d == 64 && pb.r == 64 && pb.p == 4) return PSF_AT(64, 64, 4);
     if (pb.d == 64 && pb.r == 32 && pb.p == 4) return PSF_AT(64, 32, 4);
     if (pb.d == 64 && pb.r == 64 && pb.p == 8) return PSF_AT(64, 64, 8);

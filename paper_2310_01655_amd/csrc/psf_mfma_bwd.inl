@@ -1108,9 +1108,9 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
     {
         const size_t octets = rows / 8;
         const unsigned grid = (unsigned)((octets * D + kWg - 1) / kWg);
-        hipLaunchKernelGGL((k_v_octets<D>), dim3(grid), dim3(kWg), 0, s, rq, w.Q8, octets);
+        hipLaunchKernelGGL((k_v_octets<D>), dim3(grid), dim3(kWg), 0, s, rq, w.Q8, octets, 0u, 0u);
         PSF_LAUNCH_CHECK();
-        hipLaunchKernelGGL((k_v_octets<D>), dim3(grid), dim3(kWg), 0, s, rk, w.K8, octets);
+        hipLaunchKernelGGL((k_v_octets<D>), dim3(grid), dim3(kWg), 0, s, rk, w.K8, octets, 0u, 0u);
         PSF_LAUNCH_CHECK();
         const size_t pieces = rows * D / 8;
         const unsigned gridp = (unsigned)((pieces + kWg - 1) / kWg);
