@@ -10,8 +10,8 @@
 // f32_plan() chooses the span.
 //
 // Measured against the vector kernels (us a call, forward / forward and backward): 36 units of 3000
-// tokens, r = 32, b = 200, bf16 storage 8530 -> 450; 24 units of 1950, b = 150, forward and backward
-// 26950 -> 870; one unit of 1024, r = 16, fp32 storage 248 -> 35.  Relative error against float64
+// tokens, r = 32, b = 200, bf16 storage 8530 -> 387; 24 units of 1950, b = 150, forward and backward
+// 26950 -> 826; one unit of 1024, r = 16, fp32 storage 248 -> 35.  Relative error against float64
 // (fp32 storage, 2048 tokens, r = 64): 1.6e-6 -> 4.5e-7, gradients 4e-7 to 5e-7 on either.
 #include "psf_f32_tiles.h"
 #include "psf_f32.h"
@@ -89,27 +89,39 @@ __global__ __launch_bounds__(64) void f32_sketch_kernel(const T *__restrict__ X1
 }
 
 // ---- states: sum over the tokens of a span of phi'(x_j) [C_j | w_j] --------------------------
-// A wave owns one sketch index a and walks the tokens: A = m_j[a] m_j[b'] (made in registers, one
-// multiply for the products of four column tiles), B = C_j.  The denominator column is a running
-// sum of the A operands.  Wide values (VT = 8) are split over two workgroups, 64 columns each.
+// A wave owns two sketch indices, one of tile row `lo` and one of tile row `hi` = RT - 1 - lo (the
+// same row for r = 16), so that every wave has RT + 1 tiles of pairs, and walks the tokens:
+// A = m_j[a] m_j[b'] (made in registers, one multiply for the products of four column tiles),
+// B = C_j.  The denominator column is a running sum of the A operands.  The four column tiles
+// are read once for both indices and each staged token serves eight indices a workgroup: 36
+// units x 2800 tokens, r = 32: 175 us with one index a wave, 112 so.  Wide values (VT = 8) are split over two workgroups,
+// 64 columns each.  Where RT + 1 tiles in two levels of sums exceed the registers (RT = 8), a
+// wave takes one index and RT tiles, of which those below the diagonal are empty.
 template <int RT, int VT, typename S>
-__global__ __launch_bounds__(kF32Threads, RT <= 2 ? 3 : RT == 4 ? 2 : 1) void f32_state_kernel(const float *__restrict__ M, const S *__restrict__ C,
-                                                                const float *__restrict__ wts, float *__restrict__ Z,
-                                                                F32Shape sh, int span0)
+__global__ __launch_bounds__(kF32Threads, RT <= 2 ? 3 : RT == 4 ? 2 : 1) void f32_state_kernel(
+    const float *__restrict__ M, const S *__restrict__ C, const float *__restrict__ wts, float *__restrict__ Z,
+    F32Shape sh, int span0)
 {
     constexpr int MP = pitch_of<RT>(), VP = pitch_of<4>(), KT = RT > 4 ? 32 : 64;
+    constexpr bool TWO = RT <= 4;
+    constexpr int SLOTS = TWO ? RT + 1 : RT;
     __shared__ __attribute__((aligned(16))) float ms[KT * MP], vs[KT * VP], ws[KT];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, g = lane >> 4;
-    const int a = 4 * (blockIdx.x / (VT / 4)) + wave, at = a >> 4, c0 = 64 * (blockIdx.x % (VT / 4));
+    const int grp = blockIdx.x / (VT / 4), c0 = 64 * (blockIdx.x % (VT / 4));
+    // TWO: groups of four index pairs; r = 16 pairs a with a + 8 of the one tile row
+    const int lo = RT == 1 ? 0 : grp / 4, a_lo = RT == 1 ? 4 * grp + wave : 16 * lo + 4 * (grp % 4) + wave;
+    const int hi = TWO ? RT - 1 - lo : lo, a_hi = RT == 1 ? a_lo + 8 : 16 * hi + 4 * (grp % 4) + wave;
+    const int split = RT - lo;                              // slots of a_lo; the others are a_hi's
     const int span = span0 + blockIdx.y, u = blockIdx.z;
     const int j_begin = span * sh.span, j_end = min(sh.n, j_begin + sh.span);
-    f4 acc[RT][4];
-    float den[RT];
+    f4 acc[SLOTS][4];
+    float den[SLOTS];
+    int mcol[SLOTS];                                        // first sketch column of the slot's tile
 #pragma unroll
-    for (int q = 0; q < RT; ++q) {
-        den[q] = 0.f;
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct) acc[q][ct] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int e = 0; e < SLOTS; ++e) {
+        den[e] = 0.f;
+        mcol[e] = 16 * (e < split ? lo + e : min(hi + e - split, RT - 1));
+        clear(acc[e]);
     }
     for (int j0 = j_begin; j0 < j_end; j0 += KT) {
         const size_t row = (size_t)u * sh.n + j0;
@@ -126,48 +138,49 @@ __global__ __launch_bounds__(kF32Threads, RT <= 2 ? 3 : RT == 4 ? 2 : 1) void f3
         else stage_scalar<4, KT>(cp, sh.dv, nv, sh.dv - c0, vs);
         if (threadIdx.x < KT) ws[threadIdx.x] = wts && (int)threadIdx.x < nv ? wts[row + threadIdx.x] : 1.f;
         __syncthreads();
-        f4 part[RT][4];                                     // two levels of summation, as in psf_f32_bwd.hip
+        f4 part[SLOTS][4];                                  // two levels of summation, as in psf_f32_bwd.hip
 #pragma unroll
-        for (int q = 0; q < RT; ++q) clear(part[q]);
+        for (int e = 0; e < SLOTS; ++e) clear(part[e]);
         for (int t16 = 0; t16 < KT; t16 += 16) {
             if (t16 >= nv) break;
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 const int j = t16 + 4 * g + s;
-                const float ma = ms[j * MP + a], wt = ws[j];
+                const float wt = ws[j], ma_lo = ms[j * MP + a_lo], ma_hi = TWO ? ms[j * MP + a_hi] : 0.f;
                 float vb[4];
 #pragma unroll
                 for (int ct = 0; ct < 4; ++ct) vb[ct] = vs[j * VP + 16 * ct + li];
 #pragma unroll
-                for (int q = 0; q < RT; ++q)
-                    if (q >= at) {
-                        const float av = ms[j * MP + 16 * q + li] * (q > at ? 2.f * ma : ma);
-                        den[q] += av * wt;
+                for (int e = 0; e < SLOTS; ++e) {
+                    if (!TWO && e >= split) break;
+                    // the first tile of an index is on the diagonal, the others stand for their mirror too
+                    const float ma = e == 0 ? ma_lo : e < split ? 2.f * ma_lo : e == split ? ma_hi : 2.f * ma_hi;
+                    const float av = ms[j * MP + mcol[e] + li] * ma;
+                    den[e] += av * wt;
 #pragma unroll
-                        for (int ct = 0; ct < 4; ++ct) part[q][ct] = mm(av, vb[ct], part[q][ct]);
-                    }
+                    for (int ct = 0; ct < 4; ++ct) part[e][ct] = mm(av, vb[ct], part[e][ct]);
+                }
             }
         }
 #pragma unroll
-        for (int q = 0; q < RT; ++q)
-            if (q >= at) add_to(acc[q], part[q]);
+        for (int e = 0; e < SLOTS; ++e) add_to(acc[e], part[e]);
     }
     settle();
     float *rec = Z + ((size_t)u * sh.spans + span) * record_floats(RT, VT);
     float *srec = rec + (size_t)tile_pairs(RT) * 256 * 16 * VT;
-    const int pair0 = at * RT - at * (at - 1) / 2;          // (at, at)
 #pragma unroll
-    for (int q = 0; q < RT; ++q)
-        if (q >= at) {
-            const size_t pa = (size_t)(pair0 + q - at) * 16 + (a & 15);
-            const float dsum = over_groups(den[q]);
-            if (g == 0 && c0 == 0) srec[pa * 16 + li] = dsum;
+    for (int e = 0; e < SLOTS; ++e) {
+        if (!TWO && e >= split) break;
+        const int at = e < split ? lo : hi, a = e < split ? a_lo : a_hi, q = mcol[e] / 16;
+        const size_t pa = (size_t)(at * RT - at * (at - 1) / 2 + q - at) * 16 + (a & 15);
+        const float dsum = over_groups(den[e]);
+        if (g == 0 && c0 == 0) srec[pa * 16 + li] = dsum;
 #pragma unroll
-            for (int ct = 0; ct < 4; ++ct)
+        for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    rec[(pa * 16 + 4 * g + k) * (16 * VT) + c0 + 16 * ct + li] = acc[q][ct][k];
-        }
+            for (int k = 0; k < 4; ++k)
+                rec[(pa * 16 + 4 * g + k) * (16 * VT) + c0 + 16 * ct + li] = acc[e][ct][k];
+    }
 }
 
 // In place over the spans of a unit: exclusive prefix, exclusive suffix, or the total in slot 0.
@@ -420,7 +433,7 @@ psf_status states(const Problem &pb, const F32Plan &pl, const float *M, const S 
     sh.vec_v = pieces_ok<S>(pb.dv, {C});
     return with_tiles(pb, [&](auto dt, auto rt) -> psf_status {
         constexpr int VT = decltype(dt)::value, RT = decltype(rt)::value;
-        hipLaunchKernelGGL((f32_state_kernel<RT, VT, S>), dim3(RT * VT, (unsigned)count, (unsigned)pb.units),
+        hipLaunchKernelGGL((f32_state_kernel<RT, VT, S>), dim3((RT <= 4 ? RT * 2 : RT * 4) * (VT / 4), (unsigned)count, (unsigned)pb.units),
                            dim3(kF32Threads), 0, s, M, C, wts, Z, sh, span0);
         PSF_LAUNCH_CHECK();
         const size_t rec = record_floats(RT, VT), pieces = (size_t)pb.units * (rec / 4);
