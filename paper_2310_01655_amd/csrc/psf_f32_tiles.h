@@ -14,6 +14,7 @@
 #ifndef PSF_F32_TILES_H
 #define PSF_F32_TILES_H
 
+#include <type_traits>
 #include "psf_internal.h"
 
 namespace psf {
@@ -253,24 +254,33 @@ __device__ __forceinline__ void project(const T *G, int in, int r, int c0, const
     f4 odd[H];                                              // two chains a result: shorter sums
     clear(out);
     clear(odd);
-    int e0 = 0;
-    if (c0 + 16 <= r)
-        for (; e0 + 32 <= in; e0 += 32)
+    // STEP rows of G: all loads first
+    auto run = [&](auto step, int e0) {
+        constexpr int STEP = decltype(step)::value;
+        float a[STEP / 4];
 #pragma unroll
-            for (int e = 0; e < 32; e += 16) {
-                f4 xv[H];
+        for (int e = 0; e < STEP; e += 16)
 #pragma unroll
-                for (int h = 0; h < H; ++h) xv[h] = *(const f4 *)(xr + 16 * h * pitch + e0 + e);
+            for (int s = 0; s < 4; ++s) a[e / 4 + s] = load_f(ga, (size_t)((e0 + e + s) * r));
 #pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const float a = load_f(ga, (size_t)(e0 + e + s) * r);
+        for (int e = 0; e < STEP; e += 16) {
+            f4 xv[H];
 #pragma unroll
-                    for (int h = 0; h < H; ++h) {
-                        if (e) odd[h] = mm(a, xv[h][s], odd[h]);
-                        else out[h] = mm(a, xv[h][s], out[h]);
-                    }
+            for (int h = 0; h < H; ++h) xv[h] = *(const f4 *)(xr + 16 * h * pitch + e0 + e);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int h = 0; h < H; ++h) {
+                    if (e & 16) odd[h] = mm(a[e / 4 + s], xv[h][s], odd[h]);
+                    else out[h] = mm(a[e / 4 + s], xv[h][s], out[h]);
                 }
-            }
+        }
+    };
+    int e0 = 0;
+    if (c0 + 16 <= r) {
+        for (; e0 + 64 <= in; e0 += 64) run(std::integral_constant<int, 64>{}, e0);
+        if (e0 + 32 <= in) { run(std::integral_constant<int, 32>{}, e0); e0 += 32; }
+    }
     for (; e0 < in; e0 += 16) {
         f4 xv[H];
 #pragma unroll
