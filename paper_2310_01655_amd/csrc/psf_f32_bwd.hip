@@ -24,6 +24,7 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? 2 : 1) void f32_bwd_kernel(
     static_assert(WR == 4 || KT == 64, "the waves of a 16-row workgroup take one group of streamed rows each");
     static_assert(DT == VT, "the state is staged through the buffers of the streamed rows in turn");
     __shared__ __attribute__((aligned(16))) float lds[kTileFloats + KT];
+    __shared__ __attribute__((aligned(16))) float sden[2][16 * ZA];   // denominator column of a state piece
     float *xs = lds, *cs = xs + KT * KP, *ms = cs + KT * VP, *gs = lds + kTileFloats;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, g = lane >> 4, u = blockIdx.y;
     const int per_span = (min(sh.span, sh.n) + ROWS - 1) / ROWS;
@@ -151,13 +152,15 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? 2 : 1) void f32_bwd_kernel(
         const float *zs = z + (size_t)tile_pairs(RT) * 256 * 16 * VT;
         constexpr int PIECE = KT * 16 * VT, NP = PIECE / 4 / kF32Threads;
         constexpr int CH = 16 / ZA, LAST = tile_pairs(RT) * CH - 1;
-        f4 pre[NP];
+        f4 pre[NP], pre_s = {0.f, 0.f, 0.f, 0.f};
         auto fetch = [&](int piece) {
 #pragma unroll
             for (int k = 0; k < NP; ++k)
                 pre[k] = *(const f4 *)(z + (size_t)piece * PIECE + (k * kF32Threads + threadIdx.x) * 4);
+            if (threadIdx.x < 4 * ZA) pre_s = *(const f4 *)(zs + (size_t)piece * ZA * 16 + threadIdx.x * 4);
         };
-        auto put = [&](float *dst) {
+        auto put = [&](float *dst, int buf) {
+            if (threadIdx.x < 4 * ZA) *(f4 *)&sden[buf][threadIdx.x * 4] = pre_s;
 #pragma unroll
             for (int k = 0; k < NP; ++k) {
                 const int idx = k * kF32Threads + threadIdx.x;
@@ -166,7 +169,7 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? 2 : 1) void f32_bwd_kernel(
         };
         fetch(0);
         __syncthreads();
-        put(xs);
+        put(xs, 0);
         float *own = ms + ((WR == 4 ? 16 * wave : 0) + li) * MP;
 #pragma unroll
         for (int q = 0; q < RT; ++q)
@@ -194,7 +197,7 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? 2 : 1) void f32_bwd_kernel(
             clear(pc);
 #pragma unroll
             for (int k = 0; k < ZW; ++k)
-                U[k] = *(const f4 *)(zs + ((size_t)piece * ZA + (WR == 1 ? wave : k)) * 16 + 4 * g) * own_den;
+                U[k] = *(const f4 *)&sden[piece & 1][(WR == 1 ? wave : k) * 16 + 4 * g] * own_den;
 #pragma unroll
             for (int qq = 0; qq < VT; ++qq)
 #pragma unroll
@@ -229,7 +232,7 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? 2 : 1) void f32_bwd_kernel(
                 }
             }
             if constexpr (KSIDE) add_to(ac, pc);
-            if (piece < LAST) put(piece & 1 ? xs : cs);
+            if (piece < LAST) put(piece & 1 ? xs : cs, ~piece & 1);
         }
         flush(at, ma_sum);
         flush(q, mb_sum);

@@ -226,6 +226,7 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void 
     static_assert(WR == 4 || KT == 64, "the waves of a 16-row workgroup take one key group each");
     static_assert(DT == VT, "the state is staged through the buffers of K and V in turn");
     __shared__ __attribute__((aligned(16))) float lds[kTileFloats];
+    __shared__ __attribute__((aligned(16))) float sden[2][16 * ZA];   // denominator column of a state piece
     float *ks = lds, *vs = lds + KT * KP, *ms = vs + KT * VP;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, g = lane >> 4, u = blockIdx.y;
     const int per_span = (min(sh.span, sh.n) + ROWS - 1) / ROWS;
@@ -307,13 +308,15 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void 
         const float *zs = z + (size_t)tile_pairs(RT) * 256 * 16 * VT;
         constexpr int PIECE = KT * 16 * VT, NP = PIECE / 4 / kF32Threads;     // floats of a piece; 16-byte loads a thread
         constexpr int CH = 16 / ZA, LAST = tile_pairs(RT) * CH - 1;
-        f4 pre[NP];
+        f4 pre[NP], pre_s = {0.f, 0.f, 0.f, 0.f};
         auto fetch = [&](int piece) {
 #pragma unroll
             for (int k = 0; k < NP; ++k)
                 pre[k] = *(const f4 *)(z + (size_t)piece * PIECE + (k * kF32Threads + threadIdx.x) * 4);
+            if (threadIdx.x < 4 * ZA) pre_s = *(const f4 *)(zs + (size_t)piece * ZA * 16 + threadIdx.x * 4);
         };
-        auto put = [&](float *dst) {
+        auto put = [&](float *dst, int buf) {
+            if (threadIdx.x < 4 * ZA) *(f4 *)&sden[buf][threadIdx.x * 4] = pre_s;
 #pragma unroll
             for (int k = 0; k < NP; ++k) {
                 const int idx = k * kF32Threads + threadIdx.x;
@@ -322,7 +325,7 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void 
         };
         fetch(0);
         __syncthreads();
-        put(ks);
+        put(ks, 0);
         // the wave's own sketch rows, where they can be indexed (sync: the last pairs have been read)
         float *own = ms + ((WR == 4 ? 16 * wave : 0) + li) * MP;
 #pragma unroll
@@ -343,7 +346,7 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void 
             for (int k = 0; k < ZW; ++k) {
                 const int aa = WR == 1 ? wave : k;
                 const float ma = own[16 * at + ZA * ch + aa];
-                const f4 sd = *(const f4 *)(zs + ((size_t)piece * ZA + aa) * 16 + 4 * g);
+                const f4 sd = *(const f4 *)&sden[piece & 1][aa * 16 + 4 * g];
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
                     const float phi = ma * mq[s];
@@ -353,7 +356,7 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void 
                         acc[ct] = mm(zt[(aa * 16 + 4 * g + s) * VP + 16 * ct + li], phi, acc[ct]);
                 }
             }
-            if (piece < LAST) put(piece & 1 ? ks : vs);
+            if (piece < LAST) put(piece & 1 ? ks : vs, ~piece & 1);
         }
     }
 
