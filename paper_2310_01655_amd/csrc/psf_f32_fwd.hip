@@ -228,11 +228,13 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void 
     __shared__ __attribute__((aligned(16))) float lds[kTileFloats];
     __shared__ __attribute__((aligned(16))) float sden[2][16 * ZA];   // denominator column of a state piece
     float *ks = lds, *vs = lds + KT * KP, *ms = vs + KT * VP;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, g = lane >> 4, u = blockIdx.y;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, g = lane >> 4;
+    // the longest rows of all units first: what is dealt last is short, and the workgroups that
+    // share a CU are of different lengths
     const int per_span = (min(sh.span, sh.n) + ROWS - 1) / ROWS;
-    const int x = gridDim.x - 1 - blockIdx.x;               // the longest rows of a span first
-    const int span = x / per_span, s_begin = span * sh.span, s_end = min(sh.n, s_begin + sh.span);
-    const int i0 = s_begin + (x % per_span) * ROWS;
+    const int u = blockIdx.x % sh.units, x = blockIdx.x / sh.units;
+    const int span = sh.spans - 1 - x % sh.spans, s_begin = span * sh.span, s_end = min(sh.n, s_begin + sh.span);
+    const int i0 = s_begin + (per_span - 1 - x / sh.spans) * ROWS;
     if (i0 >= s_end) return;
     const int iw = i0 + (WR == 4 ? 16 * wave : 0), i = iw + li;
     const int i_last = min(i0 + ROWS, s_end) - 1, iw_last = min(iw + 15, s_end - 1);
@@ -460,7 +462,7 @@ psf_status rows_launch(const Problem &pb, const F32Plan &pl, const float *MQ, co
         constexpr int DT = decltype(dt)::value, RT = decltype(rt)::value;
         auto go = [&](auto kernel, int rows) {
             const int per_span = ((pl.span < pb.n ? pl.span : pb.n) + rows - 1) / rows;
-            hipLaunchKernelGGL(kernel, dim3((unsigned)(per_span * pl.spans), (unsigned)pb.units), dim3(kF32Threads), 0,
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(per_span * pl.spans) * (unsigned)pb.units), dim3(kF32Threads), 0,
                                s, MQ, MK, (const T *)Q, (const T *)K, (const T *)V, Z, (T *)O, (const T *)dO, GV, gden,
                                sh);
         };
@@ -492,7 +494,7 @@ bool f32_split_rows(const Problem &pb)
 F32Shape f32_shape(const Problem &pb, const F32Plan &pl)
 {
     F32Shape sh = {};
-    sh.n = pb.n; sh.d = pb.d; sh.dv = pb.dv; sh.mcols = pb.mcols; sh.p = pb.p; sh.b = pb.b; sh.heads = pb.heads;
+    sh.n = pb.n; sh.d = pb.d; sh.dv = pb.dv; sh.mcols = pb.mcols; sh.p = pb.p; sh.b = pb.b; sh.units = pb.units;
     sh.span = pl.span; sh.spans = pl.spans;
     sh.local_exact = pb.local_exact && !pl.noncausal;
     sh.noncausal = pl.noncausal; sh.pairs = pl.pairs; sh.states = pl.states;

@@ -328,7 +328,7 @@ __host__ __device__ constexpr size_t record_floats(int rt, int vt) { return (siz
 
 // Everything the kernels need to know about the shape and how the sequence is cut.
 struct F32Shape {
-    int n, d, dv, mcols, p, b, heads;
+    int n, d, dv, mcols, p, b, units;
     int span, spans;          // tokens between two states; number of such spans
     int local_exact, noncausal, pairs, states;
     int vec_x, vec_v, vec_m, vec_g;   // 4-column pieces of Q, K (d), V, O (dv), m (mcols), G (r)
