@@ -12,7 +12,8 @@
 //     and phi = m (x) m gives dm[a] = sum_b (dphi[a,b] + dphi[b,a]) m[b];
 //   pairs inside a block: w = <q,k>^p (Section 3.2) or <m(q),m(k)>^2 (Section 3.1), pair by pair;
 //   finally dQ += J^T dm(Q), dK += J^T dm(K) through Algorithm 1.
-// These are plain fp32 LDS-staged kernels for every descriptor with sketch features (any d, dv,
+// d, dv and sketch columns up to 128 run on fp32 matrix instructions (psf_f32_bwd.hip).  These are
+// plain fp32 LDS-staged kernels for every descriptor with sketch features (any d, dv,
 // r <= 256, p in {2,4,8,16}, either in-block rule, fp32 or bf16 storage).  The sketch matrices
 // are constants.  With learned sketches (Algorithm 2) the last step goes through the networks
 // instead and can also return the gradient with respect to their parameters.

@@ -10,8 +10,8 @@
 // f32_plan() chooses the span.
 //
 // Measured against the vector kernels (us a call, forward / forward and backward): 36 units of 3000
-// tokens, r = 32, b = 200, bf16 storage 8530 -> 387; 24 units of 1950, b = 150, forward and backward
-// 26950 -> 826; one unit of 1024, r = 16, fp32 storage 248 -> 35.  Relative error against float64
+// tokens, r = 32, b = 200, bf16 storage 8540 -> 346; 24 units of 1950, b = 150, forward and backward
+// 26940 -> 747; one unit of 1024, r = 16, fp32 storage 248 -> 33.  Relative error against float64
 // (fp32 storage, 2048 tokens, r = 64): 1.6e-6 -> 4.5e-7, gradients 4e-7 to 5e-7 on either.
 #include "psf_f32_tiles.h"
 #include "psf_f32.h"
