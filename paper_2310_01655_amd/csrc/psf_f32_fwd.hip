@@ -113,7 +113,7 @@ __global__ __launch_bounds__(kF32Threads, RT <= 2 ? 3 : RT == 4 ? 2 : 1) void f3
     const int hi = TWO ? RT - 1 - lo : lo, a_hi = RT == 1 ? a_lo + 8 : 16 * hi + 4 * (grp % 4) + wave;
     const int split = RT - lo;                              // slots of a_lo; the others are a_hi's
     const int span = span0 + blockIdx.y, u = blockIdx.z;
-    const int j_begin = span * sh.span, j_end = min(sh.n, j_begin + sh.span);
+    const auto [j_begin, j_end] = state_tokens(sh.n, sh.span, span, sh.dv, c0);
     f4 acc[SLOTS][4];
     float den[SLOTS];
     int mcol[SLOTS];                                        // first sketch column of the slot's tile

@@ -1,0 +1,33 @@
+// Which rows and columns the staged loads of the fp32 matrix-core kernels touch: plain integer
+// rules, shared by the kernels and by the host code that checks them.
+#ifndef PSF_F32_INDEX_H
+#define PSF_F32_INDEX_H
+
+#ifdef __HIP__
+#include <hip/hip_runtime.h>
+#define PSF_HD __host__ __device__ __forceinline__
+#else
+#define PSF_HD inline
+#endif
+
+namespace psf {
+
+// Element a thread of a staged tile loads its four columns from: row `row`, column c of a tile whose
+// rows are ld apart, or the tile's first piece where that place is not there.  The first piece has to
+// exist: nvalid and width are at least 1.
+PSF_HD unsigned tile_piece(int row, int c, int ld, int nvalid, int width)
+{
+    return row < nvalid && c < width ? (unsigned)row * (unsigned)ld + (unsigned)c : 0u;
+}
+
+// Tokens of a span that a workgroup of the state kernel walks for the value columns from c0 on: none
+// where there are no such columns (dv <= 64 beside wider keys), whose sums are zero.
+struct TokenRange { int begin, end; };
+PSF_HD TokenRange state_tokens(int n, int span_tokens, int span, int dv, int c0)
+{
+    const int begin = span * span_tokens, end = begin + span_tokens < n ? begin + span_tokens : n;
+    return {begin, c0 < dv ? end : begin};
+}
+
+}  // namespace psf
+#endif

@@ -15,6 +15,7 @@
 #define PSF_F32_TILES_H
 
 #include <type_traits>
+#include "psf_f32_index.h"
 #include "psf_internal.h"
 
 namespace psf {
@@ -123,8 +124,8 @@ __device__ __forceinline__ void load_frags(const S *row, int width, bool there, 
 template <int NT>
 constexpr int pitch_of() { return 16 * NT + 4; }
 
-// NR rows of 16 * NT columns on their way into LDS; rows >= nvalid (at least 1) and columns >=
-// width become zero.  All loads are issued before the first result is needed, and none of them
+// NR rows of 16 * NT columns on their way into LDS; rows >= nvalid and columns >= width (at least
+// 1 either) become zero.  All loads are issued before the first result is needed, and none of them
 // sits behind a branch: places that are not there load the first piece instead.  A thread
 // holds the same columns of kPieces rows, as stored.
 template <int NT, int NR, typename S>
@@ -136,11 +137,9 @@ struct Tile {
     __device__ __forceinline__ void load(const S *src, int ld, int nvalid, int width)
     {
         const int row = threadIdx.x / (4 * NT), c = 4 * (threadIdx.x % (4 * NT));
-        const uint32_t at = ((uint32_t)row * ld + c) * sizeof(S), step = (uint32_t)kStep * ld * sizeof(S);
-        const int rows = c < width ? nvalid : 0;
 #pragma unroll
         for (int it = 0; it < kPieces; ++it)
-            v[it] = *(const raw *)((const char *)src + (row + it * kStep < rows ? at + it * step : 0u));
+            v[it] = *(const raw *)((const char *)src + tile_piece(row + it * kStep, c, ld, nvalid, width) * (uint32_t)sizeof(S));
     }
     __device__ __forceinline__ void store(float *dst, int nvalid, int width) const
     {

@@ -1,0 +1,51 @@
+"""The addresses of the fp32 matrix-core kernels' staged loads, from the rules the kernels use
+(csrc/psf_f32_index.h), on the host: every load of the state kernel stays inside the value tensor,
+for value widths on either side of the 64 columns a workgroup takes and last chunks of few rows."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "psf_f32_index.h"
+using namespace psf;
+int main()
+{
+    long long bad = 0, loads = 0;
+    for (int rows_staged : {32, 64})                       // tokens of a chunk: RT = 8, smaller RT
+        for (int dv = 4; dv <= 128; dv += 4)
+            for (int n : {1, 2, 3, 5, 17, 31, 32, 33, 63, 64, 65, 130, 205, 1025})
+                for (int span_tokens : {1, 41, 64, 205, n})
+                    for (int c0 : {0, 64}) {               // the two workgroups of a wide problem
+                        const int spans = (n + span_tokens - 1) / span_tokens;
+                        const long long end = (long long)n * dv;          // of the last unit
+                        for (int span = 0; span < spans; ++span) {
+                            const TokenRange t = state_tokens(n, span_tokens, span, dv, c0);
+                            for (int j0 = t.begin; j0 < t.end; j0 += rows_staged)
+                                for (int row = 0; row < rows_staged; ++row)
+                                    for (int c = 0; c < 64; c += 4) {
+                                        const long long at = (long long)j0 * dv + c0 +
+                                                             tile_piece(row, c, dv, t.end - j0, dv - c0);
+                                        ++loads;
+                                        if (at < 0 || at + 4 > end) {
+                                            if (bad++ < 4)
+                                                printf("dv %d n %d span %d c0 %d: %lld of %lld\n", dv, n, span, c0, at, end);
+                                        }
+                                    }
+                        }
+                    }
+    printf("loads %lld outside %lld\n", loads, bad);
+    return bad ? 1 : 0;
+}
+"""
+
+
+def test_state_kernel_loads_stay_inside_the_values(tmp_path):
+    src, exe = tmp_path / "index.cpp", tmp_path / "index"
+    src.write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_2310_01655_amd", "csrc"), str(src),
+                    "-o", str(exe)], check=True)
+    run = subprocess.run([str(exe)], stdout=subprocess.PIPE, text=True)
+    assert run.returncode == 0, run.stdout
