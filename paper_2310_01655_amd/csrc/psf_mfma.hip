@@ -69,6 +69,15 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c)
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// Two wait states at the end of a loop body that ends in products whose results the next pass reads
+// first.  The compiler counts the branches between a product and its reader before it turns some of
+// them round, which leaves one wait state fewer than it meant to on the turned way.
+__device__ __forceinline__ void branch_wait()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 1");
+}
+
 __device__ __forceinline__ bf16x8 cvt8(f32x8 v) { return __builtin_convertvector(v, bf16x8); }
 __device__ __forceinline__ bf16x4 cvt4(f32x4 v) { return __builtin_convertvector(v, bf16x4); }
 
@@ -1608,7 +1617,10 @@ __device__ __forceinline__ void out_workgroup(const bf16_t *__restrict__ Q, cons
 #pragma unroll
             for (int s = 0; s < KS; ++s) asm volatile("" ::"v"(qfr[tt][s]));
 #pragma unroll 1
-        for (int kt = 0; kt < ntiles_w - 1; ++kt) tile(std::false_type{}, kt);
+        for (int kt = 0; kt < ntiles_w - 1; ++kt) {
+            tile(std::false_type{}, kt);
+            branch_wait();
+        }
         tile(std::true_type{}, ntiles_w - 1);             // the tile that holds this wave's own tokens
         // this wave's keys are exhausted: flush the pending item while its tile is still in LDS
         apply_pv(ntiles_w * IPT - 1, (IPT - 1) / TT, (IPT - 1) % TT, pk[PAR * ((IPT - 1) & 1)]);
@@ -2429,6 +2441,7 @@ __global__ __launch_bounds__(512 / TT, 1) void k_learned_sketch(const bf16_t *__
                     }
                 }
             }
+            branch_wait();
         }
         if ((net & 1) == 0) {
 #pragma unroll
