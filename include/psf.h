@@ -100,6 +100,12 @@ int psf_kernel_path(const psf_desc *desc);
  * sketch of the query rows (Algorithm 1).  0 where none of this applies.  Host only. */
 int psf_fwd_beside_states(const psf_desc *desc);
 
+/* How the general path cuts the sequence on its fp32 matrix-core kernels: the number of spans with
+ * a state of their own, 0 where every pair of tokens is weighted directly, -1 where these kernels
+ * do not run (or the descriptor is invalid).  pass: 0 psf_causal_attn_fwd, 1 psf_noncausal_attn_fwd,
+ * 2 psf_causal_attn_bwd.  Host only. */
+int psf_general_spans(const psf_desc *desc, int32_t pass);
+
 /* Bytes of device workspace psf_causal_attn_fwd needs for this descriptor (0 if invalid).
  * Holds the sketches m(Q), m(K), the block prefix states Z_l (Section 3.1) and staging. */
 size_t psf_workspace_bytes(const psf_desc *desc);

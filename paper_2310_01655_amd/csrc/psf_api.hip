@@ -232,6 +232,14 @@ int psf_fwd_beside_states(const psf_desc *desc)
     return mfma_beside_states(pb);
 }
 
+int psf_general_spans(const psf_desc *desc, int32_t pass)
+{
+    Problem pb;
+    if (make_problem(desc, &pb) != PSF_OK || pass < 0 || pass > 2) return -1;
+    if (pass == 2 ? !general_bwd_supported(pb) || bwd_on_mfma(pb) : select_path(pb) == 1) return -1;
+    return general_spans(pb, pass);
+}
+
 size_t psf_g_len(int32_t d, int32_t r, int32_t p)
 {
     if (d <= 0 || r <= 0 || p < 4) return 0;
@@ -323,7 +331,7 @@ size_t psf_noncausal_workspace_bytes(const psf_desc *desc)
 {
     Problem pb;
     if (make_problem(desc, &pb) != PSF_OK) return 0;
-    return select_path(pb) == 1 ? mfma_noncausal_workspace_bytes(pb) : general_workspace_bytes(pb);
+    return select_path(pb) == 1 ? mfma_noncausal_workspace_bytes(pb) : general_workspace_bytes(pb, true);
 }
 
 psf_status psf_noncausal_attn_fwd(const psf_desc *desc, const void *Q, const void *K, const void *V,

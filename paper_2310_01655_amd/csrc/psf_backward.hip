@@ -1088,6 +1088,7 @@ psf_status learned_sketch_bwd(const Problem &pb, const void *X, const void *G, c
 struct BwdWs {
     float *MQ, *MK, *CV, *GC, *Z, *RB, *dMQ, *dMK, *dQd, *dKd;
     float *LS, *LP;                              // learned sketches: staging of one chunk of rows; slices of one network's sums
+    F32Choice f32;
     size_t total;
 };
 
@@ -1102,8 +1103,9 @@ BwdWs carve_bwd(const Problem &pb, void *ws)
     w.MK = take(rows * pb.mcols);
     w.CV = take(rows * kc);
     w.GC = take(rows * kc);
-    w.Z = take((size_t)pb.units * pb.t * (size_t)pb.F * kc);
-    w.RB = take((size_t)pb.units * pb.t * (size_t)pb.F * kc);
+    w.f32 = f32_choose(pb, 0, false, true);
+    w.Z = take(w.f32.z_floats);
+    w.RB = take(w.f32.z_floats);
     w.dMQ = take(rows * pb.mcols);
     w.dMK = take(rows * pb.mcols);
     w.dQd = take(rows * pb.d);
@@ -1120,7 +1122,7 @@ psf_status bwd_launch_f32(const Problem &pb, const BwdWs &w, const void *Q, cons
                           const void *G, const void *dO, void *dQ, void *dK, void *dV, hipStream_t s, StageTimer *tm)
 {
     const size_t rows = (size_t)pb.units * pb.n;
-    const F32Plan pl = f32_plan(pb, (size_t)pb.units * pb.t * (size_t)pb.F * (pb.dv + 1), false, true);
+    const F32Plan &pl = w.f32.plan;
     float *GV = w.GC, *gden = w.GC + rows * pb.dv;
     psf_status st = general_sketch_pair_f32(pb, Q, K, G, w.MQ, w.MK, s);
     if (st != PSF_OK) return st;
@@ -1153,7 +1155,7 @@ psf_status bwd_launch(const Problem &pb, const void *Q, const void *K, const voi
     BwdWs w = carve_bwd(pb, ws);
     const size_t rows = (size_t)pb.units * pb.n;
     psf_status st;
-    if (f32_supported(pb)) {
+    if (w.f32.use) {
         st = bwd_launch_f32<T>(pb, w, Q, K, V, G, dO, dQ, dK, dV, s, tm);
         if (st != PSF_OK) return st;
     } else {
@@ -1263,6 +1265,13 @@ bool general_bwd_supported(const Problem &pb)
 }
 
 size_t general_bwd_workspace_bytes(const Problem &pb) { return carve_bwd(pb, nullptr).total; }
+
+int general_spans(const Problem &pb, int pass)
+{
+    const size_t m_bytes = align_up((size_t)pb.units * pb.n * pb.mcols * 4, 256);
+    const F32Choice c = pass == 2 ? carve_bwd(pb, nullptr).f32 : f32_choose(pb, 2 * m_bytes, pass == 1, false);
+    return !c.use ? -1 : c.plan.states ? c.plan.spans : 0;
+}
 
 psf_status general_attn_bwd(const Problem &pb, const void *Q, const void *K, const void *V,
                             const void *G, const void *dO, void *dQ, void *dK, void *dV, void *ws,

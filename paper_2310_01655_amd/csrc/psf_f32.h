@@ -15,14 +15,23 @@ struct F32Plan {
     int span, spans;
     int pairs, states;       // weights of pairs inside a span taken directly; states across spans
     int noncausal;
+    double cost;             // seconds of the whole chip, see f32_plan
+};
+
+// Whether a call runs on these kernels, its plan, and the floats its state records take in the
+// workspace (each of the two sets of a backward pass).
+struct F32Choice {
+    bool use;
+    F32Plan plan;
+    size_t z_floats;
 };
 
 // rows of a staged tile: 64, or 32 where three tiles of 128 columns would leave a CU one workgroup
 constexpr int f32_tile_rows(int dt, int wr) { return dt == 8 && wr == 4 ? 32 : 64; }
 
 bool f32_supported(const Problem &pb);
-// z_floats: room for state records (the caller's workspace); grad: plan for the backward pass
-F32Plan f32_plan(const Problem &pb, size_t z_floats, bool noncausal, bool grad);
+// fixed_bytes: the rest of the call's workspace; grad: the backward pass
+F32Choice f32_choose(const Problem &pb, size_t fixed_bytes, bool noncausal, bool grad);
 F32Shape f32_shape(const Problem &pb, const F32Plan &pl);
 // 16 rows a workgroup instead of 64: fewer than two workgroups a CU otherwise
 bool f32_split_rows(const Problem &pb);

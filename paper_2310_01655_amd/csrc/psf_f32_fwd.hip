@@ -507,7 +507,8 @@ F32Shape f32_shape(const Problem &pb, const F32Plan &pl)
 // Measured with every span forced (blocks a span: us): 36 units x 3000, r 32, b 200: 1: 475, 2: 452,
 // 4: 469, 8: 534, all 15: 558; 12 x 16384, r 32, b 64: 1: 855, 4: 668, 16: 934, all: 4267; 24 x 8000,
 // r 64, b 250: 1: 2061, 2: 2061, 8: 2646; 48 x 8192, r 16, b 256: 1: 697, 4: 1224.
-F32Plan f32_plan(const Problem &pb, size_t z_floats, bool noncausal, bool grad)
+// z_floats: room for state records.
+static F32Plan f32_plan(const Problem &pb, size_t z_floats, bool noncausal, bool grad)
 {
     const bool wide = pb.d > 64 || pb.dv > 64 || pb.mcols > 64;
     int rt = 0, vt = wide ? 8 : 4;
@@ -528,16 +529,17 @@ F32Plan f32_plan(const Problem &pb, size_t z_floats, bool noncausal, bool grad)
         const size_t most = z_floats / ((size_t)pb.units * rec);
         if ((size_t)spans > most) spans = (int)most;
         best.noncausal = 1;
+        best.cost = direct;
         if (spans < 1 || direct <= with_state) {
             best.span = pb.n; best.spans = 1; best.pairs = 1;
             return best;
         }
+        best.cost = with_state;
         best.span = (pb.n + spans - 1) / spans;
         best.spans = (pb.n + best.span - 1) / best.span;
         best.states = 1;
         return best;
     }
-    double best_cost = 0;
     for (int s = 1;; s *= 2) {
         if (s > pb.t) s = pb.t;
         const int spans = (pb.t + s - 1) / s;
@@ -547,14 +549,58 @@ F32Plan f32_plan(const Problem &pb, size_t z_floats, bool noncausal, bool grad)
             if (spans > 1)
                 cost += tokens * (1.0 - 1.0 / spans) * state_flops / rate +
                         (double)pb.units * spans * rec * 4 * passes / bw + (grad ? 10e-6 : 5e-6);
-            if (best.spans == 0 || cost < best_cost) {
-                best_cost = cost;
+            if (best.spans == 0 || cost < best.cost) {
+                best.cost = cost;
                 best.span = s * pb.b; best.spans = spans; best.pairs = 1; best.states = spans > 1;
             }
         }
         if (s == pb.t) break;
     }
     return best;
+}
+
+static size_t plan_floats(const Problem &pb, const F32Plan &pl)
+{
+    size_t rec = 0;
+    with_tiles(pb, [&](auto dt, auto rt) -> psf_status {
+        rec = record_floats(decltype(rt)::value, decltype(dt)::value);
+        return PSF_OK;
+    });
+    return pl.states ? (size_t)pb.units * pl.spans * rec : 0;
+}
+
+// Records are padded to tiles (16 sketch indices, 64 or 128 value columns), the room of the vector
+// kernels, t F (dv + 1) floats a unit, is not: with few or small blocks (t mcols^2 (dv + 1) below the
+// record's floats) no record fits, and pairs alone cost time quadratic in n.  Where that room
+// makes the plan dearer than the best one by more than a quarter, the workspace grows to the
+// best plan's records (at most kMostRoom, and not past the library's static scratch where the
+// call fitted it).  If that does not bring the cost within four times the best one, the vector
+// kernels take the call, whose time is linear.  Measured, without a mask, r = 8, d = 128, dv = 16, two
+// blocks (us; pairs, best plan, vector kernels): 12 units x 4096 1274, 272, 714; 12 x 16384 20429, 1050,
+// 2487; 96 x 16384 165250, 7607, 10294.  Below 1.25 nothing is to be gained (96 x 1024: 687, 687, 750).
+F32Choice f32_choose(const Problem &pb, size_t fixed_bytes, bool noncausal, bool grad)
+{
+    constexpr size_t kMostRoom = ((size_t)1 << 30) / sizeof(float);
+    F32Choice c = {};
+    c.z_floats = (size_t)pb.units * pb.t * (size_t)pb.F * (pb.dv + 1);
+    if (!f32_supported(pb)) return c;
+    c.use = true;
+    c.plan = f32_plan(pb, c.z_floats, noncausal, grad);
+    const double best = f32_plan(pb, SIZE_MAX, noncausal, grad).cost;
+    if (c.plan.cost <= 1.25 * best) return c;
+    size_t room = kMostRoom;
+    if (!noncausal && !grad && fixed_bytes + align_up(c.z_floats * 4, 256) <= PSF_STATIC_SCRATCH_BYTES)
+        room = (PSF_STATIC_SCRATCH_BYTES - fixed_bytes) / 256 * 256 / sizeof(float);
+    if (room > c.z_floats) {
+        c.plan = f32_plan(pb, room, noncausal, grad);
+        const size_t need = plan_floats(pb, c.plan);
+        if (need > c.z_floats) c.z_floats = need;
+    }
+    if (c.plan.cost > 4.0 * best) {
+        c = {};
+        c.z_floats = (size_t)pb.units * pb.t * (size_t)pb.F * (pb.dv + 1);
+    }
+    return c;
 }
 
 psf_status f32_sketch_pair(const Problem &pb, const void *X1, const void *X2, const void *G, float *M1, float *M2,

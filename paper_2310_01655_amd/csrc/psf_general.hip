@@ -384,14 +384,16 @@ __global__ __launch_bounds__(kThreads) void gen_out_kernel(
 
 struct GeneralWs {
     float *MQ, *MK, *Z;
+    F32Choice f32;
     size_t total;
 };
 
-GeneralWs carve(const Problem &pb, void *ws)
+GeneralWs carve(const Problem &pb, void *ws, bool noncausal)
 {
     GeneralWs w;
     const size_t m_bytes = pb.exact_feat ? 0 : align_up((size_t)pb.units * pb.n * pb.mcols * 4, 256);
-    const size_t z_bytes = align_up((size_t)pb.units * pb.t * (size_t)pb.F * (pb.dv + 1) * 4, 256);
+    w.f32 = f32_choose(pb, 2 * m_bytes, noncausal, false);
+    const size_t z_bytes = align_up(w.f32.z_floats * 4, 256);
     char *base = (char *)ws;
     w.MQ = (float *)base;
     w.MK = (float *)(base + m_bytes);
@@ -434,11 +436,10 @@ template <typename T>
 psf_status attn_launch(const Problem &pb, const void *Q, const void *K, const void *V, const void *G,
                        void *O, void *ws, hipStream_t s, StageTimer *tm, bool noncausal)
 {
-    GeneralWs w = carve(pb, ws);
+    GeneralWs w = carve(pb, ws, noncausal);
     psf_status st;
-    if (f32_supported(pb)) {
-        const size_t z_floats = (size_t)pb.units * pb.t * (size_t)pb.F * (pb.dv + 1);
-        const F32Plan pl = f32_plan(pb, z_floats, noncausal, false);
+    if (w.f32.use) {
+        const F32Plan &pl = w.f32.plan;
         st = sketches_f32<T>(pb, Q, K, G, w.MQ, w.MK, s);
         if (st != PSF_OK) return st;
         if (tm) { tm->mark(); tm->mark(); }             // one launch for both
@@ -495,9 +496,9 @@ psf_status attn_launch(const Problem &pb, const void *Q, const void *K, const vo
 
 }  // namespace
 
-size_t general_workspace_bytes(const Problem &pb)
+size_t general_workspace_bytes(const Problem &pb, bool noncausal)
 {
-    return carve(pb, nullptr).total;
+    return carve(pb, nullptr, noncausal).total;
 }
 
 psf_status general_sketch(const Problem &pb, const void *X, const void *G, void *M_out, void *Phi_out,

@@ -38,7 +38,10 @@ struct StageTimer {
 };
 
 // General fp32 path (any descriptor the check admits).
-size_t general_workspace_bytes(const Problem &pb);
+size_t general_workspace_bytes(const Problem &pb, bool noncausal = false);
+// spans with a state of their own on the fp32 matrix-core kernels: 0 where pairs alone, -1 where the
+// vector kernels take the call (pass 0: causal forward, 1: no mask, 2: backward)
+int general_spans(const Problem &pb, int pass);
 psf_status general_sketch(const Problem &pb, const void *X, const void *G, void *M_out,
                           void *Phi_out, hipStream_t s);
 // noncausal: Section 2.2 (every query sees every key; b only partitions the work).

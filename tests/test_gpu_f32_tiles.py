@@ -70,3 +70,42 @@ def test_a_later_infinity_does_not_reach_earlier_rows(n, at):
     assert torch.isfinite(got[:, :, :at]).all()
     torch.testing.assert_close(got[:, :, :at], want[:, :, :at], rtol=1e-5, atol=1e-6)   # fp32 sums in another order
     assert not torch.isfinite(got[:, :, at:, 5:7]).any()
+
+
+@pytest.mark.parametrize("heads,n,d,dv,r,b,spans", [
+    (2, 4096, 16, 16, 16, 4096, (0, 16, 0)),        # without a mask, one block: the records outgrow the states' room
+    (1, 4096, 128, 16, 8, 512, (8, 16, 8)),         # causal and backward too; the upper half of a record is empty
+    (1, 4096, 64, 1, 16, 1024, (4, 16, 4)),         # one value column
+])
+def test_records_that_need_more_room_than_the_vector_kernels_states(heads, n, d, dv, r, b, spans):
+    q, k, v, G = case_inputs(1, heads, n, d, dv, 4, r, b, "f32")
+    dO = inputs.make_dout(1, heads, n, dv, seed=7, dtype="f32")
+    desc = psf.make_desc(1, heads, n, d, 4, r, b, "f32", dv=dv, per_head=True)
+    assert tuple(psf.general_spans(desc, i) for i in range(3)) == spans
+    args = [x.cuda() for x in (q, k, v, G)]
+    O = psf.psf_causal_attn_fwd(desc, *args)
+    N = psf.psf_noncausal_attn_fwd(desc, *args)
+    grads = psf.psf_causal_attn_bwd(desc, *args, dO.cuda())
+    f, rows = [as_f64(x) for x in (q, k, v, G)], [0, 1, b - 1, b % n, n // 2 + 1, n - 2, n - 1]
+    want, _ = oracle.attn_def_batch(*f, 4, r, b, rows=rows)
+    assert_close(O[:, :, rows].float().cpu().numpy(), want, "f32", "forward")
+    last = heads - 1
+    want = oracle.attn_noncausal(f[0][0, last, rows], *(x[0, last] for x in f[1:3]), f[3][last], 4, r)
+    assert_close(N[0, last, rows].float().cpu().numpy(), want[0] if isinstance(want, tuple) else want, "f32", "noncausal")
+    for name, got, w in zip(("dQ", "dK", "dV"), grads, oracle.attn_bwd_batch(*f, as_f64(dO), 4, r, b)):
+        assert_close_scaled(got.float().cpu().numpy(), w, "f32", name)
+
+
+def test_the_static_scratch_takes_a_call_whose_records_do_not_fit_it():
+    desc = psf.make_desc(1, 40, 16384, 128, 4, 4, 16, "f32", dv=1)
+    assert psf.general_spans(desc) == -1 and psf.workspace_bytes(desc) <= psf.STATIC_SCRATCH_BYTES
+    q, k, v = inputs.make_qkv(1, 40, 16384, 128, dv=1, seed=7, dtype="f32")
+    G = inputs.make_sketch_matrices(40, 128, 4, 4, per_head=False, seed=3, dtype="f32")
+    args = [x.cuda() for x in (q, k, v, G)]
+    O = psf.psf_causal_attn_fwd(desc, *args)
+    again = torch.empty_like(O)
+    psf.psf_causal_attn_fwd_static(desc, *args, again)
+    assert torch.equal(O, again)
+    rows = [0, 15, 16, 8000, 16383]
+    want, _ = oracle.attn_def_batch(*(as_f64(x) for x in (q, k, v, G)), 4, 4, 16, rows=rows)
+    assert_close(O[:, :, rows].float().cpu().numpy(), want, "f32", "forward")
