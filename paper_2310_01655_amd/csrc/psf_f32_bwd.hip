@@ -28,7 +28,9 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? 2 : 1) void f32_bwd_kernel(
     float *xs = lds, *cs = xs + KT * KP, *ms = cs + KT * VP, *gs = lds + kTileFloats;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, g = lane >> 4;
     const int per_span = (min(sh.span, sh.n) + ROWS - 1) / ROWS;
-    const int u = blockIdx.x % sh.units, x = blockIdx.x / sh.units;     // the longest walks of all units first
+    const unsigned flat = blockIdx.y * gridDim.x + blockIdx.x;
+    const int u = flat % sh.units, x = flat / sh.units;     // the longest walks of all units first
+    if (x >= per_span * sh.spans) return;
     const int span = KSIDE ? x % sh.spans : sh.spans - 1 - x % sh.spans;
     const int s_begin = span * sh.span, s_end = min(sh.n, s_begin + sh.span);
     const int o0 = s_begin + (KSIDE ? x / sh.spans : per_span - 1 - x / sh.spans) * ROWS;
@@ -420,7 +422,8 @@ psf_status side_launch(const Problem &pb, const F32Plan &pl, const float *MQ, co
         constexpr int DT = decltype(dt)::value, RT = decltype(rt)::value;
         auto go = [&](auto kernel, int rows) {
             const int per_span = ((pl.span < pb.n ? pl.span : pb.n) + rows - 1) / rows;
-            hipLaunchKernelGGL(kernel, dim3((unsigned)(per_span * pl.spans) * (unsigned)pb.units), dim3(kF32Threads), 0,
+            const FlatGrid grid = flat_grid((unsigned long long)per_span * pl.spans * pb.units);
+            hipLaunchKernelGGL(kernel, dim3(grid.x, grid.y), dim3(kF32Threads), 0,
                                s, KSIDE ? MK : MQ, KSIDE ? MQ : MK, (const T *)(KSIDE ? K : Q),
                                (const T *)(KSIDE ? Q : K), (const T *)V, GV, gden, Z, dM, dX, (T *)dV, sh);
         };

@@ -232,7 +232,9 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void 
     // the longest rows of all units first: what is dealt last is short, and the workgroups that
     // share a CU are of different lengths
     const int per_span = (min(sh.span, sh.n) + ROWS - 1) / ROWS;
-    const int u = blockIdx.x % sh.units, x = blockIdx.x / sh.units;
+    const unsigned flat = blockIdx.y * gridDim.x + blockIdx.x;
+    const int u = flat % sh.units, x = flat / sh.units;
+    if (x >= per_span * sh.spans) return;
     const int span = sh.spans - 1 - x % sh.spans, s_begin = span * sh.span, s_end = min(sh.n, s_begin + sh.span);
     const int i0 = s_begin + (per_span - 1 - x / sh.spans) * ROWS;
     if (i0 >= s_end) return;
@@ -462,7 +464,8 @@ psf_status rows_launch(const Problem &pb, const F32Plan &pl, const float *MQ, co
         constexpr int DT = decltype(dt)::value, RT = decltype(rt)::value;
         auto go = [&](auto kernel, int rows) {
             const int per_span = ((pl.span < pb.n ? pl.span : pb.n) + rows - 1) / rows;
-            hipLaunchKernelGGL(kernel, dim3((unsigned)(per_span * pl.spans) * (unsigned)pb.units), dim3(kF32Threads), 0,
+            const FlatGrid grid = flat_grid((unsigned long long)per_span * pl.spans * pb.units);
+            hipLaunchKernelGGL(kernel, dim3(grid.x, grid.y), dim3(kF32Threads), 0,
                                s, MQ, MK, (const T *)Q, (const T *)K, (const T *)V, Z, (T *)O, (const T *)dO, GV, gden,
                                sh);
         };

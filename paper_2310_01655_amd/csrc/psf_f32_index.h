@@ -29,5 +29,16 @@ PSF_HD TokenRange state_tokens(int n, int span_tokens, int span, int dv, int c0)
     return {begin, c0 < dv ? end : begin};
 }
 
+// Grid of a launch that numbers its workgroups (256 threads) through: a dimension holds fewer than 2^32
+// threads, so more than 2^23 workgroups (2^29 rows of 64 a workgroup) go into rows of 2^23.  The last
+// row may hold numbers that are not there.
+constexpr unsigned kGridRow = 1u << 23;
+struct FlatGrid { unsigned x, y; };
+PSF_HD FlatGrid flat_grid(unsigned long long groups)
+{
+    if (groups <= kGridRow) return {(unsigned)groups, 1u};
+    return {kGridRow, (unsigned)((groups + kGridRow - 1) / kGridRow)};
+}
+
 }  // namespace psf
 #endif

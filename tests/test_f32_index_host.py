@@ -41,11 +41,41 @@ int main()
 }
 """
 
+GRIDS = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "psf_f32_index.h"
+using namespace psf;
+int main()
+{
+    int bad = 0;
+    for (unsigned long long groups : {1ull, 7ull, (1ull << 23) - 1, 1ull << 23, (1ull << 23) + 1, 1ull << 24,
+                                      (1ull << 24) + 12345, 65535ull * 257, 1ull << 28}) {
+        const FlatGrid g = flat_grid(groups);
+        const unsigned long long all = (unsigned long long)g.x * g.y;
+        if (all < groups || all >= groups + g.x || g.x * 256ull >= 1ull << 32 || g.y > 65535 || all >> 32) {
+            printf("%llu workgroups: %u x %u\n", groups, g.x, g.y);
+            ++bad;
+        }
+    }
+    return bad;
+}
+"""
 
-def test_state_kernel_loads_stay_inside_the_values(tmp_path):
+
+def test_large_launches_stay_within_a_grid_dimension(tmp_path):
+    """2^24 workgroups of 256 threads (2^30 rows) are too many for one dimension."""
+    run_host(tmp_path, GRIDS)
+
+
+def run_host(tmp_path, program):
     src, exe = tmp_path / "index.cpp", tmp_path / "index"
-    src.write_text(PROGRAM)
+    src.write_text(program)
     subprocess.run(["g++", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_2310_01655_amd", "csrc"), str(src),
                     "-o", str(exe)], check=True)
     run = subprocess.run([str(exe)], stdout=subprocess.PIPE, text=True)
     assert run.returncode == 0, run.stdout
+
+
+def test_state_kernel_loads_stay_inside_the_values(tmp_path):
+    run_host(tmp_path, PROGRAM)
