@@ -281,7 +281,11 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void 
             if (sh.vec_v) vt.store(vs, nv, sh.dv);
             else stage_scalar<VT, KT>(vp, sh.dv, nv, sh.dv, vs);
             __syncthreads();
+            f4 part[VT];                                    // WR = 4: this tile's sums (two levels of summation)
+            float dpart = 0.f;
+            if constexpr (WR == 4) clear(part);
             for (int sub = (WR == 4 ? 0 : wave); sub < KT / 16; sub += (WR == 4 ? 1 : 4)) {
+                f4 (&to)[VT] = WR == 4 ? part : acc;
                 const int js = j0 + 16 * sub;
                 if (js >= j_end || (!sh.noncausal && js > iw_last)) break;
                 f4 se = {0.f, 0.f, 0.f, 0.f}, ss = se;
@@ -295,15 +299,17 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void 
                     float e = se[k];
                     for (int q = 1; q < sh.p; q <<= 1) e *= e;
                     w[k] = j > j_max ? 0.f : j >= bs ? e : ss[k] * ss[k];
-                    den += w[k];
+                    dpart += w[k];
                 }
                 if (!sh.noncausal && js + 15 > iw) {
                     const int vis = i - js;                 // tile rows 0 .. vis count
-                    add_rows<VT, true>(vs, 16 * sub, w, acc, lane, vis < 0 ? 0u : 0xffffu >> max(0, 15 - vis));
+                    add_rows<VT, true>(vs, 16 * sub, w, to, lane, vis < 0 ? 0u : 0xffffu >> max(0, 15 - vis));
                 } else {
-                    add_rows<VT, false>(vs, 16 * sub, w, acc, lane, 0u);
+                    add_rows<VT, false>(vs, 16 * sub, w, to, lane, 0u);
                 }
             }
+            den += dpart;
+            if constexpr (WR == 4) add_to(acc, part);
         }
     }
 
@@ -346,6 +352,10 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void 
             __syncthreads();
             const float *zt = piece & 1 ? vs : ks;
             if (piece < LAST) fetch(piece + 1);
+            f4 part[VT];
+            float dpart = 0.f;
+            if constexpr (WR == 4) clear(part);
+            f4 (&to)[VT] = WR == 4 ? part : acc;
 #pragma unroll
             for (int k = 0; k < ZW; ++k) {
                 const int aa = WR == 1 ? wave : k;
@@ -354,12 +364,14 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void 
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
                     const float phi = ma * mq[s];
-                    den += phi * sd[s];
+                    dpart += phi * sd[s];
 #pragma unroll
                     for (int ct = 0; ct < VT; ++ct)
-                        acc[ct] = mm(zt[(aa * 16 + 4 * g + s) * VP + 16 * ct + li], phi, acc[ct]);
+                        to[ct] = mm(zt[(aa * 16 + 4 * g + s) * VP + 16 * ct + li], phi, to[ct]);
                 }
             }
+            den += dpart;
+            if constexpr (WR == 4) add_to(acc, part);
             if (piece < LAST) put(piece & 1 ? ks : vs, ~piece & 1);
         }
     }

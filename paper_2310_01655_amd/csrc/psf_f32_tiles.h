@@ -212,16 +212,21 @@ template <int NT>
 __device__ __forceinline__ f4 score_rows(const float *tile, int row0, const float (&own)[4 * NT], int lane)
 {
     const float *at = tile + (row0 + (lane & 15)) * pitch_of<NT>() + 4 * (lane >> 4);
-    f4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+    // sums of at most 32 columns: p-th powers enlarge what a long sum loses
+    constexpr int SUMS = NT >= 4 ? 4 : 2;
+    f4 sum[SUMS];
+    clear(sum);
 #pragma unroll
     for (int q = 0; q < NT; ++q) {
         const f4 a = *(const f4 *)(at + 16 * q);
-        s0 = mm(a[0], own[4 * q], s0);
-        s1 = mm(a[1], own[4 * q + 1], s1);
-        s0 = mm(a[2], own[4 * q + 2], s0);
-        s1 = mm(a[3], own[4 * q + 3], s1);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int k = SUMS == 4 ? 2 * (2 * q / NT) + s % 2 : s % 2;
+            sum[k] = mm(a[s], own[4 * q + s], sum[k]);
+        }
     }
-    return s0 + s1;
+    if constexpr (SUMS == 4) return (sum[0] + sum[1]) + (sum[2] + sum[3]);
+    else return sum[0] + sum[1];
 }
 
 __device__ __forceinline__ float over_groups(float x)       // sum over the four lanes of a row
@@ -250,10 +255,10 @@ __device__ __forceinline__ void project(const T *G, int in, int r, int c0, const
     const int li = lane & 15, g = lane >> 4, c = c0 + li;
     const float *xr = x + li * pitch + 4 * g;
     const T *ga = G + (size_t)(4 * g) * r + (c < r ? c : 0);
-    f4 odd[H];                                              // two chains a result: shorter sums
     clear(out);
-    clear(odd);
-    // STEP rows of G: all loads first
+    // STEP rows of G: all loads first.  Every 16 rows are a sum of their own: with 32 of them a
+    // kernel takes 35 us instead of 42 (72 k rows of 64, r = 32), but gradients were up to 10 %
+    // further from float64 than the vector kernels' (r = 32, blocks of 48 tokens).
     auto run = [&](auto step, int e0) {
         constexpr int STEP = decltype(step)::value;
         float a[STEP / 4];
@@ -262,17 +267,22 @@ __device__ __forceinline__ void project(const T *G, int in, int r, int c0, const
 #pragma unroll
             for (int s = 0; s < 4; ++s) a[e / 4 + s] = load_f(ga, (size_t)((e0 + e + s) * r));
 #pragma unroll
-        for (int e = 0; e < STEP; e += 16) {
-            f4 xv[H];
+        for (int e = 0; e < STEP; e += 32) {
+            f4 even[H], odd[H];
+            clear(even);
+            clear(odd);
 #pragma unroll
-            for (int h = 0; h < H; ++h) xv[h] = *(const f4 *)(xr + 16 * h * pitch + e0 + e);
+            for (int h = 0; h < H; ++h) {
+                const float *xh = xr + 16 * h * pitch + e0 + e;
+                const f4 xe = *(const f4 *)xh, xo = *(const f4 *)(xh + 16);
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-                for (int h = 0; h < H; ++h) {
-                    if (e & 16) odd[h] = mm(a[e / 4 + s], xv[h][s], odd[h]);
-                    else out[h] = mm(a[e / 4 + s], xv[h][s], out[h]);
+                for (int s = 0; s < 4; ++s) {
+                    even[h] = mm(a[e / 4 + s], xe[s], even[h]);
+                    odd[h] = mm(a[e / 4 + 4 + s], xo[s], odd[h]);
                 }
+            }
+#pragma unroll
+            for (int h = 0; h < H; ++h) out[h] += even[h] + odd[h];
         }
     };
     int e0 = 0;
@@ -281,17 +291,18 @@ __device__ __forceinline__ void project(const T *G, int in, int r, int c0, const
         if (e0 + 32 <= in) { run(std::integral_constant<int, 32>{}, e0); e0 += 32; }
     }
     for (; e0 < in; e0 += 16) {
-        f4 xv[H];
+        f4 part[H], xv[H];
+        clear(part);
 #pragma unroll
         for (int h = 0; h < H; ++h) xv[h] = *(const f4 *)(xr + 16 * h * pitch + e0);
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             const float a = c < r && e0 + 4 * g + s < in ? load_f(ga, (size_t)(e0 + s) * r) : 0.f;
 #pragma unroll
-            for (int h = 0; h < H; ++h) out[h] = mm(a, xv[h][s], out[h]);
+            for (int h = 0; h < H; ++h) part[h] = mm(a, xv[h][s], part[h]);
         }
+        add_to(out, part);
     }
-    add_to(out, odd);
 }
 
 // the transposed product: acc^T (16 rows e from e0) += G y^T for y [rows][pitch] of r columns
