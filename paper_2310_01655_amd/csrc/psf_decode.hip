@@ -357,8 +357,11 @@ __global__ __launch_bounds__(kThreads) void dec_zero_kernel(float *__restrict__ 
 // MODE 4: as MODE 3, but the slice that arrives last at its unit's counter adds the slices up, in
 // their order, and does the rest as MODE 2: one launch.  The counter is the first word of the
 // partial sums of slice kSlices - 1, which such a call does not have; psf_decode_reset clears
-// it, and the last slice sets it back.  Measured, one sequence of 12 heads, d = r = 64: 17 us
-// against 13 + 7 and a gap between the two launches (24 steps 536 -> 471 us).
+// it, and the last slice sets it back.  Measured against MODE 3 (us a step in the second block, bf16
+// storage; r = 64: 1 unit, 8 slices, 16.6 and 20.1; 96 units, 8: 23.0 and 27.1; 192, 4: 28.7 and 31.8;
+// 384, 2: 38.3 and 41.2; 700, 2: 68.8 and 69.2.  r = 128: 52 units, 15 slices, 48.9 and 55.8; 64, 12: 50.8 and
+// 56.9; 128, 6: 76.5 and 81.0; 500, 3: 254.9 and 257.5; 384, 3 is the one point behind: 219.5 and 217.2).
+// With 16 slices there is no room for a counter, and MODE 3 stays.
 struct DecSketchArgs {
     const void *G;           // sketch matrices, storage type
     size_t g_len;            // entries per set
@@ -550,7 +553,11 @@ __global__ __launch_bounds__(kThreads) void dec_state_kernel(const T *__restrict
         // The slices of a unit run on different dies, whose caches do not see each other's plain
         // writes: device-scope stores and loads, which go past those caches.  Every thread waits
         // until its stores have arrived before the workgroup counts itself in (a release fence
-        // here would write back the whole cache of the die: 20 us a step instead of 17).
+        // here would write back the whole cache of the die: 20 us a step instead of 17).  This
+        // rests on the hardware and not on the language's memory model, whose way would be that
+        // fence: a device-scope store is acknowledged (vmcnt) once it is where every die sees it, the
+        // barrier puts all of the workgroup's acknowledgements before the count, and the loads of
+        // the last slice are issued after the count has come back.
         for (int c = tid; c < kc; c += kThreads)
             __hip_atomic_store(out + c, rowp[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -848,7 +855,7 @@ __global__ __launch_bounds__(kThreads, 2) void dec_fold_mfma_kernel(float *__res
         // accumulator: lane x = column c, register v = row b' = 8 (v / 4) + 4 h + v % 4.  All rows
         // are read before the first is written: the reads and writes go to one array, so that in
         // one loop every read would wait for the write before it (768 units of r = d = 64:
-        // 1240 -> 875 us).
+        // 1240 -> 840 to 885 us).
         float old[TC][16];
 #pragma unroll
         for (int ct = 0; ct < TC; ++ct)
@@ -1107,8 +1114,9 @@ static int prefill_fast_tokens(const Problem &pb, int n_prompt)
 // Workspace of a hand-over, in this order: the fp32 sketches of the prompt keys that go through
 // the cache (learned sketches only: all of them, or those after the last block boundary when
 // the forward kernels take the complete blocks), a contiguous copy of those keys (same case),
-// contiguous copies of the complete blocks of K and V (when a tail follows them), the forward
-// kernels' own buffers.
+// room for contiguous copies of the complete blocks of K and V (when a tail follows them; only
+// learned sketches still make these copies, the size the query returns is the same for both), the
+// forward kernels' own buffers.
 struct PrefillPlan {
     int n_full, m_rows;                   // tokens through the forward kernels; sketched rows per unit
     size_t m_bytes, ktail_bytes, copy_bytes, total;
@@ -1199,7 +1207,7 @@ static psf_status prefill_launch(const Problem &pb, const void *K, const void *V
         const dim3 grid((unsigned)((count + kPrefillTokens - 1) / kPrefillTokens), (unsigned)pb.units);
         if (!have_m && f32_supported(pb)) {
             // sketches on the fp32 matrix cores, straight into the cache (768 units x 1012 tokens of
-            // d = r = 64: 347 us and 76 for the rows, against 1690 by two rows a workgroup)
+            // d = r = 64: 310 us and 78 for the rows, against 1690 by two rows a workgroup)
             Problem part = pb;
             part.n = count;
             st = f32_sketch_rows(part, (const T *)K + (size_t)pos0 * pb.d, (size_t)n_prompt * pb.d, G, state + L.cm,

@@ -10,9 +10,10 @@
 // f32_plan() chooses the span.
 //
 // Measured against the vector kernels (us a call, forward / forward and backward): 36 units of 3000
-// tokens, r = 32, b = 200, bf16 storage 8540 -> 346; 24 units of 1950, b = 150, forward and backward
-// 26940 -> 747; one unit of 1024, r = 16, fp32 storage 248 -> 33.  Relative error against float64
-// (fp32 storage, 2048 tokens, r = 64): 1.6e-6 -> 4.5e-7, gradients 4e-7 to 5e-7 on either.
+// tokens, r = 32, b = 200, bf16 storage 8540 -> 361; 24 units of 1950, b = 150, forward and backward
+// 26940 -> 772; one unit of 1024, r = 16, fp32 storage 248 -> 33.  Relative error against float64
+// (fp32 storage, 2400 tokens, r = 64): forward 1.6e-6 -> 3.9e-7, gradients 3.8e-7 to 4.7e-7 -> 3.0e-7
+// to 3.7e-7; over 81 shapes no result is further off than on the vector kernels.
 #include "psf_f32_tiles.h"
 #include "psf_f32.h"
 
@@ -212,6 +213,9 @@ __global__ __launch_bounds__(kF32Threads) void f32_scan_kernel(float *__restrict
 // WR = 4: 64 rows a workgroup, a wave per 16 of them, every staged tile serves all four.
 // WR = 1: 16 rows a workgroup, the waves share the work on them (keys, state rows) and add up at
 // the end: four times the workgroups, for problems that would not fill the chip otherwise.
+// With WR = 4 a wave has the whole row, so the sums of a staged tile and of a state piece are formed
+// apart and then added to the total; one running sum over 3000 tokens (r = 64, 15 blocks) was 6.8e-7
+// from float64, this is 3.3e-7 (36 units x 3000, r = 32: 210 us then, 215 to 220 now).
 // GRAD: instead of the output, G_i = [dO_i / D_i | -<dO_i, o_i> / D_i] for the backward pass.
 template <int DT, int RT, int VT, int WR, bool GRAD, typename T>
 __global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void f32_rows_kernel(
@@ -516,12 +520,16 @@ F32Shape f32_shape(const Problem &pb, const F32Plan &pl)
     return sh;
 }
 
-// Where the states lie.  Costs in seconds of the whole chip at the rates these kernels reach
-// (states 90 TFLOP/s, pairs 65 TFLOP/s, state traffic 4 TB/s, 5 us for the two further
-// launches): forming a record and applying it against the pairs that a longer span takes directly.
-// Measured with every span forced (blocks a span: us): 36 units x 3000, r 32, b 200: 1: 475, 2: 452,
-// 4: 469, 8: 534, all 15: 558; 12 x 16384, r 32, b 64: 1: 855, 4: 668, 16: 934, all: 4267; 24 x 8000,
-// r 64, b 250: 1: 2061, 2: 2061, 8: 2646; 48 x 8192, r 16, b 256: 1: 697, 4: 1224.
+// Where the states lie.  Costs in seconds of the whole chip: states at 90 TFLOP/s, pairs at 65 (72 over
+// 3000 tokens, 50 over 1950, where the launch is short), state traffic at 4 TB/s, 5 us for the two
+// further launches: forming a record and applying it against the pairs that a longer span takes
+// directly.  Measured with every span forced (blocks a span: us of a forward call, of a backward call;
+// * the plan's choice; two runs of one span differ by up to 6 %):
+//   36 units x 3000, r 32, b 200   1: 410, 1277   2: 393*, 1245*   4: 391, 1293   8: 456, 1570   all 15: 469, 1842
+//   24 x 1950, r 32, b 150         1: 214, 619    2: 185, 600*     4: 223, 759    8: 246, 776    all 13: 201*, 686
+//   12 x 16384, r 32, b 64         1: 806, 2291   4: 569, 1916*    8: 573*, 2050  16: 666, 2444  all: 3535, 14920
+//   24 x 8000, r 64, b 250         1: 1634, 5082  2: 1591, 5146*   4: 1658*, 5592 8: 1949, 6737
+//   48 x 8192, r 16, b 256         1: 609*, 2074* 2: 667, 2385     4: 832, 3106
 // z_floats: room for state records.
 static F32Plan f32_plan(const Problem &pb, size_t z_floats, bool noncausal, bool grad)
 {

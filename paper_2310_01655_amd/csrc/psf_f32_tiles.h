@@ -62,7 +62,7 @@ __device__ __forceinline__ void clear(f4 (&a)[N])
 // inserts these waits itself, but it can miss one where a product and its reader lie in different
 // basic blocks with a longer and a shorter way between them (seen: the last result of a state
 // piece read three instructions after its product); so results that leave a branch or a loop
-// are read after this.
+// are read after this.  tests/test_matrix_waits_host.py follows every way through the machine code.
 __device__ __forceinline__ void settle()
 {
     __builtin_amdgcn_sched_barrier(0);
