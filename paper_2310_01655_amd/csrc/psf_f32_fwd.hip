@@ -1,7 +1,7 @@
 // fp32 matrix-core kernels of the general path: sketches, states, rows of the output, for
 // sketch features with d, dv and sketch columns <= 128 (any block size, fp32 or bf16 storage).
 // Everything is computed in fp32 as the vector kernels of psf_general.hip do (which keep explicit
-// exact features, and sizes above 128).  Layouts and operand conventions: psf_f32_tiles.h.
+// exact features, sizes above 128 and what f32_choose leaves to them).  Layouts and operand conventions: psf_f32_tiles.h.
 //
 // The in-block rule only says which weight a pair of tokens gets; it does not force a state per
 // block.  A state is kept per span of several blocks, and pairs of different blocks inside a span

@@ -2,8 +2,8 @@
 // p in {2,4,8,16}, exact features x^{(x)p}, either in-block rule, fp32 or bf16 storage).
 // Sketch features of moderate sizes run on fp32 matrix instructions (psf_f32_fwd.hip); the plain
 // LDS-staged VALU kernels here, which follow the block algorithm of PolySketchFormer (arXiv
-// 2310.01655, Sections 3.1 and 3.2) step by step, keep explicit features, sizes above 128 and the
-// networks of learned sketches.  The tuned bf16 MFMA kernels for the large shapes live in
+// 2310.01655, Sections 3.1 and 3.2) step by step, keep explicit features, sizes above 128, the
+// networks of learned sketches and calls whose state records find no room (f32_choose).  The tuned bf16 MFMA kernels for the large shapes live in
 // psf_mfma.hip.
 #include "psf_internal.h"
 #include "psf_f32.h"
