@@ -1,4 +1,4 @@
-// Host interface of the fp32 matrix-core kernels (psf_f32_fwd.hip, psf_f32_bwd.hip).
+// Host interface of the fp32 matrix-core kernels (psf_f32_fwd.hip, psf_f32_bwd.hip, psf_f32_sketch.h).
 #ifndef PSF_F32_H
 #define PSF_F32_H
 
@@ -33,8 +33,6 @@ bool f32_supported(const Problem &pb);
 // fixed_bytes: the rest of the call's workspace; grad: the backward pass
 F32Choice f32_choose(const Problem &pb, size_t fixed_bytes, bool noncausal, bool grad);
 F32Shape f32_shape(const Problem &pb, const F32Plan &pl);
-// 16 rows a workgroup instead of 64: fewer than two workgroups a CU otherwise
-bool f32_split_rows(const Problem &pb);
 
 // m(x) of all rows (X2, M2 may be null); Gaussian sketches only
 psf_status f32_sketch_pair(const Problem &pb, const void *X1, const void *X2, const void *G, float *M1, float *M2,
@@ -87,6 +85,23 @@ static inline psf_status with_tiles(const Problem &pb, F f)
     if (pb.mcols <= 32) return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{});
     if (pb.mcols <= 64) return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 4>{});
     return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 8>{});
+}
+
+// How the kernels of rows share out the work: f(WR, WK), see psf_f32_fwd.hip.  blocks: workgroups of 64 rows.
+// Measured (us a call; WR 1 WK 4, WR 4 WK 2, WR 4 WK 1): forward 1 x 4292 tokens (68 workgroups), r = 32,
+// 65, -, 89; training 12 x 648 (132), r = 64, fp32 493, 357, 400; forward 16 x 1515 (384), r = 64, -, 83, 101;
+// forward 14 x 2300 (504), r = 32, -, 117, 101.
+// share: from 96 workgroups to this many, two sets of waves share the keys.
+template <int DT, typename F>
+static inline psf_status f32_deal(const Problem &pb, int share, F f)
+{
+    using std::integral_constant;
+    if constexpr (DT == 4) {
+        const long long blocks = (long long)pb.units * ((pb.n + 63) / 64);
+        if (blocks < 96) return f(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+        if (blocks < share) return f(integral_constant<int, 4>{}, integral_constant<int, 2>{});
+    }
+    return f(integral_constant<int, 4>{}, integral_constant<int, 1>{});
 }
 
 }  // namespace psf

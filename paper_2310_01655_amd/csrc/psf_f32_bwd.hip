@@ -1,50 +1,84 @@
 // fp32 matrix-core kernels of the general backward pass (sketch features, d, dv and sketch
-// columns <= 128).  The gradient itself is stated at the top of psf_backward.hip; the operand
-// conventions in psf_f32_tiles.h; spans, pairs and states as in psf_f32_fwd.hip.
+// columns <= 128).  The gradient itself is stated at the top of psf_backward.hip; layouts and
+// products in psf_f32_tiles.h and psf_parts.h; spans, pairs and states as in psf_f32_fwd.hip.
 //
 // One kernel serves both sides: a wave owns 16 queries and walks the keys of its span up to them
 // (dm(Q), dQ), or owns 16 keys and walks the queries from them on (dm(K), dK, dV).  Per group of
-// 16 streamed rows: dw = <G_i, C_j>, the scores, then the products of the pair gradients with the
+// 32 streamed rows: dw = <G_i, C_j>, the scores, then the products of the pair gradients with the
 // streamed rows; pair weights and gradients never leave the registers.
-#include "psf_f32_tiles.h"
+//
+// Bound by vector instructions and LDS reads about equally (a group: 40 to 64 products, about 200 vector
+// instructions, 18 to 36 KB of LDS reads a wave).  24 units of 1950 tokens, r = 32, bf16 storage, query and
+// key side: 113 and 190 us with v_mfma_f32_16x16x4_f32, 76 and 121 now; 8 units of 2048, r = 64, fp32 storage:
+// 120 and 176, 164 and 143.
+#include "psf_parts.h"
 #include "psf_f32.h"
 
 namespace psf {
 namespace {
 
-template <int DT, int RT, int VT, int WR, bool KSIDE, typename T>
-__global__ __launch_bounds__(kF32Threads, DT == 4 ? 2 : 1) void f32_bwd_kernel(
+// to^T += (32 streamed rows)^T w, see add_parts
+template <int NT, int P>
+__device__ __forceinline__ void add_tile(const uint16_t *tile, int plane, int pitch, const float (&w8)[8], f4 (&to)[NT],
+                                         int lane, bool odd, unsigned seen)
+{
+    f4 part[NT];
+    clear(part);
+    if (odd) {
+        add_parts_odd<NT, P>(tile, plane, pitch, w8, part, lane, seen);
+    } else {
+        Parts<3> w;
+        split8(w8, w);
+        add_parts<NT, P>(tile, plane, pitch, w, part, lane);
+    }
+    settle_parts();
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) to[t][k] += part[t][k];
+}
+
+// WR, WK as in psf_f32_fwd.hip: the sets of waves share the streamed rows of a tile and the state pieces.
+template <int DT, int RT, int WR, int WK_, bool KSIDE, typename T>
+struct SideLds {
+    static constexpr int P = parts_of<T>(), PC = KSIDE ? 3 : P, PO = KSIDE ? P : 3;   // parts of C streamed, own
+    static constexpr int MT = RT < 2 ? 2 : RT, OP = pitch_of<RT>(), ROWS = 16 * WR;
+    static constexpr int XP = tr_pitch<DT>(), MP = tr_pitch<MT>();
+    static constexpr int kRow = (P + PC) * XP + 3 * MP;               // 16-bit places of a streamed row
+    static constexpr int WK = kRow * 2 * 32 * WK_ <= 157 * 1024 ? WK_ : WK_ / 2;
+    static constexpr int kThreads = 64 * WR * WK, KT = 32 * WK, kBuffers = WK == 4 ? 1 : 2;
+    static constexpr int kX = P * KT * XP, kM = 3 * KT * MP;
+    static constexpr int kPlane = KT * XP, kPiece = 3 * kPlane, kOwn = ROWS * OP * 2;
+    static constexpr int kSums = (WK - 1) * WR * 4 * (2 * DT + RT) * 64 * 2;
+    static constexpr int most(int a, int b) { return a > b ? a : b; }
+    static constexpr int kPlaces = most(most(KT * kRow, kBuffers * kPiece + kOwn), kSums);
+};
+
+template <int DT, int RT, int WR, int WK_, bool KSIDE, typename T>
+__global__ __launch_bounds__((SideLds<DT, RT, WR, WK_, KSIDE, T>::kThreads), WK_ == 1 && DT == 4 && !(RT == 4 && sizeof(T) == 4) ? 2 : 1) void f32_bwd_kernel(
     const float *__restrict__ Mown, const float *__restrict__ Mstr, const T *__restrict__ Xown,
     const T *__restrict__ Xstr, const T *__restrict__ V, const float *__restrict__ GV, const float *__restrict__ gden,
     const float *__restrict__ Z, float *__restrict__ dM, float *__restrict__ dX, T *__restrict__ dV, F32Shape sh)
 {
-    constexpr int KT = f32_tile_rows(DT, WR), KP = pitch_of<DT>(), MP = pitch_of<RT>(), VP = pitch_of<VT>();
-    constexpr int ROWS = 16 * WR, ZA = KT / 16, ZW = WR == 1 ? 1 : ZA;
-    constexpr int kTileFloats = KT * (KP + VP) + (KT > ROWS ? KT : ROWS) * MP;
-    static_assert(WR == 4 || KT == 64, "the waves of a 16-row workgroup take one group of streamed rows each");
-    static_assert(DT == VT, "the state is staged through the buffers of the streamed rows in turn");
-    __shared__ __attribute__((aligned(16))) float lds[kTileFloats + KT];
-    __shared__ __attribute__((aligned(16))) float sden[2][16 * ZA];   // denominator column of a state piece
-    float *xs = lds, *cs = xs + KT * KP, *ms = cs + KT * VP, *gs = lds + kTileFloats;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, g = lane >> 4;
+    using L = SideLds<DT, RT, WR, WK_, KSIDE, T>;
+    constexpr int VT = DT, ROWS = L::ROWS, KT = L::KT, P = L::P, PC = L::PC, PO = L::PO, MT = L::MT, XP = L::XP, MP = L::MP;
+    constexpr int WK = L::WK, THREADS = L::kThreads;
+    __shared__ __attribute__((aligned(16))) uint16_t lds[L::kPlaces];
+    __shared__ __attribute__((aligned(16))) float gs[KT], sden[2][32 * WK];
+    __shared__ int odd_tile[2];                              // the streamed rows hold an infinity or NaN
+    uint16_t *xs = lds, *ms = xs + L::kX, *cs = ms + L::kM;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = lane & 15, g = lane >> 4;
     const int per_span = (min(sh.span, sh.n) + ROWS - 1) / ROWS;
-    const unsigned flat = blockIdx.y * gridDim.x + blockIdx.x;
-    const int u = flat % sh.units, x = flat / sh.units;     // the longest walks of all units first
-    if (x >= per_span * sh.spans) return;
-    const int span = KSIDE ? x % sh.spans : sh.spans - 1 - x % sh.spans;
+    RowPlace place;
+    if (!row_place(blockIdx.y * gridDim.x + blockIdx.x, sh.units, sh.spans, per_span, place)) return;
+    const int u = place.unit, span = KSIDE ? place.span : sh.spans - 1 - place.span;
     const int s_begin = span * sh.span, s_end = min(sh.n, s_begin + sh.span);
-    const int o0 = s_begin + (KSIDE ? x / sh.spans : per_span - 1 - x / sh.spans) * ROWS;
+    const int o0 = s_begin + (KSIDE ? place.k : per_span - 1 - place.k) * ROWS;
     if (o0 >= s_end) return;
-    const int ow = o0 + (WR == 4 ? 16 * wave : 0), o = ow + li;
+    const int wr = wave % WR, wk = wave / WR, ow = o0 + 16 * wr, o = ow + li;
     const int o_last = min(o0 + ROWS, s_end) - 1, ow_last = min(ow + 15, s_end - 1);
     const bool there = o < s_end;
     const size_t urow = (size_t)u * sh.n;
-    float xf[4 * DT], mf[4 * RT], cf[4 * VT];
-    if (sh.local_exact) load_frags<DT>(Xown + (urow + o) * sh.d, sh.d, there, sh.vec_x, g, xf);
-    load_frags<RT>(Mown + (urow + o) * sh.mcols, sh.mcols, there, sh.vec_m, g, mf);
-    if constexpr (KSIDE) load_frags<VT>(V + (urow + o) * sh.dv, sh.dv, there, sh.vec_v, g, cf);
-    else load_frags<VT>(GV + (urow + o) * sh.dv, sh.dv, there, sh.vec_g, g, cf);
-    const float own_den = KSIDE ? 1.f : there ? gden[urow + o] : 0.f;
     f4 ax[DT], am[RT], ac[VT];
     clear(ax);
     clear(am);
@@ -56,197 +90,233 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? 2 : 1) void f32_bwd_kernel(
     auto edge_of = [&](int row) { return sh.local_exact ? (row / sh.b + (KSIDE ? 1 : 0)) * sh.b : none; };
     const int edge = edge_of(o), edge_w = edge_of(ow), edge_w_last = edge_of(ow_last), edge_g = edge_of(o0),
               edge_g_last = edge_of(o_last);
-    const int x_end = KSIDE ? s_end : o_last + 1;
-    for (int x0 = KSIDE ? o0 : s_begin; x0 < x_end; x0 += KT) {
+    const int x_end = KSIDE ? s_end : o_last + 1, x_begin = KSIDE ? o0 : s_begin;
+    typedef std::conditional_t<KSIDE, float, T> C;
+    const C *cp;
+    if constexpr (KSIDE) cp = GV + urow * sh.dv;
+    else cp = V + urow * sh.dv;
+    const int vec_c = KSIDE ? sh.vec_g : sh.vec_v;
+    PartTile<DT, KT, XP, T, THREADS> xt;
+    PartTile<MT, KT, MP, float, THREADS> mt;
+    PartTile<VT, KT, XP, C, THREADS> ct;
+    auto exact_in = [&](int x0) { return KSIDE ? x0 < edge_g_last : x0 + KT > edge_g; };
+    auto cross_in = [&](int x0) { return KSIDE ? x0 + KT > edge_g : x0 < edge_g_last; };
+    auto fetch_rows = [&](int x0) {
         const int nv = min(KT, x_end - x0);
-        const size_t row = urow + x0;
-        const bool exact_g = KSIDE ? x0 < edge_g_last : x0 + KT > edge_g;
-        const bool cross_g = KSIDE ? x0 + KT > edge_g : x0 < edge_g_last;
-        Tile<DT, KT, T> xt;
-        Tile<RT, KT, float> mt;
-        typedef std::conditional_t<KSIDE, float, T> C;
-        Tile<VT, KT, C> ct;
-        const T *xp = Xstr + row * sh.d;
-        const float *mp = Mstr + row * sh.mcols;
-        const C *cp;
-        if constexpr (KSIDE) cp = GV + row * sh.dv;
-        else cp = V + row * sh.dv;
-        const int vec_c = KSIDE ? sh.vec_g : sh.vec_v;
-        if (vec_c) ct.load(cp, sh.dv, nv, sh.dv);
-        if (exact_g && sh.vec_x) xt.load(xp, sh.d, nv, sh.d);
-        if (cross_g && sh.vec_m) mt.load(mp, sh.mcols, nv, sh.mcols);
+        if (vec_c) ct.load(cp + (size_t)x0 * sh.dv, sh.dv, nv, sh.dv);
+        if (exact_in(x0) && sh.vec_x) xt.load(Xstr + (urow + x0) * sh.d, sh.d, nv, sh.d);
+        if (cross_in(x0) && sh.vec_m) mt.load(Mstr + (urow + x0) * sh.mcols, sh.mcols, nv, sh.mcols);
+    };
+    if (threadIdx.x < 2) odd_tile[threadIdx.x] = 0;
+    fetch_rows(x_begin);
+    const size_t o_row = urow + min(o, s_end - 1);           // (rows that are not there hold another's values and are not stored)
+    Parts<P> xf[DT / 2];
+    Parts<3> mf[MT / 2];
+    Parts<PO> cf[VT / 2];
+    float own_den = 1.f;
+    {
+        typedef std::conditional_t<KSIDE, T, float> CO;
+        OwnRow<DT / 2, T> x_row;
+        OwnRow<MT / 2, float> m_row;
+        OwnRow<VT / 2, CO> c_row;
+        if (sh.local_exact) x_row.load(Xown + o_row * sh.d, sh.d, sh.vec_x, g);
+        m_row.load(Mown + o_row * sh.mcols, sh.mcols, sh.vec_m, g);
+        if constexpr (KSIDE) c_row.load(V + o_row * sh.dv, sh.dv, sh.vec_v, g);
+        else c_row.load(GV + o_row * sh.dv, sh.dv, sh.vec_g, g);
+        if (!KSIDE) own_den = gden[o_row];
+        if (sh.local_exact) x_row.parts(xf, sh.d, g);
+        m_row.parts(mf, sh.mcols, g);
+        c_row.parts(cf, sh.dv, g);
+    }
+    int turn = 0;
+    for (int x0 = x_begin; x0 < x_end; x0 += KT, turn ^= 1) {
+        const int nv = min(KT, x_end - x0);
         __syncthreads();
-        if (exact_g) {
-            if (sh.vec_x) xt.store(xs, nv, sh.d);
-            else stage_scalar<DT, KT>(xp, sh.d, nv, sh.d, xs);
+        bool odd = false;
+        if (exact_in(x0)) {
+            if (sh.vec_x) odd |= xt.template store<true>(xs, nv, sh.d);
+            else odd |= stage_parts_scalar<DT, KT, XP, T, true, THREADS>(Xstr + (urow + x0) * sh.d, sh.d, nv, sh.d, xs);
         }
-        if (cross_g) {
-            if (sh.vec_m) mt.store(ms, nv, sh.mcols);
-            else stage_scalar<RT, KT>(mp, sh.mcols, nv, sh.mcols, ms);
+        if (cross_in(x0)) {
+            if (sh.vec_m) odd |= mt.template store<true>(ms, nv, sh.mcols);
+            else odd |= stage_parts_scalar<MT, KT, MP, float, true, THREADS>(Mstr + (urow + x0) * sh.mcols, sh.mcols, nv, sh.mcols, ms);
         }
-        if (vec_c) ct.store(cs, nv, sh.dv);
-        else stage_scalar<VT, KT>(cp, sh.dv, nv, sh.dv, cs);
-        if (KSIDE && threadIdx.x < KT) gs[threadIdx.x] = (int)threadIdx.x < nv ? gden[row + threadIdx.x] : 0.f;
+        // (the query side takes C in scores only)
+        if (vec_c) odd |= ct.template store<KSIDE>(cs, nv, sh.dv);
+        else odd |= stage_parts_scalar<VT, KT, XP, C, KSIDE, THREADS>(cp + (size_t)x0 * sh.dv, sh.dv, nv, sh.dv, cs);
+        if (KSIDE && threadIdx.x < KT) gs[threadIdx.x] = (int)threadIdx.x < nv ? gden[urow + x0 + threadIdx.x] : 0.f;
+        if (odd) odd_tile[turn] = 1;
         __syncthreads();
-        f4 px[DT], pm[RT], pc[VT];                          // this tile's sums: two levels of summation,
-        clear(px);                                          // as long chains of one sign or both lose digits
-        clear(pm);
-        clear(pc);
-        for (int sub = (WR == 4 ? 0 : wave); sub < KT / 16; sub += (WR == 4 ? 1 : 4)) {
-            const int r0 = 16 * sub, xw = x0 + r0;
-            if (xw >= x_end || (!KSIDE && xw > ow_last)) break;
-            if (KSIDE && xw + 15 < ow) continue;
-            const bool exact_w = KSIDE ? xw < edge_w_last : xw + 15 >= edge_w;
-            const bool cross_w = KSIDE ? xw + 15 >= edge_w : xw < edge_w_last;
-            f4 dw = score_rows<VT>(cs, r0, cf, lane);
-            if constexpr (KSIDE) dw += *(const f4 *)&gs[r0 + 4 * g];
-            else dw += f4{own_den, own_den, own_den, own_den};
-            float we[4], wx[4], wm[4];
+        odd = odd_tile[turn] != 0;
+        if (threadIdx.x == 0) odd_tile[turn ^ 1] = 0;       // (read for the last time before the barrier above)
+        if (x0 + KT < x_end) fetch_rows(x0 + KT);
+        const int r0 = 32 * wk, xw = x0 + r0;
+        if (xw >= x_end || (KSIDE ? xw + 31 < ow : xw > ow_last)) continue;
+        const bool exact_w = KSIDE ? xw < edge_w_last : xw + 31 >= edge_w;
+        const bool cross_w = KSIDE ? xw + 31 >= edge_w : xw < edge_w_last;
+        const bool masked = KSIDE ? xw < ow + 15 : xw + 31 > ow;      // some of the pairs
+        f4 dw[2], se[2], ss[2];
+        // (one after the other where their operands together exceed the registers)
+        score_parts<2, VT / 2, PC, PO>(cs, KT * XP, XP, r0, cf, lane, dw);
+        if (P == 3) __builtin_amdgcn_sched_barrier(0);
+        if (exact_w) score_parts<2, DT / 2, P, P>(xs, KT * XP, XP, r0, xf, lane, se);
+        if (P == 3) __builtin_amdgcn_sched_barrier(0);
+        if (cross_w) score_parts<2, MT / 2, 3, 3>(ms, KT * MP, MP, r0, mf, lane, ss);
+        settle_parts();
+        float we[8], wx[8], wm[8];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) we[k] = wx[k] = wm[k] = 0.f;
-            if (exact_w) {
-                const f4 se = score_rows<DT>(xs, r0, xf, lane);
+        for (int t = 0; t < 2; ++t) {
+            if constexpr (KSIDE) dw[t] += *(const f4 *)&gs[r0 + 16 * t + 4 * g];
+            else dw[t] += f4{own_den, own_den, own_den, own_den};
+        }
+        if (exact_w) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int at = xw + 4 * g + k;
-                    if (KSIDE ? at >= o && at < edge : at <= o && at >= edge) {
-                        float pw, pm1;
-                        powers(se[k], sh.p, pw, pm1);
-                        we[k] = pw;
-                        wx[k] = (float)sh.p * pm1 * dw[k];
-                    }
+            for (int k = 0; k < 8; ++k) {
+                float pm1;
+                powers(se[k >> 2][k & 3], sh.p, we[k], pm1);
+                wx[k] = (float)sh.p * pm1 * dw[k >> 2][k & 3];
+            }
+        }
+        if (cross_w) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float s = ss[k >> 2][k & 3], own = s * s;
+                wm[k] = 2.f * s * dw[k >> 2][k & 3];
+                if (exact_w) {                              // either rule: the block's edge lies in the group
+                    const int at = xw + 16 * (k >> 2) + 4 * g + (k & 3);
+                    const bool ex = KSIDE ? at < edge : at >= edge;
+                    we[k] = ex ? we[k] : own;
+                    wx[k] = ex ? wx[k] : 0.f;
+                    wm[k] = ex ? 0.f : wm[k];
+                } else {
+                    we[k] = own;
                 }
             }
-            if (cross_w) {
-                const f4 ss = score_rows<RT>(ms, r0, mf, lane);
+        }
+        if (masked) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int at = xw + 4 * g + k;
-                    if (KSIDE ? at >= o && at >= edge : at <= o && at < edge) {
-                        we[k] = ss[k] * ss[k];
-                        wm[k] = 2.f * ss[k] * dw[k];
-                    }
-                }
-            }
-            const int rel = o - xw;                         // the own row's place among the streamed ones
-            if (KSIDE ? xw < ow + 15 : xw + 15 > ow) {      // some of the 16 x 16 pairs are masked
-                const unsigned seen = KSIDE ? (rel > 15 ? 0u : 0xffffu & (0xffffu << max(0, rel)))
-                                            : (rel < 0 ? 0u : 0xffffu >> max(0, 15 - rel));
-                if (exact_w) add_rows<DT, true>(xs, r0, wx, px, lane, seen);
-                if (cross_w) add_rows<RT, true>(ms, r0, wm, pm, lane, seen);
-                if (KSIDE) add_rows<VT, true>(cs, r0, we, pc, lane, seen);
-            } else {
-                if (exact_w) add_rows<DT, false>(xs, r0, wx, px, lane, 0u);
-                if (cross_w) add_rows<RT, false>(ms, r0, wm, pm, lane, 0u);
-                if (KSIDE) add_rows<VT, false>(cs, r0, we, pc, lane, 0u);
+            for (int k = 0; k < 8; ++k) {
+                const int at = xw + 16 * (k >> 2) + 4 * g + (k & 3);
+                const bool seen = KSIDE ? at >= o : at <= o;
+                we[k] = seen ? we[k] : 0.f;
+                if (exact_w) wx[k] = seen ? wx[k] : 0.f;
+                if (cross_w) wm[k] = seen ? wm[k] : 0.f;
             }
         }
-        add_to(ax, px);
-        add_to(am, pm);
-        if constexpr (KSIDE) add_to(ac, pc);
+        // each tile's sums apart (two levels of summation, as long chains of one sign or both lose
+        // digits), one product after the other: fewer registers than all of them together
+        const int rel = o - xw;                             // the own row's place among the streamed ones
+        const unsigned seen = KSIDE ? (rel > 31 ? 0u : 0xffffffffu << max(0, rel))
+                                    : (rel < 0 ? 0u : 0xffffffffu >> max(0, 31 - rel));
+        if (exact_w) add_tile<DT, P>(xs + r0 * XP, KT * XP, XP, wx, ax, lane, odd, seen);
+        if (cross_w) add_tile<RT, 3>(ms + r0 * MP, KT * MP, MP, wm, am, lane, odd, seen);
+        if constexpr (KSIDE) add_tile<VT, PC>(cs + r0 * XP, KT * XP, XP, we, ac, lane, odd, seen);
     }
 
     // Spans before (query side) or after (key side): with the record R of the state,
     // U[b'] = sum_c R[a][b'][c] C[c] (+ the denominator column), dm[a] += 2 sum_b' U[b'] m[b'],
     // which for the doubled tiles off the diagonal is dm[a] += U m[b'] and, for their mirror,
-    // dm[b'] += U m[a]; key side also dV += R^T phi'.
+    // dm[b'] += U m[a]; key side also dV += R^T phi'.  A piece is two a with the 16 b' of a tile;
+    // every set of waves has a piece of its own.
     if (sh.states && (KSIDE ? span < sh.spans - 1 : span > 0)) {
+        constexpr int CP = 16 * VT, CH = CP / 8, G = WK, NP = 32 * G * CH / THREADS, PER = 8 / G;
+        constexpr int LAST = tile_pairs(RT) * PER - 1;      // turns of the workgroup
+        static_assert(32 * G * CH % THREADS == 0, "whole pieces");
         const float *z = Z + ((size_t)u * sh.spans + span) * record_floats(RT, VT);
-        const float *zs = z + (size_t)tile_pairs(RT) * 256 * 16 * VT;
-        constexpr int PIECE = KT * 16 * VT, NP = PIECE / 4 / kF32Threads;
-        constexpr int CH = 16 / ZA, LAST = tile_pairs(RT) * CH - 1;
-        f4 pre[NP], pre_s = {0.f, 0.f, 0.f, 0.f};
+        const float *zs = z + record_values(RT, VT) / 2 * 3;
+        RecordPiece pre[NP];
+        float pre_s = 0.f;
         auto fetch = [&](int piece) {
 #pragma unroll
-            for (int k = 0; k < NP; ++k)
-                pre[k] = *(const f4 *)(z + (size_t)piece * PIECE + (k * kF32Threads + threadIdx.x) * 4);
-            if (threadIdx.x < 4 * ZA) pre_s = *(const f4 *)(zs + (size_t)piece * ZA * 16 + threadIdx.x * 4);
+            for (int k = 0; k < NP; ++k) {
+                const int idx = k * THREADS + threadIdx.x;
+                pre[k].load(z, record_values(RT, VT), CP, piece * 32 * G + idx / CH, 8 * (idx % CH));
+            }
+            if (threadIdx.x < 32 * G) pre_s = zs[piece * 32 * G + threadIdx.x];
         };
-        auto put = [&](float *dst, int buf) {
-            if (threadIdx.x < 4 * ZA) *(f4 *)&sden[buf][threadIdx.x * 4] = pre_s;
+        auto put = [&](int buf) {
+            if (threadIdx.x < 32 * G) sden[buf][threadIdx.x] = pre_s;
 #pragma unroll
             for (int k = 0; k < NP; ++k) {
-                const int idx = k * kF32Threads + threadIdx.x;
-                *(f4 *)&dst[(idx / (4 * VT)) * VP + 4 * (idx % (4 * VT))] = pre[k];
+                const int idx = k * THREADS + threadIdx.x;
+                pre[k].store(lds + buf * L::kPiece + (idx / CH) * XP + 8 * (idx % CH), L::kPlane);
             }
         };
         fetch(0);
+        float m_own[4 * RT];
+        load_frags<RT>(Mown + o_row * sh.mcols, sh.mcols, true, sh.vec_m, g, m_own);
         __syncthreads();
-        put(xs, 0);
-        float *own = ms + ((WR == 4 ? 16 * wave : 0) + li) * MP;
+        put(0);
+        float *own = (float *)(lds + L::kBuffers * L::kPiece) + (16 * wr + li) * L::OP;
+        if (wk == 0) {
 #pragma unroll
-        for (int q = 0; q < RT; ++q)
-            *(f4 *)&own[16 * q + 4 * g] = f4{mf[4 * q], mf[4 * q + 1], mf[4 * q + 2], mf[4 * q + 3]};
+            for (int q = 0; q < RT; ++q)
+                *(f4 *)&own[16 * q + 4 * g] = f4{m_own[4 * q], m_own[4 * q + 1], m_own[4 * q + 2], m_own[4 * q + 3]};
+        }
+        __syncthreads();
         int at = 0, q = 0;
-        f4 mq = *(const f4 *)&own[4 * g], ma_sum = {0.f, 0.f, 0.f, 0.f}, mb_sum = ma_sum;
+        f4 mq = *(const f4 *)&own[4 * g], ma_sum = {0.f, 0.f, 0.f, 0.f}, mb_sum = ma_sum, pc[VT];
+        clear(pc);
         auto flush = [&](int tile, f4 v) {                  // registers cannot be indexed
 #pragma unroll
             for (int k = 0; k < RT; ++k)
                 if (k == tile) am[k] += v;
         };
         for (int piece = 0; piece <= LAST; ++piece) {
-            const int ch = piece % CH;
-            if (piece && ch == 0) {                         // the next pair of index tiles
+            const int ch = piece % PER * G + wk, buf = L::kBuffers == 2 ? piece & 1 : 0;
+            if (piece && piece % PER == 0) {                // the next pair of index tiles
                 flush(at, ma_sum);
                 flush(q, mb_sum);
                 ma_sum = mb_sum = f4{0.f, 0.f, 0.f, 0.f};
                 if (++q == RT) q = ++at;
                 mq = *(const f4 *)&own[16 * q + 4 * g];
             }
-            __syncthreads();
-            const float *zt = piece & 1 ? cs : xs;
+            if (piece) __syncthreads();
             if (piece < LAST) fetch(piece + 1);
-            f4 U[ZW], pc[VT];
-            clear(pc);
+            const int w0 = 32 * wk;
+            const uint16_t *zt = lds + buf * L::kPiece + w0 * XP;
+            f4 U[2];
+            score_parts<2, VT / 2, 3, PO>(zt, L::kPlane, XP, 0, cf, lane, U);
+            settle_parts();
+            float phi[8];
+            const float diag = at == q ? 2.f : 1.f, off = at == q ? 0.f : 1.f;
 #pragma unroll
-            for (int k = 0; k < ZW; ++k)
-                U[k] = *(const f4 *)&sden[piece & 1][(WR == 1 ? wave : k) * 16 + 4 * g] * own_den;
-#pragma unroll
-            for (int qq = 0; qq < VT; ++qq)
-#pragma unroll
-                for (int k = 0; k < ZW; ++k) {
-                    const f4 zr = *(const f4 *)&zt[((WR == 1 ? wave : k) * 16 + li) * VP + 16 * qq + 4 * g];
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) U[k] = mm(zr[s], cf[4 * qq + s], U[k]);
-                }
-#pragma unroll
-            for (int k = 0; k < ZW; ++k) {
-                const int aa = WR == 1 ? wave : k, a16 = ZA * ch + aa;
+            for (int k = 0; k < 2; ++k) {
+                const int a16 = 2 * ch + k;
                 const float ma = own[16 * at + a16];
+                U[k] += *(const f4 *)&sden[buf][w0 + 16 * k + 4 * g] * own_den;
                 float t = 0.f;
 #pragma unroll
                 for (int s = 0; s < 4; ++s) t += U[k][s] * mq[s];
-                t = over_groups(t);
-                t = at == q ? 2.f * t : t;
+                t = over_groups(t) * diag;
+                mb_sum += U[k] * (ma * off);
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
-                    const float mirror = U[k][s] * ma;
-                    mb_sum[s] += at == q ? 0.f : mirror;
                     ma_sum[s] += a16 == 4 * g + s ? t : 0.f;
-                }
-                if constexpr (KSIDE) {
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) {
-                        const float phi = ma * mq[s];
-#pragma unroll
-                        for (int ct = 0; ct < VT; ++ct)
-                            pc[ct] = mm(zt[(aa * 16 + 4 * g + s) * VP + 16 * ct + li], phi, pc[ct]);
-                    }
+                    phi[4 * k + s] = ma * mq[s];
                 }
             }
-            if constexpr (KSIDE) add_to(ac, pc);
-            if (piece < LAST) put(piece & 1 ? xs : cs, ~piece & 1);
+            if constexpr (KSIDE) {
+                Parts<3> pp;
+                split8(phi, pp);
+                add_parts<VT, 3>(zt, L::kPlane, XP, pp, pc, lane);
+                if (piece & 1) {                            // (an even number of turns)
+                    add_settled(ac, pc);
+                    clear(pc);
+                }
+            }
+            if (L::kBuffers == 1) __syncthreads();
+            if (piece < LAST) put(L::kBuffers == 2 ? buf ^ 1 : 0);
         }
         flush(at, ma_sum);
         flush(q, mb_sum);
     }
 
-    if constexpr (WR == 1) {
+    if constexpr (WK > 1) {
         constexpr int PER = 4 * (DT + RT + (KSIDE ? VT : 0));
-        static_assert(3 * PER * 64 <= kTileFloats, "sums of three waves");
         __syncthreads();
-        if (wave > 0) {
-            float *to = lds + (size_t)(wave - 1) * PER * 64 + lane;
+        if (wk > 0) {
+            float *to = (float *)lds + (size_t)((wk - 1) * WR + wr) * PER * 64 + lane;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
 #pragma unroll
@@ -259,9 +329,9 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? 2 : 1) void f32_bwd_kernel(
             }
         }
         __syncthreads();
-        if (wave > 0) return;
-        for (int w = 0; w < 3; ++w) {
-            const float *from = lds + (size_t)w * PER * 64 + lane;
+        if (wk > 0) return;
+        for (int w = 0; w < WK - 1; ++w) {
+            const float *from = (const float *)lds + (size_t)(w * WR + wr) * PER * 64 + lane;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
 #pragma unroll
@@ -285,129 +355,6 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? 2 : 1) void f32_bwd_kernel(
         for (int t = 0; t < VT; ++t) store_piece(dV + (urow + o) * sh.dv, 16 * t + 4 * g, sh.dv, sh.vec_v, ac[t]);
 }
 
-// ---- Algorithm 1's reverse -------------------------------------------------------------------
-// A wave takes 16 H rows.  The two projections U, W of every node are formed again level by level
-// and kept in LDS; from the root down they become dU = sqrt(1/r) dM * W, dW = sqrt(1/r) dM * U, and
-// dM(child 1) = dU G1^T, dM(child 2) = dW G2^T; dX = direct + the same for the first level.
-// LDS: x, then U, W of every node, then m of every node but the root.
-__host__ __device__ inline int bwd_sketch_nodes(int p) { return p == 4 ? 1 : p == 8 ? 3 : 7; }
-size_t bwd_sketch_lds(int d, int r, int p, int h)
-{
-    const int nodes = bwd_sketch_nodes(p);
-    return (size_t)16 * h * ((tiles16(d) * 16 + 4) + (3 * nodes - 1) * (tiles16(r) * 16 + 4)) * sizeof(float);
-}
-
-template <int H, typename T>
-__global__ __launch_bounds__(64) void f32_bwd_sketch_kernel(const T *__restrict__ X1, const T *__restrict__ X2,
-                                                            const T *__restrict__ G, const float *__restrict__ dM1,
-                                                            const float *__restrict__ dM2,
-                                                            const float *__restrict__ dir1,
-                                                            const float *__restrict__ dir2, T *__restrict__ dX1,
-                                                            T *__restrict__ dX2, int n, int d, int r, int p, int heads,
-                                                            int per_head, size_t g_len, int vec_x, int vec_g)
-{
-    extern __shared__ __attribute__((aligned(16))) float smem[];
-    constexpr int ROWS = 16 * H;
-    const int lane = threadIdx.x, li = lane & 15, g = lane >> 4, u = blockIdx.y, i0 = blockIdx.x * ROWS;
-    const int dp = (d + 15) / 16 * 16, rp = (r + 15) / 16 * 16, xp = dp + 4, mp = rp + 4;
-    const size_t row0 = (size_t)u * n + i0;
-    const T *X = (blockIdx.z ? X2 : X1) + row0 * d;
-    const float *dM = (blockIdx.z ? dM2 : dM1) + row0 * (p == 2 ? d : r), *dir = (blockIdx.z ? dir2 : dir1) + row0 * d;
-    T *dX = (blockIdx.z ? dX2 : dX1) + row0 * d;
-    const int nv = min(ROWS, n - i0), quads = dp / 4, vec_m = r % 4 == 0, vec_d = d % 4 == 0;
-    for (int idx = lane; idx < ROWS * quads; idx += 64) {
-        const int row = idx / quads, c = 4 * (idx % quads);
-        if (p == 2) {                                       // m(x) = x
-            if (row < nv)
-                store_piece(dX + (size_t)row * d, c, d, vec_x,
-                            row_piece(dir + (size_t)row * d, c, d, vec_d) + row_piece(dM + (size_t)row * d, c, d, vec_d));
-            continue;
-        }
-        f4 v = {0.f, 0.f, 0.f, 0.f};
-        if (row < nv) v = row_piece(X + (size_t)row * d, c, d, vec_x);
-        *(f4 *)&smem[row * xp + c] = v;
-    }
-    if (p == 2) return;
-    __syncthreads();
-    const T *gs = G + (per_head ? (size_t)(u % heads) * g_len : 0), *gi = gs + (size_t)(p / 2) * d * r;
-    const float sc = sqrtf(1.0f / (float)r);
-    const int total = bwd_sketch_nodes(p);
-    const size_t arr = (size_t)ROWS * mp;                   // floats of an array of row vectors
-    float *UW = smem + ROWS * xp, *Mn = UW + 2 * total * arr;
-    int count = p / 4, first = 0, from = -1;
-    for (;;) {
-        for (int k = 0; k < count; ++k) {
-            const int in = from < 0 ? d : r, pitch = from < 0 ? xp : mp;
-            const T *ga = from < 0 ? gs + (size_t)(2 * k) * d * r : gi + (size_t)(2 * k) * r * r;
-            const float *xa = from < 0 ? smem : Mn + (from + 2 * k) * arr, *xb = from < 0 ? smem : xa + arr;
-            float *U = UW + 2 * (first + k) * arr, *W = U + arr;
-            for (int c0 = 0; c0 < rp; c0 += 16) {
-                f4 a[H], w[H];
-                project<H>(ga, in, r, c0, xa, pitch, a, lane);
-                project<H>(ga + (size_t)in * r, in, r, c0, xb, pitch, w, lane);
-#pragma unroll
-                for (int h = 0; h < H; ++h) {
-                    const int row = 16 * h + li, at = row * mp + c0 + 4 * g;
-                    if (count == 1) {                       // the root: its gradient is given
-                        f4 dm = {0.f, 0.f, 0.f, 0.f};
-                        if (row < nv) dm = row_piece(dM + (size_t)row * r, c0 + 4 * g, r, vec_m) * sc;
-                        *(f4 *)&U[at] = dm * w[h];
-                        *(f4 *)&W[at] = dm * a[h];
-                    } else {
-                        *(f4 *)&U[at] = a[h];
-                        *(f4 *)&W[at] = w[h];
-                        *(f4 *)&Mn[(first + k) * arr + at] = a[h] * w[h] * sc;
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        if (count == 1) break;
-        if (from >= 0) gi += (size_t)(2 * count) * r * r;
-        from = first;
-        first += count;
-        count /= 2;
-    }
-    while (first > 0) {                                     // nodes of a level -> their children
-        const int below = first - 2 * count;
-        for (int k = 0; k < 2 * count; ++k) {
-            const T *ga = gi + (size_t)k * r * r;
-            const float *du = UW + (2 * first + k) * arr;   // dU of node k / 2, or its dW
-            float *U = UW + 2 * (below + k) * arr, *W = U + arr;
-            for (int e0 = 0; e0 < rp; e0 += 16) {
-                f4 dm[H];
-#pragma unroll
-                for (int h = 0; h < H; ++h) dm[h] = f4{0.f, 0.f, 0.f, 0.f};
-                back_project<H>(ga, r, r, e0, du, mp, vec_g, dm, lane);
-#pragma unroll
-                for (int h = 0; h < H; ++h) {
-                    const int at = (16 * h + li) * mp + e0 + 4 * g;
-                    const f4 a = *(const f4 *)&U[at], w = *(const f4 *)&W[at], gm = dm[h] * sc;
-                    *(f4 *)&U[at] = gm * w;
-                    *(f4 *)&W[at] = gm * a;
-                }
-            }
-        }
-        __syncthreads();
-        count *= 2;
-        first = below;
-        gi -= (size_t)(2 * count) * r * r;                  // (not read at the first level)
-    }
-    for (int e0 = 0; e0 < dp; e0 += 16) {
-        f4 acc[H];
-#pragma unroll
-        for (int h = 0; h < H; ++h) {
-            acc[h] = f4{0.f, 0.f, 0.f, 0.f};
-            if (16 * h + li < nv) acc[h] = row_piece(dir + (size_t)(16 * h + li) * d, e0 + 4 * g, d, vec_d);
-        }
-        for (int k = 0; k < 2 * count; ++k)
-            back_project<H>(gs + (size_t)k * d * r, d, r, e0, UW + k * arr, mp, vec_g, acc, lane);
-#pragma unroll
-        for (int h = 0; h < H; ++h)
-            if (16 * h + li < nv) store_piece(dX + (size_t)(16 * h + li) * d, e0 + 4 * g, d, vec_x, acc[h]);
-    }
-}
-
 template <typename T, bool KSIDE>
 psf_status side_launch(const Problem &pb, const F32Plan &pl, const float *MQ, const float *MK, const void *Q,
                        const void *K, const void *V, const float *GV, const float *gden, const float *Z, float *dM,
@@ -420,42 +367,19 @@ psf_status side_launch(const Problem &pb, const F32Plan &pl, const float *MQ, co
     sh.vec_g = pieces_ok<float>(pb.dv, {GV});
     return with_tiles(pb, [&](auto dt, auto rt) -> psf_status {
         constexpr int DT = decltype(dt)::value, RT = decltype(rt)::value;
-        auto go = [&](auto kernel, int rows) {
-            const int per_span = ((pl.span < pb.n ? pl.span : pb.n) + rows - 1) / rows;
-            const FlatGrid grid = flat_grid((unsigned long long)per_span * pl.spans * pb.units);
-            hipLaunchKernelGGL(kernel, dim3(grid.x, grid.y), dim3(kF32Threads), 0,
-                               s, KSIDE ? MK : MQ, KSIDE ? MQ : MK, (const T *)(KSIDE ? K : Q),
-                               (const T *)(KSIDE ? Q : K), (const T *)V, GV, gden, Z, dM, dX, (T *)dV, sh);
+        auto go = [&](auto wr, auto wk) {
+            constexpr int WR = decltype(wr)::value, WK = decltype(wk)::value;
+            using L = SideLds<DT, RT, WR, WK, KSIDE, T>;
+            const int per_span = ((pl.span < pb.n ? pl.span : pb.n) + L::ROWS - 1) / L::ROWS;
+            const FlatGrid grid = flat_grid(row_groups(pb.units, pl.spans, per_span));
+            hipLaunchKernelGGL((f32_bwd_kernel<DT, RT, WR, WK, KSIDE, T>), dim3(grid.x, grid.y), dim3(L::kThreads), 0, s,
+                               KSIDE ? MK : MQ, KSIDE ? MQ : MK, (const T *)(KSIDE ? K : Q), (const T *)(KSIDE ? Q : K),
+                               (const T *)V, GV, gden, Z, dM, dX, (T *)dV, sh);
+            PSF_LAUNCH_CHECK();
+            return PSF_OK;
         };
-        if constexpr (DT == 4) {
-            if (f32_split_rows(pb)) {
-                go(f32_bwd_kernel<DT, RT, DT, 1, KSIDE, T>, 16);
-                PSF_LAUNCH_CHECK();
-                return PSF_OK;
-            }
-        }
-        go(f32_bwd_kernel<DT, RT, DT, 4, KSIDE, T>, 64);
-        PSF_LAUNCH_CHECK();
-        return PSF_OK;
+        return f32_deal<DT>(pb, RT == 4 && sizeof(T) == 4 && !KSIDE ? 0 : 512, go);
     });
-}
-
-template <typename T, int H>
-psf_status sketch_bwd_launch(const Problem &pb, const void *X1, const void *X2, const void *G, const float *dM1,
-                             const float *dM2, const float *dir1, const float *dir2, void *dX1, void *dX2,
-                             hipStream_t s)
-{
-    const size_t lds = pb.p == 2 ? 0 : bwd_sketch_lds(pb.d, pb.r, pb.p, H);
-    if (lds > (64u << 10))
-        PSF_HIP_TRY(hipFuncSetAttribute((const void *)f32_bwd_sketch_kernel<H, T>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    const int vx = pieces_ok<T>(pb.d, {X1, X2 ? X2 : X1, dX1, dX2 ? dX2 : dX1}), vg = pieces_ok<T>(pb.r, {G}) && pb.d % 4 == 0;
-    const dim3 grid((unsigned)((pb.n + 16 * H - 1) / (16 * H)), (unsigned)pb.units, X2 ? 2 : 1);
-    hipLaunchKernelGGL((f32_bwd_sketch_kernel<H, T>), grid, dim3(64), lds, s, (const T *)X1, (const T *)X2,
-                       (const T *)G, dM1, dM2, dir1, dir2, (T *)dX1, (T *)dX2, pb.n, pb.d, pb.r, pb.p, pb.heads,
-                       pb.per_head ? 1 : 0, pb.g_len, vx, vg);
-    PSF_LAUNCH_CHECK();
-    return PSF_OK;
 }
 
 }  // namespace
@@ -469,24 +393,6 @@ psf_status f32_bwd_side(const Problem &pb, const F32Plan &pl, bool key_side, con
                         : side_launch<bf16_t, false>(pb, pl, MQ, MK, Q, K, V, GV, gden, Z, dM, dX, dV, s);
     return key_side ? side_launch<float, true>(pb, pl, MQ, MK, Q, K, V, GV, gden, Z, dM, dX, dV, s)
                     : side_launch<float, false>(pb, pl, MQ, MK, Q, K, V, GV, gden, Z, dM, dX, dV, s);
-}
-
-// the arrays of all nodes of 16 rows within the 160 KB of a CU (p = 16 stays below r = 120)
-bool f32_sketch_bwd_supported(const Problem &pb)
-{
-    return !pb.learned && !pb.exact_feat && pb.d <= 128 && pb.mcols <= 128 &&
-           (pb.p == 2 || bwd_sketch_lds(pb.d, pb.r, pb.p, 1) <= (160u << 10));
-}
-
-psf_status f32_sketch_bwd_pair(const Problem &pb, const void *X1, const void *X2, const void *G, const float *dM1,
-                               const float *dM2, const float *direct1, const float *direct2, void *dX1, void *dX2,
-                               hipStream_t s)
-{
-    if (pb.p <= 4)
-        return pb.bf16 ? sketch_bwd_launch<bf16_t, 2>(pb, X1, X2, G, dM1, dM2, direct1, direct2, dX1, dX2, s)
-                       : sketch_bwd_launch<float, 2>(pb, X1, X2, G, dM1, dM2, direct1, direct2, dX1, dX2, s);
-    return pb.bf16 ? sketch_bwd_launch<bf16_t, 1>(pb, X1, X2, G, dM1, dM2, direct1, direct2, dX1, dX2, s)
-                   : sketch_bwd_launch<float, 1>(pb, X1, X2, G, dM1, dM2, direct1, direct2, dX1, dX2, s);
 }
 
 }  // namespace psf

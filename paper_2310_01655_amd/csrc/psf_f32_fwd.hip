@@ -1,121 +1,56 @@
-// fp32 matrix-core kernels of the general path: sketches, states, rows of the output, for
-// sketch features with d, dv and sketch columns <= 128 (any block size, fp32 or bf16 storage).
-// Everything is computed in fp32 as the vector kernels of psf_general.hip do (which keep explicit
-// exact features, sizes above 128 and what f32_choose leaves to them).  Layouts and operand conventions: psf_f32_tiles.h.
+// fp32 matrix-core kernels of the general path: states and rows of the output, for sketch features with
+// d, dv and sketch columns <= 128 (any block size, fp32 or bf16 storage); the sketches: psf_f32_sketch.h.
+// Everything is fp32 as in the vector kernels of psf_general.hip (which keep explicit exact features,
+// sizes above 128 and what f32_choose leaves to them); the products are formed from exact bf16
+// parts, see psf_parts.h.  Layouts: psf_f32_tiles.h.
 //
 // The in-block rule only says which weight a pair of tokens gets; it does not force a state per
 // block.  A state is kept per span of several blocks, and pairs of different blocks inside a span
 // take their weight <m(q), m(k)>^2 directly: 2 (r + dv) flops a pair against about 2 r^2 dv a
-// token for forming and applying a state, and no state traffic (1 MB per block and unit with r = 64).
+// token for forming and applying a state, and no state traffic (1.5 MB per block and unit with r = 64).
 // f32_plan() chooses the span.
 //
-// Measured against the vector kernels (us a call, forward / forward and backward): 36 units of 3000
-// tokens, r = 32, b = 200, bf16 storage 8540 -> 361; 24 units of 1950, b = 150, forward and backward
-// 26940 -> 772; one unit of 1024, r = 16, fp32 storage 248 -> 33.  Relative error against float64
-// (fp32 storage, 2400 tokens, r = 64): forward 1.6e-6 -> 3.9e-7, gradients 3.8e-7 to 4.7e-7 -> 3.0e-7
-// to 3.7e-7; over 81 shapes no result is further off than on the vector kernels.
-#include "psf_f32_tiles.h"
+// Measured (us a call, forward / forward and backward; vector kernels, products by
+// v_mfma_f32_16x16x4_f32, now): 36 units of 3000 tokens, r = 32, b = 200, bf16 storage 8540, 361, 235;
+// 24 units of 1950, b = 150, forward and backward 26940, 772, 473; one unit of 1024, r = 16, fp32
+// storage 248, 33, 33.
+#include "psf_parts.h"
 #include "psf_f32.h"
 
 namespace psf {
 namespace {
 
-// ---- Algorithm 1 ------------------------------------------------------------------------
-constexpr int kSketchRows = 32;
-
-// m(x) of the rows of X1 and (blockIdx.z = 1) X2, fp32, 32 rows a wave.  LDS: x, then the nodes of the levels
-// below the root (p / 4 of the first level, for p = 16 two more); padded to 16 columns with zeros.
-__host__ __device__ inline int sketch_nodes(int p) { return p == 4 || p == 2 ? 0 : p == 8 ? 2 : 6; }
-template <typename T>
-__global__ __launch_bounds__(64) void f32_sketch_kernel(const T *__restrict__ X1, const T *__restrict__ X2,
-                                                        const T *__restrict__ G, float *__restrict__ M1,
-                                                        float *__restrict__ M2, int n, int d, int r, int p, int heads,
-                                                        int per_head, size_t g_len, size_t x_unit, size_t m_unit,
-                                                        int vec_x, int vec_m)
-{
-    // x_unit, m_unit: elements from the rows of one unit to those of the next
-    extern __shared__ __attribute__((aligned(16))) float smem[];
-    const int lane = threadIdx.x, li = lane & 15, g = lane >> 4, u = blockIdx.y, i0 = blockIdx.x * kSketchRows;
-    const int dp = (d + 15) / 16 * 16, rp = (r + 15) / 16 * 16, xp = dp + 4, mp = rp + 4;
-    const T *X = (blockIdx.z ? X2 : X1) + u * x_unit + (size_t)i0 * d;
-    float *M = (blockIdx.z ? M2 : M1) + u * m_unit + (size_t)i0 * (p == 2 ? d : r);
-    const int nv = min(kSketchRows, n - i0);
-    const int quads = dp / 4;
-    for (int idx = lane; idx < kSketchRows * quads; idx += 64) {
-        const int row = idx / quads, c = 4 * (idx % quads);
-        f4 v = {0.f, 0.f, 0.f, 0.f};
-        if (row < nv) v = row_piece(X + (size_t)row * d, c, d, vec_x);
-        if (p == 2) {
-            if (row < nv) store_piece(M + (size_t)row * d, c, d, vec_m, v);
-        } else {
-            *(f4 *)&smem[row * xp + c] = v;
-        }
-    }
-    if (p == 2) return;
-    __syncthreads();
-    const T *gs = G + (per_head ? (size_t)(u % heads) * g_len : 0), *gi = gs + (size_t)(p / 2) * d * r;
-    const float sc = sqrtf(1.0f / (float)r);
-    float *nodes = smem + kSketchRows * xp;
-    int count = p / 4, from = -1;                            // nodes of this level; first node below (-1: x)
-    for (int first = 0;; ) {
-        for (int k = 0; k < count; ++k) {
-            const int in = from < 0 ? d : r, pitch = from < 0 ? xp : mp;
-            const T *ga = from < 0 ? gs + (size_t)(2 * k) * d * r : gi + (size_t)(2 * k) * r * r;
-            const float *xa = from < 0 ? smem : nodes + (size_t)(from + 2 * k) * kSketchRows * mp;
-            const float *xb = from < 0 ? smem : xa + (size_t)kSketchRows * mp;
-            for (int c0 = 0; c0 < rp; c0 += 16) {
-                f4 a[2], w[2];
-                project<2>(ga, in, r, c0, xa, pitch, a, lane);
-                project<2>(ga + (size_t)in * r, in, r, c0, xb, pitch, w, lane);
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    f4 m;
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) m[s] = sc * (a[h][s] * w[h][s]);
-                    const int row = 16 * h + li;
-                    if (count > 1)
-                        *(f4 *)&nodes[((size_t)(first + k) * kSketchRows + row) * mp + c0 + 4 * g] = m;
-                    else if (row < nv)
-                        store_piece(M + (size_t)row * r, c0 + 4 * g, r, vec_m, m);
-                }
-            }
-        }
-        if (count == 1) break;
-        __syncthreads();
-        if (from >= 0) gi += (size_t)(2 * count) * r * r;
-        from = first;
-        first += count;
-        count /= 2;
-    }
-}
-
 // ---- states: sum over the tokens of a span of phi'(x_j) [C_j | w_j] --------------------------
 // A wave owns two sketch indices, one of tile row `lo` and one of tile row `hi` = RT - 1 - lo (the
-// same row for r = 16), so that every wave has RT + 1 tiles of pairs, and walks the tokens:
-// A = m_j[a] m_j[b'] (made in registers, one multiply for the products of four column tiles),
-// B = C_j.  The denominator column is a running sum of the A operands.  The four column tiles
-// are read once for both indices and each staged token serves eight indices a workgroup: 36
-// units x 2800 tokens, r = 32: 175 us with one index a wave, 112 so.  Wide values (VT = 8) are split over two workgroups,
-// 64 columns each.  Where RT + 1 tiles in two levels of sums exceed the registers (RT = 8), a
-// wave takes one index and RT tiles, of which those below the diagonal are empty.
+// same row for r = 16), so that every wave has RT + 1 tiles of pairs, and walks the tokens, 32 a
+// step: A = m_j[a] m_j[b'] (fp32 in registers, then parts), B = the parts of C_j.  The denominator
+// column is a running sum of the fp32 products.  The four column tiles are read once for both
+// indices.  The sketches lie in LDS by column, so that a lane reads its tokens as 16-byte pieces.
+// Bound by the vector instructions that make the operands: 60 of them a tile and step against 12 products
+// with values stored as bf16 and 24 with fp32 ones (240 cycles against 192 and 384).
+// Wide values (VT = 8) are split over two workgroups, 64 columns each.  Where RT + 1 tiles in two
+// levels of sums exceed the registers (RT = 8), a wave takes one index and RT tiles, of which
+// those below the diagonal are empty.
 template <int RT, int VT, typename S>
-__global__ __launch_bounds__(kF32Threads, RT <= 2 ? 3 : RT == 4 ? 2 : 1) void f32_state_kernel(
+__global__ __launch_bounds__(kF32Threads, RT <= 2 ? 2 : 1) void f32_state_kernel(
     const float *__restrict__ M, const S *__restrict__ C, const float *__restrict__ wts, float *__restrict__ Z,
     F32Shape sh, int span0)
 {
-    constexpr int MP = pitch_of<RT>(), VP = pitch_of<4>(), KT = RT > 4 ? 32 : 64;
+    constexpr int KT = RT > 4 ? 32 : 64, MP = KT + 4, VP = tr_pitch<4>(), P = parts_of<S>();
     constexpr bool TWO = RT <= 4;
-    constexpr int SLOTS = TWO ? RT + 1 : RT;
-    __shared__ __attribute__((aligned(16))) float ms[KT * MP], vs[KT * VP], ws[KT];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, g = lane >> 4;
+    constexpr int SLOTS = TWO ? RT + 1 : RT, NM = 4 * RT * KT / kF32Threads;
+    __shared__ __attribute__((aligned(16))) float ms[16 * RT * MP], ws[KT];
+    __shared__ __attribute__((aligned(16))) uint16_t vs[P * KT * VP];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = lane & 15, g = lane >> 4;
     const int grp = blockIdx.x / (VT / 4), c0 = 64 * (blockIdx.x % (VT / 4));
     // TWO: groups of four index pairs; r = 16 pairs a with a + 8 of the one tile row
     const int lo = RT == 1 ? 0 : grp / 4, a_lo = RT == 1 ? 4 * grp + wave : 16 * lo + 4 * (grp % 4) + wave;
     const int hi = TWO ? RT - 1 - lo : lo, a_hi = RT == 1 ? a_lo + 8 : 16 * hi + 4 * (grp % 4) + wave;
     const int split = RT - lo;                              // slots of a_lo; the others are a_hi's
     const int span = span0 + blockIdx.y, u = blockIdx.z;
-    const auto [j_begin, j_end] = state_tokens(sh.n, sh.span, span, sh.dv, c0);
-    f4 acc[SLOTS][4];
+    const TokenRange tokens_of = state_tokens(sh.n, sh.span, span, sh.dv, c0);
+    const int j_begin = tokens_of.begin, j_end = tokens_of.end;
+    f4 acc[SLOTS][4], part[SLOTS][4];                       // two levels of summation, as in psf_f32_bwd.hip
     float den[SLOTS];
     int mcol[SLOTS];                                        // first sketch column of the slot's tile
 #pragma unroll
@@ -123,52 +58,93 @@ __global__ __launch_bounds__(kF32Threads, RT <= 2 ? 3 : RT == 4 ? 2 : 1) void f3
         den[e] = 0.f;
         mcol[e] = 16 * (e < split ? lo + e : min(hi + e - split, RT - 1));
         clear(acc[e]);
+        clear(part[e]);
     }
-    for (int j0 = j_begin; j0 < j_end; j0 += KT) {
+    PartTile<4, KT, VP, S> ct;
+    f4 mt[NM];
+    float wt = 1.f;
+    // a lane takes a token, so that the stores by column go to different banks
+    const int m_tok = threadIdx.x % KT, m_c = 4 * (threadIdx.x / KT);
+    constexpr int M_STEP = 4 * (kF32Threads / KT);
+    auto fetch = [&](int j0) {
         const size_t row = (size_t)u * sh.n + j0;
         const int nv = j_end - j0;
-        const S *cp = C + row * sh.dv + c0;
-        Tile<RT, KT, float> mt;
-        Tile<4, KT, S> ct;
-        if (sh.vec_m) mt.load(M + row * sh.mcols, sh.mcols, nv, sh.mcols);
-        if (sh.vec_v) ct.load(cp, sh.dv, nv, sh.dv - c0);
-        __syncthreads();
-        if (sh.vec_m) mt.store(ms, nv, sh.mcols);
-        else stage_scalar<RT, KT>(M + row * sh.mcols, sh.mcols, nv, sh.mcols, ms);
-        if (sh.vec_v) ct.store(vs, nv, sh.dv - c0);
-        else stage_scalar<4, KT>(cp, sh.dv, nv, sh.dv - c0, vs);
-        if (threadIdx.x < KT) ws[threadIdx.x] = wts && (int)threadIdx.x < nv ? wts[row + threadIdx.x] : 1.f;
-        __syncthreads();
-        f4 part[SLOTS][4];                                  // two levels of summation, as in psf_f32_bwd.hip
+        if (sh.vec_v) ct.load(C + row * sh.dv + c0, sh.dv, nv, sh.dv - c0);
 #pragma unroll
-        for (int e = 0; e < SLOTS; ++e) clear(part[e]);
-        for (int t16 = 0; t16 < KT; t16 += 16) {
-            if (t16 >= nv) break;
+        for (int k = 0; k < NM; ++k) {
+            const float *mp = M + row * sh.mcols;
+            if (sh.vec_m) mt[k] = *(const f4 *)(mp + tile_piece(m_tok, m_c + k * M_STEP, sh.mcols, nv, sh.mcols));
+            else mt[k] = row_piece(mp + (size_t)(m_tok < nv ? m_tok : 0) * sh.mcols, m_c + k * M_STEP, sh.mcols, 0);
+        }
+        if (wts && threadIdx.x < KT) wt = (int)threadIdx.x < nv ? wts[row + threadIdx.x] : 0.f;
+    };
+    if (j_begin < j_end) fetch(j_begin);
+    for (int j0 = j_begin; j0 < j_end; j0 += KT) {
+        const int nv = j_end - j0;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NM; ++k)
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                const int j = t16 + 4 * g + s;
-                const float wt = ws[j], ma_lo = ms[j * MP + a_lo], ma_hi = TWO ? ms[j * MP + a_hi] : 0.f;
-                float vb[4];
+                const int c = m_c + k * M_STEP + s;
+                ms[c * MP + m_tok] = m_tok < nv && c < sh.mcols ? mt[k][s] : 0.f;
+            }
+        if (sh.vec_v) ct.template store<false>(vs, nv, sh.dv - c0);
+        else stage_parts_scalar<4, KT, VP, S, false>(C + ((size_t)u * sh.n + j0) * sh.dv + c0, sh.dv, nv, sh.dv - c0, vs);
+        if (threadIdx.x < KT) ws[threadIdx.x] = wt;
+        __syncthreads();
+        if (j0 + KT < j_end) fetch(j0 + KT);
 #pragma unroll
-                for (int ct = 0; ct < 4; ++ct) vb[ct] = vs[j * VP + 16 * ct + li];
+        for (int t32 = 0; t32 < KT; t32 += 32) {
+            if (t32 >= nv) break;
+            // tile order: tokens t32 + 4 g + s and 16 further on
+            const float *mrow = ms + t32 + 4 * g;
+            auto tokens = [&](const float *at, float (&x)[8]) {
+                const f4 lo4 = *(const f4 *)at, hi4 = *(const f4 *)(at + 16);
 #pragma unroll
-                for (int e = 0; e < SLOTS; ++e) {
-                    if (!TWO && e >= split) break;
-                    // the first tile of an index is on the diagonal, the others stand for their mirror too
-                    const float ma = e == 0 ? ma_lo : e < split ? 2.f * ma_lo : e == split ? ma_hi : 2.f * ma_hi;
-                    const float av = ms[j * MP + mcol[e] + li] * ma;
-                    den[e] += av * wt;
+                for (int s = 0; s < 4; ++s) { x[s] = lo4[s]; x[4 + s] = hi4[s]; }
+            };
+            Parts<P> vb[4];
 #pragma unroll
-                    for (int ct = 0; ct < 4; ++ct) part[e][ct] = mm(av, vb[ct], part[e][ct]);
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int i = 0; i < P; ++i) vb[t].v[i] = read_columns(vs + t32 * VP + i * KT * VP, VP, 16 * t, lane);
+            float ma_lo[8], ma_hi[8], wj[8];
+            tokens(mrow + a_lo * MP, ma_lo);
+            if (TWO) tokens(mrow + a_hi * MP, ma_hi);
+            if (wts) tokens(ws + t32 + 4 * g, wj);
+#pragma unroll
+            for (int e = 0; e < SLOTS; ++e) {
+                if (!TWO && e >= split) break;
+                float mb[8], av[8];
+                tokens(mrow + (mcol[e] + li) * MP, mb);
+                // the first tile of an index is on the diagonal, the others stand for their mirror too
+                const float twice = e == 0 || e == split ? 1.f : 2.f;
+                float sum = 0.f;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    av[k] = mb[k] * (!TWO || e < split ? ma_lo[k] : ma_hi[k]);
+                    sum = wts ? __builtin_fmaf(av[k], wj[k], sum) : sum + av[k];
                 }
+                den[e] = __builtin_fmaf(sum, twice, den[e]);
+                Parts<3> ap;
+                split8(av, ap);
+                mm_columns(ap, vb, part[e]);
             }
         }
+        if (((j0 - j_begin) / KT & 1) || j0 + KT >= j_end) {
+            settle_parts();
 #pragma unroll
-        for (int e = 0; e < SLOTS; ++e) add_to(acc[e], part[e]);
+            for (int e = 0; e < SLOTS; ++e) {
+                const float twice = e == 0 || e == split ? 1.f : 2.f;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[e][t] += part[e][t] * twice;
+                clear(part[e]);
+            }
+        }
     }
-    settle();
     float *rec = Z + ((size_t)u * sh.spans + span) * record_floats(RT, VT);
-    float *srec = rec + (size_t)tile_pairs(RT) * 256 * 16 * VT;
+    float *srec = rec + record_values(RT, VT) / 2 * 3;
 #pragma unroll
     for (int e = 0; e < SLOTS; ++e) {
         if (!TWO && e >= split) break;
@@ -184,75 +160,247 @@ __global__ __launch_bounds__(kF32Threads, RT <= 2 ? 3 : RT == 4 ? 2 : 1) void f3
     }
 }
 
-// In place over the spans of a unit: exclusive prefix, exclusive suffix, or the total in slot 0.
+// In place over the spans of a unit: exclusive prefix, exclusive suffix, or the total in slot 0; the
+// values leave as parts (see tile_pairs).  A thread takes eight columns, or four entries of the
+// denominator column, of all spans; the next span's record is loaded before this one is written.
 // The record that an exclusive sum never reads (the last, or the first) need not be there.
 enum { kScanPrefix = 0, kScanSuffix = 1, kScanTotal = 2 };
-__global__ __launch_bounds__(kF32Threads) void f32_scan_kernel(float *__restrict__ Z, size_t pieces, size_t rec,
-                                                               int spans, int mode)
+__global__ __launch_bounds__(kF32Threads) void f32_scan_kernel(float *__restrict__ Z, int units, size_t values,
+                                                               size_t rec, int spans, int mode)
 {
-    const size_t idx = (size_t)blockIdx.x * kF32Threads + threadIdx.x;
-    if (idx >= pieces) return;
-    const size_t per = rec / 4;
-    float *z = Z + (idx / per) * (size_t)spans * rec + (idx % per) * 4;
-    f4 run = {0.f, 0.f, 0.f, 0.f};
-    if (mode == kScanTotal) {
-        for (int l = 0; l < spans; ++l) run += *(const f4 *)(z + (size_t)l * rec);
-        *(f4 *)z = run;
-        return;
-    }
+    const size_t idx = (size_t)blockIdx.x * kF32Threads + threadIdx.x, per = values / 8 + (rec - values / 2 * 3) / 4;
+    if (idx >= (size_t)units * per) return;
+    const size_t in = idx % per;
+    const bool vals = in < values / 8;
+    float *z = Z + (idx / per) * (size_t)spans * rec + (vals ? in * 8 : values / 2 * 3 + (in - values / 8) * 4);
+    float *zl = Z + (idx / per) * (size_t)spans * rec + values + in * 4;
+    f4 run[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}}, next[2] = {run[0], run[0]};
+    auto load = [&](int k) {
+        if (k >= (mode == kScanTotal ? spans : spans - 1)) return;
+        const float *at = z + (size_t)(mode == kScanSuffix ? spans - 1 - k : k) * rec;
+        next[0] = *(const f4 *)at;
+        if (vals) next[1] = *(const f4 *)(at + 4);
+    };
+    auto store = [&](int k) {
+        const size_t at = (size_t)(mode == kScanSuffix ? spans - 1 - k : k) * rec;
+        if (!vals) {
+            *(f4 *)(z + at) = run[0];
+            return;
+        }
+        const float x[8] = {run[0][0], run[0][1], run[0][2], run[0][3], run[1][0], run[1][1], run[1][2], run[1][3]};
+        Parts<3> p;
+        split8(x, p);
+        *(bf8 *)(z + at) = p.v[0];
+        *(bf8 *)(z + at + 4) = p.v[1];
+        *(bf8 *)(zl + at) = p.v[2];
+    };
+    load(0);
     for (int k = 0; k < spans; ++k) {
-        const int l = mode == kScanSuffix ? spans - 1 - k : k;
-        f4 h = {0.f, 0.f, 0.f, 0.f};
-        if (k < spans - 1) h = *(const f4 *)(z + (size_t)l * rec);
-        *(f4 *)(z + (size_t)l * rec) = run;
-        run += h;
+        const f4 h0 = next[0], h1 = next[1];
+        load(k + 1);
+        if (mode != kScanTotal) store(k);
+        run[0] += h0;
+        run[1] += h1;
+    }
+    if (mode == kScanTotal) store(0);
+}
+
+// the end of a row: acc^T holds its unnormalised output
+template <int VT, bool GRAD, typename T>
+__device__ __forceinline__ void finish_row(const f4 (&acc)[VT], float D, bool there, int li, int g, size_t row,
+                                           T *__restrict__ O, const T *__restrict__ dO, float *__restrict__ GV,
+                                           float *__restrict__ gden, const F32Shape &sh)
+{
+    if constexpr (!GRAD) {
+#pragma unroll
+        for (int ct = 0; ct < VT; ++ct)
+            store_piece(O + row * sh.dv, 16 * ct + 4 * g, sh.dv, sh.vec_v,
+                        f4{acc[ct][0] / D, acc[ct][1] / D, acc[ct][2] / D, acc[ct][3] / D});
+    } else {
+        float go[4 * VT], dot = 0.f;
+        load_frags<VT>(dO + row * sh.dv, sh.dv, there, sh.vec_v, g, go);
+#pragma unroll
+        for (int ct = 0; ct < VT; ++ct)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) dot += go[4 * ct + k] * acc[ct][k];
+        dot = over_groups(dot);
+        if (!there) return;
+#pragma unroll
+        for (int ct = 0; ct < VT; ++ct)
+            store_piece(GV + row * sh.dv, 16 * ct + 4 * g, sh.dv, sh.dv % 4 == 0,
+                        f4{go[4 * ct] / D, go[4 * ct + 1] / D, go[4 * ct + 2] / D, go[4 * ct + 3] / D});
+        if (g == 0) gden[row] = -(dot / D) / D;
     }
 }
 
 // ---- rows: pairs of the row's span, then phi'(q_i)^T Z, then the division --------------------
-// WR = 4: 64 rows a workgroup, a wave per 16 of them, every staged tile serves all four.
-// WR = 1: 16 rows a workgroup, the waves share the work on them (keys, state rows) and add up at
-// the end: four times the workgroups, for problems that would not fill the chip otherwise.
-// With WR = 4 a wave has the whole row, so the sums of a staged tile and of a state piece are formed
-// apart and then added to the total; one running sum over 3000 tokens (r = 64, 15 blocks) was 6.8e-7
-// from float64, this is 3.3e-7 (36 units x 3000, r = 32: 210 us then, 215 to 220 now).
+// WR waves take 16 rows each, and WK such sets share the keys of a tile (32 each) and the indices a of a
+// state and add up at the end; every staged tile serves all of them.
+//   WR 4, WK 1: two or more workgroups a CU; two groups of 32 keys a tile, one after the other
+//   WR 4, WK 2: fewer, but one for most CUs: half the steps each
+//   WR 1, WK 4: four times the workgroups
+// The sums of a staged tile are formed apart and then added to the total.
 // GRAD: instead of the output, G_i = [dO_i / D_i | -<dO_i, o_i> / D_i] for the backward pass.
-template <int DT, int RT, int VT, int WR, bool GRAD, typename T>
-__global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void f32_rows_kernel(
+template <int DT, int RT, int WR, int WK_, typename T>
+struct RowsLds {
+    static constexpr int P = parts_of<T>(), MT = RT < 2 ? 2 : RT, OP = pitch_of<RT>(), ROWS = 16 * WR;
+    static constexpr int KP = row_pitch<DT>(), VP = tr_pitch<DT>(), MP = row_pitch<MT>();
+    static constexpr int kRow = P * KP + P * VP + 3 * MP;             // 16-bit places of a key
+    static constexpr int WK = kRow * 2 * 32 * WK_ <= 150 * 1024 ? WK_ : WK_ / 2;
+    static constexpr int kThreads = 64 * WR * WK, KT = WK == 1 ? f32_tile_rows(DT, 4) : 32 * WK;
+    static constexpr int kKeys = P * KT * KP, kVals = P * KT * VP;
+    static constexpr int kBuffers = WK == 4 ? 1 : 2;
+    static constexpr int kPiece = 3 * 32 * VP, kOwn = ROWS * OP * 2;  // a state piece; sketches of the rows, fp32
+    static constexpr int kBack = WK * ROWS * (16 * DT + 4) * 2;       // the states' share of the rows, fp32
+    static constexpr int kSums = (WK - 1) * WR * (4 * DT + 1) * 64 * 2;
+    static constexpr int most(int a, int b) { return a > b ? a : b; }
+    static constexpr int kPlaces = most(most(KT * kRow, kBuffers * WK * kPiece + kOwn), most(kBack, kSums));
+};
+
+template <int DT, int RT, int WR, int WK_, bool GRAD, typename T>
+__global__ __launch_bounds__((RowsLds<DT, RT, WR, WK_, T>::kThreads), WK_ == 1 && DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void f32_rows_kernel(
     const float *__restrict__ MQ, const float *__restrict__ MK, const T *__restrict__ Q, const T *__restrict__ K,
     const T *__restrict__ V, const float *__restrict__ Z, T *__restrict__ O, const T *__restrict__ dO,
     float *__restrict__ GV, float *__restrict__ gden, F32Shape sh)
 {
-    constexpr int KT = f32_tile_rows(DT, WR), KP = pitch_of<DT>(), MP = pitch_of<RT>(), VP = pitch_of<VT>();
-    constexpr int ROWS = 16 * WR, ZA = KT / 16;             // sketch indices a per staged piece of the state,
-    constexpr int ZW = WR == 1 ? 1 : ZA;                    // and how many of them a wave takes
-    constexpr int kTileFloats = KT * (KP + VP) + (KT > ROWS ? KT : ROWS) * MP;
-    static_assert(WR == 4 || KT == 64, "the waves of a 16-row workgroup take one key group each");
-    static_assert(DT == VT, "the state is staged through the buffers of K and V in turn");
-    __shared__ __attribute__((aligned(16))) float lds[kTileFloats];
-    __shared__ __attribute__((aligned(16))) float sden[2][16 * ZA];   // denominator column of a state piece
-    float *ks = lds, *vs = lds + KT * KP, *ms = vs + KT * VP;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, g = lane >> 4;
-    // the longest rows of all units first: what is dealt last is short, and the workgroups that
-    // share a CU are of different lengths
+    using L = RowsLds<DT, RT, WR, WK_, T>;
+    constexpr int VT = DT, ROWS = L::ROWS, KT = L::KT, P = L::P, MT = L::MT, KP = L::KP, VP = L::VP, MP = L::MP;
+    constexpr int WK = L::WK, THREADS = L::kThreads;
+    __shared__ __attribute__((aligned(16))) uint16_t lds[L::kPlaces];
+    __shared__ __attribute__((aligned(16))) float sden[2][32 * WK];        // denominator column of a state piece
+    __shared__ int odd_tile[2];                                       // the tile of V holds an infinity or NaN
+    uint16_t *ks = lds, *vs = ks + L::kKeys, *ms = vs + L::kVals;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = lane & 15, g = lane >> 4;
+    RowPlace at_rows;
     const int per_span = (min(sh.span, sh.n) + ROWS - 1) / ROWS;
-    const unsigned flat = blockIdx.y * gridDim.x + blockIdx.x;
-    const int u = flat % sh.units, x = flat / sh.units;
-    if (x >= per_span * sh.spans) return;
-    const int span = sh.spans - 1 - x % sh.spans, s_begin = span * sh.span, s_end = min(sh.n, s_begin + sh.span);
-    const int i0 = s_begin + (per_span - 1 - x / sh.spans) * ROWS;
+    if (!row_place(blockIdx.y * gridDim.x + blockIdx.x, sh.units, sh.spans, per_span, at_rows)) return;
+    const int u = at_rows.unit, span = sh.spans - 1 - at_rows.span;
+    const int s_begin = span * sh.span, s_end = min(sh.n, s_begin + sh.span);
+    const int i0 = s_begin + (per_span - 1 - at_rows.k) * ROWS;
     if (i0 >= s_end) return;
-    const int iw = i0 + (WR == 4 ? 16 * wave : 0), i = iw + li;
+    const int wr = wave % WR, wk = wave / WR, iw = i0 + 16 * wr, i = iw + li;
     const int i_last = min(i0 + ROWS, s_end) - 1, iw_last = min(iw + 15, s_end - 1);
     const bool there = i < s_end;
     const size_t urow = (size_t)u * sh.n;
-    float qf[4 * DT], mf[4 * RT];
-    if (sh.local_exact) load_frags<DT>(Q + (urow + i) * sh.d, sh.d, there, sh.vec_x, g, qf);
-    load_frags<RT>(MQ + (urow + i) * sh.mcols, sh.mcols, there, sh.vec_m, g, mf);
+    const size_t i_row = urow + min(i, s_end - 1);          // (rows that are not there hold another's values and are not stored)
     f4 acc[VT];
     float den = 0.f;
+    clear(acc);
+
+    // The state's share.  T_a = sum over b' of Z[a][b'] m(q)[b'] is a product with the rows' sketches as fixed
+    // operands, and the share is sum over a of m(q)[a] T_a in fp32 vector arithmetic: 16 of them a
+    // lane for 24 products, where features phi' as operands cost 8 multiplications and 44 instructions to take
+    // them apart.  A wave takes 16 columns (32 of wide values) of all 64 rows, so that an operand read
+    // from LDS serves four products of rows.  A piece is one a with 32 b' (two index tiles, the
+    // first of which holds zeros where it lies left of the diagonal).
+    if (sh.states && (sh.noncausal || span > 0)) {
+        constexpr int KS = MT / 2, C = VT / WR, H = WR, OP = L::OP, CP = 16 * VT, CH = CP / 8;
+        const float *z = Z + ((size_t)u * sh.spans + (sh.noncausal ? 0 : span)) * record_floats(RT, VT);
+        const float *zs = z + record_values(RT, VT) / 2 * 3;
+        constexpr int NP = 32 * CH * WK / THREADS;
+        static_assert(32 * CH * WK % THREADS == 0 && 16 % WK == 0, "whole pieces");
+        RecordPiece pre[NP];
+        float pre_s = 0.f;
+        int fa = 0, fk = 0;                                 // the pieces to fetch: first sketch index, pair of tiles
+        auto fetch = [&]() {
+            const int at = fa >> 4, first = at * RT - at * (at - 1) / 2 - at;
 #pragma unroll
-    for (int ct = 0; ct < VT; ++ct) acc[ct] = f4{0.f, 0.f, 0.f, 0.f};
+            for (int k = 0; k < NP; ++k) {
+                const int idx = k * THREADS + threadIdx.x, row = idx / CH % 32, q = 2 * fk + (row >> 4);
+                const int a16 = (fa & 15) + idx / (32 * CH);
+                if (q >= at && q < RT)
+                    pre[k].load(z, record_values(RT, VT), CP, ((first + q) * 16 + a16) * 16 + (row & 15), 8 * (idx % CH));
+                else pre[k].zero();
+            }
+            if (threadIdx.x < 32 * WK) {
+                const int q = 2 * fk + (threadIdx.x >> 4 & 1), a16 = (fa & 15) + threadIdx.x / 32;
+                pre_s = q >= at && q < RT ? zs[((first + q) * 16 + a16) * 16 + (threadIdx.x & 15)] : 0.f;
+            }
+            if (++fk == KS) { fa += WK; fk = fa >> 5; }
+        };
+        auto put = [&](int buf) {
+            if (threadIdx.x < 32 * WK) sden[buf][threadIdx.x] = pre_s;
+#pragma unroll
+            for (int k = 0; k < NP; ++k) {
+                const int idx = k * THREADS + threadIdx.x;
+                pre[k].store(lds + (buf * WK + idx / (32 * CH)) * L::kPiece + (idx / CH % 32) * VP + 8 * (idx % CH), 32 * VP);
+            }
+        };
+        fetch();
+        // the rows' sketches, where they can be indexed
+        float *own = (float *)(lds + L::kBuffers * WK * L::kPiece);
+        Parts<3> mb[H][KS];
+        float md[8 * KS];                                   // of the wave's 16 rows, for the denominator
+        {
+            OwnRow<KS, float> rows[H], mine;
+#pragma unroll
+            for (int h = 0; h < H; ++h)
+                rows[h].load(MQ + (urow + min(i0 + 16 * h + li, s_end - 1)) * sh.mcols, sh.mcols, sh.vec_m, g);
+            mine.load(MQ + i_row * sh.mcols, sh.mcols, sh.vec_m, g);
+            put(0);
+#pragma unroll
+            for (int h = 0; h < H; ++h) rows[h].parts(mb[h], sh.mcols, g);
+#pragma unroll
+            for (int e = 0; e < 2 * KS; ++e) {
+                const f4 v = mine.at(e, sh.mcols, g);
+                const int c = 32 * (e / 2) + 8 * g + 4 * (e % 2);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) md[4 * e + s] = v[s];
+                if (wk == 0 && c < 16 * RT) *(f4 *)&own[(16 * wr + li) * OP + c] = v;
+            }
+        }
+        f4 sum[H * C];
+        clear(sum);
+        int buf = 0;
+        for (int a0 = 0; a0 < 16 * RT; a0 += WK) {
+            const int a = a0 + wk;
+            f4 ta[H * C];
+            clear(ta);
+            float sd = 0.f;
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+                if (k < (a0 >> 5)) continue;
+                __syncthreads();
+                const bool more = fa < 16 * RT;
+                if (more) fetch();
+#pragma unroll
+                for (int e = 0; e < 8; e += 4) {
+                    const f4 s = *(const f4 *)&sden[buf][32 * wk + 8 * g + e];
+                    sd += (s[0] * md[8 * k + e] + s[1] * md[8 * k + e + 1]) + (s[2] * md[8 * k + e + 2] + s[3] * md[8 * k + e + 3]);
+                }
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    Parts<3> zp;
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        zp.v[i] = read_rows_tr(lds + (buf * WK + wk) * L::kPiece + i * 32 * VP, VP, 16 * (C * wr + c), lane);
+                    mm_rows(zp, mb, k, ta + H * c);
+                }
+                settle_parts();                             // (the step may be left out)
+                if (L::kBuffers == 1) __syncthreads();
+                else buf ^= 1;
+                if (more) put(buf);
+            }
+            float ma[H];
+#pragma unroll
+            for (int h = 0; h < H; ++h) ma[h] = own[(16 * h + li) * OP + a];
+            den += own[(16 * wr + li) * OP + a] * sd;
+#pragma unroll
+            for (int h = 0; h < H; ++h)
+#pragma unroll
+                for (int c = 0; c < C; ++c) sum[H * c + h] += ta[H * c + h] * ma[h];
+        }
+        // from columns of all rows to all columns of the wave's rows
+        __syncthreads();
+        float *back = (float *)lds + wk * ROWS * (CP + 4);
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int c = 0; c < C; ++c) *(f4 *)&back[(16 * h + li) * (CP + 4) + 16 * (C * wr + c) + 4 * g] = sum[H * c + h];
+        __syncthreads();
+#pragma unroll
+        for (int ct = 0; ct < VT; ++ct) acc[ct] = *(const f4 *)&back[(16 * wr + li) * (CP + 4) + 16 * ct + 4 * g];
+    }
 
     if (sh.pairs) {
         // exact weights for keys from the start of the row's block on
@@ -262,132 +410,106 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void 
         const int bs_w = sh.local_exact ? iw / sh.b * sh.b : 0x7fffffff;
         const int bs_w_last = sh.local_exact ? iw_last / sh.b * sh.b : 0x7fffffff;
         const int j_end = sh.noncausal ? sh.n : i_last + 1;
-        for (int j0 = sh.noncausal ? 0 : s_begin; j0 < j_end; j0 += KT) {
+        const int j_max = sh.noncausal ? sh.n - 1 : i, all_see = sh.noncausal ? sh.n - 1 : iw;
+        if (threadIdx.x < 2) odd_tile[threadIdx.x] = 0;
+        int turn = 0;
+        PartTile<DT, KT, KP, T, THREADS> kt;
+        PartTile<MT, KT, MP, float, THREADS> mt;
+        PartTile<VT, KT, VP, T, THREADS> vt;
+        auto fetch = [&](int j0) {
+            const int nv = min(KT, j_end - j0);
+            if (sh.vec_v) vt.load(V + (urow + j0) * sh.dv, sh.dv, nv, sh.dv);
+            if (j0 + KT > bs_wg && sh.vec_x) kt.load(K + (urow + j0) * sh.d, sh.d, nv, sh.d);
+            if (j0 < bs_wg_last && sh.vec_m) mt.load(MK + (urow + j0) * sh.mcols, sh.mcols, nv, sh.mcols);
+        };
+        const int j_begin = sh.noncausal ? 0 : s_begin;
+        fetch(j_begin);
+        Parts<P> qf[DT / 2];
+        Parts<3> mf[MT / 2];
+        {
+            OwnRow<DT / 2, T> q_row;
+            OwnRow<MT / 2, float> m_row;
+            if (sh.local_exact) q_row.load(Q + i_row * sh.d, sh.d, sh.vec_x, g);
+            m_row.load(MQ + i_row * sh.mcols, sh.mcols, sh.vec_m, g);
+            if (sh.local_exact) q_row.parts(qf, sh.d, g);
+            m_row.parts(mf, sh.mcols, g);
+        }
+        for (int j0 = j_begin; j0 < j_end; j0 += KT, turn ^= 1) {
             const int nv = min(KT, j_end - j0);
             const bool exact_g = j0 + KT > bs_wg, cross_g = j0 < bs_wg_last;
-            Tile<DT, KT, T> kt;
-            Tile<RT, KT, float> mt;
-            Tile<VT, KT, T> vt;
-            const T *vp = V + (urow + j0) * sh.dv, *kp = K + (urow + j0) * sh.d;
-            const float *mp = MK + (urow + j0) * sh.mcols;
-            if (sh.vec_v) vt.load(vp, sh.dv, nv, sh.dv);
-            if (exact_g && sh.vec_x) kt.load(kp, sh.d, nv, sh.d);
-            if (cross_g && sh.vec_m) mt.load(mp, sh.mcols, nv, sh.mcols);
             __syncthreads();
             if (exact_g) {
-                if (sh.vec_x) kt.store(ks, nv, sh.d);
-                else stage_scalar<DT, KT>(kp, sh.d, nv, sh.d, ks);
+                if (sh.vec_x) kt.template store<false>(ks, nv, sh.d);
+                else stage_parts_scalar<DT, KT, KP, T, false, THREADS>(K + (urow + j0) * sh.d, sh.d, nv, sh.d, ks);
             }
             if (cross_g) {
-                if (sh.vec_m) mt.store(ms, nv, sh.mcols);
-                else stage_scalar<RT, KT>(mp, sh.mcols, nv, sh.mcols, ms);
+                if (sh.vec_m) mt.template store<false>(ms, nv, sh.mcols);
+                else stage_parts_scalar<MT, KT, MP, float, false, THREADS>(MK + (urow + j0) * sh.mcols, sh.mcols, nv, sh.mcols, ms);
             }
-            if (sh.vec_v) vt.store(vs, nv, sh.dv);
-            else stage_scalar<VT, KT>(vp, sh.dv, nv, sh.dv, vs);
+            bool odd;
+            if (sh.vec_v) odd = vt.template store<true>(vs, nv, sh.dv);
+            else odd = stage_parts_scalar<VT, KT, VP, T, true, THREADS>(V + (urow + j0) * sh.dv, sh.dv, nv, sh.dv, vs);
+            if (odd) odd_tile[turn] = 1;
             __syncthreads();
-            f4 part[VT];                                    // WR = 4: this tile's sums (two levels of summation)
+            odd = odd_tile[turn] != 0;
+            if (threadIdx.x == 0) odd_tile[turn ^ 1] = 0;   // (read for the last time before the barrier above)
+            if (j0 + KT < j_end) fetch(j0 + KT);
+            f4 part[VT];                                    // this tile's sums (two levels of summation)
             float dpart = 0.f;
-            if constexpr (WR == 4) clear(part);
-            for (int sub = (WR == 4 ? 0 : wave); sub < KT / 16; sub += (WR == 4 ? 1 : 4)) {
-                f4 (&to)[VT] = WR == 4 ? part : acc;
-                const int js = j0 + 16 * sub;
+            clear(part);
+            for (int sub = wk; sub < KT / 32; sub += WK) {
+                const int js = j0 + 32 * sub;
                 if (js >= j_end || (!sh.noncausal && js > iw_last)) break;
-                f4 se = {0.f, 0.f, 0.f, 0.f}, ss = se;
-                if (js + 15 >= bs_w) se = score_rows<DT>(ks, 16 * sub, qf, lane);
-                if (js < bs_w_last) ss = score_rows<RT>(ms, 16 * sub, mf, lane);
-                float w[4];
-                const int j_max = sh.noncausal ? sh.n - 1 : i;
+                const bool exact_w = js + 31 >= bs_w, cross_w = js < bs_w_last;
+                f4 w[2], ss[2];
+                if (exact_w) score_parts<2, DT / 2, P, P>(ks, KT * KP, KP, 32 * sub, qf, lane, w);
+                if (cross_w) score_parts<2, MT / 2, 3, 3>(ms, KT * MP, MP, 32 * sub, mf, lane, ss);
+                settle_parts();
+                if (exact_w)
+                    for (int q = 1; q < sh.p; q <<= 1) { w[0] *= w[0]; w[1] *= w[1]; }
+                if (cross_w) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int j = js + 4 * g + k;
-                    float e = se[k];
-                    for (int q = 1; q < sh.p; q <<= 1) e *= e;
-                    w[k] = j > j_max ? 0.f : j >= bs ? e : ss[k] * ss[k];
-                    dpart += w[k];
+                    for (int t = 0; t < 2; ++t) {
+                        ss[t] *= ss[t];
+                        if (exact_w) {
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) w[t][k] = js + 16 * t + 4 * g + k >= bs ? w[t][k] : ss[t][k];
+                        } else {
+                            w[t] = ss[t];
+                        }
+                    }
                 }
-                if (!sh.noncausal && js + 15 > iw) {
-                    const int vis = i - js;                 // tile rows 0 .. vis count
-                    add_rows<VT, true>(vs, 16 * sub, w, to, lane, vis < 0 ? 0u : 0xffffu >> max(0, 15 - vis));
+                if (js + 31 > all_see) {
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) w[t][k] = js + 16 * t + 4 * g + k > j_max ? 0.f : w[t][k];
+                }
+                dpart += ((w[0][0] + w[0][1]) + (w[0][2] + w[0][3])) + ((w[1][0] + w[1][1]) + (w[1][2] + w[1][3]));
+                const float flat_w[8] = {w[0][0], w[0][1], w[0][2], w[0][3], w[1][0], w[1][1], w[1][2], w[1][3]};
+                if (odd) {
+                    const int vis = j_max - js;             // tile rows 0 .. vis count
+                    add_parts_odd<VT, P>(vs + 32 * sub * VP, KT * VP, VP, flat_w, part, lane,
+                                         vis < 0 ? 0u : vis >= 31 ? 0xffffffffu : (2u << vis) - 1u);
                 } else {
-                    add_rows<VT, false>(vs, 16 * sub, w, to, lane, 0u);
+                    Parts<3> wp;
+                    split8(flat_w, wp);
+                    add_parts<VT, P>(vs + 32 * sub * VP, KT * VP, VP, wp, part, lane);
                 }
+                settle_parts();
             }
             den += dpart;
-            if constexpr (WR == 4) add_to(acc, part);
+            add_settled(acc, part);
         }
     }
 
-    if (sh.states && (sh.noncausal || span > 0)) {
-        const float *z = Z + ((size_t)u * sh.spans + (sh.noncausal ? 0 : span)) * record_floats(RT, VT);
-        const float *zs = z + (size_t)tile_pairs(RT) * 256 * 16 * VT;
-        constexpr int PIECE = KT * 16 * VT, NP = PIECE / 4 / kF32Threads;     // floats of a piece; 16-byte loads a thread
-        constexpr int CH = 16 / ZA, LAST = tile_pairs(RT) * CH - 1;
-        f4 pre[NP], pre_s = {0.f, 0.f, 0.f, 0.f};
-        auto fetch = [&](int piece) {
-#pragma unroll
-            for (int k = 0; k < NP; ++k)
-                pre[k] = *(const f4 *)(z + (size_t)piece * PIECE + (k * kF32Threads + threadIdx.x) * 4);
-            if (threadIdx.x < 4 * ZA) pre_s = *(const f4 *)(zs + (size_t)piece * ZA * 16 + threadIdx.x * 4);
-        };
-        auto put = [&](float *dst, int buf) {
-            if (threadIdx.x < 4 * ZA) *(f4 *)&sden[buf][threadIdx.x * 4] = pre_s;
-#pragma unroll
-            for (int k = 0; k < NP; ++k) {
-                const int idx = k * kF32Threads + threadIdx.x;
-                *(f4 *)&dst[(idx / (4 * VT)) * VP + 4 * (idx % (4 * VT))] = pre[k];
-            }
-        };
-        fetch(0);
-        __syncthreads();
-        put(ks, 0);
-        // the wave's own sketch rows, where they can be indexed (sync: the last pairs have been read)
-        float *own = ms + ((WR == 4 ? 16 * wave : 0) + li) * MP;
-#pragma unroll
-        for (int q = 0; q < RT; ++q)
-            *(f4 *)&own[16 * q + 4 * g] = f4{mf[4 * q], mf[4 * q + 1], mf[4 * q + 2], mf[4 * q + 3]};
-        int at = 0, q = 0;
-        f4 mq = *(const f4 *)&own[4 * g];
-        for (int piece = 0; piece <= LAST; ++piece) {
-            const int ch = piece % CH;
-            if (piece && ch == 0) {                         // the next pair of index tiles
-                if (++q == RT) q = ++at;
-                mq = *(const f4 *)&own[16 * q + 4 * g];
-            }
-            __syncthreads();
-            const float *zt = piece & 1 ? vs : ks;
-            if (piece < LAST) fetch(piece + 1);
-            f4 part[VT];
-            float dpart = 0.f;
-            if constexpr (WR == 4) clear(part);
-            f4 (&to)[VT] = WR == 4 ? part : acc;
-#pragma unroll
-            for (int k = 0; k < ZW; ++k) {
-                const int aa = WR == 1 ? wave : k;
-                const float ma = own[16 * at + ZA * ch + aa];
-                const f4 sd = *(const f4 *)&sden[piece & 1][aa * 16 + 4 * g];
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const float phi = ma * mq[s];
-                    dpart += phi * sd[s];
-#pragma unroll
-                    for (int ct = 0; ct < VT; ++ct)
-                        to[ct] = mm(zt[(aa * 16 + 4 * g + s) * VP + 16 * ct + li], phi, to[ct]);
-                }
-            }
-            den += dpart;
-            if constexpr (WR == 4) add_to(acc, part);
-            if (piece < LAST) put(piece & 1 ? ks : vs, ~piece & 1);
-        }
-    }
-
-    settle();
+    settle_parts();
     den = over_groups(den);
-    if constexpr (WR == 1) {
+    if constexpr (WK > 1) {
         constexpr int PER = 4 * VT + 1;
-        static_assert(3 * PER * 64 <= kTileFloats, "sums of three waves");
         __syncthreads();
-        if (wave > 0) {
-            float *to = lds + (size_t)(wave - 1) * PER * 64 + lane;
+        if (wk > 0) {
+            float *to = (float *)lds + (size_t)((wk - 1) * WR + wr) * PER * 64 + lane;
 #pragma unroll
             for (int ct = 0; ct < VT; ++ct)
 #pragma unroll
@@ -395,9 +517,9 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void 
             to[4 * VT * 64] = den;
         }
         __syncthreads();
-        if (wave > 0) return;
-        for (int o = 0; o < 3; ++o) {
-            const float *from = lds + (size_t)o * PER * 64 + lane;
+        if (wk > 0) return;
+        for (int o = 0; o < WK - 1; ++o) {
+            const float *from = (const float *)lds + (size_t)(o * WR + wr) * PER * 64 + lane;
 #pragma unroll
             for (int ct = 0; ct < VT; ++ct)
 #pragma unroll
@@ -407,44 +529,7 @@ __global__ __launch_bounds__(kF32Threads, DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void 
     }
     if (!there && !GRAD) return;
     const float D = 1.f + den;
-    if constexpr (!GRAD) {
-#pragma unroll
-        for (int ct = 0; ct < VT; ++ct)
-            store_piece(O + (urow + i) * sh.dv, 16 * ct + 4 * g, sh.dv, sh.vec_v,
-                        f4{acc[ct][0] / D, acc[ct][1] / D, acc[ct][2] / D, acc[ct][3] / D});
-    } else {
-        float go[4 * VT], dot = 0.f;
-        load_frags<VT>(dO + (urow + i) * sh.dv, sh.dv, there, sh.vec_v, g, go);
-#pragma unroll
-        for (int ct = 0; ct < VT; ++ct)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) dot += go[4 * ct + k] * acc[ct][k];
-        dot = over_groups(dot);
-        if (!there) return;
-#pragma unroll
-        for (int ct = 0; ct < VT; ++ct)
-            store_piece(GV + (urow + i) * sh.dv, 16 * ct + 4 * g, sh.dv, sh.dv % 4 == 0,
-                        f4{go[4 * ct] / D, go[4 * ct + 1] / D, go[4 * ct + 2] / D, go[4 * ct + 3] / D});
-        if (g == 0) gden[urow + i] = -(dot / D) / D;
-    }
-}
-
-template <typename T>
-psf_status sketch_pair(const Problem &pb, const void *X1, const void *X2, const void *G, float *M1, float *M2,
-                       size_t x_unit, size_t m_unit, hipStream_t s)
-{
-    const dim3 grid((unsigned)((pb.n + kSketchRows - 1) / kSketchRows), (unsigned)pb.units, X2 ? 2 : 1);
-    const int vx = x_unit % 4 == 0 && (X2 ? pieces_ok<T>(pb.d, {X1, X2}) : pieces_ok<T>(pb.d, {X1}));
-    const int vm = m_unit % 4 == 0 && pieces_ok<float>(pb.mcols, {M1, M2 ? M2 : M1});
-    const int dp = tiles16(pb.d) * 16, rp = tiles16(pb.r) * 16;
-    const size_t lds = (size_t)kSketchRows * (dp + 4 + sketch_nodes(pb.p) * (rp + 4)) * sizeof(float);
-    if (lds > (64u << 10))                               // p = 16 with wide sketches: up to 118 KB
-        PSF_HIP_TRY(hipFuncSetAttribute((const void *)f32_sketch_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        (int)lds));
-    hipLaunchKernelGGL(f32_sketch_kernel<T>, grid, dim3(64), lds, s, (const T *)X1, (const T *)X2, (const T *)G, M1, M2,
-                       pb.n, pb.d, pb.r, pb.p, pb.heads, pb.per_head ? 1 : 0, pb.g_len, x_unit, m_unit, vx, vm);
-    PSF_LAUNCH_CHECK();
-    return PSF_OK;
+    finish_row<VT, GRAD>(acc, D, there, li, g, urow + i, O, dO, GV, gden, sh);
 }
 
 template <typename S>
@@ -459,9 +544,10 @@ psf_status states(const Problem &pb, const F32Plan &pl, const float *M, const S 
         hipLaunchKernelGGL((f32_state_kernel<RT, VT, S>), dim3((RT <= 4 ? RT * 2 : RT * 4) * (VT / 4), (unsigned)count, (unsigned)pb.units),
                            dim3(kF32Threads), 0, s, M, C, wts, Z, sh, span0);
         PSF_LAUNCH_CHECK();
-        const size_t rec = record_floats(RT, VT), pieces = (size_t)pb.units * (rec / 4);
+        const size_t rec = record_floats(RT, VT), values = record_values(RT, VT);
+        const size_t pieces = (size_t)pb.units * (values / 8 + tile_pairs(RT) * 64);
         hipLaunchKernelGGL(f32_scan_kernel, dim3((unsigned)((pieces + kF32Threads - 1) / kF32Threads)),
-                           dim3(kF32Threads), 0, s, Z, pieces, rec, pl.spans, mode);
+                           dim3(kF32Threads), 0, s, Z, pb.units, values, rec, pl.spans, mode);
         PSF_LAUNCH_CHECK();
         return PSF_OK;
     });
@@ -478,23 +564,17 @@ psf_status rows_launch(const Problem &pb, const F32Plan &pl, const float *MQ, co
     sh.vec_m = pieces_ok<float>(pb.mcols, {MQ, MK});
     return with_tiles(pb, [&](auto dt, auto rt) -> psf_status {
         constexpr int DT = decltype(dt)::value, RT = decltype(rt)::value;
-        auto go = [&](auto kernel, int rows) {
-            const int per_span = ((pl.span < pb.n ? pl.span : pb.n) + rows - 1) / rows;
-            const FlatGrid grid = flat_grid((unsigned long long)per_span * pl.spans * pb.units);
-            hipLaunchKernelGGL(kernel, dim3(grid.x, grid.y), dim3(kF32Threads), 0,
-                               s, MQ, MK, (const T *)Q, (const T *)K, (const T *)V, Z, (T *)O, (const T *)dO, GV, gden,
-                               sh);
+        auto go = [&](auto wr, auto wk) {
+            constexpr int WR = decltype(wr)::value, WK = decltype(wk)::value;
+            using L = RowsLds<DT, RT, WR, WK, T>;
+            const int per_span = ((pl.span < pb.n ? pl.span : pb.n) + L::ROWS - 1) / L::ROWS;
+            const FlatGrid grid = flat_grid(row_groups(pb.units, pl.spans, per_span));
+            hipLaunchKernelGGL((f32_rows_kernel<DT, RT, WR, WK, GRAD, T>), dim3(grid.x, grid.y), dim3(L::kThreads), 0, s,
+                               MQ, MK, (const T *)Q, (const T *)K, (const T *)V, Z, (T *)O, (const T *)dO, GV, gden, sh);
+            PSF_LAUNCH_CHECK();
+            return PSF_OK;
         };
-        if constexpr (DT == 4) {
-            if (f32_split_rows(pb)) {
-                go(f32_rows_kernel<DT, RT, DT, 1, GRAD, T>, 16);
-                PSF_LAUNCH_CHECK();
-                return PSF_OK;
-            }
-        }
-        go(f32_rows_kernel<DT, RT, DT, 4, GRAD, T>, 64);
-        PSF_LAUNCH_CHECK();
-        return PSF_OK;
+        return f32_deal<DT>(pb, RT == 4 && sizeof(T) == 4 ? 1024 : 512, go);
     });
 }
 
@@ -503,11 +583,6 @@ psf_status rows_launch(const Problem &pb, const F32Plan &pl, const float *MQ, co
 bool f32_supported(const Problem &pb)
 {
     return !pb.exact_feat && pb.d <= 128 && pb.dv <= 128 && pb.mcols <= 128;
-}
-
-bool f32_split_rows(const Problem &pb)
-{
-    return (long long)pb.units * ((pb.n + 63) / 64) < 512;
 }
 
 F32Shape f32_shape(const Problem &pb, const F32Plan &pl)
@@ -520,16 +595,18 @@ F32Shape f32_shape(const Problem &pb, const F32Plan &pl)
     return sh;
 }
 
-// Where the states lie.  Costs in seconds of the whole chip: states at 90 TFLOP/s, pairs at 65 (72 over
-// 3000 tokens, 50 over 1950, where the launch is short), state traffic at 4 TB/s, 5 us for the two
-// further launches: forming a record and applying it against the pairs that a longer span takes
-// directly.  Measured with every span forced (blocks a span: us of a forward call, of a backward call;
-// * the plan's choice; two runs of one span differ by up to 6 %):
-//   36 units x 3000, r 32, b 200   1: 410, 1277   2: 393*, 1245*   4: 391, 1293   8: 456, 1570   all 15: 469, 1842
-//   24 x 1950, r 32, b 150         1: 214, 619    2: 185, 600*     4: 223, 759    8: 246, 776    all 13: 201*, 686
-//   12 x 16384, r 32, b 64         1: 806, 2291   4: 569, 1916*    8: 573*, 2050  16: 666, 2444  all: 3535, 14920
-//   24 x 8000, r 64, b 250         1: 1634, 5082  2: 1591, 5146*   4: 1658*, 5592 8: 1949, 6737
-//   48 x 8192, r 16, b 256         1: 609*, 2074* 2: 667, 2385     4: 832, 3106
+// Where the states lie.  Costs in seconds of the whole chip, relative to each other: states at 90
+// TFLOP/s, pairs at 65, state traffic at 4 TB/s, 5 us for the two further launches: forming a record and
+// applying it against the pairs that a longer span takes directly.  (Rates of the fp32 matrix
+// instructions; the products from parts are faster by about the same factor on both sides.)
+// Measured with every span forced (blocks a span: us of a forward call, of a forward and a backward call;
+// * the plan's choice; two runs of one span differ by up to 5 %):
+//   36 units x 3000, r 32, b 200   1: 266, 1110   2: 233*, 1010*   4: 224, 1001   8: 250, 1207   all 15: 224, 1249
+//   24 x 1950, r 32, b 150         1: 87, 448     2: 112, 491*     4: 119, 525    8: 119, 545    all 13: 86*, 453
+//   12 x 16384, r 32, b 64         1: 843, 2965   4: 412, 1780*    8: 366*, 1707  16: -          all: 1496, 9796
+//   24 x 8000, r 64, b 250         1: 1327, 4979  2: 1154, 4545*   4: 1059*, 4481 8: 1098, 4940  all 32: 1154, 6614
+//   48 x 8192, r 16, b 256, fp32   1: 607, 2553   2: 642*, 2825*   4: 788, 3656   8: 1115, 5048
+//   12 x 2600, r 64, b 100         1: 390, 1414   2: 296, 1181     4: 240, 926    8: 255, 1009   all 26: 111*, 526*
 // z_floats: room for state records.
 static F32Plan f32_plan(const Problem &pb, size_t z_floats, bool noncausal, bool grad)
 {
@@ -540,7 +617,7 @@ static F32Plan f32_plan(const Problem &pb, size_t z_floats, bool noncausal, bool
     const size_t rec = record_floats(rt, vt);
     const double state_flops = tile_pairs(rt) * 256.0 * 16 * vt * 2 * (grad ? 6 : 2);
     const double pair_flops = 2.0 * 16 * (grad ? 5 * rt + 4 * vt : rt + vt);
-    const double passes = grad ? 9 : 4;
+    const double traffic = (grad ? 9 : 4) * (rt * (rt + 1) / 2) * 256.0 * (16 * vt + 1) * 4;    // bytes a record
     F32Plan best = {};
     if (noncausal) {
         const double direct = tokens * pb.n * pair_flops / pair_rate;
@@ -571,7 +648,7 @@ static F32Plan f32_plan(const Problem &pb, size_t z_floats, bool noncausal, bool
             double cost = tokens * (span < pb.n ? span : pb.n) / 2 * pair_flops / pair_rate;
             if (spans > 1)
                 cost += tokens * (1.0 - 1.0 / spans) * state_flops / rate +
-                        (double)pb.units * spans * rec * 4 * passes / bw + (grad ? 10e-6 : 5e-6);
+                        (double)pb.units * spans * traffic / bw + (grad ? 10e-6 : 5e-6);
             if (best.spans == 0 || cost < best.cost) {
                 best.cost = cost;
                 best.span = s * pb.b; best.spans = spans; best.pairs = 1; best.states = spans > 1;
@@ -596,21 +673,22 @@ static size_t plan_floats(const Problem &pb, const F32Plan &pl)
 // kernels, t F (dv + 1) floats a unit, is not: with few or small blocks (t mcols^2 (dv + 1) below the
 // record's floats) no record fits, and pairs alone cost time quadratic in n.  Where that room
 // makes the plan dearer than the best one by more than a quarter, the workspace grows to the
-// best plan's records (at most kMostRoom, and not past the library's static scratch where the
+// best plan's records (at most kMostRoom, 1.5 GiB, and not past the library's static scratch where the
 // call fitted it).  If that does not bring the cost within four times the best one, the vector
 // kernels take the call, whose time is linear.  Measured, without a mask, r = 8, d = 128, dv = 16, two
 // blocks (us; pairs, best plan, vector kernels): 12 units x 4096 1274, 272, 714; 12 x 16384 20429, 1050,
 // 2487; 96 x 16384 165250, 7607, 10294.  Below 1.25 nothing is to be gained (96 x 1024: 687, 687, 750).
 F32Choice f32_choose(const Problem &pb, size_t fixed_bytes, bool noncausal, bool grad)
 {
-    constexpr size_t kMostRoom = ((size_t)1 << 30) / sizeof(float);
+    constexpr size_t kMostRoom = ((size_t)3 << 29) / sizeof(float);
     F32Choice c = {};
     c.z_floats = (size_t)pb.units * pb.t * (size_t)pb.F * (pb.dv + 1);
     if (!f32_supported(pb)) return c;
     c.use = true;
     c.plan = f32_plan(pb, c.z_floats, noncausal, grad);
-    const double best = f32_plan(pb, SIZE_MAX, noncausal, grad).cost;
-    if (c.plan.cost <= 1.25 * best) return c;
+    const F32Plan most = f32_plan(pb, SIZE_MAX, noncausal, grad);
+    const double best = most.cost;
+    if (c.plan.cost <= 1.25 * best && !(noncausal && most.states && c.plan.spans < most.spans)) return c;
     size_t room = kMostRoom;
     if (!noncausal && !grad && fixed_bytes + align_up(c.z_floats * 4, 256) <= PSF_STATIC_SCRATCH_BYTES)
         room = (PSF_STATIC_SCRATCH_BYTES - fixed_bytes) / 256 * 256 / sizeof(float);
@@ -624,21 +702,6 @@ F32Choice f32_choose(const Problem &pb, size_t fixed_bytes, bool noncausal, bool
         c.z_floats = (size_t)pb.units * pb.t * (size_t)pb.F * (pb.dv + 1);
     }
     return c;
-}
-
-psf_status f32_sketch_pair(const Problem &pb, const void *X1, const void *X2, const void *G, float *M1, float *M2,
-                           hipStream_t s)
-{
-    const size_t x_unit = (size_t)pb.n * pb.d, m_unit = (size_t)pb.n * pb.mcols;
-    return pb.bf16 ? sketch_pair<bf16_t>(pb, X1, X2, G, M1, M2, x_unit, m_unit, s)
-                   : sketch_pair<float>(pb, X1, X2, G, M1, M2, x_unit, m_unit, s);
-}
-
-psf_status f32_sketch_rows(const Problem &pb, const void *X, size_t x_unit, const void *G, float *M, size_t m_unit,
-                           hipStream_t s)
-{
-    return pb.bf16 ? sketch_pair<bf16_t>(pb, X, nullptr, G, M, nullptr, x_unit, m_unit, s)
-                   : sketch_pair<float>(pb, X, nullptr, G, M, nullptr, x_unit, m_unit, s);
 }
 
 psf_status f32_key_states(const Problem &pb, const F32Plan &pl, const float *MK, const void *V, float *Z, hipStream_t s)

@@ -40,5 +40,35 @@ PSF_HD FlatGrid flat_grid(unsigned long long groups)
     return {kGridRow, (unsigned)((groups + kGridRow - 1) / kGridRow)};
 }
 
+// Which rows a workgroup of the row kernels takes: the k-th block of rows of a span of a unit.
+// Workgroups go to the eight dies in turn, and the ones of a span read the same state record and
+// keys; so with kDieGroups spans of all units or more, a span's workgroups follow each other on one
+// die and find them in its cache.  With fewer, the k-th blocks of all spans follow each other, which
+// fills the chip evenly.  Either way a span's longest walks come first (k counts from them).
+// False: a number that is not there.
+struct RowPlace { int unit, span, k; };
+constexpr int kDieGroups = 64;
+PSF_HD unsigned long long row_groups(int units, int spans, int per_span)
+{
+    const long long groups = (long long)units * spans;
+    return (unsigned long long)(groups >= kDieGroups ? (groups + 7) / 8 * 8 : groups) * (unsigned long long)per_span;
+}
+PSF_HD bool row_place(unsigned flat, int units, int spans, int per_span, RowPlace &at)
+{
+    const long long groups = (long long)units * spans;
+    long long group;
+    if (groups >= kDieGroups) {
+        const unsigned turn = flat / 8;
+        group = (long long)(turn / (unsigned)per_span) * 8 + flat % 8;
+        at.k = (int)(turn % (unsigned)per_span);
+    } else {
+        group = flat % (unsigned)groups;
+        at.k = (int)(flat / (unsigned)groups);
+    }
+    at.unit = (int)(group % units);
+    at.span = (int)(group / units);
+    return group < groups && at.k < per_span;
+}
+
 }  // namespace psf
 #endif

@@ -1,0 +1,62 @@
+"""The kernels that form fp32 products from bf16 parts, at every way of sharing out the rows and either
+storage type: a token's infinity or NaN stays out of the rows before it and arrives in its own, forward
+and backward, and is finite everywhere else; and values whose parts are far apart.  Reference: the
+same call without the odd token (rows before it), plain torch in float64."""
+import pytest
+import torch
+
+from paper_2310_01655_amd import binding as psf
+from paper_2310_01655_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+# rows that share a tile with the odd token take their sums in another order: fp32 sums differ by
+# about 1e-6, their roundings to bf16 by at most 2^-8
+SAME = {"f32": 1e-5, "bf16": 4e-3}
+SHAPES = [(2, 1300, 325), (12, 600, 150), (40, 1000, 200)]      # 42, 120 and 640 workgroups of 64 rows
+
+
+def same(x, y, dtype):
+    x, y = x.double(), y.double()
+    return bool(x.isfinite().all()) and float((x - y).norm()) <= SAME[dtype] * float(y.norm())
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("heads,n,b", SHAPES)
+def test_an_infinite_value_stays_in_its_place(heads, n, b, dtype):
+    at = n // 2 + 7
+    q, k, v = (x.cuda() for x in inputs.make_qkv(1, heads, n, 64, seed=5, dtype=dtype))
+    G = inputs.make_sketch_matrices(heads, 64, 32, 4, per_head=True, seed=3, dtype=dtype).cuda()
+    dO = inputs.make_dout(1, heads, n, 64, seed=5, dtype=dtype).cuda()
+    desc = psf.make_desc(1, heads, n, 64, 4, 32, b, dtype, per_head=True)
+    assert psf.kernel_path(desc) == 0
+    want = psf.psf_causal_attn_fwd(desc, q, k, v, G)
+    grads = psf.psf_causal_attn_bwd(desc, q, k, v, G, dO)
+    v2 = v.clone()
+    v2[:, :, at, 5], v2[:, :, at, 6] = float("inf"), float("nan")
+    got = psf.psf_causal_attn_fwd(desc, q, k, v2, G)
+    assert same(got[:, :, :at], want[:, :, :at], dtype)
+    own = got[:, :, at:at // b * b + b]                     # the rest of the block: weights are positive
+    assert (own[..., 5] == float("inf")).all() and own[..., 6].isnan().all()
+    assert not got[:, :, at:, 5:7].isfinite().any()
+    others = [c for c in range(64) if c not in (5, 6)]
+    assert got[..., others].isfinite().all()
+    # the odd gradient of one row reaches the keys up to it and no later one
+    dO2 = dO.clone()
+    dO2[:, :, at, 3] = float("inf")
+    dq, dk, dv = psf.psf_causal_attn_bwd(desc, q, k, v, G, dO2)
+    for x, y in ((dk, grads[1]), (dv, grads[2])):
+        assert same(x[:, :, at + 1:], y[:, :, at + 1:], dtype)
+    rows = [i for i in range(n) if i != at]
+    assert same(dq[:, :, rows], grads[0][:, :, rows], dtype) and not dv[:, :, at, 3].isfinite().any()
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -40, 1.0, 2.0 ** 30])
+def test_values_of_any_size_keep_24_bits(scale):
+    # V enters linearly: scaled by a power of two, every output is scaled by it, to the bit
+    heads, n = 3, 330
+    q, k, v = (x.cuda() for x in inputs.make_qkv(1, heads, n, 64, seed=9, dtype="f32"))
+    G = inputs.make_sketch_matrices(heads, 64, 16, 4, per_head=True, seed=3, dtype="f32").cuda()
+    desc = psf.make_desc(1, heads, n, 64, 4, 16, 110, "f32", per_head=True)
+    O = psf.psf_causal_attn_fwd(desc, q, k, v, G)
+    assert torch.equal(psf.psf_causal_attn_fwd(desc, q, k, v * scale, G), O * scale)
