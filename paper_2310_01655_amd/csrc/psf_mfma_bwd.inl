@@ -155,57 +155,61 @@ __global__ __launch_bounds__(kWg) void k_bwd_qoct(const bf16_t *__restrict__ MQ,
 //      the free sketch index e as the row of an MFMA A operand.  Workgroup = (octet of b, snapshot).
 // DC value columns per workgroup (blockIdx.z picks the range): D = 128 goes in two halves so that
 // two workgroups fit a CU.
+// A thread takes 8 x 8 blocks (eight value columns of one row and octet, 128 bytes), turns them round in
+// registers and stores whole octets; the LDS tile only puts the rows e in order for the stores to memory.
+// Bound by memory since (744 snapshots of r = d = 64: 205 -> 132 us, 4.4 TB/s; d = 128: 225 -> 170): single
+// values into LDS, and the divisions that found their places, cost more than the traffic.
 template <int R, int D, int DC = D>
 __global__ __launch_bounds__(kWg) void k_bwd_relayout(const bf16_t *__restrict__ Zs, bf16_t *__restrict__ ZT)
 {
-    static_assert(DC >= 64 && D % DC == 0, "the swizzle needs eight column octets");
+    static_assert(DC == 64 && D % DC == 0, "eight column octets: the swizzle and the blocks' order");
     // [b % 8][e][c], the 16-byte column c / 8 of row e stored at (c / 8) ^ (e % 8): the final
     // reads walk e with a fixed column and would otherwise all hit the same banks
     __shared__ __attribute__((aligned(16))) bf16_t F[8][R][DC];
-    auto at = [&](int b8, int e, int c) -> bf16_t & { return F[b8][e][(((c >> 3) ^ (e & 7)) << 3) + (c & 7)]; };
     const int tid = threadIdx.x, ob = blockIdx.x, c0 = blockIdx.z * DC;
     const bf16_t *src = Zs + (size_t)blockIdx.y * R * R * D;
     bf16_t *dst = ZT + (size_t)blockIdx.y * R * R * D;
-    auto twice = [](uint32_t bits) { return f32_to_bf16(2.0f * bf16_to_f32((bf16_t)bits)); };
-    // 16-byte pieces of the source, all loads of a thread issued before their use:
-    //   pieces [0, 8 ob DC): rows e < 8 ob, octet ob (b > e there: 2 Z[e][b][c] = Zs[e][b][c])
+    constexpr int PIECES = 8 * DC * (R / 8) / kWg, BLOCKS = PIECES / 8;
+    static_assert(PIECES % 8 == 0, "whole blocks");
+    // Blocks in the order (row, column octet), all loads of a thread issued before their use:
+    //   rows e < 8 ob, octet ob (b > e there: 2 Z[e][b][c] = Zs[e][b][c])
     //   the rest: rows a of this octet, column octets ob2 >= ob
-    constexpr int PIECES = 8 * DC * (R / 8) / kWg;
-    const int n_a = 8 * ob * DC, per_a = (R / 8 - ob) * DC;
-    uint4 pk[PIECES];
+    const int c8 = tid % 8;
+    uint4 pk[BLOCKS][8];
 #pragma unroll
-    for (int i = 0; i < PIECES; ++i) {
-        const int idx = tid + i * kWg;
-        size_t off;
-        if (idx < n_a) {
-            off = ((size_t)(idx / DC) * (R / 8) + ob) * D + c0 + idx % DC;
-        } else {
-            const int k2 = idx - n_a, a8 = k2 / per_a, rem = k2 % per_a;
-            off = ((size_t)(8 * ob + a8) * (R / 8) + ob + rem / DC) * D + c0 + rem % DC;
-        }
-        pk[i] = *(const uint4 *)&src[off * 8];
+    for (int i = 0; i < BLOCKS; ++i) {
+        const int t = (tid + i * kWg) / 8, k = t - 8 * ob;
+        const int row = k < 0 ? t : 8 * ob + k % 8, oct = k < 0 ? ob : ob + k / 8;
+        const bf16_t *from = src + (((size_t)row * (R / 8) + oct) * D + c0 + 8 * c8) * 8;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) pk[i][c] = *(const uint4 *)(from + 8 * c);
     }
+    auto put = [&](int b8, int e, const uint4 &cols) { *(uint4 *)&F[b8][e][8 * (c8 ^ (e & 7))] = cols; };
+    auto twice = [](uint32_t two) {
+        return (uint32_t)f32_to_bf16(2.0f * bf16_to_f32((bf16_t)(two & 0xffffu))) |
+               (uint32_t)f32_to_bf16(2.0f * bf16_to_f32((bf16_t)(two >> 16))) << 16;
+    };
 #pragma unroll
-    for (int i = 0; i < PIECES; ++i) {
-        const int idx = tid + i * kWg;
-        const uint32_t w[4] = {pk[i].x, pk[i].y, pk[i].z, pk[i].w};
-        if (idx < n_a) {
-            const int e = idx / DC, c = idx % DC;
+    for (int i = 0; i < BLOCKS; ++i) {
+        const int t = (tid + i * kWg) / 8, k = t - 8 * ob;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) at(j, e, c) = (bf16_t)((w[j / 2] >> (16 * (j % 2))) & 0xffffu);
-        } else {
-            const int k2 = idx - n_a, a8 = k2 / per_a, rem = k2 % per_a, ob2 = ob + rem / DC, c = rem % DC;
-            const int a = 8 * ob + a8;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int bp = 8 * ob2 + j;
-                const uint32_t bits = (w[j / 2] >> (16 * (j % 2))) & 0xffffu;
-                if (bp > a) {
-                    at(a8, bp, c) = (bf16_t)bits;          // (b = a, e = b')
-                    if (ob2 == ob) at(j, a, c) = (bf16_t)bits;   // mirror inside the diagonal octet: (b = b', e = a)
-                } else if (bp == a) {
-                    at(a8, a, c) = twice(bits);
-                }
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t half = j % 2 ? 0x07060302u : 0x05040100u;
+            auto pair = [&](int c) {                        // column j of the block's rows c, c + 1
+                const uint32_t lo[4] = {pk[i][c].x, pk[i][c].y, pk[i][c].z, pk[i][c].w};
+                const uint32_t hi[4] = {pk[i][c + 1].x, pk[i][c + 1].y, pk[i][c + 1].z, pk[i][c + 1].w};
+                return __builtin_amdgcn_perm(hi[j / 2], lo[j / 2], half);
+            };
+            const uint4 cols = make_uint4(pair(0), pair(2), pair(4), pair(6));
+            if (k < 0) {
+                put(j, t, cols);                           // (b = 8 ob + j, e)
+            } else if (k >= 8) {
+                put(k % 8, 8 * (ob + k / 8) + j, cols);    // (b = a, e = b')
+            } else if (j > k) {                            // the diagonal octet: (b = a, e = b') and its mirror
+                put(k, 8 * ob + j, cols);
+                put(j, 8 * ob + k, cols);
+            } else if (j == k) {
+                put(k, 8 * ob + k, make_uint4(twice(cols.x), twice(cols.y), twice(cols.z), twice(cols.w)));
             }
         }
     }
