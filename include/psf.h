@@ -331,8 +331,12 @@ psf_status psf_decode_step(const psf_desc *desc, const void *q, const void *k, c
  *   are -- the complete blocks of the prompt go through the forward path's sketch and state
  *   kernels (their buffers are the workspace; K, V and G must then be 16-byte aligned, else
  *   PSF_ERR_ALIGNMENT) and the state starts from their bf16 result, as the forward pass's own
- *   prefix states do; learned sketches need the fp32 sketches of all prompt keys; otherwise
- *   the workspace is empty and the prompt is folded block by block.
+ *   prefix states do; learned sketches need the fp32 sketches of all prompt keys; other prompts
+ *   in bf16 storage with r (d where p = 2) in {32, 64} and dv a multiple of 32 are folded many blocks at a time
+ *   from fp32 sketches in the workspace (at most 1 GiB of them) -- block by block, with the same
+ *   result up to the order of its sums, where workspace_bytes is less than the query asks for or the
+ *   workspace is null or not 256-byte aligned; for everything else the workspace is empty and the prompt
+ *   is folded block by block.
  * Nothing is allocated and nothing synchronises; everything is enqueued on hip_stream.
  */
 size_t psf_decode_prefill_workspace_bytes(const psf_desc *desc, int32_t n_prompt);

@@ -524,13 +524,14 @@ psf_status psf_decode_prefill(const psf_desc *desc, const void *K, const void *V
     if (n_prompt < 0 || n_prompt > pb.n) return PSF_ERR_SHAPE;
     if (n_prompt > 0 && (!K || !V)) return PSF_ERR_NULL;
     if (pb.g_len > 0 && !G) return PSF_ERR_NULL;
-    const size_t need = decode_prefill_workspace_bytes(pb, n_prompt);
+    // (less than the query asks for is enough for a prompt that can also be folded block by block)
+    const size_t need = decode_prefill_least_bytes(pb, n_prompt);
     if (need > 0 && !workspace) return PSF_ERR_NULL;
     if (workspace_bytes < need || (need > 0 && ((uintptr_t)workspace & 255u) != 0)) return PSF_ERR_WORKSPACE;
     // (the hand-over has its own rule for when the forward pass's MFMA kernels take the complete
     // blocks of the prompt: it does not depend on b % 256 or on the in-block rule)
     if (decode_prefill_uses_mfma(pb, n_prompt) && !aligned16({K, V, G})) return PSF_ERR_ALIGNMENT;
-    return decode_prefill(pb, K, V, G, n_prompt, state, workspace, (hipStream_t)hip_stream);
+    return decode_prefill(pb, K, V, G, n_prompt, state, workspace, workspace_bytes, (hipStream_t)hip_stream);
 }
 
 const char *psf_stage_name(int path, int32_t stage)

@@ -25,6 +25,7 @@
 // split over several workgroups).
 // A step is bound by reading the state once (Fs * (dv * s + 4) bytes per unit, s = 2 with the
 // bf16 copy, 4 without) and the cached keys and values of the current block.
+#include <algorithm>
 #include <type_traits>
 
 #include "psf_internal.h"
@@ -734,6 +735,15 @@ __global__ __launch_bounds__(kThreads) void dec_fold_kernel(float *__restrict__ 
 // are dealt evenly to the four waves, a wave's items sharing one range (and with it the
 // fragments of m_j[b'] and of v).  64 tokens at a time are staged transposed ([column][token])
 // so that a lane's eight tokens of one column are neighbours.
+//
+// Bound by LDS reads, the vector work of the fragments and, with few tokens, the state's own traffic (us, 768
+// units of r = d = 64, 1024 tokens: 819 -> 669; 192 of d = 128, 512 tokens: 835 -> 213; 12 of d = 64: 56 -> 47; 768 of
+// r = 32, 256 tokens: 87 -> 92): single values stored column by column met 4-way bank conflicts, and branches on
+// a wave's number of rows and on the end of the tokens kept loads and products in order.
+// `count` tokens of unit u come from msrc + u m_unit (fp32 sketches) and vsrc + u v_unit (values): the
+// unit's block cache, or a prompt's sketches and its values in place.  slices > 1: each slice of the
+// tokens leaves its sums in part [unit][slice][pairs (dv + 1)] and dec_fold_sum_kernel adds them to the
+// state; slices = 1: they are added here.
 typedef __bf16 dec_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float dec_f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kFoldMfmaTok = 64, kFoldMfmaMaxM = 64, kFoldMfmaMaxDv = 128;
@@ -746,7 +756,10 @@ struct FoldShape {
 };
 
 template <int MC, int DV>
-__global__ __launch_bounds__(kThreads, 2) void dec_fold_mfma_kernel(float *__restrict__ state, DecodeLayout L, int b)
+__global__ __launch_bounds__(kThreads, 2) void dec_fold_mfma_kernel(float *state, DecodeLayout L, int count,
+                                                                    const float *msrc, size_t m_unit,
+                                                                    const bf16_t *vsrc, size_t v_unit,
+                                                                    float *part, int slices)
 {
     constexpr int mcols = MC, dv = DV;
     constexpr int NB = FoldShape<MC, DV>::NB, TC = FoldShape<MC, DV>::TC, IPW = FoldShape<MC, DV>::IPW;
@@ -754,19 +767,22 @@ __global__ __launch_bounds__(kThreads, 2) void dec_fold_mfma_kernel(float *__res
     // rows of 64 tokens: pitches of 68 floats / 72 bf16 keep every 16-byte read aligned and spread
     // the 16 lanes of a read phase over all banks
     constexpr int TOK = kFoldMfmaTok, PITCH = TOK + 4, PITCHV = TOK + 8;
-    __shared__ __attribute__((aligned(16))) float mts[MC][PITCH];
-    __shared__ __attribute__((aligned(16))) bf16_t vts[DV][PITCHV];
-    // The MC / NA workgroups of a unit all stream the unit's block cache.  Consecutive workgroup
+    __shared__ __attribute__((aligned(16))) float mts2[2][MC][PITCH];
+    __shared__ __attribute__((aligned(16))) bf16_t vts2[2][DV][PITCHV];
+    // The MC / NA workgroups of a unit's slice all stream the same tokens.  Consecutive workgroup
     // ids go to different XCDs, so give each XCD a contiguous range of (unit, row group) pairs:
     // the groups of a unit then share one L2 and run at about the same time.
     constexpr int GROUPS = MC / NA;
     int wg = blockIdx.x;
     if ((gridDim.x & 7) == 0) wg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    const int u = wg / GROUPS, a0 = (wg % GROUPS) * NA;
+    const int u = wg / GROUPS / slices, slice = wg / GROUPS % slices, a0 = (wg % GROUPS) * NA;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int x = lane & 31, h = lane >> 5;
     float *su = state + (size_t)u * L.per_unit;
+    const int chunks = (count + TOK - 1) / TOK;
+    const int first = (int)((long long)chunks * slice / slices) * TOK;
+    const int last = min(count, (int)((long long)chunks * (slice + 1) / slices) * TOK);
     // this wave's items: rows a0 + row0 .. + rpw - 1 of range bt
     const int bt_min = a0 / 32, nb_act = NB - bt_min;
     const int rpw = NA * nb_act / 4;                         // 1 .. IPW
@@ -781,77 +797,143 @@ __global__ __launch_bounds__(kThreads, 2) void dec_fold_mfma_kernel(float *__res
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[k][ct][v] = 0.f;
     }
-    // A chunk of 64 tokens goes global -> registers (16-byte / 8-byte pieces of a cached row) ->
-    // LDS (transposed); the loads of the next chunk are in flight while this one is multiplied.
-    constexpr int MP = TOK * MC / 4 / kThreads, VP = TOK * DV / 4 / kThreads;
-    float4 m_pre[MP];
-    uint2 v_pre[VP];
-    const float *cm = su + L.cm;
-    const bf16_t *cvv = (const bf16_t *)(su + L.cv);
+    // A chunk of 64 tokens goes global -> registers -> LDS, transposed on the way: a thread takes four
+    // columns of four tokens (neighbouring threads neighbouring columns: whole rows) and stores four tokens
+    // of a column at once.  Token quads (m) and octets (v) of column c lie at their number ^ (c / 16) % 4, which
+    // keeps the stores' lanes, 16 columns apart in their banks' pattern, off each other.  The loads of the
+    // next chunk are in flight while this one is multiplied; two buffers, one barrier a chunk.
+    constexpr int MBLK = TOK / 4 * (MC / 4), VBLK = TOK / 4 * (DV / 4);
+    constexpr int MP = (MBLK + kThreads - 1) / kThreads, VP = (VBLK + kThreads - 1) / kThreads;
+    float4 m_pre[MP][4];
+    uint2 v_pre[VP][4];
+    const float *cm = msrc + (size_t)u * m_unit;
+    const bf16_t *cvv = vsrc + (size_t)u * v_unit;
+    // Past the end the last token is loaded again and put() writes zeros over it: loads behind a branch, or
+    // registers changed behind one, made the compiler wait for them before the products.
     auto fetch = [&](int j0) {
 #pragma unroll
         for (int i = 0; i < MP; ++i) {
-            const int idx = tid + i * kThreads, jj = idx / (MC / 4), c4 = idx % (MC / 4);
-            m_pre[i] = j0 + jj < b ? *(const float4 *)(cm + (size_t)(j0 + jj) * MC + 4 * c4) : make_float4(0.f, 0.f, 0.f, 0.f);
+            const int idx = min(tid + i * kThreads, MBLK - 1), tb = idx / (MC / 4), c4 = idx % (MC / 4);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                m_pre[i][t] = *(const float4 *)(cm + (size_t)(unsigned)min(j0 + 4 * tb + t, last - 1) * MC + 4 * c4);
         }
 #pragma unroll
         for (int i = 0; i < VP; ++i) {
-            const int idx = tid + i * kThreads, jj = idx / (DV / 4), c4 = idx % (DV / 4);
-            v_pre[i] = j0 + jj < b ? *(const uint2 *)(cvv + (size_t)(j0 + jj) * DV + 4 * c4) : make_uint2(0u, 0u);
+            const int idx = min(tid + i * kThreads, VBLK - 1), tb = idx / (DV / 4), c4 = idx % (DV / 4);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                v_pre[i][t] = *(const uint2 *)(cvv + (size_t)(unsigned)min(j0 + 4 * tb + t, last - 1) * DV + 4 * c4);
         }
     };
-    auto put = [&]() {
+    auto put = [&](int buf, int j0) {
 #pragma unroll
         for (int i = 0; i < MP; ++i) {
-            const int idx = tid + i * kThreads, jj = idx / (MC / 4), c4 = idx % (MC / 4);
-            mts[4 * c4 + 0][jj] = m_pre[i].x; mts[4 * c4 + 1][jj] = m_pre[i].y;
-            mts[4 * c4 + 2][jj] = m_pre[i].z; mts[4 * c4 + 3][jj] = m_pre[i].w;
+            const int idx = tid + i * kThreads, tb = idx / (MC / 4), c4 = idx % (MC / 4);
+            if (MBLK % kThreads == 0 || idx < MBLK) {
+                const float4 *m4 = m_pre[i];
+                float(*to)[PITCH] = &mts2[buf][4 * c4];
+                const int at = 4 * (tb ^ (c4 / 4 % 4));
+                *(float4 *)&to[0][at] = make_float4(m4[0].x, m4[1].x, m4[2].x, m4[3].x);
+                *(float4 *)&to[1][at] = make_float4(m4[0].y, m4[1].y, m4[2].y, m4[3].y);
+                *(float4 *)&to[2][at] = make_float4(m4[0].z, m4[1].z, m4[2].z, m4[3].z);
+                *(float4 *)&to[3][at] = make_float4(m4[0].w, m4[1].w, m4[2].w, m4[3].w);
+                if (j0 + TOK > last)                        // the same for the workgroup
+                    for (int t = max(0, last - j0 - 4 * tb); t < 4; ++t)
+                        to[0][at + t] = to[1][at + t] = to[2][at + t] = to[3][at + t] = 0.f;
+            }
         }
 #pragma unroll
         for (int i = 0; i < VP; ++i) {
-            const int idx = tid + i * kThreads, jj = idx / (DV / 4), c4 = idx % (DV / 4);
-            vts[4 * c4 + 0][jj] = (bf16_t)(v_pre[i].x & 0xffffu); vts[4 * c4 + 1][jj] = (bf16_t)(v_pre[i].x >> 16);
-            vts[4 * c4 + 2][jj] = (bf16_t)(v_pre[i].y & 0xffffu); vts[4 * c4 + 3][jj] = (bf16_t)(v_pre[i].y >> 16);
+            const int idx = tid + i * kThreads, tb = idx / (DV / 4), c4 = idx % (DV / 4);
+            if (VBLK % kThreads == 0 || idx < VBLK) {
+                const uint2 *v4 = v_pre[i];
+                bf16_t(*to)[PITCHV] = &vts2[buf][4 * c4];
+                const int at = 8 * (tb / 2 ^ (c4 / 4 % 4)) + 4 * (tb % 2);
+                auto low = [](uint32_t p, uint32_t q) { return (p & 0xffffu) | (q << 16); };
+                auto high = [](uint32_t p, uint32_t q) { return (p >> 16) | (q & 0xffff0000u); };
+                *(uint2 *)&to[0][at] = make_uint2(low(v4[0].x, v4[1].x), low(v4[2].x, v4[3].x));
+                *(uint2 *)&to[1][at] = make_uint2(high(v4[0].x, v4[1].x), high(v4[2].x, v4[3].x));
+                *(uint2 *)&to[2][at] = make_uint2(low(v4[0].y, v4[1].y), low(v4[2].y, v4[3].y));
+                *(uint2 *)&to[3][at] = make_uint2(high(v4[0].y, v4[1].y), high(v4[2].y, v4[3].y));
+                if (j0 + TOK > last)
+                    for (int t = max(0, last - j0 - 4 * tb); t < 4; ++t)
+                        to[0][at + t] = to[1][at + t] = to[2][at + t] = to[3][at + t] = 0;
+            }
         }
     };
-    fetch(0);
-    for (int j0 = 0; j0 < b; j0 += TOK) {
-        __syncthreads();
-        put();
-        __syncthreads();
-        if (j0 + TOK < b) fetch(j0 + TOK);
+    const int quad_b = 4 * ((2 * bt + x / 16) % 4);
+    // items: the wave's rows, a constant so that no branch lies between an item's products and the next
+    // item's operands
+    auto multiply = [&](auto items, int buf) {
+        constexpr int ITEMS = decltype(items)::value;
+        const auto &mts = mts2[buf];
+        const auto &vts = vts2[buf];
+        float dchunk[ITEMS];                                // the ones column, a chunk at a time: shorter sums
 #pragma unroll
+        for (int k = 0; k < ITEMS; ++k) dchunk[k] = 0.f;
+#pragma unroll 2                                            // (all four: spills)
         for (int sstep = 0; sstep < TOK / 16; ++sstep) {
             const int tok = 16 * sstep + 8 * h;
-            const float4 mb0 = *(const float4 *)&mts[32 * bt + x][tok], mb1 = *(const float4 *)&mts[32 * bt + x][tok + 4];
+            const float *mcol = mts[32 * bt + x];
+            const float4 mb0 = *(const float4 *)&mcol[tok ^ quad_b], mb1 = *(const float4 *)&mcol[(tok + 4) ^ quad_b];
             const float mb[8] = {mb0.x, mb0.y, mb0.z, mb0.w, mb1.x, mb1.y, mb1.z, mb1.w};
             dec_bf16x8 fb[TC];
 #pragma unroll
-            for (int ct = 0; ct < TC; ++ct) fb[ct] = *(const dec_bf16x8 *)&vts[32 * ct + x][tok];
+            for (int ct = 0; ct < TC; ++ct) fb[ct] = *(const dec_bf16x8 *)&vts[32 * ct + x][tok ^ (8 * ((2 * ct + x / 16) % 4))];
 #pragma unroll
-            for (int k = 0; k < IPW; ++k) {
-                if (k >= rpw) break;                        // wave-uniform
+            for (int k = 0; k < ITEMS; ++k) {
                 const int a = a0 + row0 + k;
-                const float4 ma0 = *(const float4 *)&mts[a][tok], ma1 = *(const float4 *)&mts[a][tok + 4];
+                const int quad_a = 4 * (a / 16 % 4);
+                const float4 ma0 = *(const float4 *)&mts[a][tok ^ quad_a], ma1 = *(const float4 *)&mts[a][(tok + 4) ^ quad_a];
                 const float ma[8] = {ma0.x, ma0.y, ma0.z, ma0.w, ma1.x, ma1.y, ma1.z, ma1.w};
                 dec_bf16x8 fa;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const float pr = ma[e] * mb[e];
                     fa[e] = (__bf16)pr;
-                    drow[k] += pr;
+                    dchunk[k] += pr;
                 }
 #pragma unroll
                 for (int ct = 0; ct < TC; ++ct)
                     acc[k][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb[ct], acc[k][ct], 0, 0, 0);
             }
         }
-    }
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) drow[k] += dchunk[k];
+    };
+    auto walk = [&](auto items) {
+        fetch(first);
+        for (int j0 = first, buf = 0; j0 < last; j0 += TOK, buf ^= 1) {
+            put(buf, j0);
+            __syncthreads();
+            fetch(j0 + TOK);
+            multiply(items, buf);
+        }
+    };
+    if (rpw == IPW)
+        walk(std::integral_constant<int, IPW>{});
+    else if constexpr (NB > 1)
+        walk(std::integral_constant<int, IPW / 2>{});
 #pragma unroll
     for (int k = 0; k < IPW; ++k) {
         if (k >= rpw) break;
         const int a = a0 + row0 + k;
         const size_t rowbase = (size_t)tri_row(a, mcols);
+        if (slices > 1) {
+            float *const pu = part + ((size_t)u * slices + slice) * tri_count(mcols) * (dv + 1);
+#pragma unroll
+            for (int ct = 0; ct < TC; ++ct)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int bp = 32 * bt + 8 * (v / 4) + 4 * h + (v % 4);
+                    if (bp >= a) pu[(rowbase + bp - a) * dv + 32 * ct + x] = (bp > a ? 2.f : 1.f) * acc[k][ct][v];
+                }
+            const float tot = drow[k] + __shfl_xor(drow[k], 32);
+            const int bp = 32 * bt + x;
+            if (h == 0 && bp >= a) pu[(size_t)tri_count(mcols) * dv + rowbase + bp - a] = (bp > a ? 2.f : 1.f) * tot;
+            continue;
+        }
         // accumulator: lane x = column c, register v = row b' = 8 (v / 4) + 4 h + v % 4.  All rows
         // are read before the first is written: the reads and writes go to one array, so that in
         // one loop every read would wait for the write before it (768 units of r = d = 64:
@@ -882,6 +964,25 @@ __global__ __launch_bounds__(kThreads, 2) void dec_fold_mfma_kernel(float *__res
         const int bp = 32 * bt + x;
         if (h == 0 && bp >= a) su[L.zd + rowbase + bp - a] += (bp > a ? 2.f : 1.f) * tot;
     }
+}
+
+// The slices' sums of dec_fold_mfma_kernel are added to the state, in their order: ZV (and its bf16 copy),
+// then ZD, one value a thread.
+__global__ __launch_bounds__(kThreads) void dec_fold_sum_kernel(float *__restrict__ state, DecodeLayout L,
+                                                                const float *__restrict__ part, int slices,
+                                                                int pairs, int dv)
+{
+    const int i = blockIdx.x * kThreads + threadIdx.x, total = pairs * (dv + 1);
+    if (i >= total) return;
+    const int u = blockIdx.y;
+    float *su = state + (size_t)u * L.per_unit;
+    const float *from = part + (size_t)u * slices * total + i;
+    const bool value = i < pairs * dv;
+    const size_t at = value ? L.zv + i : L.zd + (i - pairs * dv);
+    float sum = su[at];
+    for (int q = 0; q < slices; ++q) sum += from[(size_t)q * total];
+    su[at] = sum;
+    if (value && L.shadow) ((bf16_t *)(su + L.zh))[i] = f32_to_bf16(sum);
 }
 
 // Prompt tokens pos0 + j (j < count) of every unit go into cache slots j: keys and values as
@@ -1002,21 +1103,52 @@ __global__ __launch_bounds__(kThreads) void dec_gather_rows_kernel(const bf16_t 
     *(uint4 *)(dst + i * 8) = *(const uint4 *)(src + (u * n_prompt + first) * w + r8 * 8);
 }
 
+// Shapes of dec_fold_mfma_kernel.
+bool fold_on_mfma(const Problem &pb)
+{
+    return pb.bf16 && pb.mcols % 32 == 0 && pb.mcols <= kFoldMfmaMaxM && pb.dv % 32 == 0 && pb.dv <= kFoldMfmaMaxDv;
+}
+
+// Sketch rows a per workgroup of that kernel.
+int fold_rows(const Problem &pb)
+{
+    const int tc = pb.dv / 32, nb = pb.mcols / 32, ipw = 8 / tc < 4 ? 8 / tc : 4;
+    return 4 * ipw / nb;
+}
+
+psf_status launch_fold_mfma(const Problem &pb, const DecodeLayout &L, float *state, int count, const float *m,
+                            size_t m_unit, const bf16_t *v, size_t v_unit, float *part, int slices, hipStream_t s)
+{
+    const dim3 grid((unsigned)(pb.mcols / fold_rows(pb) * pb.units * slices));
+#define PSF_FOLD(MC_, DV_)                                                                                       \
+    if (pb.mcols == MC_ && pb.dv == DV_) {                                                                        \
+        static_assert(FoldShape<MC_, DV_>::NA * FoldShape<MC_, DV_>::NB == 4 * FoldShape<MC_, DV_>::IPW, "");     \
+        hipLaunchKernelGGL((dec_fold_mfma_kernel<MC_, DV_>), grid, dim3(kThreads), 0, s, state, L, count, m,      \
+                           m_unit, v, v_unit, part, slices);                                                      \
+    }
+    PSF_FOLD(32, 32) PSF_FOLD(32, 64) PSF_FOLD(32, 96) PSF_FOLD(32, 128)
+    PSF_FOLD(64, 32) PSF_FOLD(64, 64) PSF_FOLD(64, 96) PSF_FOLD(64, 128)
+#undef PSF_FOLD
+    PSF_LAUNCH_CHECK();
+    if (slices > 1) {
+        const int pairs = (int)tri_count(pb.mcols), total = pairs * (pb.dv + 1);
+        hipLaunchKernelGGL(dec_fold_sum_kernel, dim3((unsigned)((total + kThreads - 1) / kThreads), (unsigned)pb.units),
+                           dim3(kThreads), 0, s, state, L, part, slices, pairs, pb.dv);
+        PSF_LAUNCH_CHECK();
+    }
+    return PSF_OK;
+}
+
 // Folds the b tokens in the block cache into the state (the block is complete).
 template <typename T>
 psf_status launch_fold(const Problem &pb, const DecodeLayout &L, float *state, hipStream_t s)
 {
+    if (fold_on_mfma(pb))
+        return launch_fold_mfma(pb, L, state, pb.b, state + L.cm, L.per_unit, (const bf16_t *)(state + L.cv),
+                                2 * L.per_unit, nullptr, 1, s);
     const long long Fs = tri_count(pb.mcols);
     const dim3 fgrid((unsigned)((Fs + kFoldFeat - 1) / kFoldFeat), (unsigned)pb.units);
-    if (pb.bf16 && pb.mcols % 32 == 0 && pb.mcols <= kFoldMfmaMaxM && pb.dv % 32 == 0 && pb.dv <= kFoldMfmaMaxDv) {
-#define PSF_FOLD(MC_, DV_)                                                                                       \
-    if (pb.mcols == MC_ && pb.dv == DV_)                                                                          \
-    hipLaunchKernelGGL((dec_fold_mfma_kernel<MC_, DV_>), dim3((unsigned)(MC_ / FoldShape<MC_, DV_>::NA * pb.units)), \
-                       dim3(kThreads), 0, s, state, L, pb.b)
-        PSF_FOLD(32, 32); PSF_FOLD(32, 64); PSF_FOLD(32, 96); PSF_FOLD(32, 128);
-        PSF_FOLD(64, 32); PSF_FOLD(64, 64); PSF_FOLD(64, 96); PSF_FOLD(64, 128);
-#undef PSF_FOLD
-    } else if (pb.dv <= 32)
+    if (pb.dv <= 32)
         hipLaunchKernelGGL((dec_fold_kernel<T, 8>), fgrid, dim3(kThreads), 0, s, state, L, pb.dv, pb.b, pb.mcols, Fs);
     else if (pb.dv <= 64)
         hipLaunchKernelGGL((dec_fold_kernel<T, 16>), fgrid, dim3(kThreads), 0, s, state, L, pb.dv, pb.b, pb.mcols, Fs);
@@ -1111,20 +1243,34 @@ static int prefill_fast_tokens(const Problem &pb, int n_prompt)
     return n_full > 0 && pb.mcols % 8 == 0 && mfma_total_state_supported(pb, n_full) ? n_full : 0;
 }
 
+// Complete blocks that the forward kernels do not take (blocks whose tokens are no multiple of 256, p = 2)
+// go into the state together where the fold runs on MFMA: a state does not depend on where the blocks
+// ended, and a fold reads and writes the whole state, 0.8 MB a unit, for what may be 48 tokens.  Sketches
+// of up to kFoldRoom bytes at a time, their values in place.  A chunk holds at least one block, or the
+// prompt goes block by block as before; so does one whose caller has no workspace, or values at odd addresses.
+// Few units: the tokens are cut into slices (of 256 and more, until every CU has two workgroups) with sums
+// of their own.  (Prompt and twelve steps, us, block by block and together: 288 units of r = 64, 5000
+// tokens in blocks of 200: 4801, 1457; 12 of r = 32, 3000 in blocks of 48: 2105, 214; 36 of d = 128 and degree 8, 2000
+// in blocks of 300: 1985, 611; 48 with p = 2, 3000 in blocks of 512: 516, 339.)
+constexpr size_t kFoldRoom = (size_t)1 << 30;
+constexpr int kFoldSlices = 16, kFoldWorkgroups = 512, kFoldSliceTokens = 256;
+
 // Workspace of a hand-over, in this order: the fp32 sketches of the prompt keys that go through
 // the cache (learned sketches only: all of them, or those after the last block boundary when
 // the forward kernels take the complete blocks), a contiguous copy of those keys (same case),
 // room for contiguous copies of the complete blocks of K and V (when a tail follows them; only
 // learned sketches still make these copies, the size the query returns is the same for both), the
-// forward kernels' own buffers.
+// forward kernels' own buffers; or, where those take nothing, the sketches of a chunk and the slices' sums.
 struct PrefillPlan {
     int n_full, m_rows;                   // tokens through the forward kernels; sketched rows per unit
-    size_t m_bytes, ktail_bytes, copy_bytes, total;
+    int fold_tokens, fold_slices;         // tokens of a chunk that is folded at once (0: block by block)
+    size_t m_bytes, ktail_bytes, copy_bytes, fold_m_bytes;
+    size_t least, total;                  // what the call cannot do without; what it asks for
 };
 
 static PrefillPlan prefill_plan(const Problem &pb, int n_prompt)
 {
-    PrefillPlan pl;
+    PrefillPlan pl = {};
     const bool learned = pb.learned && pb.p > 2;
     pl.n_full = prefill_fast_tokens(pb, n_prompt);
     const int tail = n_prompt - pl.n_full;
@@ -1132,18 +1278,34 @@ static PrefillPlan prefill_plan(const Problem &pb, int n_prompt)
     pl.m_bytes = align_up((size_t)pb.units * pl.m_rows * pb.mcols * sizeof(float), 256);
     pl.ktail_bytes = learned && pl.n_full > 0 ? align_up((size_t)pb.units * tail * pb.d * 2, 256) : 0;
     pl.copy_bytes = pl.n_full > 0 && tail > 0 ? align_up((size_t)pb.units * pl.n_full * pb.d * 2, 256) : 0;
-    pl.total = pl.m_bytes + pl.ktail_bytes + 2 * pl.copy_bytes +
-               (pl.n_full > 0 ? mfma_total_state_workspace_bytes(pb, pl.n_full) : 0);
+    pl.least = pl.total = pl.m_bytes + pl.ktail_bytes + 2 * pl.copy_bytes +
+                          (pl.n_full > 0 ? mfma_total_state_workspace_bytes(pb, pl.n_full) : 0);
+    const int blocks = n_prompt / pb.b * pb.b;
+    if (pl.n_full > 0 || blocks == 0 || !fold_on_mfma(pb) || !(learned || f32_supported(pb))) return pl;
+    const size_t row = (size_t)pb.units * pb.mcols * sizeof(float);
+    size_t tokens = (size_t)blocks;
+    if (!learned && tokens * row > kFoldRoom) tokens = kFoldRoom / row / kFoldMfmaTok * kFoldMfmaTok;
+    if (tokens < (size_t)pb.b) return pl;
+    pl.fold_tokens = (int)tokens;
+    const int groups = pb.mcols / fold_rows(pb);
+    const long long fill = kFoldWorkgroups / ((long long)pb.units * groups);
+    pl.fold_slices = (int)std::max<long long>(1, std::min<long long>({fill, kFoldSlices, pl.fold_tokens / kFoldSliceTokens}));
+    pl.fold_m_bytes = learned ? 0 : align_up(tokens * row, 256);
+    pl.total += pl.fold_m_bytes;
+    if (pl.fold_slices > 1)
+        pl.total += align_up((size_t)pb.units * pl.fold_slices * tri_count(pb.mcols) * (pb.dv + 1) * sizeof(float), 256);
     return pl;
 }
 
 size_t decode_prefill_workspace_bytes(const Problem &pb, int n_prompt) { return prefill_plan(pb, n_prompt).total; }
 
+size_t decode_prefill_least_bytes(const Problem &pb, int n_prompt) { return prefill_plan(pb, n_prompt).least; }
+
 bool decode_prefill_uses_mfma(const Problem &pb, int n_prompt) { return prefill_fast_tokens(pb, n_prompt) > 0; }
 
 template <typename T>
 static psf_status prefill_launch(const Problem &pb, const void *K, const void *V, const void *G, int n_prompt,
-                                 float *state, void *ws, hipStream_t s)
+                                 float *state, void *ws, size_t ws_bytes, hipStream_t s)
 {
     const DecodeLayout L = decode_layout(pb);
     psf_status st = decode_reset(pb, state, s);
@@ -1202,7 +1364,31 @@ static psf_status prefill_launch(const Problem &pb, const void *K, const void *V
         if (st != PSF_OK) return st;
     }
     const DecSketchArgs ska{G, pb.g_len, pb.heads, pb.per_head ? 1 : 0, pb.r};
-    for (int pos0 = first; pos0 < n_prompt; pos0 += pb.b) {
+    int cached = first;                                    // tokens before this one are in the state
+    if constexpr (std::is_same_v<T, bf16_t>) {
+        if (pl.fold_tokens > 0 && ws_bytes >= pl.total && (pl.total == 0 || (ws && ((uintptr_t)ws & 255u) == 0)) &&
+            ((uintptr_t)V & 7u) == 0) {
+            const int blocks = n_prompt / pb.b * pb.b;
+            float *const m = (float *)wsp, *const part = (float *)(wsp + pl.fold_m_bytes);
+            for (int c0 = 0; c0 < blocks; c0 += pl.fold_tokens) {
+                const int count = std::min(pl.fold_tokens, blocks - c0);
+                if (!have_m) {
+                    Problem chunk = pb;
+                    chunk.n = count;
+                    st = f32_sketch_rows(chunk, (const T *)K + (size_t)c0 * pb.d, (size_t)n_prompt * pb.d, G, m,
+                                         (size_t)pl.fold_tokens * pb.mcols, s);
+                    if (st != PSF_OK) return st;
+                }
+                const int slices = std::min(pl.fold_slices, (count + kFoldMfmaTok - 1) / kFoldMfmaTok);
+                st = launch_fold_mfma(pb, L, state, count, have_m ? m_tail + (size_t)c0 * pb.mcols : m,
+                                      (size_t)(have_m ? pl.m_rows : pl.fold_tokens) * pb.mcols,
+                                      (const bf16_t *)V + (size_t)c0 * pb.dv, (size_t)n_prompt * pb.dv, part, slices, s);
+                if (st != PSF_OK) return st;
+            }
+            cached = blocks;
+        }
+    }
+    for (int pos0 = cached; pos0 < n_prompt; pos0 += pb.b) {
         const int count = n_prompt - pos0 < pb.b ? n_prompt - pos0 : pb.b;
         const dim3 grid((unsigned)((count + kPrefillTokens - 1) / kPrefillTokens), (unsigned)pb.units);
         if (!have_m && f32_supported(pb)) {
@@ -1241,10 +1427,10 @@ static psf_status prefill_launch(const Problem &pb, const void *K, const void *V
 }
 
 psf_status decode_prefill(const Problem &pb, const void *K, const void *V, const void *G, int n_prompt, void *state,
-                          void *ws, hipStream_t s)
+                          void *ws, size_t ws_bytes, hipStream_t s)
 {
-    return pb.bf16 ? prefill_launch<bf16_t>(pb, K, V, G, n_prompt, (float *)state, ws, s)
-                   : prefill_launch<float>(pb, K, V, G, n_prompt, (float *)state, ws, s);
+    return pb.bf16 ? prefill_launch<bf16_t>(pb, K, V, G, n_prompt, (float *)state, ws, ws_bytes, s)
+                   : prefill_launch<float>(pb, K, V, G, n_prompt, (float *)state, ws, ws_bytes, s);
 }
 
 psf_status decode_step(const Problem &pb, const void *q, const void *k, const void *v, const void *G, int pos,
