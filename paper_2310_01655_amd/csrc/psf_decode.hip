@@ -332,10 +332,14 @@ __device__ __forceinline__ int cache_rows_group(int wa, int nk, int dv, int nv)
     return lg <= 64 ? lg : 0;
 }
 
-__global__ __launch_bounds__(kThreads) void dec_zero_kernel(float *__restrict__ p, size_t count)
+// Zeroes `count` floats from p + first on, of every unit (blockIdx.y; units `stride` floats apart).  All offsets
+// of the layout are multiples of 64 floats, and the state is 16-byte aligned at least.
+__global__ __launch_bounds__(kThreads) void dec_zero_kernel(float *__restrict__ p, size_t first, size_t count,
+                                                            size_t stride)
 {
-    for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < count; i += (size_t)gridDim.x * kThreads)
-        p[i] = 0.f;
+    float4 *const to = (float4 *)(p + first + blockIdx.y * stride);
+    for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < count / 4; i += (size_t)gridDim.x * kThreads)
+        to[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
 // part[u][s][c] = the share of slice s in row [N | S] of the new token:
@@ -1226,12 +1230,29 @@ bool decode_supported(const Problem &pb) { return !pb.exact_feat; }
 
 size_t decode_state_bytes(const Problem &pb) { return decode_layout(pb).total * sizeof(float); }
 
-psf_status decode_reset(const Problem &pb, void *state, hipStream_t s)
+// Zeroes the state; prefix = false: all but ZV, ZD and ZH, which dec_import_state_kernel writes whole (768
+// units of r = d = 64, b = 1024: 0.39 of 1.02 GB).
+static psf_status zero_state(const Problem &pb, float *state, bool prefix, hipStream_t s)
 {
-    const size_t count = decode_layout(pb).total;
-    hipLaunchKernelGGL(dec_zero_kernel, dim3(2048), dim3(kThreads), 0, s, (float *)state, count);
+    const DecodeLayout L = decode_layout(pb);
+    if (prefix) {
+        hipLaunchKernelGGL(dec_zero_kernel, dim3(2048), dim3(kThreads), 0, s, state, (size_t)0, L.total, (size_t)0);
+        PSF_LAUNCH_CHECK();
+        return PSF_OK;
+    }
+    const size_t cache = L.per_unit - L.ck;
+    const unsigned grid = (unsigned)std::max<size_t>(1, std::min<size_t>(2048 / (size_t)pb.units, cache / 4 / kThreads));
+    hipLaunchKernelGGL(dec_zero_kernel, dim3(grid, (unsigned)pb.units), dim3(kThreads), 0, s, state, L.ck, cache,
+                       L.per_unit);
+    PSF_LAUNCH_CHECK();
+    hipLaunchKernelGGL(dec_zero_kernel, dim3(16), dim3(kThreads), 0, s, state, L.mq, L.total - L.mq, (size_t)0);
     PSF_LAUNCH_CHECK();
     return PSF_OK;
+}
+
+psf_status decode_reset(const Problem &pb, void *state, hipStream_t s)
+{
+    return zero_state(pb, (float *)state, true, s);
 }
 
 // The complete blocks of a prompt go through the forward path's kernels where those exist
@@ -1308,9 +1329,9 @@ static psf_status prefill_launch(const Problem &pb, const void *K, const void *V
                                  float *state, void *ws, size_t ws_bytes, hipStream_t s)
 {
     const DecodeLayout L = decode_layout(pb);
-    psf_status st = decode_reset(pb, state, s);
-    if (st != PSF_OK) return st;
     const PrefillPlan pl = prefill_plan(pb, n_prompt);
+    psf_status st = zero_state(pb, state, pl.n_full == 0, s);
+    if (st != PSF_OK) return st;
     const int first = pl.n_full, tail = n_prompt - first;  // prompt tokens before `first` go through the forward kernels
     float *m_tail = (float *)ws;
     char *ktail = (char *)ws + pl.m_bytes, *wsp = ktail + pl.ktail_bytes;
