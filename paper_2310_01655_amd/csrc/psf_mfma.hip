@@ -880,8 +880,8 @@ struct StateLds {
 // column ranges beta >= a / 16, so only those (a, beta) segments are computed: 16 (beta + 1)
 // rows a per range beta, R/16 * (R/16 + 1) / 2 * 16 segments in all (160 of 256 for R = 64).
 // A 32-row MFMA tile is two segments that share beta (lanes x < 16 and x >= 16 of the A operand
-// carry different rows a), a wave owns NA = 2 tiles = four consecutive rows a of one beta, and
-// the waves are numbered range by range: beta = 0 first (4 waves), then 1 (8 waves), ...
+// carry different rows a), a wave owns NA = 2 (or 4) tiles = four (eight) consecutive rows a of one beta, and
+// the waves are numbered range by range: beta = 0 first (4 waves, or 2), then 1 (8, 4), ...
 // NG = 2: eight waves, two per SIMD.  Waves w and w + 4 own the same tiles and take the even and
 // the odd 16-token steps, so the vector instructions that generate one wave's next fragment
 // run under the other wave's MFMAs; at a block boundary the two exchange partial sums through
@@ -914,7 +914,7 @@ __device__ __forceinline__ void state_body(const float *__restrict__ M8, const b
     int a0, beta = 0, bcol;
     if (SYM) {
         int w = grp * 4 + wave;                // wave of the unit
-        while (w >= 4 * (beta + 1)) { w -= 4 * (beta + 1); ++beta; }
+        while (w >= 8 / NA * (beta + 1)) { w -= 8 / NA * (beta + 1); ++beta; }
         a0 = w * NA * SEG;
         bcol = 16 * beta + (x & 15);
     } else {
@@ -1102,13 +1102,13 @@ __device__ __forceinline__ void state_workgroup(const float *__restrict__ M8, co
     constexpr int NTHR = kWg * NG;
     constexpr int DMA_PER_CHUNK = (TC * R * 4 + TC * D * 2) / 16 / NTHR;
     constexpr int AG = NA * 4 / (R / 32);
-    static_assert(!SYM || NA == 2, "tile deal of the symmetric variant");
+    static_assert(!SYM || NA == 2 || (NA == 4 && R == 64), "tile deal of the symmetric variant: whole workgroups");
 
     // XCD-aware order: consecutive workgroup ids go to different XCDs, so give each XCD a
     // contiguous range of (unit, group) pairs; the groups of one unit then share one L2.
     int wg = bid;
     if ((nblk & 7) == 0) wg = (bid & 7) * (nblk >> 3) + (bid >> 3);
-    constexpr int GROUPS = SYM ? (R / 16) * (R / 16 + 1) / 2 : R / AG;   // workgroups per unit
+    constexpr int GROUPS = SYM ? (R / 16) * (R / 16 + 1) / NA : R / AG;   // workgroups per unit
     const int u = wg / GROUPS, grp = wg % GROUPS;
     if (u >= units || t < 2) return;
 
@@ -2681,7 +2681,15 @@ psf_status launch_state(const Problem &pb, const float *M8, const bf16_t *V8, bf
             } else if (grid_sym <= 256)
                 hipLaunchKernelGGL((k_state<R, D, 2, true, 64, 1>), dim3(grid_sym), dim3(kWg), 0, s, M8, V8, Zg,
                                    pb.n, pb.b, pb.t, pb.units);
-            else
+            else if (R == 64 && grid_sym > 800) {
+                // Four tiles a wave: the operands of a step, five LDS reads, serve eight products instead
+                // of four, and a token is staged by half as many workgroups.  Where half the workgroups
+                // still fill the chip (us, two tiles and four, 8192 tokens: 48 units 171, 210; 72: 215, 213; 96: 339,
+                // 324; 132: 380, 366; 192: 650, 631; 768: 1985, 1754).
+                if constexpr (R == 64)
+                    hipLaunchKernelGGL((k_state<R, D, 4, true, 32, 2>), dim3(grid_sym / 2), dim3(kWg), 0, s, M8, V8,
+                                       Zg, pb.n, pb.b, pb.t, pb.units);
+            } else
                 hipLaunchKernelGGL((k_state<R, D, 2, true, 32, 2>), dim3(grid_sym), dim3(kWg), 0, s, M8, V8, Zg,
                                    pb.n, pb.b, pb.t, pb.units);
         }
