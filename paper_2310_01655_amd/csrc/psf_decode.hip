@@ -1055,42 +1055,52 @@ __global__ __launch_bounds__(kThreads) void dec_cache_rows_kernel(const T *__res
 // The state after the complete blocks of a prompt, taken from the forward path's state kernel:
 // Zg [units][a][b'/8][c][8] bf16 holds sum_j phi'(k_j) v_j^T with this file's convention already
 // applied (b' > a doubled, b' < a zero); Spart [units][parts][r][r] fp32 the partial m^T m.
-// ZV (and its bf16 copy) take the pairs a <= b' of Zg, ZD the weighted sums of the partials.
+// ZV (and its bf16 copy) take the pairs a <= b' of Zg, ZD the weighted sums of the partials: the first
+// zd_groups workgroups of a unit, the longest chains of loads.  Bound by memory.
 __global__ __launch_bounds__(kThreads) void dec_import_state_kernel(const bf16_t *__restrict__ Zg,
                                                                     const float *__restrict__ Spart,
                                                                     float *__restrict__ state, DecodeLayout L,
-                                                                    int dv, int mcols, long long pairs, int parts)
+                                                                    int dv, int mcols, int pairs, int parts,
+                                                                    int zd_groups)
 {
     const int u = blockIdx.y;
     float *su = state + (size_t)u * L.per_unit;
-    const bf16_t *zu = Zg + (size_t)u * mcols * mcols * dv;
-    const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
-    // one 16-byte piece of Zg per thread: row a, eight columns b' = 8 o .., value column c
-    // (consecutive threads: consecutive c, so reads and the stores of a row are contiguous)
-    if (idx < (long long)mcols * (mcols / 8) * dv) {
-        const int c = (int)(idx % dv), o = (int)((idx / dv) % (mcols / 8)), a = (int)(idx / dv / (mcols / 8));
-        if (8 * o + 7 >= a) {
-            const uint4 raw = *(const uint4 *)(zu + (size_t)idx * 8);
-            const uint32_t wds[4] = {raw.x, raw.y, raw.z, raw.w};
-            const size_t row0 = (size_t)tri_row(a, mcols);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int bp = 8 * o + e;
-                if (bp < a) continue;
-                const bf16_t h16 = (bf16_t)((e & 1) ? wds[e / 2] >> 16 : wds[e / 2] & 0xffffu);
-                const size_t at = (row0 + bp - a) * dv + c;
-                su[L.zv + at] = bf16_to_f32(h16);
-                if (L.shadow) ((bf16_t *)(su + L.zh))[at] = h16;
-            }
-        }
-    }
-    if (idx < pairs) {
+    if ((int)blockIdx.x < zd_groups) {
+        const int idx = blockIdx.x * kThreads + threadIdx.x;
+        if (idx >= pairs) return;
         int a, bp;
         tri_pair(idx, mcols, a, bp);
         const float *sp = Spart + (size_t)u * parts * mcols * mcols + (size_t)a * mcols + bp;
         float sacc = 0.f;
+#pragma unroll 8
         for (int q2 = 0; q2 < parts; ++q2) sacc += sp[(size_t)q2 * mcols * mcols];
         su[L.zd + idx] = (bp > a ? 2.f : 1.f) * sacc;
+        return;
+    }
+    // Four 16-byte pieces of Zg per thread: row a, eight columns b' = 8 o .., value columns 4 c4 .. (consecutive
+    // threads: consecutive c4, so reads and the stores of a row are contiguous).  dv is 64 or 128 here.
+    const int idx = (blockIdx.x - zd_groups) * kThreads + threadIdx.x, cq = dv / 4;
+    const int c4 = idx % cq, o = idx / cq % (mcols / 8), a = idx / cq / (mcols / 8);
+    if (a >= mcols || 8 * o + 7 < a) return;
+    const uint4 *from = (const uint4 *)(Zg + (size_t)u * mcols * mcols * dv) + (size_t)idx * 4;
+    uint4 raw[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) raw[c] = from[c];
+    const size_t row0 = (size_t)tri_row(a, mcols);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int bp = 8 * o + e;
+        if (bp < a) continue;
+        uint32_t bits[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint32_t wds[4] = {raw[c].x, raw[c].y, raw[c].z, raw[c].w};
+            bits[c] = (e & 1) ? wds[e / 2] >> 16 : wds[e / 2] & 0xffffu;
+        }
+        const size_t at = (row0 + bp - a) * dv + 4 * c4;
+        *(float4 *)&su[L.zv + at] = make_float4(bf16_to_f32((bf16_t)bits[0]), bf16_to_f32((bf16_t)bits[1]),
+                                                bf16_to_f32((bf16_t)bits[2]), bf16_to_f32((bf16_t)bits[3]));
+        if (L.shadow) *(uint2 *)&((bf16_t *)(su + L.zh))[at] = make_uint2(bits[0] | bits[1] << 16, bits[2] | bits[3] << 16);
     }
 }
 
@@ -1357,11 +1367,11 @@ static psf_status prefill_launch(const Problem &pb, const void *K, const void *V
             int parts = 0;
             st = mfma_total_state(pb, first, src_n, kc, vc, G, wsp + 2 * pl.copy_bytes, s, &zg, &spart, &parts);
             if (st != PSF_OK) return st;
-            const long long pairs = tri_count(pb.mcols);
-            const long long pieces = (long long)pb.mcols * (pb.mcols / 8) * pb.dv;      // >= pairs
-            const dim3 grid((unsigned)((pieces + kThreads - 1) / kThreads), (unsigned)pb.units);
+            const int pairs = (int)tri_count(pb.mcols), threads = pb.mcols * (pb.mcols / 8) * (pb.dv / 4);
+            const int zd_groups = (pairs + kThreads - 1) / kThreads;
+            const dim3 grid((unsigned)(zd_groups + (threads + kThreads - 1) / kThreads), (unsigned)pb.units);
             hipLaunchKernelGGL(dec_import_state_kernel, grid, dim3(kThreads), 0, s, (const bf16_t *)zg, spart, state, L,
-                               pb.dv, pb.mcols, pairs, parts);
+                               pb.dv, pb.mcols, pairs, parts, zd_groups);
             PSF_LAUNCH_CHECK();
         }
     }
