@@ -2708,6 +2708,13 @@ psf_status launch_state(const Problem &pb, const float *M8, const bf16_t *V8, bf
     return PSF_OK;
 }
 
+// Launches of the output kernel of at most this many workgroups of 256 tokens take 128 instead: those are
+// bound by one workgroup's chain of key tiles and chunks of the state, which is half as long then, and two of
+// the smaller ones fit a CU (us, 256 and 128 tokens a workgroup, causal and without a mask: 24 of the
+// former 16.3, 10.9 and 10.8, 6.8; 96: 16.9, 12.0 and 10.7, 8.0; 192: 28.5, 26.6 and 11.9, 10.9; 256: 22.1, 20.2 and 12.9,
+// 11.6; r = 64, degree 8, no mask: 64: 26.4, 15.5).  A row's sums keep their order.
+constexpr unsigned kSmallOutGrid = 256;
+
 // Den (1 + sum of weights per row, fp32) and MK_rm (m(K) as bf16 rows) are extra outputs the
 // backward pass asks for; the forward entry point passes null.
 template <int D, int R, int P>
@@ -2925,18 +2932,26 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
             } else {
                 return PSF_ERR_UNSUPPORTED;
             }
-        } else if (noncausal)
-            hipLaunchKernelGGL((k_out<R, D, P, TT, false, true>), dim3(grid), dim3(kWg), 0, s, (const bf16_t *)Q,
-                               (const bf16_t *)K, w.V8, w.MQ, w.Zg, w.Shi, w.Slo, (bf16_t *)O, Den, nullptr, nullptr, pb.n,
-                               pb.b, pb.t);
-        else if (Den)
-            hipLaunchKernelGGL((k_out<R, D, P, TT, true>), dim3(grid), dim3(kWg), 0, s, (const bf16_t *)Q,
-                               (const bf16_t *)K, w.V8, w.MQ, w.Zg, w.Shi, w.Slo, (bf16_t *)O, Den, nullptr, nullptr, pb.n,
-                               pb.b, pb.t);
-        else
-            hipLaunchKernelGGL((k_out<R, D, P, TT, false>), dim3(grid), dim3(kWg), 0, s, (const bf16_t *)Q,
-                               (const bf16_t *)K, w.V8, w.MQ, w.Zg, w.Shi, w.Slo, (bf16_t *)O, Den, nullptr, nullptr, pb.n,
-                               pb.b, pb.t);
+        } else {
+            auto launch = [&](auto tt) {
+                constexpr int T = decltype(tt)::value;
+                const dim3 wgs((unsigned)((size_t)pb.units * (pb.n / (128 * T))));
+                const bf16_t *q = (const bf16_t *)Q, *k = (const bf16_t *)K;
+                if (noncausal)
+                    hipLaunchKernelGGL((k_out<R, D, P, T, false, true>), wgs, dim3(kWg), 0, s, q, k, w.V8, w.MQ, w.Zg,
+                                       w.Shi, w.Slo, (bf16_t *)O, Den, nullptr, nullptr, pb.n, pb.b, pb.t);
+                else if (Den)
+                    hipLaunchKernelGGL((k_out<R, D, P, T, true>), wgs, dim3(kWg), 0, s, q, k, w.V8, w.MQ, w.Zg, w.Shi,
+                                       w.Slo, (bf16_t *)O, Den, nullptr, nullptr, pb.n, pb.b, pb.t);
+                else
+                    hipLaunchKernelGGL((k_out<R, D, P, T, false>), wgs, dim3(kWg), 0, s, q, k, w.V8, w.MQ, w.Zg, w.Shi,
+                                       w.Slo, (bf16_t *)O, Den, nullptr, nullptr, pb.n, pb.b, pb.t);
+            };
+            if (TT == 2 && grid <= kSmallOutGrid)
+                launch(std::integral_constant<int, 1>{});
+            else
+                launch(std::integral_constant<int, TT>{});
+        }
         PSF_LAUNCH_CHECK();
     }
     if (tm) tm->mark();
