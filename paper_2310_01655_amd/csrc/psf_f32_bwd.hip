@@ -243,6 +243,15 @@ __global__ __launch_bounds__((SideLds<DT, RT, WR, WK_, KSIDE, T>::kThreads), WK_
             }
         };
         fetch(0);
+        // key side: an infinity or NaN of a later token's gradient is in its column of every row of the record,
+        // the first among them; dV takes it from fp32 products, as within the span
+        bool odd_record = false;
+        if constexpr (KSIDE) {
+            const uint16_t *first = (const uint16_t *)(z + (lane & ~7)) + (lane & 7);
+#pragma unroll
+            for (int c = 0; c < VT / 4; ++c) odd_record |= (first[128 * c] & 0x7f80u) == 0x7f80u;
+            odd_record = __any(odd_record);
+        }
         float m_own[4 * RT];
         load_frags<RT>(Mown + o_row * sh.mcols, sh.mcols, true, sh.vec_m, g, m_own);
         __syncthreads();
@@ -297,9 +306,13 @@ __global__ __launch_bounds__((SideLds<DT, RT, WR, WK_, KSIDE, T>::kThreads), WK_
                 }
             }
             if constexpr (KSIDE) {
-                Parts<3> pp;
-                split8(phi, pp);
-                add_parts<VT, 3>(zt, L::kPlane, XP, pp, pc, lane);
+                if (odd_record) {
+                    add_parts_odd<VT, 3>(zt, L::kPlane, XP, phi, pc, lane, 0xffffffffu);
+                } else {
+                    Parts<3> pp;
+                    split8(phi, pp);
+                    add_parts<VT, 3>(zt, L::kPlane, XP, pp, pc, lane);
+                }
                 if (piece & 1) {                            // (an even number of turns)
                     add_settled(ac, pc);
                     clear(pc);

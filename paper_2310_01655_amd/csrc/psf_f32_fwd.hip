@@ -143,6 +143,33 @@ __global__ __launch_bounds__(kF32Threads, RT <= 2 ? 2 : 1) void f32_state_kernel
             }
         }
     }
+    // An infinity or NaN among the values: its parts are no sum of them (inf - inf), so the wave forms these
+    // sums from fp32 products instead.
+    if (any_odd(acc)) {
+#pragma unroll
+        for (int e = 0; e < SLOTS; ++e) clear(acc[e]);
+#pragma unroll 1
+        for (int j = j_begin; j < j_end; ++j) {
+            const float *mp = M + ((size_t)u * sh.n + j) * sh.mcols;
+            const S *cp = C + ((size_t)u * sh.n + j) * sh.dv + c0;
+            auto m_of = [&](int c) { return c < sh.mcols ? mp[c] : 0.f; };
+            const float ma_lo = m_of(a_lo), ma_hi = TWO ? m_of(a_hi) : 0.f;
+            float v[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[t] = c0 + 16 * t + li < sh.dv ? load_f(cp, 16 * t + li) : 0.f;
+#pragma unroll
+            for (int e = 0; e < SLOTS; ++e) {
+                if (!TWO && e >= split) break;
+                const float ma = (!TWO || e < split ? ma_lo : ma_hi) * (e == 0 || e == split ? 1.f : 2.f);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float phi = ma * m_of(mcol[e] + 4 * g + k);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) acc[e][t][k] += phi * v[t];
+                }
+            }
+        }
+    }
     float *rec = Z + ((size_t)u * sh.spans + span) * record_floats(RT, VT);
     float *srec = rec + record_values(RT, VT) / 2 * 3;
 #pragma unroll
@@ -189,7 +216,7 @@ __global__ __launch_bounds__(kF32Threads) void f32_scan_kernel(float *__restrict
         }
         const float x[8] = {run[0][0], run[0][1], run[0][2], run[0][3], run[1][0], run[1][1], run[1][2], run[1][3]};
         Parts<3> p;
-        split8(x, p);
+        split8<true>(x, p);
         *(bf8 *)(z + at) = p.v[0];
         *(bf8 *)(z + at + 4) = p.v[1];
         *(bf8 *)(zl + at) = p.v[2];
@@ -400,6 +427,24 @@ __global__ __launch_bounds__((RowsLds<DT, RT, WR, WK_, T>::kThreads), WK_ == 1 &
         __syncthreads();
 #pragma unroll
         for (int ct = 0; ct < VT; ++ct) acc[ct] = *(const f4 *)&back[(16 * wr + li) * (CP + 4) + 16 * ct + 4 * g];
+        // an infinity or NaN in the record, as in the state kernel: the set's share again, from fp32 products
+        static_assert(L::kBack <= L::kBuffers * WK * L::kPiece, "the rows' sketches are still there");
+        if (any_odd(acc)) {
+            clear(acc);
+            const float *m_row = own + (16 * wr + li) * OP;
+#pragma unroll 1
+            for (int a = wk; a < 16 * RT; a += WK) {
+                const int at = a >> 4, first = at * RT - at * (at - 1) / 2 - at;
+#pragma unroll 1
+                for (int b = 16 * at; b < 16 * RT; ++b) {
+                    const int row = ((first + (b >> 4)) * 16 + (a & 15)) * 16 + (b & 15);
+                    const float phi = m_row[a] * m_row[b];
+#pragma unroll
+                    for (int ct = 0; ct < VT; ++ct)
+                        acc[ct] += record_columns(z, record_values(RT, VT), CP, row, 16 * ct + 4 * g) * phi;
+                }
+            }
+        }
     }
 
     if (sh.pairs) {

@@ -72,12 +72,13 @@ __device__ __forceinline__ PairParts split_pair_inf(float a, float b)
     return rest_parts(__builtin_amdgcn_perm(ub, ua, 0x07060302u), __builtin_isinf(a) ? 0.f : ra, __builtin_isinf(b) ? 0.f : rb);
 }
 
+template <bool INF = false>
 __device__ __forceinline__ void split8(const float (&x)[8], Parts<3> &p)
 {
     u4v h, m, l;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const PairParts q = split_pair(x[2 * k], x[2 * k + 1]);
+        const PairParts q = INF ? split_pair_inf(x[2 * k], x[2 * k + 1]) : split_pair(x[2 * k], x[2 * k + 1]);
         h[k] = q.h;
         m[k] = q.m;
         l[k] = q.l;
@@ -424,6 +425,37 @@ struct RecordPiece {
     }
     __device__ __forceinline__ void zero() { h = m = l = u4v{0u, 0u, 0u, 0u}; }
 };
+
+// four columns of a record's row in fp32
+__device__ __forceinline__ f4 record_columns(const float *z, size_t values, int cp, int row, int c)
+{
+    const uint16_t *at = (const uint16_t *)(z + (size_t)row * cp + (c & ~7)) + (c & 7);
+    const uint16_t *low = (const uint16_t *)(z + values) + (size_t)row * cp + c;
+    return widen(*(const uint2 *)at) + (widen(*(const uint2 *)(at + 8)) + widen(*(const uint2 *)low));
+}
+
+// Whether a lane of the wave holds an infinity or NaN among its sums.  Values that are one show up here, as their
+// parts multiply to NaN.
+template <int N>
+__device__ __forceinline__ float odd_probe(const f4 (&a)[N])
+{
+    float probe = 0.f;
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) probe = __builtin_fmaf(a[k][s], 0.f, probe);
+    return probe;
+}
+template <int N>
+__device__ __forceinline__ bool any_odd(const f4 (&a)[N]) { return __any(odd_probe(a) != 0.f); }
+template <int M, int N>
+__device__ __forceinline__ bool any_odd(const f4 (&a)[M][N])
+{
+    float probe = 0.f;
+#pragma unroll
+    for (int k = 0; k < M; ++k) probe += odd_probe(a[k]);
+    return __any(probe != 0.f);
+}
 
 }  // namespace psf
 #endif

@@ -60,3 +60,31 @@ def test_values_of_any_size_keep_24_bits(scale):
     desc = psf.make_desc(1, heads, n, 64, 4, 16, 110, "f32", per_head=True)
     O = psf.psf_causal_attn_fwd(desc, q, k, v, G)
     assert torch.equal(psf.psf_causal_attn_fwd(desc, q, k, v * scale, G), O * scale)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("heads,n,d,r,b", [
+    (2, 3024, 64, 16, 48), (8, 3150, 64, 32, 150), (40, 1350, 64, 16, 150), (9, 4545, 64, 64, 101), (4, 5959, 128, 32, 59),
+    (1, 14529, 128, 128, 29),
+])
+def test_an_infinite_value_keeps_its_sign_through_a_state(heads, n, d, r, b, dtype):
+    """Sketches and rows of one sign: every weight is positive, so an infinity of V arrives as itself in
+    its column of all later rows, and one of dO in dV of all earlier tokens, spans between them or not."""
+    at = 7
+    q, k, v = (x.cuda() for x in inputs.make_qkv(1, heads, n, d, seed=5, dtype=dtype))
+    q, k = q.abs(), k.abs()
+    G = inputs.make_sketch_matrices(heads, d, r, 4, per_head=True, seed=3, dtype=dtype).cuda().abs()
+    dO = inputs.make_dout(1, heads, n, d, seed=5, dtype=dtype).cuda()
+    desc = psf.make_desc(1, heads, n, d, 4, r, b, dtype, per_head=True)
+    assert psf.kernel_path(desc) == 0 and psf.general_spans(desc, 0) > 1 and psf.general_spans(desc, 2) > 1
+    v[:, :, at, 5], v[:, :, at, 6], v[:, :, at, 7] = float("inf"), float("-inf"), float("nan")
+    calls = [psf.psf_causal_attn_fwd(desc, q, k, v, G)[:, :, at:], psf.psf_noncausal_attn_fwd(desc, q, k, v, G)]
+    others = [c for c in range(d) if c not in (5, 6, 7)]
+    for got in calls:
+        assert (got[..., 5] == float("inf")).all() and (got[..., 6] == float("-inf")).all() and got[..., 7].isnan().all()
+        assert got[..., others].isfinite().all()
+    v = inputs.make_qkv(1, heads, n, d, seed=5, dtype=dtype)[2].cuda()
+    dO[:, :, n - at, 3], dO[:, :, n - at, 4] = float("inf"), float("-inf")
+    dV = psf.psf_causal_attn_bwd(desc, q, k, v, G, dO)[2][:, :, :n - at]
+    assert (dV[..., 3] == float("inf")).all() and (dV[..., 4] == float("-inf")).all()
+    assert dV[..., [c for c in range(d) if c not in (3, 4)]].isfinite().all()
