@@ -8,9 +8,10 @@
 // streamed rows; pair weights and gradients never leave the registers.
 //
 // Bound by vector instructions and LDS reads about equally (a group: 40 to 64 products, about 200 vector
+// Bound by vector instructions and LDS reads about equally (a group: 40 to 64 products, about 200 vector
 // instructions, 18 to 36 KB of LDS reads a wave).  24 units of 1950 tokens, r = 32, bf16 storage, query and
-// key side: 113 and 190 us with v_mfma_f32_16x16x4_f32, 76 and 121 now; 8 units of 2048, r = 64, fp32 storage:
-// 120 and 176, 164 and 143.
+// key side: 111 and 186 us with v_mfma_f32_16x16x4_f32, 74 and 119 now; 8 units of 2048, r = 64, fp32 storage:
+// 116 and 169, 98 and 120 (158 and 134 when both rules' scores and weights were in registers at once).
 #include "psf_parts.h"
 #include "psf_f32.h"
 
@@ -155,62 +156,65 @@ __global__ __launch_bounds__((SideLds<DT, RT, WR, WK_, KSIDE, T>::kThreads), WK_
         const bool exact_w = KSIDE ? xw < edge_w_last : xw + 31 >= edge_w;
         const bool cross_w = KSIDE ? xw + 31 >= edge_w : xw < edge_w_last;
         const bool masked = KSIDE ? xw < ow + 15 : xw + 31 > ow;      // some of the pairs
-        f4 dw[2], se[2], ss[2];
-        // (one after the other where their operands together exceed the registers)
+        const int rel = o - xw;                             // the own row's place among the streamed ones
+        const unsigned seen = KSIDE ? (rel > 31 ? 0u : 0xffffffffu << max(0, rel))
+                                    : (rel < 0 ? 0u : 0xffffffffu >> max(0, 31 - rel));
+        auto place_of = [&](int k) { return xw + 16 * (k >> 2) + 4 * g + (k & 3); };
+        auto mask = [&](float (&w)[8]) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) w[k] = (KSIDE ? place_of(k) >= o : place_of(k) <= o) ? w[k] : 0.f;
+        };
+        // Each rule's weights go into their sums before the other's scores are formed, and each tile's sums
+        // are formed apart (two levels of summation, as long chains of one sign or both lose digits): the
+        // fewest registers.
+        f4 dw[2];
+        float we[8];
         score_parts<2, VT / 2, PC, PO>(cs, KT * XP, XP, r0, cf, lane, dw);
-        if (P == 3) __builtin_amdgcn_sched_barrier(0);
-        if (exact_w) score_parts<2, DT / 2, P, P>(xs, KT * XP, XP, r0, xf, lane, se);
-        if (P == 3) __builtin_amdgcn_sched_barrier(0);
-        if (cross_w) score_parts<2, MT / 2, 3, 3>(ms, KT * MP, MP, r0, mf, lane, ss);
         settle_parts();
-        float we[8], wx[8], wm[8];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             if constexpr (KSIDE) dw[t] += *(const f4 *)&gs[r0 + 16 * t + 4 * g];
             else dw[t] += f4{own_den, own_den, own_den, own_den};
         }
         if (exact_w) {
+            f4 se[2];
+            float wx[8];
+            score_parts<2, DT / 2, P, P>(xs, KT * XP, XP, r0, xf, lane, se);
+            settle_parts();
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 float pm1;
                 powers(se[k >> 2][k & 3], sh.p, we[k], pm1);
                 wx[k] = (float)sh.p * pm1 * dw[k >> 2][k & 3];
+                if (cross_w) wx[k] = (KSIDE ? place_of(k) < edge : place_of(k) >= edge) ? wx[k] : 0.f;
             }
+            if (masked) mask(wx);
+            add_tile<DT, P>(xs + r0 * XP, KT * XP, XP, wx, ax, lane, odd, seen);
         }
         if (cross_w) {
+            f4 ss[2];
+            float wm[8];
+            score_parts<2, MT / 2, 3, 3>(ms, KT * MP, MP, r0, mf, lane, ss);
+            settle_parts();
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const float s = ss[k >> 2][k & 3], own = s * s;
                 wm[k] = 2.f * s * dw[k >> 2][k & 3];
                 if (exact_w) {                              // either rule: the block's edge lies in the group
-                    const int at = xw + 16 * (k >> 2) + 4 * g + (k & 3);
-                    const bool ex = KSIDE ? at < edge : at >= edge;
+                    const bool ex = KSIDE ? place_of(k) < edge : place_of(k) >= edge;
                     we[k] = ex ? we[k] : own;
-                    wx[k] = ex ? wx[k] : 0.f;
                     wm[k] = ex ? 0.f : wm[k];
                 } else {
                     we[k] = own;
                 }
             }
+            if (masked) mask(wm);
+            add_tile<RT, 3>(ms + r0 * MP, KT * MP, MP, wm, am, lane, odd, seen);
         }
-        if (masked) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int at = xw + 16 * (k >> 2) + 4 * g + (k & 3);
-                const bool seen = KSIDE ? at >= o : at <= o;
-                we[k] = seen ? we[k] : 0.f;
-                if (exact_w) wx[k] = seen ? wx[k] : 0.f;
-                if (cross_w) wm[k] = seen ? wm[k] : 0.f;
-            }
+        if constexpr (KSIDE) {
+            if (masked) mask(we);
+            add_tile<VT, PC>(cs + r0 * XP, KT * XP, XP, we, ac, lane, odd, seen);
         }
-        // each tile's sums apart (two levels of summation, as long chains of one sign or both lose
-        // digits), one product after the other: fewer registers than all of them together
-        const int rel = o - xw;                             // the own row's place among the streamed ones
-        const unsigned seen = KSIDE ? (rel > 31 ? 0u : 0xffffffffu << max(0, rel))
-                                    : (rel < 0 ? 0u : 0xffffffffu >> max(0, 31 - rel));
-        if (exact_w) add_tile<DT, P>(xs + r0 * XP, KT * XP, XP, wx, ax, lane, odd, seen);
-        if (cross_w) add_tile<RT, 3>(ms + r0 * MP, KT * MP, MP, wm, am, lane, odd, seen);
-        if constexpr (KSIDE) add_tile<VT, PC>(cs + r0 * XP, KT * XP, XP, we, ac, lane, odd, seen);
     }
 
     // Spans before (query side) or after (key side): with the record R of the state,
@@ -391,7 +395,7 @@ psf_status side_launch(const Problem &pb, const F32Plan &pl, const float *MQ, co
             PSF_LAUNCH_CHECK();
             return PSF_OK;
         };
-        return f32_deal<DT>(pb, RT == 4 && sizeof(T) == 4 && !KSIDE ? 0 : 512, go);
+        return f32_deal<DT>(pb, 512, go);
     });
 }
 
