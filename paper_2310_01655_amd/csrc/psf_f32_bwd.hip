@@ -8,7 +8,6 @@
 // streamed rows; pair weights and gradients never leave the registers.
 //
 // Bound by vector instructions and LDS reads about equally (a group: 40 to 64 products, about 200 vector
-// Bound by vector instructions and LDS reads about equally (a group: 40 to 64 products, about 200 vector
 // instructions, 18 to 36 KB of LDS reads a wave).  24 units of 1950 tokens, r = 32, bf16 storage, query and
 // key side: 111 and 186 us with v_mfma_f32_16x16x4_f32, 74 and 119 now; 8 units of 2048, r = 64, fp32 storage:
 // 116 and 169, 98 and 120 (158 and 134 when both rules' scores and weights were in registers at once).

@@ -379,6 +379,7 @@ __global__ __launch_bounds__((RowsLds<DT, RT, WR, WK_, T>::kThreads), WK_ == 1 &
         f4 sum[H * C];
         clear(sum);
         int buf = 0;
+#pragma unroll 1                                            // (r = 16 and two sets: all eight turns at once spill)
         for (int a0 = 0; a0 < 16 * RT; a0 += WK) {
             const int a = a0 + wk;
             f4 ta[H * C];
