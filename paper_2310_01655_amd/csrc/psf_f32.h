@@ -4,6 +4,7 @@
 
 #include <initializer_list>
 #include <type_traits>
+#include "psf_f32_index.h"
 #include "psf_internal.h"
 
 namespace psf {
@@ -87,21 +88,35 @@ static inline psf_status with_tiles(const Problem &pb, F f)
     return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 8>{});
 }
 
-// How the kernels of rows share out the work: f(WR, WK), see psf_f32_fwd.hip.  blocks: workgroups of 64 rows.
-// Measured (us a call; WR 1 WK 4, WR 4 WK 2, WR 4 WK 1): forward 1 x 4292 tokens (68 workgroups), r = 32,
-// 65, -, 89; training 12 x 648 (132), r = 64, fp32 493, 357, 400; forward 16 x 1515 (384), r = 64, -, 83, 101;
-// forward 14 x 2300 (504), r = 32, -, 117, 101.
-// share: from 96 workgroups to this many, two sets of waves share the keys.
-template <int DT, typename F>
-static inline psf_status f32_deal(const Problem &pb, int share, F f)
+// How the kernels of rows share out the work: f(WR, WK), see psf_f32_fwd.hip.  By row_walks(), W: what counts is for
+// how long how many CUs are busy.  Four sets of waves have a chain half as long as two, and two half as long as
+// one.  But the former take 16 rows a workgroup instead of 64 and stage every key four times as often:
+// below `few`, where that fills CUs that would be idle.  And two sets fill a CU that would else hold two
+// workgroups of one: up to 256 of them.
+// Measured (us a call; WR 1 WK 4, WR 4 WK 2, WR 4 WK 1; forward, bf16 storage):
+//   r = 16, 12 x 500  W 54: 19, 23, 26    16 x 750 W 104: 29, 28, 34    12 x 2000 W 305: 74, 63, 56    14 x 2300 W 401: 86, 86, 61
+//   r = 32, 4 x 2000  W 66: 44, 58, 78    32 x 500 W 144: 31, 25, 29    12 x 2000 W 198: 81, 64, 81    96 x 300 W 288: 46, 33, 28
+//   r = 64, 2 x 2000  W 33: 53, 68, 93    12 x 700 W 72: 42, 34, 42     7 x 4000 W 224: 341, 142, 182  40 x 1000 W 340: 175, 77, 61
+// Without a mask, r = 32, 32 x 500, W 256: 35, 24, 28.  few: 70, and 110 for rows in bf16 storage with r up to 32, where two
+// workgroups of four sets fit a CU (12 x 700, r = 16, W 72: 23, 28, 33).
+// fp32 storage with r = 64 has two sets always (TWO): four do not fit the LDS and were two, and one set
+// needs more registers than two waves a SIMD leave it (12 x 500, W 54: 39, 31, 39; 40 x 1000, W 340: 217, 88, 110).
+template <int DT, bool TWO, typename F>
+static inline psf_status f32_deal(const Problem &pb, const F32Plan &pl, int rt, int few, F f)
 {
     using std::integral_constant;
     if constexpr (DT == 4) {
-        const long long blocks = (long long)pb.units * ((pb.n + 63) / 64);
-        if (blocks < 96) return f(integral_constant<int, 1>{}, integral_constant<int, 4>{});
-        if (blocks < share) return f(integral_constant<int, 4>{}, integral_constant<int, 2>{});
+        if constexpr (!TWO) {
+            const int per_span = ((pl.span < pb.n ? pl.span : pb.n) + 63) / 64;
+            const double walks = row_walks(pb.units, pl.spans, per_span, !pl.noncausal,
+                                           !pl.states ? 0 : rt == 4 ? 24 : 4 * rt);
+            if (walks < few) return f(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+            if (walks > 256) return f(integral_constant<int, 4>{}, integral_constant<int, 1>{});
+        }
+        return f(integral_constant<int, 4>{}, integral_constant<int, 2>{});
+    } else {
+        return f(integral_constant<int, 4>{}, integral_constant<int, 1>{});
     }
-    return f(integral_constant<int, 4>{}, integral_constant<int, 1>{});
 }
 
 }  // namespace psf

@@ -55,7 +55,7 @@ struct SideLds {
 };
 
 template <int DT, int RT, int WR, int WK_, bool KSIDE, typename T>
-__global__ __launch_bounds__((SideLds<DT, RT, WR, WK_, KSIDE, T>::kThreads), WK_ == 1 && DT == 4 && !(RT == 4 && sizeof(T) == 4) ? 2 : 1) void f32_bwd_kernel(
+__global__ __launch_bounds__((SideLds<DT, RT, WR, WK_, KSIDE, T>::kThreads), WK_ == 1 && DT == 4 ? 2 : 1) void f32_bwd_kernel(
     const float *__restrict__ Mown, const float *__restrict__ Mstr, const T *__restrict__ Xown,
     const T *__restrict__ Xstr, const T *__restrict__ V, const float *__restrict__ GV, const float *__restrict__ gden,
     const float *__restrict__ Z, float *__restrict__ dM, float *__restrict__ dX, T *__restrict__ dV, F32Shape sh)
@@ -394,7 +394,7 @@ psf_status side_launch(const Problem &pb, const F32Plan &pl, const float *MQ, co
             PSF_LAUNCH_CHECK();
             return PSF_OK;
         };
-        return f32_deal<DT>(pb, 512, go);
+        return f32_deal<DT, RT == 4 && sizeof(T) == 4>(pb, pl, RT, 70, go);
     });
 }
 

@@ -620,7 +620,7 @@ psf_status rows_launch(const Problem &pb, const F32Plan &pl, const float *MQ, co
             PSF_LAUNCH_CHECK();
             return PSF_OK;
         };
-        return f32_deal<DT>(pb, RT == 4 && sizeof(T) == 4 ? 1024 : 512, go);
+        return f32_deal<DT, RT == 4 && sizeof(T) == 4>(pb, pl, RT, sizeof(T) == 2 && RT <= 2 ? 110 : 70, go);
     });
 }
 

@@ -70,5 +70,14 @@ PSF_HD bool row_place(unsigned flat, int units, int spans, int per_span, RowPlac
     return group < groups && at.k < per_span;
 }
 
+// How many workgroups of 64 rows the row kernels have in hand, counted as if each walked as far as the longest:
+// in a causal call the k-th block of a span walks k blocks of keys.  state_walk: blocks of keys that applying
+// a state is worth (0: no states).  Not causal: every block walks alike.
+PSF_HD double row_walks(int units, int spans, int per_span, int causal, double state_walk)
+{
+    const double blocks = (double)units * spans * per_span;
+    return causal ? blocks * ((per_span + 1) / 2.0 + state_walk) / (per_span + state_walk) : blocks;
+}
+
 }  // namespace psf
 #endif

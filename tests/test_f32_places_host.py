@@ -27,6 +27,14 @@ int main()
                     else ++seen[((size_t)at.unit * spans + at.span) * per_span + at.k];
                 }
                 for (int s : seen) bad += s != 1;
+                // how far the blocks of rows walk, over the longest of them
+                for (double state : {0.0, 4.0, 24.0}) {
+                    double sum = 0;
+                    for (int k = 1; k <= per_span; ++k) sum += units * spans * (k + state) / (per_span + state);
+                    const double walks = row_walks(units, spans, per_span, 1, state);
+                    bad += !(walks > 0.999 * sum && walks < 1.001 * sum);
+                }
+                bad += row_walks(units, spans, per_span, 0, 4.0) != (double)units * spans * per_span;
             }
     printf("%d\n", bad);
     return bad != 0;
