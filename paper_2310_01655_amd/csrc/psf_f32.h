@@ -99,20 +99,21 @@ static inline psf_status with_tiles(const Problem &pb, F f)
 //   r = 64, 2 x 2000  W 33: 53, 68, 93    12 x 700 W 72: 42, 34, 42     7 x 4000 W 224: 341, 142, 182  40 x 1000 W 340: 175, 77, 61
 // Without a mask, r = 32, 32 x 500, W 256: 35, 24, 28.  few: 70, and 110 for rows in bf16 storage with r up to 32, where two
 // workgroups of four sets fit a CU (12 x 700, r = 16, W 72: 23, 28, 33).
-// fp32 storage with r = 64 has two sets always (TWO): four do not fit the LDS and were two, and one set
-// needs more registers than two waves a SIMD leave it (12 x 500, W 54: 39, 31, 39; 40 x 1000, W 340: 217, 88, 110).
-template <int DT, bool TWO, typename F>
+// fp32 storage with r = 64 never has one set, which needs more registers than two waves a SIMD leave it (40 x 1000, W
+// 340: 217, 88, 110), and its backward kernels never four, which do not fit the LDS; few is 50 for its rows
+// (2 x 2000, W 33: 67, 80, 115; 12 x 500, W 54: 33, 31, 39).
+template <int DT, bool FOUR, bool ONE, typename F>
 static inline psf_status f32_deal(const Problem &pb, const F32Plan &pl, int rt, int few, F f)
 {
     using std::integral_constant;
     if constexpr (DT == 4) {
-        if constexpr (!TWO) {
-            const int per_span = ((pl.span < pb.n ? pl.span : pb.n) + 63) / 64;
-            const double walks = row_walks(pb.units, pl.spans, per_span, !pl.noncausal,
-                                           !pl.states ? 0 : rt == 4 ? 24 : 4 * rt);
+        const int per_span = ((pl.span < pb.n ? pl.span : pb.n) + 63) / 64;
+        const double walks = row_walks(pb.units, pl.spans, per_span, !pl.noncausal,
+                                       !pl.states ? 0 : rt == 4 ? 24 : 4 * rt);
+        if constexpr (FOUR)
             if (walks < few) return f(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+        if constexpr (ONE)
             if (walks > 256) return f(integral_constant<int, 4>{}, integral_constant<int, 1>{});
-        }
         return f(integral_constant<int, 4>{}, integral_constant<int, 2>{});
     } else {
         return f(integral_constant<int, 4>{}, integral_constant<int, 1>{});

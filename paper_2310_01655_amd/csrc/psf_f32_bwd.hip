@@ -39,13 +39,12 @@ __device__ __forceinline__ void add_tile(const uint16_t *tile, int plane, int pi
 }
 
 // WR, WK as in psf_f32_fwd.hip: the sets of waves share the streamed rows of a tile and the state pieces.
-template <int DT, int RT, int WR, int WK_, bool KSIDE, typename T>
+template <int DT, int RT, int WR, int WK, bool KSIDE, typename T>
 struct SideLds {
     static constexpr int P = parts_of<T>(), PC = KSIDE ? 3 : P, PO = KSIDE ? P : 3;   // parts of C streamed, own
     static constexpr int MT = RT < 2 ? 2 : RT, OP = pitch_of<RT>(), ROWS = 16 * WR;
     static constexpr int XP = tr_pitch<DT>(), MP = tr_pitch<MT>();
     static constexpr int kRow = (P + PC) * XP + 3 * MP;               // 16-bit places of a streamed row
-    static constexpr int WK = kRow * 2 * 32 * WK_ <= 157 * 1024 ? WK_ : WK_ / 2;
     static constexpr int kThreads = 64 * WR * WK, KT = 32 * WK, kBuffers = WK == 4 ? 1 : 2;
     static constexpr int kX = P * KT * XP, kM = 3 * KT * MP;
     static constexpr int kPlane = KT * XP, kPiece = 3 * kPlane, kOwn = ROWS * OP * 2;
@@ -54,15 +53,15 @@ struct SideLds {
     static constexpr int kPlaces = most(most(KT * kRow, kBuffers * kPiece + kOwn), kSums);
 };
 
-template <int DT, int RT, int WR, int WK_, bool KSIDE, typename T>
-__global__ __launch_bounds__((SideLds<DT, RT, WR, WK_, KSIDE, T>::kThreads), WK_ == 1 && DT == 4 ? 2 : 1) void f32_bwd_kernel(
+template <int DT, int RT, int WR, int WK, bool KSIDE, typename T>
+__global__ __launch_bounds__((SideLds<DT, RT, WR, WK, KSIDE, T>::kThreads), WK == 1 && DT == 4 ? 2 : 1) void f32_bwd_kernel(
     const float *__restrict__ Mown, const float *__restrict__ Mstr, const T *__restrict__ Xown,
     const T *__restrict__ Xstr, const T *__restrict__ V, const float *__restrict__ GV, const float *__restrict__ gden,
     const float *__restrict__ Z, float *__restrict__ dM, float *__restrict__ dX, T *__restrict__ dV, F32Shape sh)
 {
-    using L = SideLds<DT, RT, WR, WK_, KSIDE, T>;
+    using L = SideLds<DT, RT, WR, WK, KSIDE, T>;
     constexpr int VT = DT, ROWS = L::ROWS, KT = L::KT, P = L::P, PC = L::PC, PO = L::PO, MT = L::MT, XP = L::XP, MP = L::MP;
-    constexpr int WK = L::WK, THREADS = L::kThreads;
+    constexpr int THREADS = L::kThreads;
     __shared__ __attribute__((aligned(16))) uint16_t lds[L::kPlaces];
     __shared__ __attribute__((aligned(16))) float gs[KT], sden[2][32 * WK];
     __shared__ int odd_tile[2];                              // the streamed rows hold an infinity or NaN
@@ -394,7 +393,8 @@ psf_status side_launch(const Problem &pb, const F32Plan &pl, const float *MQ, co
             PSF_LAUNCH_CHECK();
             return PSF_OK;
         };
-        return f32_deal<DT, RT == 4 && sizeof(T) == 4>(pb, pl, RT, 70, go);
+        constexpr bool PARTS4 = RT == 4 && sizeof(T) == 4;
+        return f32_deal<DT, !PARTS4, !PARTS4>(pb, pl, RT, 70, go);
     });
 }
 

@@ -268,33 +268,36 @@ __device__ __forceinline__ void finish_row(const f4 (&acc)[VT], float D, bool th
 //   WR 1, WK 4: four times the workgroups
 // The sums of a staged tile are formed apart and then added to the total.
 // GRAD: instead of the output, G_i = [dO_i / D_i | -<dO_i, o_i> / D_i] for the backward pass.
-template <int DT, int RT, int WR, int WK_, typename T>
+template <int DT, int RT, int WR, int WK, typename T>
 struct RowsLds {
     static constexpr int P = parts_of<T>(), MT = RT < 2 ? 2 : RT, OP = pitch_of<RT>(), ROWS = 16 * WR;
-    static constexpr int KP = row_pitch<DT>(), VP = tr_pitch<DT>(), MP = row_pitch<MT>();
+    // (fp32 storage, r = 64: four sets only fit with narrower rows of V, which cost bank conflicts.  1024 tokens of a
+    // unit 52 us with two sets of 16 rows, 32 so; 64 rows 40.)
+    static constexpr bool TIGHT = WR == 1 && DT == 4 && MT == 4 && P == 3;
+    static constexpr int KP = row_pitch<DT>(), VP = TIGHT ? 16 * DT + 4 : tr_pitch<DT>(), MP = row_pitch<MT>();
+    static constexpr int ZP = tr_pitch<DT>();                         // rows of a state piece
     static constexpr int kRow = P * KP + P * VP + 3 * MP;             // 16-bit places of a key
-    static constexpr int WK = kRow * 2 * 32 * WK_ <= 150 * 1024 ? WK_ : WK_ / 2;
     static constexpr int kThreads = 64 * WR * WK, KT = WK == 1 ? f32_tile_rows(DT, 4) : 32 * WK;
     static constexpr int kKeys = P * KT * KP, kVals = P * KT * VP;
     static constexpr int kBuffers = WK == 4 ? 1 : 2;
-    static constexpr int kPiece = 3 * 32 * VP, kOwn = ROWS * OP * 2;  // a state piece; sketches of the rows, fp32
+    static constexpr int kPiece = 3 * 32 * ZP, kOwn = ROWS * OP * 2;  // a state piece; sketches of the rows, fp32
     static constexpr int kBack = WK * ROWS * (16 * DT + 4) * 2;       // the states' share of the rows, fp32
     static constexpr int kSums = (WK - 1) * WR * (4 * DT + 1) * 64 * 2;
     static constexpr int most(int a, int b) { return a > b ? a : b; }
     static constexpr int kPlaces = most(most(KT * kRow, kBuffers * WK * kPiece + kOwn), most(kBack, kSums));
 };
 
-template <int DT, int RT, int WR, int WK_, bool GRAD, typename T>
-__global__ __launch_bounds__((RowsLds<DT, RT, WR, WK_, T>::kThreads), WK_ == 1 && DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void f32_rows_kernel(
+template <int DT, int RT, int WR, int WK, bool GRAD, typename T>
+__global__ __launch_bounds__((RowsLds<DT, RT, WR, WK, T>::kThreads), WK == 1 && DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void f32_rows_kernel(
     const float *__restrict__ MQ, const float *__restrict__ MK, const T *__restrict__ Q, const T *__restrict__ K,
     const T *__restrict__ V, const float *__restrict__ Z, T *__restrict__ O, const T *__restrict__ dO,
     float *__restrict__ GV, float *__restrict__ gden, F32Shape sh)
 {
-    using L = RowsLds<DT, RT, WR, WK_, T>;
+    using L = RowsLds<DT, RT, WR, WK, T>;
     constexpr int VT = DT, ROWS = L::ROWS, KT = L::KT, P = L::P, MT = L::MT, KP = L::KP, VP = L::VP, MP = L::MP;
-    constexpr int WK = L::WK, THREADS = L::kThreads;
+    constexpr int THREADS = L::kThreads;
     __shared__ __attribute__((aligned(16))) uint16_t lds[L::kPlaces];
-    __shared__ __attribute__((aligned(16))) float sden[2][32 * WK];        // denominator column of a state piece
+    __shared__ __attribute__((aligned(16))) float sden[L::kBuffers][32 * WK];        // denominator column of a state piece
     __shared__ int odd_tile[2];                                       // the tile of V holds an infinity or NaN
     uint16_t *ks = lds, *vs = ks + L::kKeys, *ms = vs + L::kVals;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = lane & 15, g = lane >> 4;
@@ -321,7 +324,7 @@ __global__ __launch_bounds__((RowsLds<DT, RT, WR, WK_, T>::kThreads), WK_ == 1 &
     // from LDS serves four products of rows.  A piece is one a with 32 b' (two index tiles, the
     // first of which holds zeros where it lies left of the diagonal).
     if (sh.states && (sh.noncausal || span > 0)) {
-        constexpr int KS = MT / 2, C = VT / WR, H = WR, OP = L::OP, CP = 16 * VT, CH = CP / 8;
+        constexpr int KS = MT / 2, ZP = L::ZP, C = VT / WR, H = WR, OP = L::OP, CP = 16 * VT, CH = CP / 8;
         const float *z = Z + ((size_t)u * sh.spans + (sh.noncausal ? 0 : span)) * record_floats(RT, VT);
         const float *zs = z + record_values(RT, VT) / 2 * 3;
         constexpr int NP = 32 * CH * WK / THREADS;
@@ -350,7 +353,7 @@ __global__ __launch_bounds__((RowsLds<DT, RT, WR, WK_, T>::kThreads), WK_ == 1 &
 #pragma unroll
             for (int k = 0; k < NP; ++k) {
                 const int idx = k * THREADS + threadIdx.x;
-                pre[k].store(lds + (buf * WK + idx / (32 * CH)) * L::kPiece + (idx / CH % 32) * VP + 8 * (idx % CH), 32 * VP);
+                pre[k].store(lds + (buf * WK + idx / (32 * CH)) * L::kPiece + (idx / CH % 32) * ZP + 8 * (idx % CH), 32 * ZP);
             }
         };
         fetch();
@@ -401,7 +404,7 @@ __global__ __launch_bounds__((RowsLds<DT, RT, WR, WK_, T>::kThreads), WK_ == 1 &
                     Parts<3> zp;
 #pragma unroll
                     for (int i = 0; i < 3; ++i)
-                        zp.v[i] = read_rows_tr(lds + (buf * WK + wk) * L::kPiece + i * 32 * VP, VP, 16 * (C * wr + c), lane);
+                        zp.v[i] = read_rows_tr(lds + (buf * WK + wk) * L::kPiece + i * 32 * ZP, ZP, 16 * (C * wr + c), lane);
                     mm_rows(zp, mb, k, ta + H * c);
                 }
                 settle_parts();                             // (the step may be left out)
@@ -620,7 +623,8 @@ psf_status rows_launch(const Problem &pb, const F32Plan &pl, const float *MQ, co
             PSF_LAUNCH_CHECK();
             return PSF_OK;
         };
-        return f32_deal<DT, RT == 4 && sizeof(T) == 4>(pb, pl, RT, sizeof(T) == 2 && RT <= 2 ? 110 : 70, go);
+        constexpr bool PARTS4 = RT == 4 && sizeof(T) == 4;
+        return f32_deal<DT, true, !PARTS4>(pb, pl, RT, PARTS4 ? 50 : sizeof(T) == 2 && RT <= 2 ? 110 : 70, go);
     });
 }
 

@@ -15,7 +15,7 @@ MOST = 32                                                # bytes a lane
 
 
 @pytest.mark.skipif(not os.path.exists(READELF), reason="no reader of the metadata")
-@pytest.mark.parametrize("kernel,variants", [("f32_bwd_kernel", 32), ("f32_rows_kernel", 32)])
+@pytest.mark.parametrize("kernel,variants", [("f32_bwd_kernel", 32), ("f32_rows_kernel", 34)])
 def test_scratch_of_narrow_kernels(tmp_path, kernel, variants):
     if not os.path.exists(lib_build.LIB):
         lib_build.build()
