@@ -88,6 +88,9 @@ static inline psf_status with_tiles(const Problem &pb, F f)
     return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 8>{});
 }
 
+// Blocks of 64 keys that applying a state of rt tiles to 64 rows is worth, by its products.
+static inline double state_walk(int rt) { return rt == 1 ? 4 : rt == 2 ? 8 : rt == 4 ? 24 : 88; }
+
 // How the kernels of rows share out the work: f(WR, WK), see psf_f32_fwd.hip.  By row_walks(), W: what counts is for
 // how long how many CUs are busy.  Four sets of waves have a chain half as long as two, and two half as long as
 // one.  But the former take 16 rows a workgroup instead of 64 and stage every key four times as often:
@@ -108,8 +111,7 @@ static inline psf_status f32_deal(const Problem &pb, const F32Plan &pl, int rt, 
     using std::integral_constant;
     if constexpr (DT == 4) {
         const int per_span = ((pl.span < pb.n ? pl.span : pb.n) + 63) / 64;
-        const double walks = row_walks(pb.units, pl.spans, per_span, !pl.noncausal,
-                                       !pl.states ? 0 : rt == 4 ? 24 : 4 * rt);
+        const double walks = row_walks(pb.units, pl.spans, per_span, !pl.noncausal, pl.states ? state_walk(rt) : 0);
         if constexpr (FOUR)
             if (walks < few) return f(integral_constant<int, 1>{}, integral_constant<int, 4>{});
         if constexpr (ONE)

@@ -645,33 +645,38 @@ F32Shape f32_shape(const Problem &pb, const F32Plan &pl)
     return sh;
 }
 
-// Where the states lie.  Costs in seconds of the whole chip, relative to each other: states at 90
-// TFLOP/s, pairs at 65, state traffic at 4 TB/s, 5 us for the two further launches: forming a record and
-// applying it against the pairs that a longer span takes directly.  (Rates of the fp32 matrix
-// instructions; the products from parts are faster by about the same factor on both sides.)
+// Where the states lie.  Costs in seconds of the whole chip, relative to each other (wide tiles in brackets):
+// forming and applying states at 90 (80) TFLOP/s, pairs at 75 (60), with the rows that a span is padded to 64 with;
+// state traffic at 4 TB/s; 7 us for two further launches, 14 for the four of a backward call; and the longest walk of a workgroup, 1 (1.5)
+// us a block of 64 keys where r + dv = 128, which is what a call of few rows takes.
 // Measured with every span forced (blocks a span: us of a forward call, of a forward and a backward call;
-// * the plan's choice; two runs of one span differ by up to 5 %):
-//   36 units x 3000, r 32, b 200   1: 266, 1110   2: 233*, 1010*   4: 224, 1001   8: 250, 1207   all 15: 224, 1249
-//   24 x 1950, r 32, b 150         1: 87, 448     2: 112, 491*     4: 119, 525    8: 119, 545    all 13: 86*, 453
-//   12 x 16384, r 32, b 64         1: 843, 2965   4: 412, 1780*    8: 366*, 1707  16: -          all: 1496, 9796
-//   24 x 8000, r 64, b 250         1: 1327, 4979  2: 1154, 4545*   4: 1059*, 4481 8: 1098, 4940  all 32: 1154, 6614
-//   48 x 8192, r 16, b 256, fp32   1: 607, 2553   2: 642*, 2825*   4: 788, 3656   8: 1115, 5048
-//   12 x 2600, r 64, b 100         1: 390, 1414   2: 296, 1181     4: 240, 926    8: 255, 1009   all 26: 111*, 526*
+// * the plan's own choice; bf16 storage where nothing is said):
+//   36 units x 3000, r 32, b 200   1: 226, 1056    2: 199, 936*    4: 188*, 933   8: 222, 1171   all 15: 185, 1163
+//   24 x 1950, r 32, b 150         1: 128, 535     2: 105, 473     4: 113, 524    8: 116, 543    all 13: 82*, 441*
+//   12 x 8192, r 32, b 64          1: 435, 1542    2: 232, 994     4: 188*, 861*  8: 188, 872    all 128: 412
+//   24 x 8000, r 64, b 250         1: 1334, 4939   2: 1158, 4546   4: 1065*, 4434* 8: 1102, 4885 all 32: 1139, 6352
+//   48 x 8192, r 16, b 256, fp32   1: 585*, 2383*  2: 616, 2629    4: 758, 3344   8: 1077, 4868
+//   3 x 2048, r 16, b 256, fp32    1: 44*, 179*    2: 59, 229      4: 80, 306     all 8: 57, 258
+//   36 x 3000, r 64, b 200         1: 869, 3229    2: 686, 2694    4: 542, 2250   8: 511, 2224   all 15: 272*, 1519*
+// Over 230 such calls (r 16 to 128, d 64 and 128, 1 to 48 units, both storage types) the choice is within 2 % of the best
+// one in the mean; it misses most where few rows make a call short (1 unit x 1024 to 3 x 2048: up to a third).
 // z_floats: room for state records.
 static F32Plan f32_plan(const Problem &pb, size_t z_floats, bool noncausal, bool grad)
 {
     const bool wide = pb.d > 64 || pb.dv > 64 || pb.mcols > 64;
     int rt = 0, vt = wide ? 8 : 4;
     with_tiles(pb, [&](auto, auto r) -> psf_status { rt = decltype(r)::value; return PSF_OK; });
-    const double tokens = (double)pb.units * pb.n, rate = 90e12, pair_rate = 65e12, bw = 4e12;
+    const double tokens = (double)pb.units * pb.n, bw = 4e12;
+    const double rate = wide ? 80e12 : 90e12, pair_rate = wide ? 60e12 : 75e12;
     const size_t rec = record_floats(rt, vt);
     const double state_flops = tile_pairs(rt) * 256.0 * 16 * vt * 2 * (grad ? 6 : 2);
     const double pair_flops = 2.0 * 16 * (grad ? 5 * rt + 4 * vt : rt + vt);
     const double traffic = (grad ? 9 : 4) * (rt * (rt + 1) / 2) * 256.0 * (16 * vt + 1) * 4;    // bytes a record
+    const double step = (wide ? 1.5e-6 : 1e-6) * (rt + vt) / 8 * (grad ? 3 : 1);                // of the longest walk
     F32Plan best = {};
     if (noncausal) {
-        const double direct = tokens * pb.n * pair_flops / pair_rate;
-        const double with_state = tokens * state_flops / rate + 10e-6;
+        const double direct = tokens * pb.n * pair_flops / pair_rate + step * ((pb.n + 63) / 64);
+        const double with_state = tokens * state_flops / rate + 12e-6 + step * state_walk(rt);
         // spans only split the sum over the tokens: enough workgroups to fill the chip
         int spans = (int)((2048 + (long long)pb.units * 4 * rt - 1) / ((long long)pb.units * 4 * rt));
         if (spans > pb.n / 256) spans = pb.n / 256;
@@ -692,13 +697,13 @@ static F32Plan f32_plan(const Problem &pb, size_t z_floats, bool noncausal, bool
     }
     for (int s = 1;; s *= 2) {
         if (s > pb.t) s = pb.t;
-        const int spans = (pb.t + s - 1) / s;
-        const double span = (double)s * pb.b;
+        const int spans = (pb.t + s - 1) / s, span = (long long)s * pb.b < pb.n ? s * pb.b : pb.n;
         if (spans == 1 || (size_t)spans * pb.units * rec <= z_floats) {
-            double cost = tokens * (span < pb.n ? span : pb.n) / 2 * pair_flops / pair_rate;
+            const double blocks = (span + 63) / 64, padded = blocks * 64 / span;
+            double cost = padded * tokens * span / 2 * pair_flops / pair_rate + step * blocks;
             if (spans > 1)
-                cost += tokens * (1.0 - 1.0 / spans) * state_flops / rate +
-                        (double)pb.units * spans * traffic / bw + (grad ? 10e-6 : 5e-6);
+                cost += (1 + padded) / 2 * tokens * (1.0 - 1.0 / spans) * state_flops / rate +
+                        (double)pb.units * spans * traffic / bw + (grad ? 14e-6 : 7e-6) + step * state_walk(rt);
             if (best.spans == 0 || cost < best.cost) {
                 best.cost = cost;
                 best.span = s * pb.b; best.spans = spans; best.pairs = 1; best.states = spans > 1;
@@ -719,15 +724,16 @@ static size_t plan_floats(const Problem &pb, const F32Plan &pl)
     return pl.states ? (size_t)pb.units * pl.spans * rec : 0;
 }
 
-// Records are padded to tiles (16 sketch indices, 64 or 128 value columns), the room of the vector
-// kernels, t F (dv + 1) floats a unit, is not: with few or small blocks (t mcols^2 (dv + 1) below the
-// record's floats) no record fits, and pairs alone cost time quadratic in n.  Where that room
-// makes the plan dearer than the best one by more than a quarter, the workspace grows to the
-// best plan's records (at most kMostRoom, 1.5 GiB, and not past the library's static scratch where the
-// call fitted it).  If that does not bring the cost within four times the best one, the vector
-// kernels take the call, whose time is linear.  Measured, without a mask, r = 8, d = 128, dv = 16, two
-// blocks (us; pairs, best plan, vector kernels): 12 units x 4096 1274, 272, 714; 12 x 16384 20429, 1050,
-// 2487; 96 x 16384 165250, 7607, 10294.  Below 1.25 nothing is to be gained (96 x 1024: 687, 687, 750).
+// Records are padded to tiles (16 sketch indices, 64 or 128 value columns) and hold three bf16 parts a value; the
+// room of the vector kernels, t F (dv + 1) floats a unit, is neither.  Few or small blocks find no room for any record
+// (pairs alone cost time quadratic in n), r = 16 and 32 none for one a block.  Where that room makes the plan
+// dearer than the best one the workspace grows to the best plan's records (at most kMostRoom, 1.5 GiB, and not past
+// the library's static scratch where the call fitted it).  If that does not bring the cost
+// within four times the best one, the vector kernels take the call, whose time is linear.  Measured, without a
+// mask, r = 8, d = 128, dv = 16, two blocks (us; pairs, best plan, vector kernels): 12 units x 4096 1274, 272, 714;
+// 12 x 16384 20429, 1050, 2487; 96 x 16384 165250, 7607, 10294.  A state for two blocks instead of each, r = 16, b =
+// 256, 48 x 8192: 616 against 585 us, with the backward pass 2629 against 2383; below 4 % or 1.5 us of modelled
+// loss nothing is to be gained.
 F32Choice f32_choose(const Problem &pb, size_t fixed_bytes, bool noncausal, bool grad)
 {
     constexpr size_t kMostRoom = ((size_t)3 << 29) / sizeof(float);
@@ -738,7 +744,7 @@ F32Choice f32_choose(const Problem &pb, size_t fixed_bytes, bool noncausal, bool
     c.plan = f32_plan(pb, c.z_floats, noncausal, grad);
     const F32Plan most = f32_plan(pb, SIZE_MAX, noncausal, grad);
     const double best = most.cost;
-    if (c.plan.cost <= 1.25 * best && !(noncausal && most.states && c.plan.spans < most.spans)) return c;
+    if (c.plan.cost <= 1.04 * best + 1.5e-6 && !(noncausal && most.states && c.plan.spans < most.spans)) return c;
     size_t room = kMostRoom;
     if (!noncausal && !grad && fixed_bytes + align_up(c.z_floats * 4, 256) <= PSF_STATIC_SCRATCH_BYTES)
         room = (PSF_STATIC_SCRATCH_BYTES - fixed_bytes) / 256 * 256 / sizeof(float);

@@ -64,3 +64,12 @@ def test_where_the_static_scratch_leaves_no_room_the_vector_kernels_stay():
     assert m + z <= STATIC
     assert psf.workspace_bytes(desc) <= STATIC
     assert psf.general_spans(desc, 0) == -1 and psf.general_spans(desc, 2) >= 4
+
+
+@pytest.mark.parametrize("units,n,r,b", [(48, 8192, 16, 256), (24, 8192, 32, 512), (24, 8000, 16, 250)])
+def test_narrow_sketches_keep_a_state_for_every_block(units, n, r, b):
+    # a record is half as large again as the vector kernels' state (its values are three bf16 parts); two
+    # blocks a span cost a tenth of the forward call and a sixth of the backward call more
+    desc = psf.make_desc(1, units, n, 64, 4, r, b, "f32")
+    for which in (0, 2):
+        assert psf.general_spans(desc, which) == n // b, which
