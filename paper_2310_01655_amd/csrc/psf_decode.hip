@@ -741,8 +741,9 @@ __global__ __launch_bounds__(kThreads) void dec_fold_kernel(float *__restrict__ 
 // so that a lane's eight tokens of one column are neighbours.
 //
 // Bound by LDS reads, the vector work of the fragments and, with few tokens, the state's own traffic (us, 768
-// units of r = d = 64, 1024 tokens: 819 -> 669; 192 of d = 128, 512 tokens: 835 -> 213; 12 of d = 64: 56 -> 47; 768 of
-// r = 32, 256 tokens: 87 -> 92): single values stored column by column met 4-way bank conflicts, and branches on
+// units of r = d = 64, 1024 tokens: 812 -> 618, 256: 383 -> 367; 96 of d = 128, 512 tokens: 423 -> 101; 768 of r = 32,
+// 1024, 256 and 48 tokens: 204 -> 197, 86.5 -> 87.5, 61 -> 64: a chunk alone takes no advantage of the second buffer
+// and waits a little longer for its rows): single values stored column by column met 4-way bank conflicts, and branches on
 // a wave's number of rows and on the end of the tokens kept loads and products in order.
 // `count` tokens of unit u come from msrc + u m_unit (fp32 sketches) and vsrc + u v_unit (values): the
 // unit's block cache, or a prompt's sketches and its values in place.  slices > 1: each slice of the
@@ -779,14 +780,22 @@ __global__ __launch_bounds__(kThreads, 2) void dec_fold_mfma_kernel(float *state
     constexpr int GROUPS = MC / NA;
     int wg = blockIdx.x;
     if ((gridDim.x & 7) == 0) wg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    const int u = wg / GROUPS / slices, slice = wg / GROUPS % slices, a0 = (wg % GROUPS) * NA;
+    int u = wg / GROUPS, slice = 0;
+    const int a0 = (wg % GROUPS) * NA;
+    if (slices > 1) {
+        slice = u % slices;
+        u /= slices;
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int x = lane & 31, h = lane >> 5;
     float *su = state + (size_t)u * L.per_unit;
-    const int chunks = (count + TOK - 1) / TOK;
-    const int first = (int)((long long)chunks * slice / slices) * TOK;
-    const int last = min(count, (int)((long long)chunks * (slice + 1) / slices) * TOK);
+    int first = 0, last = count;
+    if (slices > 1) {                                       // chunks * slices < 2^30
+        const unsigned chunks = (count + TOK - 1) / TOK;
+        first = (int)(chunks * slice / slices) * TOK;
+        last = min(count, (int)(chunks * (slice + 1) / slices) * TOK);
+    }
     // this wave's items: rows a0 + row0 .. + rpw - 1 of range bt
     const int bt_min = a0 / 32, nb_act = NB - bt_min;
     const int rpw = NA * nb_act / 4;                         // 1 .. IPW
