@@ -1,12 +1,13 @@
 """The kernels that form fp32 products from bf16 parts, at every way of sharing out the rows and either
 storage type: a token's infinity or NaN stays out of the rows before it and arrives in its own, forward
-and backward, and is finite everywhere else; and values whose parts are far apart.  Reference: the
+and backward, and is finite everywhere else; and every part of every operand counts.  References: the
 same call without the odd token (rows before it), plain torch in float64."""
 import pytest
 import torch
 
 from paper_2310_01655_amd import binding as psf
 from paper_2310_01655_amd import inputs
+from test_gpu_f32_states import reference
 
 pytestmark = pytest.mark.gpu
 
@@ -51,9 +52,47 @@ def test_an_infinite_value_stays_in_its_place(heads, n, b, dtype):
     assert same(dq[:, :, rows], grads[0][:, :, rows], dtype) and not dv[:, :, at, 3].isfinite().any()
 
 
-@pytest.mark.parametrize("scale", [2.0 ** -40, 1.0, 2.0 ** 30])
-def test_values_of_any_size_keep_24_bits(scale):
-    # V enters linearly: scaled by a power of two, every output is scaled by it, to the bit
+def cut(x):
+    """x without its third part: 16 to 17 of its 24 bits."""
+    h = (x.view(torch.int32) & -65536).view(torch.float32)
+    return h + (x - h).bfloat16().float()
+
+
+@pytest.mark.parametrize("heads,n,r,b", [(3, 330, 16, 110), (2, 3024, 16, 48), (5, 3131, 32, 101), (2, 4650, 64, 150)])
+def test_every_part_counts(heads, n, r, b):
+    """Rows of V, and columns of Q and K, over many binades.  Bound: fp32 sums err by 3e-7 to 6e-7 here; without its
+    third part an operand is off by 2^-18.5 = 2.7e-6 in the mean, which the float64 evaluation of cut operands
+    shows to be visible in some result of this case for each of Q, K, V, G and dO."""
+    q, k, v = (x.cuda() for x in inputs.make_qkv(1, heads, n, 64, seed=9, dtype="f32"))
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4)
+    binades = lambda *shape: torch.randint(-6, 7, shape, generator=g, device="cuda").float().exp2()
+    v = v * binades(1, heads, n, 1)
+    q, k = ((x * c) / (x * c).norm(dim=-1, keepdim=True) for x, c in ((q, binades(64)), (k, binades(64))))
+    G = inputs.make_sketch_matrices(heads, 64, r, 4, per_head=True, seed=3, dtype="f32").cuda()
+    dO = inputs.make_dout(1, heads, n, 64, seed=9, dtype="f32").cuda()
+    desc = psf.make_desc(1, heads, n, 64, 4, r, b, "f32", per_head=True)
+    assert psf.kernel_path(desc) == 0
+    got = [psf.psf_causal_attn_fwd(desc, q, k, v, G), psf.psf_noncausal_attn_fwd(desc, q, k, v, G),
+           *psf.psf_causal_attn_bwd(desc, q, k, v, G, dO)]
+    u = heads - 1
+    operands = [q[0, u], k[0, u], v[0, u], G[u], dO[0, u]]
+    want = reference(*operands, 4, r, b)
+
+    def far(results):
+        return [float((x.double() - w).norm() / w.norm()) for x, w in zip(results, want)]
+
+    bound = 1e-6
+    assert max(far([x[0, u] for x in got])) <= bound, far([x[0, u] for x in got])
+    for i in range(5):
+        changed = [cut(x) if i == j else x for j, x in enumerate(operands)]
+        assert max(far(reference(*changed, 4, r, b))) > 1.5 * bound, i
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -40, 2.0 ** 30])
+def test_small_and_large_values_scale(scale):
+    # V enters linearly: scaled by a power of two, every output is scaled by it, to the bit, and no part
+    # leaves bf16's range
     heads, n = 3, 330
     q, k, v = (x.cuda() for x in inputs.make_qkv(1, heads, n, 64, seed=9, dtype="f32"))
     G = inputs.make_sketch_matrices(heads, 64, 16, 4, per_head=True, seed=3, dtype="f32").cuda()

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 CASES = [
     # heads, n, d, p, r, b; errors of O, dQ, dK, dV on the vector kernels
     (2, 2400, 128, 8, 32, 240, (9.78e-7, 8.03e-7, 6.75e-7, 6.00e-7)),       # long sums over 128 columns, 8th powers
-    (12, 3000, 64, 4, 64, 200, (1.62e-6, 4.66e-7, 4.24e-7, 3.62e-7)),       # 64 rows a workgroup, 15 blocks
+    (12, 3000, 64, 4, 64, 200, (1.62e-6, 4.66e-7, 4.24e-7, 3.62e-7)),       # 15 blocks
     (30, 1200, 64, 2, 64, 48, (1.36e-6, 2.41e-7, 2.36e-7, 2.18e-7)),        # m(x) = x, pairs across 25 blocks
     (30, 1200, 64, 4, 32, 48, (8.54e-7, 3.96e-7, 3.39e-7, 3.18e-7)),
 ]

@@ -1,6 +1,6 @@
 """Every instance of the fp32 matrix-core kernels that forms and applies states: sketch widths of 1, 2, 4
-and 8 tiles, narrow and wide heads, 16 and 64 rows a workgroup, forward, without a mask and backward,
-with an odd number of blocks so that the last span is shorter.  The plan is asserted, so that a case
+and 8 tiles, narrow and wide heads, forward, without a mask and backward (the ways of sharing out the
+rows: test_gpu_f32_deals.py), with an odd number of blocks so that the last span is shorter.  The plan is asserted, so that a case
 that stops reaching the states is noticed.  Reference: plain torch in float64, the last unit.
 Bounds: fp32 sums err by 3e-7 to 1e-6 here, a rounding to bf16 by 1.7e-3."""
 import pytest
@@ -13,13 +13,13 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # heads, n, d, dv, r, p, b, dtype
-    (2, 3024, 64, 64, 16, 4, 48, "f32"),         # 1 tile, 16 rows a workgroup
-    (40, 1189, 64, 64, 16, 4, 29, "f32"),        # 1 tile, 64 rows
+    (2, 3024, 64, 64, 16, 4, 48, "f32"),         # 1 tile
+    (40, 1189, 64, 64, 16, 4, 29, "f32"),        # 1 tile, many units
     (40, 1350, 64, 64, 16, 4, 150, "bf16"),
-    (6, 3150, 64, 60, 30, 4, 150, "f32"),        # 2 tiles, 16 rows
-    (40, 2987, 64, 64, 32, 4, 29, "f32"),        # 2 tiles, 64 rows
-    (1, 5555, 64, 40, 50, 4, 101, "f32"),        # 4 tiles, 16 rows
-    (9, 4545, 64, 64, 64, 4, 101, "f32"),        # 4 tiles, 64 rows
+    (6, 3150, 64, 60, 30, 4, 150, "f32"),        # 2 tiles
+    (40, 2987, 64, 64, 32, 4, 29, "f32"),        # 2 tiles, many units
+    (1, 5555, 64, 40, 50, 4, 101, "f32"),        # 4 tiles, few units
+    (9, 4545, 64, 64, 64, 4, 101, "f32"),        # 4 tiles
     (2, 2929, 128, 64, 32, 8, 101, "f32"),       # wide, no value columns for the second workgroup
     (1, 3219, 66, 127, 17, 4, 29, "f32"),        # wide in the values, widths that four does not divide
     (1, 5959, 128, 32, 60, 4, 101, "f32"),       # wide, 4 tiles

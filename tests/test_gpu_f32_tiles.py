@@ -1,6 +1,6 @@
 """The fp32 matrix-core kernels of the general path at the edges of their tiles: sketch and head
 widths around multiples of 16 and 64, blocks around 16 and 64 tokens, last tiles with one row,
-spans with and without states, either split of the rows.  Against the float64 oracle with the
+spans with and without states.  Against the float64 oracle with the
 bounds of parity.py (1e-4 for fp32 storage; sums of non-negative fp32 terms err by about 1e-6)."""
 import numpy as np
 import pytest
@@ -15,14 +15,14 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # batch, heads, n, d, dv, p, r, b, dtype, local
-    (1, 2, 2046, 64, 64, 4, 16, 66, "f32", psf.LOCAL_EXACT),       # many spans, 16 rows a workgroup
+    (1, 2, 2046, 64, 64, 4, 16, 66, "f32", psf.LOCAL_EXACT),       # many spans
     (2, 3, 1040, 64, 64, 4, 17, 65, "f32", psf.LOCAL_EXACT),       # a sketch tile with one column
     (1, 1, 2400, 60, 62, 4, 33, 48, "bf16", psf.LOCAL_EXACT),      # widths that four does not divide
     (1, 2, 2040, 65, 64, 4, 16, 120, "f32", psf.LOCAL_EXACT),      # wide tiles, one column over
     (1, 1, 1530, 128, 128, 8, 32, 255, "f32", psf.LOCAL_SKETCH),
     (1, 1, 2600, 100, 128, 2, 100, 100, "f32", psf.LOCAL_EXACT),     # m(x) = x, 100 columns
     (1, 1, 390, 128, 128, 16, 128, 130, "bf16", psf.LOCAL_EXACT),  # largest sizes, three levels
-    (40, 14, 66, 16, 8, 4, 8, 33, "f32", psf.LOCAL_EXACT),         # 64 rows a workgroup, tiny sequences
+    (40, 14, 66, 16, 8, 4, 8, 33, "f32", psf.LOCAL_EXACT),         # many tiny sequences
     (16, 34, 65, 128, 16, 4, 16, 65, "bf16", psf.LOCAL_EXACT),
     (1, 1, 1, 64, 64, 4, 32, 1, "f32", psf.LOCAL_EXACT),
     (1, 2, 1300, 64, 64, 4, 32, 13, "f32", psf.LOCAL_SKETCH),
