@@ -28,7 +28,7 @@ struct F32Choice {
 };
 
 // rows of a staged tile: 64, or 32 where three tiles of 128 columns would leave a CU one workgroup
-constexpr int f32_tile_rows(int dt, int wr) { return dt == 8 && wr == 4 ? 32 : 64; }
+constexpr int f32_tile_rows(int dt) { return dt == 8 ? 32 : 64; }
 
 bool f32_supported(const Problem &pb);
 // fixed_bytes: the rest of the call's workspace; grad: the backward pass

@@ -11,9 +11,9 @@
 // f32_plan() chooses the span.
 //
 // Measured (us a call, forward / forward and backward; vector kernels, products by
-// v_mfma_f32_16x16x4_f32, now): 36 units of 3000 tokens, r = 32, b = 200, bf16 storage 8540, 361, 235;
-// 24 units of 1950, b = 150, forward and backward 26940, 772, 473; one unit of 1024, r = 16, fp32
-// storage 248, 33, 33.
+// v_mfma_f32_16x16x4_f32, now): 36 units of 3000 tokens, r = 32, b = 200, bf16 storage 8540, 361, 190;
+// 24 units of 1950, b = 150, forward and backward 26940, 772, 450; one unit of 1024, r = 16, fp32
+// storage 248, 33, 32.
 #include "psf_parts.h"
 #include "psf_f32.h"
 
@@ -277,7 +277,7 @@ struct RowsLds {
     static constexpr int KP = row_pitch<DT>(), VP = TIGHT ? 16 * DT + 4 : tr_pitch<DT>(), MP = row_pitch<MT>();
     static constexpr int ZP = tr_pitch<DT>();                         // rows of a state piece
     static constexpr int kRow = P * KP + P * VP + 3 * MP;             // 16-bit places of a key
-    static constexpr int kThreads = 64 * WR * WK, KT = WK == 1 ? f32_tile_rows(DT, 4) : 32 * WK;
+    static constexpr int kThreads = 64 * WR * WK, KT = WK == 1 ? f32_tile_rows(DT) : 32 * WK;
     static constexpr int kKeys = P * KT * KP, kVals = P * KT * VP;
     static constexpr int kBuffers = WK == 4 ? 1 : 2;
     static constexpr int kPiece = 3 * 32 * ZP, kOwn = ROWS * OP * 2;  // a state piece; sketches of the rows, fp32

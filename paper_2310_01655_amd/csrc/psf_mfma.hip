@@ -2685,7 +2685,8 @@ psf_status launch_state(const Problem &pb, const float *M8, const bf16_t *V8, bf
                 // Four tiles a wave: the operands of a step, five LDS reads, serve eight products instead
                 // of four, and a token is staged by half as many workgroups.  Where half the workgroups
                 // still fill the chip (us, two tiles and four, 8192 tokens: 48 units 171, 210; 72: 215, 213; 96: 339,
-                // 324; 132: 380, 366; 192: 650, 631; 768: 1985, 1754).
+                // 324; 132: 380, 366; 192: 650, 631; 768: 1985, 1754; 46 registers of the wider form go through
+                // scratch, which these times contain).
                 if constexpr (R == 64)
                     hipLaunchKernelGGL((k_state<R, D, 4, true, 32, 2>), dim3(grid_sym / 2), dim3(kWg), 0, s, M8, V8,
                                        Zg, pb.n, pb.b, pb.t, pb.units);

@@ -2,6 +2,8 @@
 //
 // An fp32 value is the sum of three bf16 values: h, its upper 16 bits; m, the remainder x - h
 // (exact, at most 16 significant bits) rounded to bf16; l, what is left (exact, at most 8 bits).
+// (From 2^-110 on.  Below that l, then m, lose bits, as bf16 ends at 2^-133: all of V near 2^-112, 2^-114, 2^-118 and
+// 2^-126 gives O a relative error of 2.6e-7, 6.2e-7, 9e-6 and 2.3e-3; 2.2e-7 from 2^-110 on.)
 // h truncates, so that no finite value becomes an infinity; m rounds, so that the terms left out
 // below have no sign of their own.  A product of two such sums is formed from the six products of
 // parts down to 2^-16 of the largest (h h, h m, m h, m m, h l, l h), smallest first; what is left out is
