@@ -332,14 +332,16 @@ __device__ __forceinline__ int cache_rows_group(int wa, int nk, int dv, int nv)
     return lg <= 64 ? lg : 0;
 }
 
-// Zeroes `count` floats from p + first on, of every unit (blockIdx.y; units `stride` floats apart).  All offsets
-// of the layout are multiples of 64 floats, and the state is 16-byte aligned at least.
+// Zeroes `count` floats from p + first on, of every unit (blockIdx.y; units `stride` floats apart), and `rest_count`
+// from p + rest on.  All offsets of the layout are multiples of 64 floats, and the state is 16-byte aligned at least.
 __global__ __launch_bounds__(kThreads) void dec_zero_kernel(float *__restrict__ p, size_t first, size_t count,
-                                                            size_t stride)
+                                                            size_t stride, size_t rest, size_t rest_count)
 {
-    float4 *const to = (float4 *)(p + first + blockIdx.y * stride);
-    for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < count / 4; i += (size_t)gridDim.x * kThreads)
-        to[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 *const to = (float4 *)(p + first + blockIdx.y * stride), *const to2 = (float4 *)(p + rest);
+    const size_t step = (size_t)gridDim.x * kThreads, i0 = (size_t)blockIdx.x * kThreads + threadIdx.x;
+    for (size_t i = i0; i < count / 4; i += step) to[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (size_t i = blockIdx.y * step + i0; i < rest_count / 4; i += gridDim.y * step)
+        to2[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
 // part[u][s][c] = the share of slice s in row [N | S] of the new token:
@@ -1255,16 +1257,15 @@ static psf_status zero_state(const Problem &pb, float *state, bool prefix, hipSt
 {
     const DecodeLayout L = decode_layout(pb);
     if (prefix) {
-        hipLaunchKernelGGL(dec_zero_kernel, dim3(2048), dim3(kThreads), 0, s, state, (size_t)0, L.total, (size_t)0);
+        hipLaunchKernelGGL(dec_zero_kernel, dim3(2048), dim3(kThreads), 0, s, state, (size_t)0, L.total, (size_t)0,
+                           (size_t)0, (size_t)0);
         PSF_LAUNCH_CHECK();
         return PSF_OK;
     }
     const size_t cache = L.per_unit - L.ck;
     const unsigned grid = (unsigned)std::max<size_t>(1, std::min<size_t>(2048 / (size_t)pb.units, cache / 4 / kThreads));
     hipLaunchKernelGGL(dec_zero_kernel, dim3(grid, (unsigned)pb.units), dim3(kThreads), 0, s, state, L.ck, cache,
-                       L.per_unit);
-    PSF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(dec_zero_kernel, dim3(16), dim3(kThreads), 0, s, state, L.mq, L.total - L.mq, (size_t)0);
+                       L.per_unit, L.mq, L.total - L.mq);
     PSF_LAUNCH_CHECK();
     return PSF_OK;
 }
