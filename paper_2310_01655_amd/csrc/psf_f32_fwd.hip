@@ -191,7 +191,7 @@ __global__ __launch_bounds__(kF32Threads, RT <= 2 ? 2 : 1) void f32_state_kernel
 // values leave as parts (see tile_pairs).  A thread takes eight columns, or four entries of the
 // denominator column, of all spans.  Bound by the latency of a step where units are few and spans many: the next four
 // records are loaded before these four are written, so that a thread waits once for four of them, and a workgroup is a
-// wave (6 units x 32256, r = 16, 126 spans, fp32: the call 343 -> 328 us; 326 with fp32 records).
+// wave (6 units x 32256, r = 16, 126 spans, fp32: the call 357 -> 337 us; 332 with fp32 records).
 // The record that an exclusive sum never reads (the last, or the first) need not be there.
 enum { kScanPrefix = 0, kScanSuffix = 1, kScanTotal = 2 };
 constexpr int kScanThreads = 64;                            // few units: as many CUs as there are waves
