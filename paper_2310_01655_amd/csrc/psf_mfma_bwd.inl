@@ -148,80 +148,6 @@ __global__ __launch_bounds__(kWg) void k_bwd_qoct(const bf16_t *__restrict__ MQ,
         }
 }
 
-// ---- state snapshots re-laid for the gradient ------------------------------------------------
-// In:  Zs [snap][a][b'/8][c][8], the format the state kernel writes (b' > a doubled, b' = a once,
-//      b' < a zero).  Out: ZT [snap][b][c/8][e][8] = 2 Z[e][b][c], twice the full symmetric state
-//      (so only the diagonal needs arithmetic) with the value column as the contraction octet and
-//      the free sketch index e as the row of an MFMA A operand.  Workgroup = (octet of b, snapshot).
-// DC value columns per workgroup (blockIdx.z picks the range): D = 128 goes in two halves so that
-// two workgroups fit a CU.
-// A thread takes 8 x 8 blocks (eight value columns of one row and octet, 128 bytes), turns them round in
-// registers and stores whole octets; the LDS tile only puts the rows e in order for the stores to memory.
-// Bound by memory since (744 snapshots of r = d = 64: 205 -> 132 us, 4.4 TB/s; d = 128: 225 -> 170): single
-// values into LDS, and the divisions that found their places, cost more than the traffic.
-template <int R, int D, int DC = D>
-__global__ __launch_bounds__(kWg) void k_bwd_relayout(const bf16_t *__restrict__ Zs, bf16_t *__restrict__ ZT)
-{
-    static_assert(DC == 64 && D % DC == 0, "eight column octets: the swizzle and the blocks' order");
-    // [b % 8][e][c], the 16-byte column c / 8 of row e stored at (c / 8) ^ (e % 8): the final
-    // reads walk e with a fixed column and would otherwise all hit the same banks
-    __shared__ __attribute__((aligned(16))) bf16_t F[8][R][DC];
-    const int tid = threadIdx.x, ob = blockIdx.x, c0 = blockIdx.z * DC;
-    const bf16_t *src = Zs + (size_t)blockIdx.y * R * R * D;
-    bf16_t *dst = ZT + (size_t)blockIdx.y * R * R * D;
-    constexpr int PIECES = 8 * DC * (R / 8) / kWg, BLOCKS = PIECES / 8;
-    static_assert(PIECES % 8 == 0, "whole blocks");
-    // Blocks in the order (row, column octet), all loads of a thread issued before their use:
-    //   rows e < 8 ob, octet ob (b > e there: 2 Z[e][b][c] = Zs[e][b][c])
-    //   the rest: rows a of this octet, column octets ob2 >= ob
-    const int c8 = tid % 8;
-    uint4 pk[BLOCKS][8];
-#pragma unroll
-    for (int i = 0; i < BLOCKS; ++i) {
-        const int t = (tid + i * kWg) / 8, k = t - 8 * ob;
-        const int row = k < 0 ? t : 8 * ob + k % 8, oct = k < 0 ? ob : ob + k / 8;
-        const bf16_t *from = src + (((size_t)row * (R / 8) + oct) * D + c0 + 8 * c8) * 8;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) pk[i][c] = *(const uint4 *)(from + 8 * c);
-    }
-    auto put = [&](int b8, int e, const uint4 &cols) { *(uint4 *)&F[b8][e][8 * (c8 ^ (e & 7))] = cols; };
-    auto twice = [](uint32_t two) {
-        return (uint32_t)f32_to_bf16(2.0f * bf16_to_f32((bf16_t)(two & 0xffffu))) |
-               (uint32_t)f32_to_bf16(2.0f * bf16_to_f32((bf16_t)(two >> 16))) << 16;
-    };
-#pragma unroll
-    for (int i = 0; i < BLOCKS; ++i) {
-        const int t = (tid + i * kWg) / 8, k = t - 8 * ob;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint32_t half = j % 2 ? 0x07060302u : 0x05040100u;
-            auto pair = [&](int c) {                        // column j of the block's rows c, c + 1
-                const uint32_t lo[4] = {pk[i][c].x, pk[i][c].y, pk[i][c].z, pk[i][c].w};
-                const uint32_t hi[4] = {pk[i][c + 1].x, pk[i][c + 1].y, pk[i][c + 1].z, pk[i][c + 1].w};
-                return __builtin_amdgcn_perm(hi[j / 2], lo[j / 2], half);
-            };
-            const uint4 cols = make_uint4(pair(0), pair(2), pair(4), pair(6));
-            if (k < 0) {
-                put(j, t, cols);                           // (b = 8 ob + j, e)
-            } else if (k >= 8) {
-                put(k % 8, 8 * (ob + k / 8) + j, cols);    // (b = a, e = b')
-            } else if (j > k) {                            // the diagonal octet: (b = a, e = b') and its mirror
-                put(k, 8 * ob + j, cols);
-                put(j, 8 * ob + k, cols);
-            } else if (j == k) {
-                put(k, 8 * ob + k, make_uint4(twice(cols.x), twice(cols.y), twice(cols.z), twice(cols.w)));
-            }
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < PIECES; ++i) {
-        const int idx = tid + i * kWg;
-        const int b8 = idx / ((DC / 8) * R), c8 = (idx / R) % (DC / 8), e = idx % R;
-        *(uint4 *)&dst[((((size_t)(8 * ob + b8)) * (D / 8) + c0 / 8 + c8) * R + e) * 8] = *(const uint4 *)&F[b8][e][8 * (c8 ^ (e & 7))];
-    }
-}
-
 // ---- through Algorithm 1 (p = 4), one 32-token tile of a wave --------------------------------
 // dx = dXacc (if ADD_BASE) + sqrt(1/r) [(dm * (x G2)) G1^T + (dm * (x G1)) G2^T].  lds: the transposed sketch
 // matrices as the forward sketch kernel stages them (for the recomputed projections); go: G1,
@@ -537,9 +463,167 @@ struct Cross {
     }
 };
 
+// An operand fragment whose contraction index runs across rows in LDS: every group of 16 lanes reads 4 rows x 16
+// columns of 16-bit values (lane s: row s / 4, columns 4 (s % 4) ..+3 at its address) and lane i gets column i, rows
+// 0..3 in order.  `a` gives entries 0..3 of the fragment, `b` entries 4..7.
+__device__ __forceinline__ bf16x8 read_turned(const void *a, const void *b)
+{
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    typedef __attribute__((address_space(3))) s16x4 *at;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((at)(__attribute__((address_space(3))) const void *)a);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((at)(__attribute__((address_space(3))) const void *)b);
+    return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// ---- contraction of the states with a row's gradient (or value) --------------------------------
+// dm[e] = sum_b 2 Z[e][b][.] . vec  m[b] for 32 TT tokens a wave, from the snapshots as the state kernel writes
+// them ([a][b'/8][c][8]: b' > a doubled, b' = a once, b' < a zero).  With T[a][b'] = sum_c Zs[a][b'][c] vec[c]:
+//     dm[a] += T[a][b'] m[b'],  dm[b'] += T[a][b'] m[a]   for every stored segment (a, 16 columns b'),
+// the diagonal 16 x 16 squares included (what is stored doubled meets each of the two once, what is stored
+// once meets itself twice).  vec is the fixed B operand (lane = token), so no operand is generated and
+// T stays fp32: 62 % of the products of a contraction over (b, c) pairs at r = 64, 75 % at r = 32, and 8 (D =
+// 64) or 4 (D = 128) vector instructions a product instead of 6 (r = 64) or 12 (r = 32).
+// A fragments run along c while the snapshot's octets run along b': ds_read_b64_tr_b16 turns 4 columns c x 16
+// columns b' round on the way out of LDS, so no re-laid copy of the states is needed.
+// A tile is two segments of the rows a and a + 4 and one 16-wide range of b': a lane's half of
+// the rows of T then lines up with the half of m and dm it holds (index 8 (i / 4) + 4 h + i % 4 of a range),
+// and the two halves' sums for a and a + 4 change places with one swap.  Its four planes (octets 2 beta, 2 beta + 1
+// of both rows, one per wave of the copy) lie 64 bytes apart modulo 256, so that the 16-lane groups of a
+// transposed read meet different banks.
+// The tiles stream through a ring of four chunks of G tiles, three of them in flight: with two chunks of 32 KB the
+// waves spent two fifths of their time waiting for the copies.
+template <int R, int D, int TT>
+struct StateTimesRow {
+    static constexpr int RS = R / 16, VS = D / 16, DW = D / 64;
+    static constexpr int PS = D * 16 + 64, TILE = 4 * PS;      // plane and tile in LDS
+    static constexpr int G = 4 / DW, SLOTS = 4 * G;            // tiles per chunk, of the ring
+    static constexpr int TILES = 8 * (RS * (RS + 1) / 2);
+    static constexpr int LDS_BYTES = SLOTS * TILE;
+    static_assert(LDS_BYTES <= 81920 && TILES % G == 0, "two workgroups per CU");
+    // tile it: ranges s0 of the rows in order, in each its 8 row pairs, for each the ranges beta >= s0
+    static constexpr int first_tile(int s0) { return s0 == 0 ? 0 : first_tile(s0 - 1) + 8 * (RS - s0 + 1); }
+    static constexpr int range_of(int it)
+    {
+        int s0 = 0;
+        while (s0 + 1 < RS && it >= first_tile(s0 + 1)) ++s0;
+        return s0;
+    }
+    static constexpr int pair_of(int it) { return (it - first_tile(range_of(it))) / (RS - range_of(it)); }
+    static constexpr int beta_of(int it) { return range_of(it) + (it - first_tile(range_of(it))) % (RS - range_of(it)); }
+
+    // this wave's plane of tile IT
+    template <int IT>
+    static __device__ __forceinline__ void stage(const unsigned char *__restrict__ z_wave, uint32_t lds_wave, uint32_t lane16)
+    {
+        constexpr int P = pair_of(IT), A = 16 * range_of(IT) + 8 * (P / 4) + P % 4;
+        constexpr int FROM = (A * (R / 8) + 2 * beta_of(IT)) * D * 16, TO = IT % SLOTS * TILE;
+#pragma unroll
+        for (int dw = 0; dw < DW; ++dw) dma16_sbase(z_wave + FROM + dw * 1024, lane16, lds_wave + TO + dw * 1024);
+    }
+    // where a wave's planes come from and go to
+    static __device__ __forceinline__ const unsigned char *source(const bf16_t *__restrict__ Z, int wave)
+    {
+        return (const unsigned char *)Z + (size_t)(4 * (wave / 2) * (R / 8) + wave % 2) * D * 16;
+    }
+    static __device__ __forceinline__ void stage_first(const bf16_t *__restrict__ Z, unsigned char *lds)
+    {
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        static_for<SLOTS>([&](auto it) {
+            stage<decltype(it)::value>(source(Z, wave), lds_address(lds) + wave * PS, (uint32_t)lane * 16);
+        });
+    }
+    // the products of tile IT with the row: m, dm in the order of the accumulators (index 8 range + i)
+    template <int IT>
+    static __device__ __forceinline__ void consume(const f32x16 &T, const float (&m)[8 * RS], float (&dm)[8 * RS],
+                                                   float &ma, float &mb, float &sa, float &sb)
+    {
+        constexpr int S0 = range_of(IT), BETA = beta_of(IT), P = pair_of(IT), I = 8 * S0 + P;   // I: the index of a and a + 4
+        if constexpr (BETA == S0) {
+            const uint32_t w = __float_as_uint(m[I]);
+            const auto both = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+            ma = __uint_as_float(both[0]);
+            mb = __uint_as_float(both[1]);
+            sa = sb = 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            dm[8 * BETA + i] = fmaf(T[i], ma, dm[8 * BETA + i]);
+            sa = fmaf(T[i], m[8 * BETA + i], sa);
+            dm[8 * BETA + i] = fmaf(T[8 + i], mb, dm[8 * BETA + i]);
+            sb = fmaf(T[8 + i], m[8 * BETA + i], sb);
+        }
+        if constexpr (BETA == RS - 1) {
+            const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(sa), __float_as_uint(sb), false, false);
+            dm[I] += __uint_as_float(s[0]) + __uint_as_float(s[1]);
+        }
+    }
+    // The ring's first tiles are on their way (stage_first).  vec: B operands; ends with a barrier.
+    static __device__ __forceinline__ void run(const bf16_t *__restrict__ Z, const bf16x8 (&vec)[TT][VS],
+                                               const float (&m)[TT][8 * RS], float (&dm)[TT][8 * RS], unsigned char *lds)
+    {
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int h = lane >> 5, s16 = lane & 15;
+        const unsigned char *const z_wave = source(Z, wave);
+        const uint32_t lds_wave = lds_address(lds) + wave * PS, lane16 = (uint32_t)lane * 16;
+        // (offsets of a read reach 64 KB: a base for each half of the ring)
+        const unsigned char *const lane_lo =
+            lds + (2 * ((lane >> 4) & 1) + ((s16 & 3) >> 1)) * PS + (8 * h + (s16 >> 2)) * 16 + (s16 & 1) * 8;
+        const unsigned char *const lane_hi = lane_lo + SLOTS / 2 * TILE;
+        bf16x8 af[2][VS];
+        auto load = [&](auto it_tag) {
+            constexpr int IT = decltype(it_tag)::value, SLOT = IT % SLOTS;
+            const unsigned char *base = SLOT < SLOTS / 2 ? lane_lo + SLOT * TILE : lane_hi + (SLOT - SLOTS / 2) * TILE;
+#pragma unroll
+            for (int s = 0; s < VS; ++s) af[IT & 1][s] = read_turned(base + s * 256, base + s * 256 + 64);
+        };
+        // chunk c has landed for every wave, and nobody reads the chunk before it any more
+        auto next_chunk = [&](auto left_tag) {
+            wait_vmem_le<decltype(left_tag)::value>();
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        };
+        next_chunk(std::integral_constant<int, (SLOTS - G) * DW>{});
+        load(std::integral_constant<int, 0>{});
+        float ma[TT], mb[TT], sa[TT], sb[TT];
+        f32x16 T[2];
+        static_for<TILES>([&](auto it_tag) {
+            constexpr int IT = decltype(it_tag)::value;
+            if constexpr (IT % G == G - 1 && IT + 1 < TILES) {
+                constexpr int ISSUED = IT + 3 * G + 1 < SLOTS ? SLOTS : (IT + 3 * G + 1 < TILES ? IT + 3 * G + 1 : TILES);
+                constexpr int LEFT = ISSUED - (IT + 1 + G);
+                next_chunk(std::integral_constant<int, (LEFT > 0 ? LEFT : 0) * DW>{});
+            }
+            constexpr int COPY = IT + 3 * G + 1;               // the slot this tile's chunk before left
+            if constexpr (COPY >= SLOTS && COPY < TILES) stage<COPY>(z_wave, lds_wave, lane16);
+            static_for<TT>([&](auto tt_tag) {
+                constexpr int tt = decltype(tt_tag)::value, Q = IT * TT + tt;
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (tt == 0 && IT + 1 < TILES) load(std::integral_constant<int, IT + 1>{});
+                f32x16 acc = {0};
+#pragma unroll
+                for (int s = 0; s < VS; ++s) acc = mfma32(af[IT & 1][s], vec[tt][s], acc);
+                // the tile before this one, under these products
+                constexpr int TP = tt > 0 ? tt - 1 : TT - 1, ITP = tt > 0 ? IT : IT - 1;
+                if constexpr (ITP >= 0) consume<ITP>(T[(Q + 1) & 1], m[TP], dm[TP], ma[TP], mb[TP], sa[TP], sb[TP]);
+                T[Q & 1] = acc;
+                if constexpr (tt == 0 && IT + 1 < TILES) __builtin_amdgcn_sched_group_barrier(0x100, 2 * VS, 0);
+#pragma unroll
+                for (int s = 0; s < VS; ++s) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 36 / VS, 0);
+                }
+            });
+        });
+        consume<TILES - 1>(T[(TILES * TT + 1) & 1], m[TT - 1], dm[TT - 1], ma[TT - 1], mb[TT - 1], sa[TT - 1], sb[TT - 1]);
+        __syncthreads();                                       // the caller may reuse the stage
+    }
+};
+
 // ---- dm(q) and dm(k): cross-block part -------------------------------------------------------
-// QSIDE: tokens of block l >= 1 with ZT / S of slot l - 1, vec = g, coefficient c_i.
-// key side: tokens of block l <= t - 2 with RT / Rc of the mirror slot t - 2 - l, vec = v,
+// QSIDE: tokens of block l >= 1 with Z / S of slot l - 1, vec = g, coefficient c_i.
+// key side: tokens of block l <= t - 2 with R / Rc of the mirror slot t - 2 - l, vec = v,
 // coefficient 1.  Blocks without a cross-block term have dm = 0.  dm stays in registers and goes
 // straight through Algorithm 1 (sketch_grad_tile): dX = bf16(dXacc + J_m(x)^T dm), with dXacc the
 // in-block part, for the rows X (Q or K) of the workgroup.
@@ -549,14 +633,14 @@ struct Cross {
 // RAW (learned sketches): dm itself is the result, fp32 rows [rows][R] in dMout (no sketch matrices).
 template <int R, int D, bool QSIDE, int TT, bool LS = false, bool RAW = false>
 __global__ __launch_bounds__(kWg, 2) void k_bwd_dm(const bf16_t *__restrict__ M, const bf16_t *__restrict__ Vec,
-                                                  const float *__restrict__ Cc, const bf16_t *__restrict__ ZT,
+                                                  const float *__restrict__ Cc, const bf16_t *__restrict__ Zs,
                                                   const bf16_t *__restrict__ Shi, const bf16_t *__restrict__ Slo,
                                                   const bf16_t *__restrict__ Xrows, const bf16_t *__restrict__ Gt,
                                                   const bf16_t *__restrict__ G, const float *__restrict__ dXacc,
                                                   bf16_t *__restrict__ dX, int n, int b, int t, int heads,
                                                   int per_head, size_t g_len, float *__restrict__ dMout = nullptr)
 {
-    using X = Cross<R, D, R, false, TT>;
+    using X = StateTimesRow<R, D, TT>;
     static_assert(RAW || sizeof(SketchLds<D, R>) + 2 * D * (R + 8) * 2 <= X::LDS_BYTES, "the sketch matrices reuse the stage");
     constexpr int AT = R / 32, RS = R / 16, VS = D / 16, TOK_WG = 128 * TT;
     __shared__ __attribute__((aligned(16))) unsigned char stage[X::LDS_BYTES];
@@ -577,17 +661,8 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_dm(const bf16_t *__restrict__ M,
 #pragma unroll
         for (int at = 0; at < AT; ++at) out[tt][at] = f32x16{0};
     if (has) {
-        f32x8 vec[TT][VS];
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-            for (int s = 0; s < VS; ++s) {
-                const bf16x8 raw = *(const bf16x8 *)&Vec[(urow + i0 + wave * 32 * TT + 32 * tt + x) * D + 16 * s + 8 * h];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) vec[tt][s][e] = (float)raw[e];
-            }
-        X::run(M + (urow + i0) * R, vec, ZT + ((size_t)u * (t - 1) + slot) * R * R * D, out, stage);
-
+        const bf16_t *z = Zs + ((size_t)u * (t - 1) + slot) * R * R * D;
+        X::stage_first(z, stage);
         // ones column: (S m)[a] per token with S as hi + lo A operands [b'/8][a][8]
         bf16x8 mfr[TT][RS];
 #pragma unroll
@@ -595,6 +670,7 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_dm(const bf16_t *__restrict__ M,
 #pragma unroll
             for (int s = 0; s < RS; ++s)
                 mfr[tt][s] = *(const bf16x8 *)&M[(urow + i0 + wave * 32 * TT + 32 * tt + x) * R + 16 * s + 8 * h];
+        float dm[TT][8 * RS], m[TT][8 * RS];                // entry 8 s + i: sketch column 16 s + 8 (i / 4) + 4 h + i % 4
         const size_t sbase = ((size_t)u * (t - 1) + slot) * R * R;
 #pragma unroll
         for (int at = 0; at < AT; ++at) {
@@ -615,9 +691,35 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_dm(const bf16_t *__restrict__ M,
             for (int tt = 0; tt < TT; ++tt) {
                 const float coef = QSIDE ? Cc[urow + i0 + wave * 32 * TT + 32 * tt + x] : 1.0f;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) out[tt][at][v] += 2.0f * coef * td[tt][v];   // the state operand is stored doubled
+                for (int v = 0; v < 16; ++v) dm[tt][16 * at + v] = 2.0f * coef * td[tt][v];   // the states count twice, too
             }
         }
+        // m in the same order: the B operands hold columns 16 s + 8 h + e, one swap per register pair
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+            for (int s = 0; s < RS; ++s) {
+                const uint4 w = __builtin_bit_cast(uint4, mfr[tt][s]);
+                const auto s0 = __builtin_amdgcn_permlane32_swap(w.x, w.z, false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(w.y, w.w, false, false);
+                const uint32_t pr[4] = {s0[0], s1[0], s0[1], s1[1]};
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    m[tt][8 * s + i] = __uint_as_float((i & 1) ? (pr[i / 2] & 0xffff0000u) : (pr[i / 2] << 16));
+            }
+        bf16x8 vec[TT][VS];
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+            for (int s = 0; s < VS; ++s)
+                vec[tt][s] = *(const bf16x8 *)&Vec[(urow + i0 + wave * 32 * TT + 32 * tt + x) * D + 16 * s + 8 * h];
+        X::run(z, vec, m, dm, stage);
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+            for (int at = 0; at < AT; ++at)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) out[tt][at][v] = dm[tt][16 * at + v];
     }
     if constexpr (RAW) {
         // register v of out[tt][at]: sketch column 32 at + 8 (v / 4) + 4 h + v % 4
@@ -1022,7 +1124,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 512 / (64 * NW) : 1) void k_bwd_
 // ---- host ---------------------------------------------------------------------------------------
 struct MfmaBwdWs {
     void *fwd;                                               // the forward workspace
-    bf16_t *O, *MK, *G_rm, *G8, *G8r, *Q8, *K8, *QF, *KF, *VF, *GF, *Rg, *ZT, *RT, *Rchi, *Rclo;
+    bf16_t *O, *MK, *G_rm, *G8, *G8r, *Q8, *K8, *QF, *KF, *VF, *GF, *Rg, *Rchi, *Rclo;
     float *Den, *Cc, *M8r, *ScPart, *dVc, *dQacc, *dKacc;
     // learned sketches: backward weight stream, what the row kernel leaves for the parameter
     // kernel (one side at a time), its workgroup sums, the per-unit parameter sums of both sides
@@ -1053,8 +1155,6 @@ MfmaBwdWs carve_bwd(const Problem &pb, void *ws)
     w.VF = (bf16_t *)take(rows * D * 2);
     w.GF = (bf16_t *)take(rows * D * 2);
     w.Rg = (bf16_t *)take(snaps * R * R * D * 2);
-    w.ZT = (bf16_t *)take(snaps * R * R * D * 2);
-    w.RT = (bf16_t *)take(snaps * R * R * D * 2);
     w.Rchi = (bf16_t *)take(snaps * R * R * 2);
     w.Rclo = (bf16_t *)take(snaps * R * R * 2);
     w.Den = (float *)take(rows * 4);
@@ -1163,7 +1263,7 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
         PSF_LAUNCH_CHECK();
     }
     if (tm) tm->mark();
-    // mirror states R_l (the forward state kernel on block-reversed inputs), re-laid states
+    // mirror states R_l (the forward state kernel on block-reversed inputs)
     if (pb.t > 1) {
         hipLaunchKernelGGL((k_bwd_qoct<R>), dim3((unsigned)(rows / 256)), dim3(kWg), 0, s, f.MQ, w.Cc, w.M8r,
                            w.ScPart, pb.n, pb.b, pb.t);
@@ -1172,12 +1272,6 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
         if (st != PSF_OK) return st;
         hipLaunchKernelGGL((k_den_scan<R>), dim3(R * R / kWg, pb.units), dim3(kWg), 0, s, w.ScPart, w.Rchi, w.Rclo,
                            pb.t, pb.b / 256, pb.n / 256);
-        PSF_LAUNCH_CHECK();
-        constexpr int DC = 64;                              // value columns per re-layout workgroup
-        const dim3 grid(R / 8, (unsigned)((size_t)pb.units * (pb.t - 1)), D / DC);
-        hipLaunchKernelGGL((k_bwd_relayout<R, D, DC>), grid, dim3(kWg), 0, s, f.Zg, w.ZT);
-        PSF_LAUNCH_CHECK();
-        hipLaunchKernelGGL((k_bwd_relayout<R, D, DC>), grid, dim3(kWg), 0, s, w.Rg, w.RT);
         PSF_LAUNCH_CHECK();
     }
     if (tm) tm->mark();
@@ -1223,10 +1317,10 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
         if constexpr (R == D && P == 4) {
             if (ls) {
                 hipLaunchKernelGGL((k_bwd_dm<R, D, true, TT, true>), dim3(grid), dim3(kWg), 0, s, f.MQ, w.G_rm, w.Cc,
-                                   w.ZT, f.Shi, f.Slo, q, f.Gt, (const bf16_t *)G, w.dQacc, (bf16_t *)dQ, pb.n, pb.b,
+                                   f.Zg, f.Shi, f.Slo, q, f.Gt, (const bf16_t *)G, w.dQacc, (bf16_t *)dQ, pb.n, pb.b,
                                    pb.t, pb.heads, ph, pb.g_len);
                 PSF_LAUNCH_CHECK();
-                hipLaunchKernelGGL((k_bwd_dm<R, D, false, TT, true>), dim3(grid), dim3(kWg), 0, s, w.MK, v, w.Cc, w.RT,
+                hipLaunchKernelGGL((k_bwd_dm<R, D, false, TT, true>), dim3(grid), dim3(kWg), 0, s, w.MK, v, w.Cc, w.Rg,
                                    w.Rchi, w.Rclo, k, f.Gt, (const bf16_t *)G, w.dKacc, (bf16_t *)dK, pb.n, pb.b, pb.t,
                                    pb.heads, ph, pb.g_len);
                 PSF_LAUNCH_CHECK();
@@ -1247,11 +1341,11 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
             for (int side = 0; side < 2; ++side) {
                 if (side == 0)
                     hipLaunchKernelGGL((k_bwd_dm<R, D, true, TT, false, true>), dim3(grid), dim3(kWg), 0, s, f.MQ, w.G_rm,
-                                       w.Cc, w.ZT, f.Shi, f.Slo, q, nullptr, nullptr, nullptr, nullptr, pb.n, pb.b, pb.t,
+                                       w.Cc, f.Zg, f.Shi, f.Slo, q, nullptr, nullptr, nullptr, nullptr, pb.n, pb.b, pb.t,
                                        pb.heads, ph, pb.g_len, w.M8r);
                 else
                     hipLaunchKernelGGL((k_bwd_dm<R, D, false, TT, false, true>), dim3(grid), dim3(kWg), 0, s, w.MK, v,
-                                       w.Cc, w.RT, w.Rchi, w.Rclo, k, nullptr, nullptr, nullptr, nullptr, pb.n, pb.b, pb.t,
+                                       w.Cc, w.Rg, w.Rchi, w.Rclo, k, nullptr, nullptr, nullptr, nullptr, pb.n, pb.b, pb.t,
                                        pb.heads, ph, pb.g_len, w.M8r);
                 PSF_LAUNCH_CHECK();
                 const bf16_t *xr = side == 0 ? q : k;
@@ -1284,11 +1378,11 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
                 PSF_LAUNCH_CHECK();
             }
         } else if (!ls) {
-            hipLaunchKernelGGL((k_bwd_dm<R, D, true, TT>), dim3(grid), dim3(kWg), 0, s, f.MQ, w.G_rm, w.Cc, w.ZT, f.Shi,
+            hipLaunchKernelGGL((k_bwd_dm<R, D, true, TT>), dim3(grid), dim3(kWg), 0, s, f.MQ, w.G_rm, w.Cc, f.Zg, f.Shi,
                                f.Slo, q, f.Gt, (const bf16_t *)G, w.dQacc, (bf16_t *)dQ, pb.n, pb.b, pb.t, pb.heads, ph,
                                pb.g_len);
             PSF_LAUNCH_CHECK();
-            hipLaunchKernelGGL((k_bwd_dm<R, D, false, TT>), dim3(grid), dim3(kWg), 0, s, w.MK, v, w.Cc, w.RT, w.Rchi,
+            hipLaunchKernelGGL((k_bwd_dm<R, D, false, TT>), dim3(grid), dim3(kWg), 0, s, w.MK, v, w.Cc, w.Rg, w.Rchi,
                                w.Rclo, k, f.Gt, (const bf16_t *)G, w.dKacc, (bf16_t *)dK, pb.n, pb.b, pb.t, pb.heads, ph,
                                pb.g_len);
             PSF_LAUNCH_CHECK();
@@ -1299,11 +1393,11 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
             for (int side = 0; side < 2; ++side) {
                 if (side == 0)
                     hipLaunchKernelGGL((k_bwd_dm<R, D, true, TT, false, true>), dim3(grid), dim3(kWg), 0, s, f.MQ, w.G_rm,
-                                       w.Cc, w.ZT, f.Shi, f.Slo, q, nullptr, nullptr, nullptr, nullptr, pb.n, pb.b, pb.t,
+                                       w.Cc, f.Zg, f.Shi, f.Slo, q, nullptr, nullptr, nullptr, nullptr, pb.n, pb.b, pb.t,
                                        pb.heads, ph, pb.g_len, w.M8r);
                 else
                     hipLaunchKernelGGL((k_bwd_dm<R, D, false, TT, false, true>), dim3(grid), dim3(kWg), 0, s, w.MK, v,
-                                       w.Cc, w.RT, w.Rchi, w.Rclo, k, nullptr, nullptr, nullptr, nullptr, pb.n, pb.b, pb.t,
+                                       w.Cc, w.Rg, w.Rchi, w.Rclo, k, nullptr, nullptr, nullptr, nullptr, pb.n, pb.b, pb.t,
                                        pb.heads, ph, pb.g_len, w.M8r);
                 PSF_LAUNCH_CHECK();
                 hipLaunchKernelGGL((k_bwd_sketch_rows<D, R, P>), dim3((unsigned)(rows / 128)), dim3(kWg), 0, s,
