@@ -140,6 +140,14 @@ __device__ __forceinline__ void dma16_sbase(const void *gsrc_uniform, uint32_t l
                  : "v"(lane_byte_off), "s"(gsrc_uniform), "s"(__builtin_amdgcn_readfirstlane(lds_wave_addr))
                  : "memory");
 }
+// Four bytes per lane: lane i of the wave lands at the destination + 4 i.
+__device__ __forceinline__ void dma4_sbase(const void *gsrc_uniform, uint32_t lane_byte_off, uint32_t lds_wave_addr)
+{
+    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1"
+                 :
+                 : "v"(lane_byte_off), "s"(gsrc_uniform), "s"(__builtin_amdgcn_readfirstlane(lds_wave_addr))
+                 : "memory");
+}
 __device__ __forceinline__ uint32_t lds_address(const void *p)
 {
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;

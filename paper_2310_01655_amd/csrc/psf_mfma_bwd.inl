@@ -26,13 +26,13 @@ __device__ __forceinline__ float pow_n(float x)
 }
 
 // ---- g, c and the layouts of g ------------------------------------------------------------
-// One wave per token octet, lane = value column.  G_rm: g as bf16 rows; G8: octets [rows/8][D][8];
-// G8r: the same octets with the blocks of every unit in reverse order (input of the mirror
-// state kernel, which then is the forward state kernel unchanged); Cc: c as fp32.
+// One wave per token octet, lane = value column.  G_rm: g as bf16 rows; G8r: octets [rows/8][D][8]
+// with the blocks of every unit in reverse order (input of the mirror state kernel, which then is the
+// forward state kernel unchanged); Cc: c as fp32.
 template <int D>
 __global__ __launch_bounds__(kWg) void k_bwd_prep(const bf16_t *__restrict__ dO, const bf16_t *__restrict__ O,
                                                   const float *__restrict__ Den, bf16_t *__restrict__ G_rm,
-                                                  bf16_t *__restrict__ G8, bf16_t *__restrict__ G8r,
+                                                  bf16_t *__restrict__ G8r,
                                                   float *__restrict__ Cc, int n, int b, int t)
 {
     static_assert(D % 64 == 0, "D / 64 value columns per lane");
@@ -71,7 +71,6 @@ __global__ __launch_bounds__(kWg) void k_bwd_prep(const bf16_t *__restrict__ dO,
         pk.y = gb[cl][2] | ((uint32_t)gb[cl][3] << 16);
         pk.z = gb[cl][4] | ((uint32_t)gb[cl][5] << 16);
         pk.w = gb[cl][6] | ((uint32_t)gb[cl][7] << 16);
-        *(uint4 *)&G8[(oct * D + col) * 8] = pk;
         *(uint4 *)&G8r[(((u * n + rpos) >> 3) * D + col) * 8] = pk;
     }
 }
@@ -810,121 +809,82 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_dvc(const bf16_t *__restrict__ M
 }
 
 // ---- in-block pairs ---------------------------------------------------------------------------
-// Both kernels: workgroup = 32 NW "own" rows (wave = 32, held in registers as B operands), the
-// other side streams through LDS in tiles of 64 rows, double buffered: its rows as
-// [D/8][64][8] (16-byte A fragments, contraction over d) and its octets [8][D][8] (A fragments
-// with contraction over the tile's rows).  Score tiles come out transposed (lane = own row,
-// registers = streamed rows), are turned into bf16 B operands with one half-wave swap per
-// register pair (as in the forward output kernel) and contracted with the octets.
+// Both kernels: workgroup = 32 NW "own" rows (wave = 32, held in registers as B operands), the other side streams
+// through LDS in tiles of 64 rows, double buffered, as its rows lie in memory.  Score tiles come out transposed
+// (lane = own row, registers = streamed rows), are turned into bf16 B operands as they stand and contracted with
+// the same rows read transposed (ds_read_b64_tr_b16, in the order of the accumulator registers): one copy of the
+// streamed side in LDS serves both products, so no layouts of Q, K, V and g are made in memory, twice as
+// many workgroups fit a CU's LDS, and a tile costs half the copies.
 constexpr int kLocT = 64;                                   // streamed rows per tile
-// bytes of one [D/8][64][8] / [8][D][8] array
-__host__ __device__ constexpr int loc_rows_bytes(int d) { return kLocT * d * 2; }
-
-// The layouts the in-block kernels stream, of up to four arrays at once (blockIdx.y): X [rows][D] bf16 ->
-// XF [rows/64][D/8][64][8], per 64-row tile the layout those kernels keep in LDS (16-byte A fragments with
-// contraction over the D columns), so that staging a tile is a straight, fully coalesced copy; and, where
-// X8 is wanted, the octets [rows/8][D][8].
-// scale: a power of two (exact in bf16) XF is multiplied by; 1 for a plain re-layout.
-// Bound by memory.  A wave takes 64 rows of 64 columns, a lane 8 x 8 of them; rows and, turned round in
-// registers, octets go through LDS so that loads and stores alike move whole kilobytes.  One read of X
-// serves both layouts and one launch all arrays (786 k rows of 64 columns: 182 us, 215 with a launch, and
-// a read, for every copy; 393 k: 85 and 115).
-struct BwdCopies {
-    const bf16_t *X[4];
-    bf16_t *XF[4], *X8[4];
-    float scale[4];
+template <int D, int NTHR>
+struct LocTile {
+    static constexpr int BYTES = kLocT * D * 2, PIECES = D / 8, KS = D / 16, CT = D / 32;
+    static constexpr int ROWS_PER_COPY = NTHR / PIECES;     // rows one copy instruction of the workgroup moves
+    static_assert(ROWS_PER_COPY % 16 == 0 && kLocT % ROWS_PER_COPY == 0, "whole swizzle periods per copy");
+    // The 16-byte piece p of row j lies at p ^ swz(j).  Plain reads (one piece of 16 consecutive rows) and transposed
+    // ones (two neighbouring pieces of 4 consecutive rows a 16-lane group, four pieces two groups) meet every bank
+    // once, with 32 banks as with 64.
+    static __device__ __forceinline__ int swz(int j)
+    {
+        if constexpr (D == 64) return ((j & 3) << 1) ^ ((j >> 2) & 1) ^ ((j >> 2) & 2);
+        else return ((j & 1) * 10) ^ ((j & 2) << 1) ^ ((j >> 2) & 1) ^ (j & 8);
+    }
+    int x, h, tid, wave;
+    uint32_t copy_off;                                      // lane's place in a copy's source
+    uint32_t plain[KS], turned[2][CT];                      // lane's byte offsets of fragments, see rows() and columns()
+    __device__ __forceinline__ LocTile()
+    {
+        tid = threadIdx.x;
+        const int lane = tid & 63, s16 = lane & 15;
+        x = lane & 31;
+        h = lane >> 5;
+        wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int row = tid / PIECES;
+        copy_off = (uint32_t)((row * PIECES + (tid % PIECES ^ swz(row))) * 16);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) plain[s] = (uint32_t)((x * PIECES + ((2 * s + h) ^ swz(x))) * 16);
+#pragma unroll
+        for (int hi = 0; hi < 2; ++hi)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                const int j = 8 * hi + 4 * h + s16 / 4, p = 4 * ct + 2 * ((lane >> 4) & 1) + (s16 % 4) / 2;
+                turned[hi][ct] = (uint32_t)((j * PIECES + (p ^ swz(j))) * 16 + (s16 & 1) * 8);
+            }
+    }
+    // rows [j0, j0 + 64) of X -> LDS
+    __device__ __forceinline__ void stage(const bf16_t *__restrict__ X, size_t j0, uint32_t dst) const
+    {
+#pragma unroll
+        for (int q = 0; q < kLocT / ROWS_PER_COPY; ++q)
+            dma16_sbase(X + (j0 + q * ROWS_PER_COPY) * D, copy_off, dst + q * (NTHR * 16) + wave * 1024);
+    }
+    // A fragment: rows 32 sub + x, columns 16 s + 8 h + e
+    __device__ __forceinline__ bf16x8 rows(const unsigned char *tile, int sub, int s) const
+    {
+        return *(const bf16x8 *)(tile + plain[s] + sub * 32 * D * 2);
+    }
+    // A fragment: columns 32 ct + x, contraction over the rows 32 sub + 16 sp + 8 (e / 4) + 4 h + e % 4
+    __device__ __forceinline__ bf16x8 columns(const unsigned char *tile, int sub, int sp, int ct) const
+    {
+        const unsigned char *t = tile + (32 * sub + 16 * sp) * D * 2;
+        return read_turned(t + turned[0][ct], t + turned[1][ct]);
+    }
 };
-template <int D>
-__global__ __launch_bounds__(kWg) void k_bwd_row_copies(BwdCopies cp)
-{
-    static_assert(D % 64 == 0 && kLocT == 64, "64 x 64 per wave");
-    __shared__ __attribute__((aligned(16))) uint4 tile[4][64 * 8];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, y = blockIdx.y;
-    const int oct = lane / 8, doct = lane % 8;
-    const size_t job = (size_t)blockIdx.x * 4 + wave, t64 = job / (D / 64);
-    const int half = (int)(job % (D / 64));
-    const bf16_t *const X = cp.X[y] + (t64 * 64 + 8 * oct) * D + 64 * half + 8 * doct;
-    bf16_t *const X8 = cp.X8[y];
-    const float scale = cp.scale[y];
-    uint4 *const L = tile[wave];
-    uint4 in[8];
-#pragma unroll
-    for (int r = 0; r < 8; ++r) in[r] = *(const uint4 *)(X + (size_t)r * D);
-    // rows: key 8 oct + r, column octet doct at doct ^ (key % 8), so that the reads, which walk the keys, meet all banks
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        bf16x8 v = __builtin_bit_cast(bf16x8, in[r]);
-        if (scale != 1.0f) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = (__bf16)((float)v[e] * scale);
-        }
-        L[(8 * oct + r) * 8 + (doct ^ r)] = __builtin_bit_cast(uint4, v);
-    }
-    __syncthreads();
-    bf16_t *const XF = cp.XF[y] + ((t64 * (D / 8) + 8 * half) * 64 + lane) * 8;
-#pragma unroll
-    for (int o = 0; o < 8; ++o) *(uint4 *)(XF + (size_t)o * 64 * 8) = L[lane * 8 + (o ^ (lane & 7))];
-    if (!X8) return;                                       // the same for the whole launch row
-    __syncthreads();
-    // octets: column 8 doct + j of octet oct at 8 doct + (j ^ doct)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const uint32_t which = j % 2 ? 0x07060302u : 0x05040100u;
-        auto pair = [&](int r) {
-            const uint32_t lo[4] = {in[r].x, in[r].y, in[r].z, in[r].w};
-            const uint32_t hi[4] = {in[r + 1].x, in[r + 1].y, in[r + 1].z, in[r + 1].w};
-            return __builtin_amdgcn_perm(hi[j / 2], lo[j / 2], which);
-        };
-        L[oct * 64 + 8 * doct + (j ^ doct)] = make_uint4(pair(0), pair(2), pair(4), pair(6));
-    }
-    __syncthreads();
-#pragma unroll
-    for (int o = 0; o < 8; ++o)
-        *(uint4 *)(X8 + ((t64 * 8 + o) * D + 64 * half + lane) * 8) = L[o * 64 + 8 * (lane / 8) + ((lane & 7) ^ (lane / 8))];
-}
-// tile of rows [j0, j0 + 64) of XF -> LDS, straight copy
-template <int NTHR, int D>
-__device__ __forceinline__ void loc_stage_rows(const bf16_t *XF, size_t j0, unsigned char *dst, int tid, int wave)
-{
-#pragma unroll
-    for (int q = 0; q < loc_rows_bytes(D) / 16 / NTHR; ++q)
-        dma16(XF + j0 * D + (size_t)(q * NTHR + tid) * 8, dst + (size_t)(q * NTHR + wave * 64) * 16);
-}
-// octets of rows [j0, j0 + 64) of X8 ([rows/8][D][8]) -> LDS, straight copy
-template <int NTHR, int D>
-__device__ __forceinline__ void loc_stage_octets(const bf16_t *X8, size_t j0, unsigned char *dst, int tid, int wave)
-{
-#pragma unroll
-    for (int q = 0; q < loc_rows_bytes(D) / 16 / NTHR; ++q)
-        dma16(X8 + j0 * D + (size_t)(q * NTHR + tid) * 8, dst + (size_t)(q * NTHR + wave * 64) * 16);
-}
-// 16 fp32 (lane = own row, register v = streamed row 8 (v / 4) + 4 h + v % 4) -> two bf16 B
-// fragments whose 8 entries are the streamed rows 16 sp + 8 h + e
-__device__ __forceinline__ void loc_pack(const f32x16 &w, bf16x8 (&pw)[2])
-{
-#pragma unroll
-    for (int sp = 0; sp < 2; ++sp) {
-        uint4 u = __builtin_bit_cast(uint4, cvt8_from16(w, 8 * sp));
-        const auto s0 = __builtin_amdgcn_permlane32_swap(u.x, u.z, false, false);
-        const auto s1 = __builtin_amdgcn_permlane32_swap(u.y, u.w, false, false);
-        u.x = s0[0]; u.z = s0[1]; u.y = s1[0]; u.w = s1[1];
-        pw[sp] = __builtin_bit_cast(bf16x8, u);
-    }
-}
 
 // dQ (in-block): own rows = queries, streamed = keys of the same block up to the diagonal.
 //   dq_i = sum_{j <= i} (<g_i, v_j> + c_i) p <q_i, k_j>^(p-1) k_j          -> dQacc fp32 rows
 template <int P, int NW, int D = 64>
-__global__ __launch_bounds__(64 * NW, D == 64 ? 512 / (64 * NW) : 1) void k_bwd_local_q(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ KF,
-                                                       const bf16_t *__restrict__ VF, const bf16_t *__restrict__ K8,
-                                                       const bf16_t *__restrict__ G_rm, const float *__restrict__ Cc,
-                                                       float *__restrict__ dQacc, int n, int b)
+__global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_q(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
+                                                                         const bf16_t *__restrict__ V, const bf16_t *__restrict__ G_rm,
+                                                                         const float *__restrict__ Cc, float *__restrict__ dQacc,
+                                                                         int n, int b)
 {
-    constexpr int KS = D / 16, CT = D / 32, kLocRows = loc_rows_bytes(D), BUF = 3 * kLocRows, NTHR = 64 * NW, OWN = 32 * NW;
+    constexpr int KS = D / 16, CT = D / 32, NTHR = 64 * NW, OWN = 32 * NW;
+    using Tile = LocTile<D, NTHR>;
+    constexpr int BUF = 2 * Tile::BYTES;
     __shared__ __attribute__((aligned(16))) unsigned char stage[2 * BUF];
-    const int tid = threadIdx.x, lane = tid & 63, x = lane & 31, h = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tiles_per_unit = n / OWN;
+    const Tile T;
+    const int x = T.x, h = T.h, tiles_per_unit = n / OWN;
     // XCD-aware order: consecutive workgroup ids go to different XCDs, so give each XCD a
     // contiguous range of tiles: the workgroups that stream the same rows then share one L2
     int wg = blockIdx.x;
@@ -932,78 +892,79 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 512 / (64 * NW) : 1) void k_bwd_
     const int u = wg / tiles_per_unit, i0 = (wg % tiles_per_unit) * OWN;
     const int jb = (i0 / b) * b;
     const size_t urow = (size_t)u * n;
-    const int tok0 = i0 + 32 * wave, tok = tok0 + x;
+    const int tok0 = i0 + 32 * T.wave, tok = tok0 + x;
     bf16x8 qfr[KS], gfr[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
         qfr[s] = *(const bf16x8 *)&Q[(urow + tok) * D + 16 * s + 8 * h];
         gfr[s] = *(const bf16x8 *)&G_rm[(urow + tok) * D + 16 * s + 8 * h];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) gfr[s][e] = (__bf16)((float)gfr[s][e] * (float)P);   // p of p s^(p-1), exact (power of two)
     }
-    const float c_me = (float)P * Cc[urow + tok];
+    const float c_me = Cc[urow + tok];
     f32x16 dq[CT];
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) dq[ct] = f32x16{0};
     const int ntiles = (i0 + OWN - jb) / kLocT;
+    const uint32_t stage0 = lds_address(stage);
     auto stage_tile = [&](int kt) {
-        unsigned char *dst = stage + (kt & 1) * BUF;
+        const uint32_t dst = stage0 + (kt & 1) * BUF;
         const size_t j0 = urow + jb + (size_t)kt * kLocT;
-        loc_stage_rows<NTHR, D>(KF, j0, dst, tid, wave);
-        loc_stage_rows<NTHR, D>(VF, j0, dst + kLocRows, tid, wave);
-        loc_stage_octets<NTHR, D>(K8, j0, dst + 2 * kLocRows, tid, wave);
+        T.stage(K, j0, dst);
+        T.stage(V, j0, dst + Tile::BYTES);
     };
-    stage_tile(0);
-#pragma unroll 1
-    for (int kt = 0; kt < ntiles; ++kt) {
+    auto tile = [&](auto diag_tag, int kt) {
+        constexpr bool DIAG = decltype(diag_tag)::value;
+        const unsigned char *ks = stage + (kt & 1) * BUF, *vs = ks + Tile::BYTES;
+        bf16x8 pw[2][2];
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub) {
+            f32x16 sc = {0}, dw = {0};
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                sc = mfma32(T.rows(ks, sub, s), qfr[s], sc);
+                dw = mfma32(T.rows(vs, sub, s), gfr[s], dw);
+            }
+            // key = key0 + 8 (v / 4) + 4 h + v % 4 <= tok  <=>  8 (v / 4) + v % 4 <= lim
+            const int lim = tok - (jb + kt * kLocT + 32 * sub) - 4 * h;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float sm = !DIAG || 8 * (v / 4) + (v % 4) <= lim ? sc[v] : 0.f;   // masked pairs: every power is 0
+                dw[v] = (dw[v] + c_me) * pow_n<P - 1>(sm);
+            }
+            pw[sub][0] = cvt8_from16(dw, 0);
+            pw[sub][1] = cvt8_from16(dw, 8);
+        }
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+            for (int sp = 0; sp < 2; ++sp)
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) dq[ct] = mfma32(T.columns(ks, sub, sp, ct), pw[sub][sp], dq[ct]);
+    };
+    // (loops of one body each: with both bodies in one loop the accumulators change registers and spill)
+    auto sync = [&](int kt) {
         wait_vmem_le<0>();
         __syncthreads();
         if (kt + 1 < ntiles) stage_tile(kt + 1);
-        const bf16_t *ks = (const bf16_t *)(stage + (kt & 1) * BUF);
-        const bf16_t *vs = ks + kLocRows / 2, *k8 = ks + kLocRows;
-        if (jb + kt * kLocT <= tok0 + 31) {                // wave-uniform: some key of the tile is not later than every own token
-            // both 32-key halves in one straight line: scores, then weights, then products
-            f32x16 sc[2], dw[2];
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub) {
-                sc[sub] = f32x16{0};
-                dw[sub] = f32x16{0};
-#pragma unroll
-                for (int s = 0; s < KS; ++s) {
-                    const bf16x8 kf = *(const bf16x8 *)&ks[((2 * s + h) * kLocT + 32 * sub + x) * 8];
-                    const bf16x8 vf = *(const bf16x8 *)&vs[((2 * s + h) * kLocT + 32 * sub + x) * 8];
-                    sc[sub] = mfma32(kf, qfr[s], sc[sub]);
-                    dw[sub] = mfma32(vf, gfr[s], dw[sub]);
-                }
-            }
-            bf16x8 pw[2][2];
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub) {
-                // key = key0 + 8 (v / 4) + 4 h + v % 4 <= tok  <=>  8 (v / 4) + v % 4 <= lim
-                const int lim = tok - (jb + kt * kLocT + 32 * sub) - 4 * h;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float sm = (8 * (v / 4) + (v % 4) <= lim) ? sc[sub][v] : 0.f;   // masked pairs: every power is 0
-                    dw[sub][v] = (dw[sub][v] + c_me) * pow_n<P - 1>(sm);
-                }
-                loc_pack(dw[sub], pw[sub]);
-            }
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-                for (int sp = 0; sp < 2; ++sp)
-#pragma unroll
-                    for (int ct = 0; ct < CT; ++ct) {
-                        const bf16x8 kf8 = *(const bf16x8 *)&k8[((4 * sub + 2 * sp + h) * D + 32 * ct + x) * 8];
-                        dq[ct] = mfma32(kf8, pw[sub][sp], dq[ct]);
-                    }
-        }
+    };
+    const int diag = (tok0 - jb) / kLocT;                  // the tile that holds this wave's own tokens
+    stage_tile(0);
+#pragma unroll 1
+    for (int kt = 0; kt < diag; ++kt) {
+        sync(kt);
+        tile(std::false_type{}, kt);
+        branch_wait();
     }
+    sync(diag);
+    tile(std::true_type{}, diag);
+#pragma unroll 1
+    for (int kt = diag + 1; kt < ntiles; ++kt) sync(kt);   // later tiles: only keep the barriers and copies going
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
         for (int gq = 0; gq < 4; ++gq) {
-            const f32x4 q4 = {dq[ct][4 * gq], dq[ct][4 * gq + 1], dq[ct][4 * gq + 2], dq[ct][4 * gq + 3]};
+            // (the p of p s^(p-1): a power of two, exact)
+            const f32x4 q4 = {(float)P * dq[ct][4 * gq], (float)P * dq[ct][4 * gq + 1], (float)P * dq[ct][4 * gq + 2],
+                              (float)P * dq[ct][4 * gq + 3]};
             *(f32x4 *)&dQacc[(urow + tok) * D + 32 * ct + 8 * gq + 4 * h] = q4;
         }
 }
@@ -1011,27 +972,26 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 512 / (64 * NW) : 1) void k_bwd_
 // dK (in-block) and dV (in-block + the cross-block part already in dVc): own rows = keys,
 // streamed = queries of the same block from the diagonal on.
 //   dk_j = sum_{i >= j} (<g_i, v_j> + c_i) p <q_i, k_j>^(p-1) q_i   -> dKacc fp32 rows
-//          (GF, the streamed rows of g for the first product, and the staged c carry the factor p)
 //   dv_j = sum_{i >= j} <q_i, k_j>^p g_i + dVc_j                     -> dV bf16 rows
 template <int P, int NW, int D = 64>
-__global__ __launch_bounds__(64 * NW, D == 64 ? 512 / (64 * NW) : 1) void k_bwd_local_k(const bf16_t *__restrict__ QF, const bf16_t *__restrict__ K,
-                                                       const bf16_t *__restrict__ V, const bf16_t *__restrict__ Q8,
-                                                       const bf16_t *__restrict__ GF, const bf16_t *__restrict__ G8,
-                                                       const float *__restrict__ Cc, const float *__restrict__ dVc,
-                                                       float *__restrict__ dKacc, bf16_t *__restrict__ dV, int n,
-                                                       int b)
+__global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_k(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
+                                                                         const bf16_t *__restrict__ V, const bf16_t *__restrict__ G_rm,
+                                                                         const float *__restrict__ Cc, const float *__restrict__ dVc,
+                                                                         float *__restrict__ dKacc, bf16_t *__restrict__ dV,
+                                                                         int n, int b)
 {
-    constexpr int KS = D / 16, CT = D / 32, kLocRows = loc_rows_bytes(D), BUF = 4 * kLocRows + kLocT * 4, NTHR = 64 * NW, OWN = 32 * NW;
+    constexpr int KS = D / 16, CT = D / 32, NTHR = 64 * NW, OWN = 32 * NW;
+    using Tile = LocTile<D, NTHR>;
+    constexpr int BUF = 2 * Tile::BYTES + kLocT * 4;
     __shared__ __attribute__((aligned(16))) unsigned char stage[2 * BUF];
-    const int tid = threadIdx.x, lane = tid & 63, x = lane & 31, h = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tiles_per_unit = n / OWN;
+    const Tile T;
+    const int x = T.x, h = T.h, tiles_per_unit = n / OWN;
     int wg = blockIdx.x;                                    // XCD-aware order, as in k_bwd_local_q
     if ((gridDim.x & 7) == 0) wg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
     const int u = wg / tiles_per_unit, j0 = (wg % tiles_per_unit) * OWN;
     const int jb = (j0 / b) * b;
     const size_t urow = (size_t)u * n;
-    const int key0 = j0 + 32 * wave, key = key0 + x;
+    const int key0 = j0 + 32 * T.wave, key = key0 + x;
     bf16x8 kfr[KS], vfr[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
@@ -1042,77 +1002,78 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 512 / (64 * NW) : 1) void k_bwd_
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) dk[ct] = dv[ct] = f32x16{0};
     const int first = (j0 - jb) / kLocT, ntiles = b / kLocT;
+    const uint32_t stage0 = lds_address(stage);
     auto stage_tile = [&](int qt) {
-        unsigned char *dst = stage + (qt & 1) * BUF;
+        const uint32_t dst = stage0 + (qt & 1) * BUF;
         const size_t t0 = urow + jb + (size_t)qt * kLocT;
-        loc_stage_rows<NTHR, D>(QF, t0, dst, tid, wave);
-        loc_stage_rows<NTHR, D>(GF, t0, dst + kLocRows, tid, wave);
-        loc_stage_octets<NTHR, D>(Q8, t0, dst + 2 * kLocRows, tid, wave);
-        loc_stage_octets<NTHR, D>(G8, t0, dst + 3 * kLocRows, tid, wave);
-        if (tid < kLocT) ((float *)(dst + 4 * kLocRows))[tid] = (float)P * Cc[t0 + tid];
+        T.stage(Q, t0, dst);
+        T.stage(G_rm, t0, dst + Tile::BYTES);
+        if (T.wave == 0) dma4_sbase(Cc + t0, (uint32_t)T.tid * 4, dst + 2 * Tile::BYTES);
     };
-    stage_tile(first);
-#pragma unroll 1
-    for (int qt = first; qt < ntiles; ++qt) {
-        wait_all_memory();
+    auto tile = [&](auto diag_tag, int qt) {
+        constexpr bool DIAG = decltype(diag_tag)::value;
+        const unsigned char *qs = stage + (qt & 1) * BUF, *gs = qs + Tile::BYTES;
+        const float *cs = (const float *)(qs + 2 * Tile::BYTES);
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub) {
+            __builtin_amdgcn_sched_barrier(0);              // (halves interleaved do not fit the registers)
+            f32x16 sc = {0}, dw;
+#pragma unroll
+            for (int gq = 0; gq < 4; ++gq) {                // dw starts at c of its row
+                const f32x4 c4 = *(const f32x4 *)&cs[32 * sub + 8 * gq + 4 * h];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) dw[4 * gq + j] = c4[j];
+            }
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                sc = mfma32(T.rows(qs, sub, s), kfr[s], sc);
+                dw = mfma32(T.rows(gs, sub, s), vfr[s], dw);
+            }
+            // key <= token t0 + 8 (v / 4) + 4 h + v % 4  <=>  8 (v / 4) + v % 4 >= lim
+            const int lim = key - (jb + qt * kLocT + 32 * sub) - 4 * h;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float sm = !DIAG || 8 * (v / 4) + (v % 4) >= lim ? sc[v] : 0.f;   // masked pairs: every power is 0
+                const float pm1 = pow_n<P - 1>(sm);
+                sc[v] = pm1 * sm;
+                dw[v] = dw[v] * pm1;
+            }
+#pragma unroll
+            for (int sp = 0; sp < 2; ++sp) {
+                const bf16x8 pww = cvt8_from16(sc, 8 * sp), pwp = cvt8_from16(dw, 8 * sp);
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) {
+                    dk[ct] = mfma32(T.columns(qs, sub, sp, ct), pwp, dk[ct]);
+                    dv[ct] = mfma32(T.columns(gs, sub, sp, ct), pww, dv[ct]);
+                }
+            }
+        }
+    };
+    auto sync = [&](int qt) {
+        wait_vmem_le<0>();
         __syncthreads();
         if (qt + 1 < ntiles) stage_tile(qt + 1);
-        const bf16_t *qs = (const bf16_t *)(stage + (qt & 1) * BUF);
-        const bf16_t *gs = qs + kLocRows / 2, *q8 = qs + kLocRows, *g8 = qs + 3 * (kLocRows / 2);
-        const float *cs = (const float *)(stage + (qt & 1) * BUF + 4 * kLocRows);
-        if (jb + qt * kLocT + kLocT - 1 >= key0) {         // wave-uniform: some token of the tile is not earlier than every own key
-            f32x16 sc[2], dw[2];
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub) {
-                sc[sub] = f32x16{0};
-                dw[sub] = f32x16{0};
-#pragma unroll
-                for (int s = 0; s < KS; ++s) {
-                    const bf16x8 qf = *(const bf16x8 *)&qs[((2 * s + h) * kLocT + 32 * sub + x) * 8];
-                    const bf16x8 gf = *(const bf16x8 *)&gs[((2 * s + h) * kLocT + 32 * sub + x) * 8];
-                    sc[sub] = mfma32(qf, kfr[s], sc[sub]);
-                    dw[sub] = mfma32(gf, vfr[s], dw[sub]);
-                }
-            }
-            bf16x8 pww[2][2], pwp[2][2];
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub) {
-                // key <= token t0 + 8 gq + 4 h + j  <=>  8 gq + j >= lim
-                const int lim = key - (jb + qt * kLocT + 32 * sub) - 4 * h;
-#pragma unroll
-                for (int gq = 0; gq < 4; ++gq) {
-                    const f32x4 c4 = *(const f32x4 *)&cs[32 * sub + 8 * gq + 4 * h];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int v = 4 * gq + j;
-                        const float sm = (8 * gq + j >= lim) ? sc[sub][v] : 0.f;   // masked pairs: every power is 0
-                        const float pm1 = pow_n<P - 1>(sm);
-                        sc[sub][v] = pm1 * sm;
-                        dw[sub][v] = (dw[sub][v] + c4[j]) * pm1;      // g and c arrive multiplied by p
-                    }
-                }
-                loc_pack(sc[sub], pww[sub]);
-                loc_pack(dw[sub], pwp[sub]);
-            }
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-                for (int sp = 0; sp < 2; ++sp)
-#pragma unroll
-                    for (int ct = 0; ct < CT; ++ct) {
-                        const bf16x8 qf8 = *(const bf16x8 *)&q8[((4 * sub + 2 * sp + h) * D + 32 * ct + x) * 8];
-                        const bf16x8 gf8 = *(const bf16x8 *)&g8[((4 * sub + 2 * sp + h) * D + 32 * ct + x) * 8];
-                        dk[ct] = mfma32(qf8, pwp[sub][sp], dk[ct]);
-                        dv[ct] = mfma32(gf8, pww[sub][sp], dv[ct]);
-                    }
-        }
+    };
+    const int diag = (key0 - jb) / kLocT;                  // the tile that holds this wave's own keys
+    stage_tile(first);
+#pragma unroll 1
+    for (int qt = first; qt < diag; ++qt) sync(qt);        // earlier tiles: only keep the barriers and copies going
+    sync(diag);
+    tile(std::true_type{}, diag);
+#pragma unroll 1
+    for (int qt = diag + 1; qt < ntiles; ++qt) {
+        sync(qt);
+        tile(std::false_type{}, qt);
+        branch_wait();
     }
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
         for (int gq = 0; gq < 4; ++gq) {
             const size_t off = (urow + key) * D + 32 * ct + 8 * gq + 4 * h;
-            const f32x4 k4 = {dk[ct][4 * gq], dk[ct][4 * gq + 1], dk[ct][4 * gq + 2], dk[ct][4 * gq + 3]};
+            // (the p of p s^(p-1): a power of two, exact)
+            const f32x4 k4 = {(float)P * dk[ct][4 * gq], (float)P * dk[ct][4 * gq + 1], (float)P * dk[ct][4 * gq + 2],
+                              (float)P * dk[ct][4 * gq + 3]};
             *(f32x4 *)&dKacc[off] = k4;
             const f32x4 c4 = *(const f32x4 *)&dVc[off];
             const f32x4 v4 = {dv[ct][4 * gq] + c4[0], dv[ct][4 * gq + 1] + c4[1], dv[ct][4 * gq + 2] + c4[2],
@@ -1124,7 +1085,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 512 / (64 * NW) : 1) void k_bwd_
 // ---- host ---------------------------------------------------------------------------------------
 struct MfmaBwdWs {
     void *fwd;                                               // the forward workspace
-    bf16_t *O, *MK, *G_rm, *G8, *G8r, *Q8, *K8, *QF, *KF, *VF, *GF, *Rg, *Rchi, *Rclo;
+    bf16_t *O, *MK, *G_rm, *G8r, *Rg, *Rchi, *Rclo;
     float *Den, *Cc, *M8r, *ScPart, *dVc, *dQacc, *dKacc;
     // learned sketches: backward weight stream, what the row kernel leaves for the parameter
     // kernel (one side at a time), its workgroup sums, the per-unit parameter sums of both sides
@@ -1146,14 +1107,7 @@ MfmaBwdWs carve_bwd(const Problem &pb, void *ws)
     w.O = (bf16_t *)take(rows * D * 2);
     w.MK = (bf16_t *)take(rows * R * 2);
     w.G_rm = (bf16_t *)take(rows * D * 2);
-    w.G8 = (bf16_t *)take(rows * D * 2);
     w.G8r = (bf16_t *)take(rows * D * 2);
-    w.Q8 = (bf16_t *)take(rows * D * 2);
-    w.K8 = (bf16_t *)take(rows * D * 2);
-    w.QF = (bf16_t *)take(rows * D * 2);
-    w.KF = (bf16_t *)take(rows * D * 2);
-    w.VF = (bf16_t *)take(rows * D * 2);
-    w.GF = (bf16_t *)take(rows * D * 2);
     w.Rg = (bf16_t *)take(snaps * R * R * D * 2);
     w.Rchi = (bf16_t *)take(snaps * R * R * 2);
     w.Rclo = (bf16_t *)take(snaps * R * R * 2);
@@ -1251,17 +1205,8 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
     const bf16_t *rq = ls ? f.MQ : q, *rk = ls ? w.MK : k;  // the rows the in-block weights are made of
     // g, c, layouts
     hipLaunchKernelGGL((k_bwd_prep<D>), dim3((unsigned)(rows / 32)), dim3(kWg), 0, s, (const bf16_t *)dO, w.O,
-                       w.Den, w.G_rm, w.G8, w.G8r, w.Cc, pb.n, pb.b, pb.t);
+                       w.Den, w.G_rm, w.G8r, w.Cc, pb.n, pb.b, pb.t);
     PSF_LAUNCH_CHECK();
-    {
-        // the copy of g that only feeds dW = <g, v> + c carries the factor e of d(s^e) = e s^(e-1) ds
-        const BwdCopies cp = {{rq, rk, v, w.G_rm},
-                              {w.QF, w.KF, w.VF, w.GF},
-                              {w.Q8, w.K8, nullptr, nullptr},
-                              {1.0f, 1.0f, 1.0f, ls ? 2.0f : (float)P}};
-        hipLaunchKernelGGL((k_bwd_row_copies<D>), dim3((unsigned)(rows / 256 * (D / 64)), 4), dim3(kWg), 0, s, cp);
-        PSF_LAUNCH_CHECK();
-    }
     if (tm) tm->mark();
     // mirror states R_l (the forward state kernel on block-reversed inputs)
     if (pb.t > 1) {
@@ -1280,14 +1225,14 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
         const unsigned grid = (unsigned)(rows / (32 * NWL));
         if constexpr (R == D && P == 4) {
             if (ls) {
-                hipLaunchKernelGGL((k_bwd_local_q<2, NWL, D>), dim3(grid), dim3(64 * NWL), 0, s, rq, w.KF, w.VF, w.K8,
-                                   w.G_rm, w.Cc, w.dQacc, pb.n, pb.b);
+                hipLaunchKernelGGL((k_bwd_local_q<2, NWL, D>), dim3(grid), dim3(64 * NWL), 0, s, rq, rk, v, w.G_rm,
+                                   w.Cc, w.dQacc, pb.n, pb.b);
                 PSF_LAUNCH_CHECK();
             }
         }
         if (!ls) {
-            hipLaunchKernelGGL((k_bwd_local_q<P, NWL, D>), dim3(grid), dim3(64 * NWL), 0, s, q, w.KF, w.VF, w.K8, w.G_rm,
-                               w.Cc, w.dQacc, pb.n, pb.b);
+            hipLaunchKernelGGL((k_bwd_local_q<P, NWL, D>), dim3(grid), dim3(64 * NWL), 0, s, q, k, v, w.G_rm, w.Cc,
+                               w.dQacc, pb.n, pb.b);
             PSF_LAUNCH_CHECK();
         }
     }
@@ -1298,14 +1243,14 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
         PSF_LAUNCH_CHECK();
         if constexpr (R == D && P == 4) {
             if (ls) {
-                hipLaunchKernelGGL((k_bwd_local_k<2, NWL, D>), dim3(grid), dim3(64 * NWL), 0, s, w.QF, rk, v, w.Q8, w.GF,
-                                   w.G8, w.Cc, w.dVc, w.dKacc, (bf16_t *)dV, pb.n, pb.b);
+                hipLaunchKernelGGL((k_bwd_local_k<2, NWL, D>), dim3(grid), dim3(64 * NWL), 0, s, rq, rk, v, w.G_rm, w.Cc,
+                                   w.dVc, w.dKacc, (bf16_t *)dV, pb.n, pb.b);
                 PSF_LAUNCH_CHECK();
             }
         }
         if (!ls) {
-            hipLaunchKernelGGL((k_bwd_local_k<P, NWL, D>), dim3(grid), dim3(64 * NWL), 0, s, w.QF, k, v, w.Q8, w.GF, w.G8,
-                               w.Cc, w.dVc, w.dKacc, (bf16_t *)dV, pb.n, pb.b);
+            hipLaunchKernelGGL((k_bwd_local_k<P, NWL, D>), dim3(grid), dim3(64 * NWL), 0, s, q, k, v, w.G_rm, w.Cc,
+                               w.dVc, w.dKacc, (bf16_t *)dV, pb.n, pb.b);
             PSF_LAUNCH_CHECK();
         }
     }
