@@ -30,6 +30,7 @@
 
 #include "psf_internal.h"
 #include "psf_f32.h"
+#include "psf_lds.h"
 
 namespace psf {
 namespace {
@@ -615,6 +616,292 @@ __global__ __launch_bounds__(kThreads) void dec_state_kernel(const T *__restrict
         for (int e = tid; e < mcols; e += kThreads)
             su[L.cm + (size_t)slot * mcols + e] = SK ? mk_s[e] : mk_new[(size_t)u * mcols + e];
     }
+}
+
+// ---- the step of the common shapes --------------------------------------------------------------
+// bf16 storage, degree 4 with Gaussian sketches, exact in-block weights, d = dv = D in {64, 128}, r = R in {32, 64}:
+// what dec_state_kernel<bf16_t, true, true, 2 or 4> computes, from the same state, with the shape known.
+// A step of few units is bound by its chain of waits, so the chain is short: every first load is issued at the
+// start (matrices, rows, state, cache), the sketches are one 16 x 16 product per 16 columns with the rows
+// q and k as rows of A (bf16 operands, exact products, fp32 sums), pairs (a, b') are found under the loads,
+// state and cached rows add into the same registers, one sum over the lanes and one over the waves serve both,
+// and one wave hands the slice over.
+// A lane group of D / 8 lanes owns a state row or a cached row, 16 bytes a lane; the lane li of a group also holds
+// the pair and the ones-column entry of the group's row li of a batch of eight.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v)
+{
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+// the sum over the lane's group of 8 or 16 lanes, the same in all of them
+template <int LANES>
+__device__ __forceinline__ float group_sum(float v)
+{
+    v += dpp<0xB1>(v);                                     // quad_perm 1 0 3 2
+    v += dpp<0x4E>(v);                                     // quad_perm 2 3 0 1
+    v += dpp<0x141>(v);                                    // row_half_mirror
+    if constexpr (LANES == 16) v += dpp<0x140>(v);         // row_mirror
+    return v;
+}
+// lane I of the lane's group of 8 or 16
+template <int LANES, int I>
+__device__ __forceinline__ float group_bcast(float v)
+{
+    const int w = (int)__float_as_uint(v);
+    if constexpr (LANES == 16) return __uint_as_float(__builtin_amdgcn_update_dpp(0, w, 0x150 + I, 0xf, 0xf, true));
+    const int lo = __builtin_amdgcn_update_dpp(0, w, 0x150 + I, 0xf, 0x3, true);
+    return __uint_as_float(__builtin_amdgcn_update_dpp(lo, w, 0x158 + I, 0xf, 0xc, false));
+}
+
+template <int D, int R, bool ALONE>
+__global__ __launch_bounds__(kThreads) void dec_step_kernel(const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
+                                                            const bf16_t *__restrict__ v, float *__restrict__ state,
+                                                            float *__restrict__ part, bf16_t *__restrict__ o,
+                                                            DecodeLayout L, int slot, int have_state, DecSketchArgs sk)
+{
+    constexpr int CL = D / 8, NG = kThreads / CL, U = 8, UC = 4, F = R * (R + 1) / 2, NV = D / 64;
+    constexpr int PITCH = R / 8;                           // 16-byte pieces of a matrix row
+    constexpr int GP = D * PITCH / kThreads;               // pieces of one matrix per thread
+    static_assert(D * PITCH % kThreads == 0, "whole pieces");
+    typedef float f32x4v __attribute__((ext_vector_type(4)));
+    __shared__ __attribute__((aligned(16))) bf16_t gl[2][D * R];
+    __shared__ float mq[R], mk[R], sums[4][D], den_s[4];
+    const int u = blockIdx.y, sl = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int li = tid % CL, grp = tid / CL, s16 = lane & 15, kc = D + 1;
+    float *const su = state + (size_t)u * L.per_unit;
+    const int slices = ALONE ? 1 : L.slices;
+    const int per = ALONE ? F : (int)((unsigned)(F + slices - 1) / (unsigned)slices), f_beg = ALONE ? 0 : sl * per;
+    const int nf = have_state ? max(0, min(F, f_beg + per) - f_beg) : 0;
+    const int per_j = ALONE ? slot : (int)((unsigned)(slot + slices - 1) / (unsigned)slices);
+    const int j_beg = ALONE ? 0 : min(slot, sl * per_j), j_end = ALONE ? slot : min(slot, j_beg + per_j);
+    const bf16_t *const zh = (const bf16_t *)(su + L.zh) + (size_t)f_beg * D + 8 * li;
+    const float *const zd = su + L.zd + f_beg;
+    const bf16_t *const keys = (const bf16_t *)(su + L.ck) + 8 * li, *const vals = (const bf16_t *)(su + L.cv) + 8 * li;
+
+    // loads, in the order in which they are needed
+    const uint4 *const g = (const uint4 *)((const bf16_t *)sk.G + (sk.per_head ? (size_t)(u % sk.heads) * sk.g_len : 0));
+    uint4 gv[2][GP];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int i = 0; i < GP; ++i) gv[m][i] = g[m * (D * PITCH) + i * kThreads + tid];
+    uint4 xf[D / 32];                                      // A operand: row 0 = q, row 1 = k, the others zero
+#pragma unroll
+    for (int s = 0; s < D / 32; ++s) {
+        xf[s] = make_uint4(0u, 0u, 0u, 0u);
+        if (s16 < 2) xf[s] = *(const uint4 *)&(s16 ? k : q)[(size_t)u * D + 32 * s + 8 * (lane >> 4)];
+    }
+    ZRow<bf16_t> qr, kr0;                                  // this lane's columns of q and k
+    qr.load(q + (size_t)u * D + 8 * li);
+    kr0.load(k + (size_t)u * D + 8 * li);
+    struct Batch {
+        ZRow<bf16_t> z[U];
+        float zd;
+        int pair;
+    };
+    auto load_batch = [&](int row0) {                      // rows row0 + grp + i NG
+        Batch b;
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int row = row0 + grp + i * NG;
+            b.z[i].zero();
+            if (row < nf) b.z[i].load(zh + (size_t)row * D);
+        }
+        const int mine = row0 + grp + li * NG;             // (li < U where there is one: CL = 16 has twice the lanes)
+        const bool on = li < U && mine < nf;
+        b.zd = on ? zd[mine] : 0.f;
+        // the pair (a, b') of the row: a in closed form, off by one at most
+        const int t = on ? f_beg + mine : 0;
+        const float sf = 2.f * R + 1.f;
+        int a = (int)((sf - sqrtf(fmaxf(sf * sf - 8.f * (float)t, 0.f))) * 0.5f);
+        a = max(0, min(a, R - 1));
+        const int first = a * R - a * (a - 1) / 2;
+        a += (first + R - a <= t) - (first > t);
+        b.pair = on ? a | (a + t - (a * R - a * (a - 1) / 2)) << 8 : -1;
+        return b;
+    };
+    Batch cur = load_batch(0);
+    struct Cached {
+        ZRow<bf16_t> key[UC], val[UC];
+    };
+    auto load_cached = [&](int j0) {
+        Cached c;
+#pragma unroll
+        for (int i = 0; i < UC; ++i) {
+            const int row = j0 + grp + i * NG;
+            c.key[i].zero();
+            c.val[i].zero();
+            if (row < j_end) {
+                c.key[i].load(keys + (size_t)row * D);
+                c.val[i].load(vals + (size_t)row * D);
+            }
+        }
+        return c;
+    };
+    Cached cc = load_cached(j_beg);
+
+    // Algorithm 1.  Matrices into LDS as they lie, the pieces of a row swapped so that the transposed reads (4 rows,
+    // two neighbouring pieces) meet different banks.
+    auto swz = [](int e) { return R == 64 ? (e & 3) << 1 : e & 2; };
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int i = 0; i < GP; ++i) {
+            const int idx = i * kThreads + tid, e = idx / PITCH;
+            *(uint4 *)&gl[m][(e * PITCH + (idx % PITCH ^ swz(e))) * 8] = gv[m][i];
+        }
+    __syncthreads();
+    if (16 * wave < R) {
+        f32x4v acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int s = 0; s < D / 32; ++s)
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                const int e = 32 * s + 8 * (lane >> 4) + s16 / 4, c8 = 2 * wave + (s16 % 4) / 2;
+                const bf16_t *const at = &gl[m][(e * PITCH + (c8 ^ swz(e))) * 8 + 4 * (s16 & 1)];
+                acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xf[s]),
+                                                                 read_turned(at, at + 4 * PITCH * 8), acc[m], 0, 0, 0);
+            }
+        if (lane < 16) {
+            const float sc = sqrtf(1.0f / (float)R);
+            mq[16 * wave + lane] = sc * (acc[0][0] * acc[1][0]);
+            mk[16 * wave + lane] = sc * (acc[0][1] * acc[1][1]);
+        }
+    }
+    // the cached rows need no sketch: they go between the sketches and the barrier
+    float qreg[8], acc[8], den = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) qreg[j] = acc[j] = 0.f;
+    qr.fma(1.f, qreg);
+    float wsum = 0.f;
+    auto weigh = [&](const Cached &c) {
+#pragma unroll
+        for (int i = 0; i < UC; ++i) {
+            float w = group_sum<CL>(c.key[i].dot(qreg));   // rows past the end are zero, and so is their weight
+            w *= w;
+            w *= w;
+            c.val[i].fma(w, acc);
+            wsum += w;
+        }
+    };
+    for (int j0 = j_beg; j0 < j_end; j0 += UC * NG) {
+        const Cached now = cc;
+        if (j0 + UC * NG < j_end) cc = load_cached(j0 + UC * NG);
+        weigh(now);
+    }
+    if (li == 0) den = wsum;
+    float w_self = group_sum<CL>(kr0.dot(qreg));
+    w_self *= w_self;
+    w_self *= w_self;
+    __syncthreads();
+    for (int row0 = 0; row0 < nf; row0 += U * NG) {
+        const Batch now = cur;
+        if (row0 + U * NG < nf) cur = load_batch(row0 + U * NG);
+        const float phi = now.pair >= 0 ? mq[now.pair & 0xff] * mq[now.pair >> 8] : 0.f;
+        den = fmaf(phi, now.zd, den);
+        now.z[0].fma(group_bcast<CL, 0>(phi), acc);
+        now.z[1].fma(group_bcast<CL, 1>(phi), acc);
+        now.z[2].fma(group_bcast<CL, 2>(phi), acc);
+        now.z[3].fma(group_bcast<CL, 3>(phi), acc);
+        now.z[4].fma(group_bcast<CL, 4>(phi), acc);
+        now.z[5].fma(group_bcast<CL, 5>(phi), acc);
+        now.z[6].fma(group_bcast<CL, 6>(phi), acc);
+        now.z[7].fma(group_bcast<CL, 7>(phi), acc);
+    }
+
+    // sum over the lane groups of the wave, halving the columns a lane holds; column 8 li + 4 h + 2 (odd 16) [+ lane / 8 % 2]
+    auto halves = [&](float a, float b) {
+        const auto r2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        return __uint_as_float(r2[0]) + __uint_as_float(r2[1]);
+    };
+    auto quarters = [&](float a, float b) {
+        const auto r2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        return __uint_as_float(r2[0]) + __uint_as_float(r2[1]);
+    };
+    float c4[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c4[j] = halves(acc[j], acc[j + 4]);
+    const float c0 = quarters(c4[0], c4[2]), c1 = quarters(c4[1], c4[3]);
+    const int col = 8 * li + 4 * (lane >> 5) + 2 * ((lane >> 4) & 1);
+    if constexpr (CL == 8) {
+        const bool up = lane & 8;
+        sums[wave][col + (up ? 1 : 0)] = (up ? c1 : c0) + dpp<0x128>(up ? c0 : c1);      // row_ror 8
+    } else {
+        sums[wave][col] = c0;
+        sums[wave][col + 1] = c1;
+    }
+    den = group_sum<16>(den);
+    den += __shfl_xor(den, 16);
+    den += __shfl_xor(den, 32);
+    if (lane == 0) den_s[wave] = den;
+    __syncthreads();
+    if (wave > 0) {
+        if (ALONE) {                                       // the cache takes the new token's sketch: see below
+            if (wave == 1 && lane < R) su[L.cm + (size_t)slot * R + lane] = mk[lane];
+        }
+        return;
+    }
+    float row[NV], s = (den_s[0] + den_s[1]) + (den_s[2] + den_s[3]);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int c = 64 * i + lane;
+        row[i] = (sums[0][c] + sums[1][c]) + (sums[2][c] + sums[3][c]);
+    }
+    if constexpr (!ALONE) {
+        // as in dec_state_kernel's MODE 4, by one wave: its stores are acknowledged before its first lane counts
+        // the slice in, and the last slice's loads are issued after the count has come back
+        float *const out = part + ((size_t)u * kSlices + sl) * kc;
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+            __hip_atomic_store(out + 64 * i + lane, row[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane == 0) __hip_atomic_store(out + D, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        int *const arrived = (int *)(part + ((size_t)u * kSlices + kSlices - 1) * kc);
+        int before = 0;
+        if (lane == 0) before = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        before = __builtin_amdgcn_readfirstlane(before);
+        if (before != slices - 1) return;
+        asm volatile("" ::: "memory");
+        if (lane == 0) __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const float *const from = part + (size_t)u * kSlices * kc;
+        // all loads before the sums, which keep the order of the slices
+        float got[kSlices - 1][NV], got_s[kSlices - 1];
+#pragma unroll
+        for (int q2 = 0; q2 < kSlices - 1; ++q2) {
+            const float *const at = from + (size_t)min(q2, slices - 1) * kc;
+            if (q2 < slices) {                             // (the same for the whole launch)
+#pragma unroll
+                for (int i = 0; i < NV; ++i)
+                    got[q2][i] = __hip_atomic_load(at + 64 * i + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                got_s[q2] = __hip_atomic_load(at + D, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+#pragma unroll
+                for (int i = 0; i < NV; ++i) got[q2][i] = 0.f;
+                got_s[q2] = 0.f;
+            }
+        }
+        s = 0.f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) row[i] = 0.f;
+#pragma unroll
+        for (int q2 = 0; q2 < kSlices - 1; ++q2) {
+#pragma unroll
+            for (int i = 0; i < NV; ++i) row[i] += got[q2][i];
+            s += got_s[q2];
+        }
+    }
+    // the new token's own pair, the division, and the token into the cache
+    const float total = 1.f + s + w_self;
+    bf16_t *const ckeys = (bf16_t *)(su + L.ck), *const cvals = (bf16_t *)(su + L.cv);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int c = 64 * i + lane;
+        const bf16_t vraw = v[(size_t)u * D + c];
+        o[(size_t)u * D + c] = f32_to_bf16((row[i] + w_self * bf16_to_f32(vraw)) / total);
+        cvals[(size_t)slot * D + c] = vraw;
+        ckeys[(size_t)slot * D + c] = k[(size_t)u * D + c];
+    }
+    if (!ALONE && lane < R) su[L.cm + (size_t)slot * R + lane] = mk[lane];
 }
 
 // The new token's key, value and m(k) go into cache slot `slot`; row = sum of the slices + the
@@ -1208,6 +1495,27 @@ psf_status step_launch(const Problem &pb, const void *q, const void *k, const vo
     const long long Fs = tri_count(pb.mcols);
     const dim3 sgrid((unsigned)L.slices, (unsigned)pb.units);
     const DecSketchArgs ska{G, pb.g_len, pb.heads, pb.per_head ? 1 : 0, pb.r};
+    // the shapes dec_step_kernel knows; it reads rows and matrices 16 bytes at a time
+    bool known = false;
+    if constexpr (std::is_same_v<T, bf16_t>) {
+        const bool aligned = (((uintptr_t)q | (uintptr_t)k | (uintptr_t)G) & 15) == 0;
+        auto launch = [&](auto d_tag, auto r_tag) {
+            constexpr int D = decltype(d_tag)::value, R = decltype(r_tag)::value;
+            if (mode == 2)
+                hipLaunchKernelGGL((dec_step_kernel<D, R, true>), sgrid, dim3(kThreads), 0, s, (const T *)q, (const T *)k,
+                                   (const T *)v, state, state + L.part, (T *)o, L, slot, have_state, ska);
+            else
+                hipLaunchKernelGGL((dec_step_kernel<D, R, false>), sgrid, dim3(kThreads), 0, s, (const T *)q, (const T *)k,
+                                   (const T *)v, state, state + L.part, (T *)o, L, slot, have_state, ska);
+        };
+        known = (mode == 2 || mode == 4) && pb.p == 4 && le && aligned && pb.d == pb.dv && (pb.d == 64 || pb.d == 128) &&
+                (pb.r == 32 || pb.r == 64);
+        using std::integral_constant;
+        if (known && pb.d == 64 && pb.r == 64) launch(integral_constant<int, 64>{}, integral_constant<int, 64>{});
+        else if (known && pb.d == 64) launch(integral_constant<int, 64>{}, integral_constant<int, 32>{});
+        else if (known && pb.r == 64) launch(integral_constant<int, 128>{}, integral_constant<int, 64>{});
+        else if (known) launch(integral_constant<int, 128>{}, integral_constant<int, 32>{});
+    }
 #define PSF_DEC_STATE(SH, LE_, MO)                                                                             \
     hipLaunchKernelGGL((dec_state_kernel<T, SH, LE_, MO>), sgrid, dim3(kThreads), 0, s, (const T *)q,             \
                        (const T *)k, (const T *)v, state, state + L.mq, state + L.mk, state + L.mq, state + L.mk, \
@@ -1225,7 +1533,8 @@ psf_status step_launch(const Problem &pb, const void *q, const void *k, const vo
         else                             \
             PSF_DEC_STATE(SH, LE_, 4);   \
     } while (0)
-    if (L.shadow) {
+    if (known) {
+    } else if (L.shadow) {
         if constexpr (std::is_same_v<T, bf16_t>) {
             if (le) PSF_DEC_STATE_MODE(true, true); else PSF_DEC_STATE_MODE(true, false);
         }

@@ -50,11 +50,11 @@
 #include <utility>
 
 #include "psf_internal.h"
+#include "psf_lds.h"
 
 namespace psf {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
