@@ -45,6 +45,7 @@
 //   A[i][k]: lane x = i, half h supplies k = 8h..8h+7 (8 bf16 per lane)
 //   B[k][j]: lane x = j, half h supplies k = 8h..8h+7
 //   D[i][j]: lane x = j, register v holds row i = 8*(v/4) + 4*h + (v%4)
+#include <algorithm>
 #include <cstdlib>
 #include <type_traits>
 #include <utility>

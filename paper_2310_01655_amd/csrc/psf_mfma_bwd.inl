@@ -1105,6 +1105,9 @@ MfmaBwdWs carve_bwd(const Problem &pb, void *ws)
     w.dVc = (float *)take(rows * D * 4);
     w.dQacc = (float *)take(rows * D * 4);
     w.dKacc = (float *)take(rows * D * 4);
+    // The size this call asked for when it kept re-laid states and row layouts of its own is still its least: callers
+    // budget with it, and a buffer made for it serves either.
+    off = std::max(off, align_up(carve(pb, nullptr).total, 256) + 2 * snaps * R * R * D * 2 + 5 * rows * D * 4);
     if (pb.learned) {
         const size_t sets = pb.per_head ? pb.heads : 1, nch = R / 4;
         w.LB = (bf16_t *)take(sets * 4 * nch * kLbSlot);
