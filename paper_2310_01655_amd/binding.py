@@ -5,6 +5,7 @@ library's HIP kernels.  There is no CPU fallback: a missing library or a CPU ten
 raises.
 """
 import ctypes
+import functools
 import os
 
 import torch
@@ -168,8 +169,10 @@ def _torch_dtype(desc):
 
 
 def _dev_ptr(t, desc, shape, name):
-    if t is None:
-        return None
+    # (the common case in one condition: a step of 7 us of kernel spent 13 us here and below)
+    if t is None or (t.is_cuda and t.dtype is _torch_dtype(desc) and t.is_contiguous() and
+                     (shape is None or t.shape == shape)):
+        return None if t is None else t.data_ptr()
     if not t.is_cuda:
         raise ValueError("%s must live on the GPU (no CPU path exists)" % name)
     if t.dtype != _torch_dtype(desc):
@@ -178,12 +181,13 @@ def _dev_ptr(t, desc, shape, name):
         raise ValueError("%s must be contiguous" % name)
     if shape is not None and tuple(t.shape) != tuple(shape):
         raise ValueError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream_ptr(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def learned_len(d, r, p):
@@ -193,8 +197,12 @@ def learned_len(d, r, p):
 def _g_shape(desc):
     if desc.feat == FEAT_EXACT or desc.p == 2:
         return None
-    per_set = learned_len(desc.d, desc.r, desc.p) if desc.learned else g_len(desc.d, desc.r, desc.p)
-    return (desc.heads if desc.sketch_per_head else 1, per_set)
+    return (desc.heads if desc.sketch_per_head else 1, _set_len(desc.d, desc.r, desc.p, bool(desc.learned)))
+
+
+@functools.lru_cache(maxsize=64)
+def _set_len(d, r, p, learned):
+    return learned_len(d, r, p) if learned else g_len(d, r, p)
 
 
 def alloc_workspace(desc, device="cuda"):
@@ -227,7 +235,7 @@ def psf_sketch(desc, X, G, want_m=True, want_phi=False, stream=None):
 def _attn_args(desc, Q, K, V, G, O, workspace, noncausal=False):
     B, H, n, d, dv = desc.batch, desc.heads, desc.n, desc.d, desc.dv
     if O is None:
-        O = torch.empty(B, H, n, dv, dtype=Q.dtype, device=Q.device)
+        O = Q.new_empty((B, H, n, dv))
     if workspace is None:
         workspace = alloc_noncausal_workspace(desc, Q.device) if noncausal else alloc_workspace(desc, Q.device)
     if not workspace.is_cuda or workspace.dtype != torch.uint8:
@@ -495,12 +503,12 @@ def psf_decode_step(desc, q, k, v, G, pos, state, o=None, stream=None):
     """Row `pos` of the attention for the sequence fed so far; q, k, v are [batch, heads, 1, d|dv]."""
     B, H, d, dv = desc.batch, desc.heads, desc.d, desc.dv
     if o is None:
-        o = torch.empty(B, H, 1, dv, dtype=q.dtype, device=q.device)
+        o = q.new_empty((B, H, 1, dv))
     gs = _g_shape(desc)
     st = lib().psf_decode_step(
         ctypes.byref(desc), _dev_ptr(q, desc, (B, H, 1, d), "q"), _dev_ptr(k, desc, (B, H, 1, d), "k"),
         _dev_ptr(v, desc, (B, H, 1, dv), "v"), _dev_ptr(G, desc, gs, "G") if gs else None, int(pos),
-        ctypes.c_void_p(state.data_ptr()), ctypes.c_size_t(state.numel()),
+        state.data_ptr(), state.numel(),
         _dev_ptr(o, desc, (B, H, 1, dv), "o"), _stream_ptr(stream))
     if st != PSF_OK:
         raise PsfError(st, "psf_decode_step")
