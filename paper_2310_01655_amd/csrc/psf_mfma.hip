@@ -1111,13 +1111,13 @@ __device__ __forceinline__ void state_workgroup(const float *__restrict__ M8, co
     constexpr int NTHR = kWg * NG;
     constexpr int DMA_PER_CHUNK = (TC * R * 4 + TC * D * 2) / 16 / NTHR;
     constexpr int AG = NA * 4 / (R / 32);
-    static_assert(!SYM || NA == 2 || (NA == 4 && R == 64), "tile deal of the symmetric variant: whole workgroups");
+    static_assert(!SYM || NA <= 2 || (NA == 4 && R == 64), "tile deal of the symmetric variant: whole workgroups");
 
     // XCD-aware order: consecutive workgroup ids go to different XCDs, so give each XCD a
     // contiguous range of (unit, group) pairs; the groups of one unit then share one L2.
     int wg = bid;
     if ((nblk & 7) == 0) wg = (bid & 7) * (nblk >> 3) + (bid >> 3);
-    constexpr int GROUPS = SYM ? (R / 16) * (R / 16 + 1) / NA : R / AG;   // workgroups per unit
+    constexpr int GROUPS = SYM ? (R / 16) * (R / 16 + 1) / NA : R / AG;   // workgroups per unit (NA = 1: 20 at r = 64, 6 at r = 32)
     const int u = wg / GROUPS, grp = wg % GROUPS;
     if (u >= units || t < 2) return;
 
@@ -2665,55 +2665,58 @@ psf_status launch_sketch(const Problem &pb, const void *X, const bf16_t *Gt, boo
     return PSF_OK;
 }
 
-// The symmetric deal of the state kernel at d = 128, r = 64: ten workgroups per unit instead of
-// sixteen with the same work each (config 5: 0.285 -> 0.254 ms for the state stage).
-constexpr bool kSymWide = true;
 // Running prefix states of (M8, V8) for every unit, snapshots into Zg.
+//
+// Which form: a workgroup walks its unit's tokens in series, a step takes longer the more tiles a wave holds, and all
+// workgroups of a unit stage the same tokens.  us of a whole call of 4096 tokens, no mask unless said:
+//   one tile a wave while its workgroups (20 a unit at r = 64, 6 at r = 32) fit one per CU -- d = 64, r = 32, against
+//     full tiles, four a wave: 1 unit 72.5 -> 49.6, 12 81 -> 58, 40 105 -> 84, causal 12 93 -> 61; d = 128, r = 64, against
+//     two a wave: 1 unit 127 -> 108, 12 145 -> 131; d = 128, r = 32: 1 unit 80 -> 69, 40 151 -> 139 (one unit more than fit: slower);
+//   d = 64, r = 32, then two tiles a wave (3 workgroups a unit) while those fit: against full tiles, causal, 48 units 134 -> 110,
+//     80 200 -> 182; with one block the tokens' steps split over two waves: 48 units 105 -> 84, 80 148 -> 130;
+//     then full tiles, four a wave, while their two a unit fit (causal, 96 units 228 against 230, 128 283 against 293);
+//     beyond, two a wave again (160 units 379 -> 344);
+//   d = 64, r = 64: two tiles a wave, from 80 units on four (below);
+//   d = 128: two tiles a wave of the symmetric deal (config 5: 0.285 -> 0.254 ms for the state stage against full tiles).
 template <int D, int R>
 psf_status launch_state(const Problem &pb, const float *M8, const bf16_t *V8, bf16_t *Zg, hipStream_t s)
 {
-    // Symmetric deal (d = 64): only the (a, 16-wide column range) segments the output kernel
-    // reads.  For r = 32 it pays once the grid is a few workgroups per CU; small grids keep
-    // the full tiles with four per wave, which fill the CUs better.
-    constexpr int GROUPS = (R / 16) * (R / 16 + 1) / 2;
+    // Symmetric deal: only the (a, 16-wide column range) segments the output kernel reads.
+    constexpr int GROUPS = (R / 16) * (R / 16 + 1) / 2;     // workgroups a unit with two tiles a wave
     const unsigned grid_sym = (unsigned)(pb.units * GROUPS);
-    if (D == 64 && (R == 64 || grid_sym > 512)) {
-        if constexpr (D == 64) {
-            // One block only (no mask, or the prompt of a decode): eight waves, two per SIMD,
-            // 8 % faster per token; with a snapshot every block the exchange and the stalled
-            // ring after the stores cost more than that.
-            // (r = 32 reaches this branch with large grids only.)
-            if (R == 64 && grid_sym <= 256 && pb.t == 2) {
-                if constexpr (R == 64)
-                    hipLaunchKernelGGL((k_state_two_waves<R, D, 64>), dim3(grid_sym), dim3(2 * kWg), 0, s, M8, V8,
-                                       Zg, pb.n, pb.b, pb.t, pb.units);
-            } else if (grid_sym <= 256)
-                hipLaunchKernelGGL((k_state<R, D, 2, true, 64, 1>), dim3(grid_sym), dim3(kWg), 0, s, M8, V8, Zg,
-                                   pb.n, pb.b, pb.t, pb.units);
-            else if (R == 64 && grid_sym > 800) {
-                // Four tiles a wave: the operands of a step, five LDS reads, serve eight products instead
-                // of four, and a token is staged by half as many workgroups.  Where half the workgroups
-                // still fill the chip (us, two tiles and four, 8192 tokens: 48 units 171, 210; 72: 215, 213; 96: 339,
-                // 324; 132: 380, 366; 192: 650, 631; 768: 1985, 1754; 46 registers of the wider form go through
-                // scratch, which these times contain).
-                if constexpr (R == 64)
-                    hipLaunchKernelGGL((k_state<R, D, 4, true, 32, 2>), dim3(grid_sym / 2), dim3(kWg), 0, s, M8, V8,
-                                       Zg, pb.n, pb.b, pb.t, pb.units);
-            } else
-                hipLaunchKernelGGL((k_state<R, D, 2, true, 32, 2>), dim3(grid_sym), dim3(kWg), 0, s, M8, V8, Zg,
-                                   pb.n, pb.b, pb.t, pb.units);
-        }
-    } else if (D == 128 && R == 64 && kSymWide) {
-        if constexpr (D == 128 && R == 64)
-            hipLaunchKernelGGL((k_state<R, D, 2, true, 64, 1>), dim3(grid_sym), dim3(kWg), 0, s, M8, V8, Zg, pb.n, pb.b,
+    const bool one_block = pb.t == 2;                       // no mask, or the prompt of a decode
+#define PSF_STATE(NA_, SYM_, TC_, OCC_, WGS)                                                                           \
+    hipLaunchKernelGGL((k_state<R, D, NA_, SYM_, TC_, OCC_>), dim3(WGS), dim3(kWg), 0, s, M8, V8, Zg, pb.n, pb.b, pb.t, \
+                       pb.units)
+    if constexpr (D == 64) {
+        // One block only: eight waves, two per SIMD, that split the tokens' steps, 8 % faster per token at r = 64; with a
+        // snapshot every block the exchange and the stalled ring after the stores cost more than that.
+        if (one_block && grid_sym <= 256 && (R == 64 || 2 * grid_sym > 256)) {
+            hipLaunchKernelGGL((k_state_two_waves<R, D, 64>), dim3(grid_sym), dim3(2 * kWg), 0, s, M8, V8, Zg, pb.n, pb.b,
                                pb.t, pb.units);
-    } else if constexpr (!(D == 64 && R == 64)) {
-        constexpr int NA = (D == 64) ? 4 : 2;
-        constexpr int AG = NA * 4 / (R / 32);
-        const unsigned grid = (unsigned)(pb.units * (R / AG));
-        hipLaunchKernelGGL((k_state<R, D, NA, false, 64, 1>), dim3(grid), dim3(kWg), 0, s, M8, V8, Zg, pb.n,
-                           pb.b, pb.t, pb.units);
+            PSF_LAUNCH_CHECK();
+            return PSF_OK;
+        }
     }
+    if (2 * grid_sym <= 256) {
+        PSF_STATE(1, true, 64, 1, 2 * grid_sym);
+    } else if constexpr (D == 128) {
+        PSF_STATE(2, true, 64, 1, grid_sym);
+    } else if constexpr (R == 64) {
+        // Four tiles a wave: the operands of a step, five LDS reads, serve eight products instead
+        // of four, and a token is staged by half as many workgroups.  Where half the workgroups
+        // still fill the chip (us, two tiles and four, 8192 tokens: 48 units 171, 210; 72: 215, 213; 96: 339,
+        // 324; 132: 380, 366; 192: 650, 631; 768: 1985, 1754; 46 registers of the wider form go through
+        // scratch, which these times contain).
+        if (grid_sym <= 256) PSF_STATE(2, true, 64, 1, grid_sym);
+        else if (grid_sym > 800) PSF_STATE(4, true, 32, 2, grid_sym / 2);
+        else PSF_STATE(2, true, 32, 2, grid_sym);
+    } else {
+        if (grid_sym > 512) PSF_STATE(2, true, 32, 2, grid_sym);
+        else if (grid_sym <= 256 || 2 * pb.units > 256) PSF_STATE(2, true, 64, 2, grid_sym);
+        else PSF_STATE(4, false, 64, 1, (unsigned)(2 * pb.units));
+    }
+#undef PSF_STATE
     PSF_LAUNCH_CHECK();
     return PSF_OK;
 }
