@@ -13,7 +13,8 @@
 //   k_transpose_g, k_sketch, k_v_octets
 //                  the same steps as separate launches: degree 8 (two levels, the first level's
 //                  accumulators are the second level's operands) and the backward pass.
-//   k_den_scan     prefix of the S partials over blocks, stored as bf16 hi + lo MFMA operands.
+//   den_scan_role  prefix of the S partials over blocks, stored as bf16 hi + lo MFMA operands: the last
+//                  workgroups of the state kernels' launches (in the backward pass of k_bwd_local_q's).
 //   k_state        running prefix state Z = sum phi'(k_j) v_j^T kept in MFMA accumulators while
 //                  one workgroup walks the blocks in order; phi'(k_j) = m_j (x) m_j is expanded
 //                  in registers (one operand broadcast across lanes with DPP) and never
@@ -763,7 +764,7 @@ __global__ __launch_bounds__(kWg, KEYS ? 2 : 4) void k_prep(const bf16_t *__rest
 template <int R>
 __device__ __forceinline__ void den_scan_workgroup(const float *__restrict__ Spart, bf16_t *__restrict__ Shi,
                                                    bf16_t *__restrict__ Slo, int t, int parts_per_block,
-                                                   int parts_per_unit, int u, int blk, bf16_t *xch)
+                                                   int parts_per_unit, int u, int blk, bf16_t *xch, int tid)
 {
     // One entry of S per thread, threads in the order of the partials (row-major [a][b']): a wave
     // reads 256 contiguous bytes of every partial.  At a block boundary the 256 results change
@@ -771,7 +772,6 @@ __device__ __forceinline__ void den_scan_workgroup(const float *__restrict__ Spa
     // layout [b'/8][a][8]: pieces of kWg / R rows x 8 columns, 16 bytes per row.
     static_assert(kWg % R == 0 && (R * R) % kWg == 0, "whole rows per workgroup");
     constexpr int ROWS = kWg / R;
-    const int tid = threadIdx.x;
     const int e = blk * kWg + tid;
     const int a0 = blk * ROWS;
     const int within = tid % (ROWS * 8), oa = a0 + within / 8, obq = 8 * (tid / (ROWS * 8)) + within % 8;
@@ -804,13 +804,23 @@ __device__ __forceinline__ void den_scan_workgroup(const float *__restrict__ Spa
     }
 }
 
-template <int R>
-__global__ __launch_bounds__(kWg) void k_den_scan(const float *__restrict__ Spart,
-                                                  bf16_t *__restrict__ Shi, bf16_t *__restrict__ Slo,
-                                                  int t, int parts_per_block, int parts_per_unit)
+// The scan as a role of another launch: its last (R * R / kWg) workgroups a unit, after n_main others.  A
+// workgroup of THREADS = 512 scans two pieces of 256 entries.  xch: THREADS * 2 entries of workgroup memory.
+struct DenScan {
+    const float *Spart;
+    bf16_t *Shi, *Slo;
+    int parts_per_block, parts_per_unit, n_main;
+};
+template <int R, int THREADS>
+__device__ __forceinline__ bool den_scan_role(const DenScan &a, int t, void *lds)
 {
-    __shared__ bf16_t xch[2 * kWg];
-    den_scan_workgroup<R>(Spart, Shi, Slo, t, parts_per_block, parts_per_unit, blockIdx.y, blockIdx.x, xch);
+    constexpr int PER_UNIT = R * R / THREADS;
+    const int bid = (int)blockIdx.x - a.n_main;
+    if (bid < 0) return false;
+    const int half = __builtin_amdgcn_readfirstlane(threadIdx.x / kWg);
+    den_scan_workgroup<R>(a.Spart, a.Shi, a.Slo, t, a.parts_per_block, a.parts_per_unit, bid / PER_UNIT,
+                          bid % PER_UNIT * (THREADS / kWg) + half, (bf16_t *)lds + half * 2 * kWg, threadIdx.x % kWg);
+    return true;
 }
 
 // ------------------------------------------------------------------------------------
@@ -1329,10 +1339,11 @@ template <int R, int D, int NA, bool SYM, int TC, int OCC>
 __global__ __launch_bounds__(kWg, OCC) void k_state(const float *__restrict__ M8,
                                                const bf16_t *__restrict__ V8,
                                                bf16_t *__restrict__ Zg, int n, int b, int t,
-                                               int units)
+                                               int units, DenScan den)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[state_lds_bytes<R, D, TC, 1>()];
-    state_workgroup<R, D, NA, SYM, TC, 1>(M8, V8, Zg, n, b, t, units, lds, blockIdx.x, gridDim.x);
+    if (den_scan_role<R, kWg>(den, t, lds)) return;
+    state_workgroup<R, D, NA, SYM, TC, 1>(M8, V8, Zg, n, b, t, units, lds, blockIdx.x, den.n_main);
 }
 
 // The symmetric deal with eight waves, two per SIMD (see state_body), one workgroup per CU.
@@ -1340,10 +1351,11 @@ template <int R, int D, int TC>
 __global__ __launch_bounds__(2 * kWg, 1) void k_state_two_waves(const float *__restrict__ M8,
                                                                  const bf16_t *__restrict__ V8,
                                                                  bf16_t *__restrict__ Zg, int n, int b, int t,
-                                                                 int units)
+                                                                 int units, DenScan den)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[state_lds_bytes<R, D, TC, 2>()];
-    state_workgroup<R, D, 2, true, TC, 2>(M8, V8, Zg, n, b, t, units, lds, blockIdx.x, gridDim.x);
+    if (den_scan_role<R, 2 * kWg>(den, t, lds)) return;
+    state_workgroup<R, D, 2, true, TC, 2>(M8, V8, Zg, n, b, t, units, lds, blockIdx.x, den.n_main);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1371,10 +1383,11 @@ template <int R, int D>
 __global__ __launch_bounds__(kWg, 2) void k_state_f16(const _Float16 *__restrict__ MKh,
                                                       const _Float16 *__restrict__ V8h,
                                                       const float *__restrict__ Kscale, bf16_t *__restrict__ Zg,
-                                                      int n, int b, int t, int units)
+                                                      int n, int b, int t, int units, DenScan den)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[kStateF16Lds];
-    state_f16_workgroup<R, D>(MKh, V8h, Kscale, Zg, n, b, t, units, lds, blockIdx.x, gridDim.x);
+    if (den_scan_role<R, kWg>(den, t, lds)) return;
+    state_f16_workgroup<R, D>(MKh, V8h, Kscale, Zg, n, b, t, units, lds, blockIdx.x, den.n_main);
 }
 
 constexpr int kKeyTilesInFlight = 4;
@@ -1936,7 +1949,7 @@ __global__ __launch_bounds__(kWg, 2) void k_state_and_in_block(const float *__re
     if (bid < a.n_den) {
         constexpr int PER_UNIT = R * R / kWg;
         den_scan_workgroup<R>(a.Spart, a.Shi, a.Slo, t, a.parts_per_block, a.parts_per_unit, bid / PER_UNIT,
-                              bid % PER_UNIT, (bf16_t *)lds);
+                              bid % PER_UNIT, (bf16_t *)lds, threadIdx.x);
         return;
     }
     bid -= a.n_den;
@@ -2679,21 +2692,28 @@ psf_status launch_sketch(const Problem &pb, const void *X, const bf16_t *Gt, boo
 //   d = 64, r = 64: two tiles a wave, from 80 units on four (below);
 //   d = 128: two tiles a wave of the symmetric deal (config 5: 0.285 -> 0.254 ms for the state stage against full tiles).
 template <int D, int R>
-psf_status launch_state(const Problem &pb, const float *M8, const bf16_t *V8, bf16_t *Zg, hipStream_t s)
+psf_status launch_state(const Problem &pb, const float *M8, const bf16_t *V8, bf16_t *Zg, hipStream_t s, DenScan den = {})
 {
+    // (the scan of the denominators, where the caller has one: its workgroups fill CUs that the states leave, and
+    // come last, so that they never hold one back)
+    const unsigned scan = den.Spart ? (unsigned)(pb.units * (R * R / kWg)) : 0u;
     // Symmetric deal: only the (a, 16-wide column range) segments the output kernel reads.
     constexpr int GROUPS = (R / 16) * (R / 16 + 1) / 2;     // workgroups a unit with two tiles a wave
     const unsigned grid_sym = (unsigned)(pb.units * GROUPS);
     const bool one_block = pb.t == 2;                       // no mask, or the prompt of a decode
-#define PSF_STATE(NA_, SYM_, TC_, OCC_, WGS)                                                                           \
-    hipLaunchKernelGGL((k_state<R, D, NA_, SYM_, TC_, OCC_>), dim3(WGS), dim3(kWg), 0, s, M8, V8, Zg, pb.n, pb.b, pb.t, \
-                       pb.units)
+#define PSF_STATE(NA_, SYM_, TC_, OCC_, WGS)                                                                          \
+    do {                                                                                                              \
+        den.n_main = (int)(WGS);                                                                                      \
+        hipLaunchKernelGGL((k_state<R, D, NA_, SYM_, TC_, OCC_>), dim3((WGS) + scan), dim3(kWg), 0, s, M8, V8, Zg, pb.n, \
+                           pb.b, pb.t, pb.units, den);                                                                \
+    } while (0)
     if constexpr (D == 64) {
         // One block only: eight waves, two per SIMD, that split the tokens' steps, 8 % faster per token at r = 64; with a
         // snapshot every block the exchange and the stalled ring after the stores cost more than that.
         if (one_block && grid_sym <= 256 && (R == 64 || 2 * grid_sym > 256)) {
-            hipLaunchKernelGGL((k_state_two_waves<R, D, 64>), dim3(grid_sym), dim3(2 * kWg), 0, s, M8, V8, Zg, pb.n, pb.b,
-                               pb.t, pb.units);
+            den.n_main = (int)grid_sym;
+            hipLaunchKernelGGL((k_state_two_waves<R, D, 64>), dim3(grid_sym + scan / 2), dim3(2 * kWg), 0, s, M8, V8, Zg,
+                               pb.n, pb.b, pb.t, pb.units, den);
             PSF_LAUNCH_CHECK();
             return PSF_OK;
         }
@@ -2866,11 +2886,7 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
         PSF_LAUNCH_CHECK();
     }
     if (tm) tm->mark();
-    if (pb.t > 1 && !beside) {
-        hipLaunchKernelGGL((k_den_scan<R>), dim3(R * R / kWg, pb.units), dim3(kWg), 0, s, w.Spart, w.Shi,
-                           w.Slo, pb.t, pb.b / part_tokens(pb), pb.n / part_tokens(pb));
-        PSF_LAUNCH_CHECK();
-    }
+    const DenScan den = {w.Spart, w.Shi, w.Slo, pb.b / part_tokens(pb), pb.n / part_tokens(pb), 0};
     if (tm) tm->mark();
     if constexpr (D == 64 && R == 64 && P != 2) {
         if (beside) {
@@ -2912,12 +2928,14 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
     }
     if (f16_alone) {
         if constexpr (D == 64 && R == 64) {
-            hipLaunchKernelGGL((k_state_f16<R, D>), dim3((unsigned)(pb.units * 10)), dim3(kWg), 0, s,
-                               (const _Float16 *)w.MK8, w.V8h, w.Kscale, w.Zg, pb.n, pb.b, pb.t, pb.units);
+            DenScan last = den;
+            last.n_main = pb.units * 10;
+            hipLaunchKernelGGL((k_state_f16<R, D>), dim3((unsigned)(pb.units * (10 + R * R / kWg))), dim3(kWg), 0, s,
+                               (const _Float16 *)w.MK8, w.V8h, w.Kscale, w.Zg, pb.n, pb.b, pb.t, pb.units, last);
             PSF_LAUNCH_CHECK();
         }
     } else if (pb.t > 1) {
-        st = launch_state<D, R>(pb, w.MK8, w.V8, w.Zg, s);
+        st = launch_state<D, R>(pb, w.MK8, w.V8, w.Zg, s, den);
         if (st != PSF_OK) return st;
     }
     if (tm) tm->mark();

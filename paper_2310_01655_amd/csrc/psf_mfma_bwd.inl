@@ -860,22 +860,25 @@ struct LocTile {
 
 // dQ (in-block): own rows = queries, streamed = keys of the same block up to the diagonal.
 //   dq_i = sum_{j <= i} (<g_i, v_j> + c_i) p <q_i, k_j>^(p-1) k_j          -> dQacc fp32 rows
-template <int P, int NW, int D = 64>
+// The launch's last workgroups scan the mirror states' ones column (R: sketch width; DenScan::n_main others come first).
+template <int P, int NW, int D, int R>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_q(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                                          const bf16_t *__restrict__ V, const bf16_t *__restrict__ G_rm,
                                                                          const float *__restrict__ Cc, float *__restrict__ dQacc,
-                                                                         int n, int b)
+                                                                         int n, int b, int t, DenScan den)
 {
     constexpr int KS = D / 16, CT = D / 32, NTHR = 64 * NW, OWN = 32 * NW;
     using Tile = LocTile<D, NTHR>;
     constexpr int BUF = 2 * Tile::BYTES;
+    static_assert(NTHR == kWg, "the scan's workgroup");
     __shared__ __attribute__((aligned(16))) unsigned char stage[2 * BUF];
+    if (den_scan_role<R, NTHR>(den, t, stage)) return;
     const Tile T;
     const int x = T.x, h = T.h, tiles_per_unit = n / OWN;
     // XCD-aware order: consecutive workgroup ids go to different XCDs, so give each XCD a
     // contiguous range of tiles: the workgroups that stream the same rows then share one L2
     int wg = blockIdx.x;
-    if ((gridDim.x & 7) == 0) wg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if ((den.n_main & 7) == 0) wg = (blockIdx.x & 7) * (den.n_main >> 3) + (blockIdx.x >> 3);
     const int u = wg / tiles_per_unit, i0 = (wg % tiles_per_unit) * OWN;
     const int jb = (i0 / b) * b;
     const size_t urow = (size_t)u * n;
@@ -1206,24 +1209,23 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
         PSF_LAUNCH_CHECK();
         st = launch_state<D, R>(pb, w.M8r, w.G8r, w.Rg, s);
         if (st != PSF_OK) return st;
-        hipLaunchKernelGGL((k_den_scan<R>), dim3(R * R / kWg, pb.units), dim3(kWg), 0, s, w.ScPart, w.Rchi, w.Rclo,
-                           pb.t, pb.b / 256, pb.n / 256);
-        PSF_LAUNCH_CHECK();
     }
     if (tm) tm->mark();
     // in-block parts
     {
-        const unsigned grid = (unsigned)(rows / (32 * NWL));
+        const unsigned main = (unsigned)(rows / (32 * NWL));
+        const DenScan den = {w.ScPart, w.Rchi, w.Rclo, pb.b / 256, pb.n / 256, (int)main};
+        const unsigned grid = main + (pb.t > 1 ? (unsigned)(pb.units * (R * R / kWg)) : 0u);
         if constexpr (R == D && P == 4) {
             if (ls) {
-                hipLaunchKernelGGL((k_bwd_local_q<2, NWL, D>), dim3(grid), dim3(64 * NWL), 0, s, rq, rk, v, w.G_rm,
-                                   w.Cc, w.dQacc, pb.n, pb.b);
+                hipLaunchKernelGGL((k_bwd_local_q<2, NWL, D, R>), dim3(grid), dim3(64 * NWL), 0, s, rq, rk, v, w.G_rm,
+                                   w.Cc, w.dQacc, pb.n, pb.b, pb.t, den);
                 PSF_LAUNCH_CHECK();
             }
         }
         if (!ls) {
-            hipLaunchKernelGGL((k_bwd_local_q<P, NWL, D>), dim3(grid), dim3(64 * NWL), 0, s, q, k, v, w.G_rm, w.Cc,
-                               w.dQacc, pb.n, pb.b);
+            hipLaunchKernelGGL((k_bwd_local_q<P, NWL, D, R>), dim3(grid), dim3(64 * NWL), 0, s, q, k, v, w.G_rm, w.Cc,
+                               w.dQacc, pb.n, pb.b, pb.t, den);
             PSF_LAUNCH_CHECK();
         }
     }
