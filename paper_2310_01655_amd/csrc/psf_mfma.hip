@@ -696,7 +696,8 @@ __device__ __forceinline__ void prep_keys_f16_role(PrepLds<D, R> &lds, const bf1
 // F16: for the half-precision state kernel -- role 1 writes fp16 key sketches and their scale
 // (prep_keys_f16_role; MK8 then points to them, Kscale gets one float per 128-token tile), role 2 also
 // writes the value rows as fp16 token octets (V8h; magnitudes beyond the fp16 range saturate).
-template <int D, int R, bool KEYS, bool F16 = false, bool ROWS = false>
+// ALL (with KEYS): all roles in turn in one launch, see kOnePrepParts.
+template <int D, int R, bool KEYS, bool F16 = false, bool ROWS = false, bool ALL = false>
 __global__ __launch_bounds__(kWg, KEYS ? 2 : 4) void k_prep(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                               const bf16_t *__restrict__ V, const bf16_t *__restrict__ G,
                                               int n, int heads, int per_head, size_t g_len, int tiles_per_wg,
@@ -707,10 +708,12 @@ __global__ __launch_bounds__(kWg, KEYS ? 2 : 4) void k_prep(const bf16_t *__rest
 {
     // (with_q == 0: the query rows are sketched elsewhere; every workgroup takes role 2)
     __shared__ __attribute__((aligned(16))) PrepLds<D, R> lds;
-    const int role = KEYS ? 1 : (with_q ? 2 * (int)(blockIdx.x % 2) : 2);
-    const size_t part = (KEYS || !with_q) ? blockIdx.x : blockIdx.x / 2;
+    static_assert(!ALL || KEYS, "the registers of the key role");
+    const int roles = with_q ? 3 : 2;                                   // ALL: keys, values, queries
+    const int role = ALL ? (int)(blockIdx.x % roles + 1) % 3 : KEYS ? 1 : (with_q ? 2 * (int)(blockIdx.x % 2) : 2);
+    const size_t part = ALL ? blockIdx.x / roles : (KEYS || !with_q) ? blockIdx.x : blockIdx.x / 2;
     const size_t tok_wg0 = part * (size_t)tiles_per_wg * 128;           // first row of the part (all units)
-    if (!KEYS && role == 2) {
+    if ((!KEYS || ALL) && role == 2) {
         // value rows -> token octets [rows/8][D][8]: one 16-byte store per thread and step
         // (UN outputs per thread and step, all their loads issued before the first is used: the
         // role is bound by memory latency otherwise)
@@ -748,7 +751,7 @@ __global__ __launch_bounds__(kWg, KEYS ? 2 : 4) void k_prep(const bf16_t *__rest
     }
     const int u = (int)(tok_wg0 / n);
     const bf16_t *g = G + (per_head ? (size_t)(u % heads) * g_len : 0);
-    if constexpr (!KEYS)
+    if (!KEYS || (ALL && role == 0))
         prep_sketch_role<D, R, true>(lds, Q, g, tok_wg0, tiles_per_wg, MQ, nullptr, nullptr);
     else if constexpr (F16)
         prep_keys_f16_role<D, R, ROWS>(lds, K, g, tok_wg0, tiles_per_wg, (_Float16 *)MK8, Kscale + part * tiles_per_wg,
@@ -2566,7 +2569,6 @@ __global__ __launch_bounds__(512 / TT, 1) void k_learned_sketch(const bf16_t *__
     }
 }
 
-int sketch_tiles_per_wg(int b);
 
 struct MfmaWs {
     bf16_t *Gt; bf16_t *MQ; float *MK8; bf16_t *V8; bf16_t *Zg; float *Spart; bf16_t *Shi, *Slo;
@@ -2585,15 +2587,34 @@ bool learned_on_mfma(const Problem &pb)
     return pb.learned && (pb.p == 4 || pb.p == 8) && (pb.d == 64 || pb.d == 128) && pb.b % 256 == 0;
 }
 
-// tokens per partial S = m^T m handed to the denominator scan
-int part_tokens(const Problem &pb) { return learned_on_mfma(pb) ? 256 : 128 * sketch_tiles_per_wg(pb.b); }
+struct MfmaWs;
+MfmaWs carve(const Problem &pb, void *ws, int tiles = 0);
+size_t carve_bytes(const Problem &pb, int tiles);
+bool in_block_beside_states(const Problem &pb);
 
-int sketch_tiles_per_wg(int b)
+// 128-token tiles per sketch workgroup, which stays inside one block: eight, so that the matrices staged in LDS are
+// reused, and fewer where that would leave less than kFewParts workgroups a tensor, because a workgroup then is a
+// chain of tiles on an idle chip.  (Blocks that end after four tiles or fewer keep them together: little to gain, and
+// a row's denominator then does not depend on how many units a call has.)  us a call, eight tiles and by this rule: 2048 tokens of r = 32, b = 1024, 1 unit 36.0, 31.6, 12
+// 39.6, 35.2, 48 68.9, 65.9; degree 8 69.5, 41.7 and 73.5, 44.4.  (The partial sums of S that more workgroups leave cost 16
+// KB each at r = 64: not where they would take a call past the library's static scratch.)
+constexpr unsigned kFewParts = 128;
+int sketch_tiles_per_wg(const Problem &pb)
 {
-    int tiles = 8;                               // workgroup = 128 * tiles tokens, inside one block
-    while (b % (tiles * 128) != 0) tiles /= 2;
-    return tiles;
+    int tiles = 8;
+    while (pb.b % (tiles * 128) != 0) tiles /= 2;
+    const size_t rows = (size_t)pb.units * pb.n;
+    int fine = tiles;
+    const int least = in_block_beside_states(pb) ? 2 : 1;   // (its launch deals a sketch part to one or more 256-token tiles)
+    const size_t few = pb.p == 8 ? 2 * kFewParts : kFewParts;   // (degree 8 has six matrices and stages them for every tile)
+    while (tiles == 8 && fine > least && rows / (128 * (size_t)fine) < few) fine /= 2;
+    if (fine != tiles && carve_bytes(pb, fine) > PSF_STATIC_SCRATCH_BYTES && carve_bytes(pb, tiles) <= PSF_STATIC_SCRATCH_BYTES)
+        return tiles;
+    return fine;
 }
+
+// tokens per partial S = m^T m handed to the denominator scan
+int part_tokens(const Problem &pb) { return learned_on_mfma(pb) ? 256 : 128 * sketch_tiles_per_wg(pb); }
 
 // The causal call with exact in-block weights at d = r = 64 runs the in-block part of the output
 // beside the state kernel when the state kernel leaves room for it: at most one state
@@ -2603,6 +2624,11 @@ constexpr int kComputeUnits = 256;
 // of launches, and the separate kernels (matrices transposed once, straight copies into LDS)
 // move the bytes 5 to 13 % faster than k_prep's roles; below, fewer launches win.
 constexpr size_t kPrepMaxRows = (size_t)1 << 22;
+// Up to this many sketch parts a tensor the queries' and values' roles run in the launch of the keys': one launch
+// less, at that role's two workgroups a CU (us a call, two launches and one: 2048 tokens, b = 1024, r = 32, 12 units 48.0,
+// 38.9, 48 74.5, 69.8; 512 tokens, 12 units 23.5, 19.9, 192 58.0, 56.9; no mask, 4096 tokens, 48 units 86.4, 83.5;
+// from 512 parts on nothing is left, and at 786 k rows the light roles lose more by the occupancy: 0.15 -> 0.19 ms).
+constexpr unsigned kOnePrepParts = 384;
 bool in_block_beside_states(const Problem &pb)
 {
     // (and at most 512 tiles of 128 tokens per unit: the half-precision state kernel keeps their scales in LDS)
@@ -2620,12 +2646,12 @@ bool half_precision_states(const Problem &pb)
            pb.n / 128 <= kStateF16Tiles;
 }
 
-MfmaWs carve(const Problem &pb, void *ws)
+MfmaWs carve(const Problem &pb, void *ws, int tiles)
 {
     MfmaWs w;
     const size_t rows = (size_t)pb.units * pb.n, R = pb.r, D = pb.d, tb = pb.t > 1 ? pb.t - 1 : 0;
     const size_t sets = pb.per_head ? pb.heads : 1;
-    const size_t parts = rows / (size_t)part_tokens(pb);
+    const size_t parts = rows / (size_t)(tiles ? 128 * tiles : part_tokens(pb));
     size_t off = 0;
     char *base = (char *)ws;
     auto take = [&](size_t bytes) { char *p = base + off; off += align_up(bytes, 256); return p; };
@@ -2652,6 +2678,8 @@ MfmaWs carve(const Problem &pb, void *ws)
     w.total = off;
     return w;
 }
+
+size_t carve_bytes(const Problem &pb, int tiles) { return carve(pb, nullptr, tiles).total; }
 
 psf_status launch_transpose_g(const Problem &pb, const void *G, bf16_t *Gt, hipStream_t s)
 {
@@ -2756,7 +2784,7 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
                      bf16_t *MK_rm = nullptr, bool noncausal = false)
 {
     MfmaWs w = carve(pb, ws);
-    const int tiles = sketch_tiles_per_wg(pb.b);
+    const int tiles = sketch_tiles_per_wg(pb);
     psf_status st;
     bool v_done = false;                         // value octets already written by the sketch launch
     // the state kernel's launch also runs the in-block part of the output, the denominator scan
@@ -2821,53 +2849,33 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
             if (st != PSF_OK) return st;
         }
         bf16_t *mk_rows = MK_rm ? MK_rm : (pb.local_exact ? nullptr : w.MKrm);
-        if (f16_alone) {
-            hipLaunchKernelGGL((k_prep<D, R, false, true>), dim3(2 * parts), dim3(kWg), 0, s, (const bf16_t *)Q,
-                               (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)G, pb.n, pb.heads,
-                               pb.per_head ? 1 : 0, pb.g_len, tiles, w.MQ, w.MK8, mk_rows, w.Spart, w.V8, 1, w.Kscale,
-                               w.V8h);
-            PSF_LAUNCH_CHECK();
-            if (mk_rows)
-                hipLaunchKernelGGL((k_prep<D, R, true, true, true>), dim3(parts), dim3(kWg), 0, s, (const bf16_t *)Q,
-                                   (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)G, pb.n, pb.heads,
-                                   pb.per_head ? 1 : 0, pb.g_len, tiles, w.MQ, w.MK8, mk_rows, w.Spart, w.V8, 1,
-                                   w.Kscale, w.V8h);
-            else
-                hipLaunchKernelGGL((k_prep<D, R, true, true>), dim3(parts), dim3(kWg), 0, s, (const bf16_t *)Q,
-                                   (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)G, pb.n, pb.heads,
-                                   pb.per_head ? 1 : 0, pb.g_len, tiles, w.MQ, w.MK8, mk_rows, w.Spart, w.V8, 1,
-                                   w.Kscale, w.V8h);
-            PSF_LAUNCH_CHECK();
-        } else if (q_beside) {
-            // the state kernel of this path works in half precision: fp16 value octets and key sketches
-            hipLaunchKernelGGL((k_prep<D, R, false, true>), dim3(parts), dim3(kWg), 0, s, (const bf16_t *)Q,
-                               (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)G, pb.n, pb.heads,
-                               pb.per_head ? 1 : 0, pb.g_len, tiles, w.MQ, w.MK8, mk_rows, w.Spart, w.V8, 0, w.Kscale,
-                               w.V8h);
-            PSF_LAUNCH_CHECK();
-            if (mk_rows)
-                hipLaunchKernelGGL((k_prep<D, R, true, true, true>), dim3(parts), dim3(kWg), 0, s, (const bf16_t *)Q,
-                                   (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)G, pb.n, pb.heads,
-                                   pb.per_head ? 1 : 0, pb.g_len, tiles, w.MQ, w.MK8, mk_rows, w.Spart, w.V8, 1,
-                                   w.Kscale, w.V8h);
-            else
-                hipLaunchKernelGGL((k_prep<D, R, true, true>), dim3(parts), dim3(kWg), 0, s, (const bf16_t *)Q,
-                                   (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)G, pb.n, pb.heads,
-                                   pb.per_head ? 1 : 0, pb.g_len, tiles, w.MQ, w.MK8, mk_rows, w.Spart, w.V8, 1,
-                                   w.Kscale, w.V8h);
-            PSF_LAUNCH_CHECK();
+        // (f16: the state kernel of this path works in half precision: fp16 value octets and key sketches; beside the
+        // states the query rows are sketched there)
+        const int with_q = q_beside ? 0 : 1;
+        const bool f16 = f16_alone || q_beside, one = parts <= kOnePrepParts;
+        auto prep = [&](auto keys, auto half, auto rows, auto all, unsigned wgs) {
+            hipLaunchKernelGGL((k_prep<D, R, decltype(keys)::value, decltype(half)::value, decltype(rows)::value, decltype(all)::value>),
+                               dim3(wgs), dim3(kWg), 0, s, (const bf16_t *)Q, (const bf16_t *)K, (const bf16_t *)V,
+                               (const bf16_t *)G, pb.n, pb.heads, pb.per_head ? 1 : 0, pb.g_len, tiles, w.MQ, w.MK8, mk_rows,
+                               w.Spart, w.V8, with_q, w.Kscale, w.V8h);
+        };
+        constexpr std::true_type yes{};
+        constexpr std::false_type no{};
+        const unsigned all_wgs = (2 + with_q) * parts;
+        if (f16) {
+            if constexpr (D == 64 && R == 64) {
+                if (!one) prep(no, yes, no, no, (1 + with_q) * parts);
+                if (mk_rows && one) prep(yes, yes, yes, yes, all_wgs);
+                else if (mk_rows) prep(yes, yes, yes, no, parts);
+                else if (one) prep(yes, yes, no, yes, all_wgs);
+                else prep(yes, yes, no, no, parts);
+            }
         } else {
-            hipLaunchKernelGGL((k_prep<D, R, false>), dim3(2 * parts), dim3(kWg), 0, s, (const bf16_t *)Q,
-                               (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)G, pb.n, pb.heads,
-                               pb.per_head ? 1 : 0, pb.g_len, tiles, w.MQ, w.MK8, mk_rows, w.Spart, w.V8, 1, nullptr,
-                               nullptr);
-            PSF_LAUNCH_CHECK();
-            hipLaunchKernelGGL((k_prep<D, R, true>), dim3(parts), dim3(kWg), 0, s, (const bf16_t *)Q,
-                               (const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)G, pb.n, pb.heads,
-                               pb.per_head ? 1 : 0, pb.g_len, tiles, w.MQ, w.MK8, mk_rows, w.Spart, w.V8, 1, nullptr,
-                               nullptr);
-            PSF_LAUNCH_CHECK();
+            if (!one) prep(no, no, no, no, 2 * parts);
+            if (one) prep(yes, no, no, yes, all_wgs);
+            else prep(yes, no, no, no, parts);
         }
+        PSF_LAUNCH_CHECK();
         v_done = true;
       }
     } else {
@@ -3180,7 +3188,7 @@ psf_status total_state_impl(const Problem &pb, int src_n, const void *K, const v
     } else {
         st = launch_transpose_g(pb, G, w.Gt, s);
         if (st != PSF_OK) return st;
-        st = launch_sketch<D, R, P>(pb, K, w.Gt, false, nullptr, w.MK8, w.Spart, sketch_tiles_per_wg(pb.b), s, src_n);
+        st = launch_sketch<D, R, P>(pb, K, w.Gt, false, nullptr, w.MK8, w.Spart, sketch_tiles_per_wg(pb), s, src_n);
         if (st != PSF_OK) return st;
     }
     const size_t octets = (size_t)pb.units * pb.n / 8;
