@@ -1362,6 +1362,163 @@ __global__ __launch_bounds__(2 * kWg, 1) void k_state_two_waves(const float *__r
 }
 
 // ------------------------------------------------------------------------------------
+// A snapshot of the states, tile by tile.  A tile is two segments: the rows a and a + 4 and one 16-wide range of
+// b' (beta >= a / 16: only those are stored, see k_state).  Its four planes (octets 2 beta, 2 beta + 1 of both rows, one
+// per wave of the copy) lie 64 bytes apart modulo 256, so that the 16-lane groups of a transposed read meet
+// different banks.
+// Tiles: the 16-wide ranges s0 of the rows in order, in each its 8 row pairs, for each the ranges beta >= s0.  They
+// stream through a ring of four chunks of G tiles, three of them in flight: with two chunks of 32 KB the waves of the
+// gradient's contraction spent two fifths of their time waiting for copies (420 -> 350 us at 24 units of 32768).
+// ------------------------------------------------------------------------------------
+template <int R, int D>
+struct StateTiles {
+    static constexpr int RS = R / 16, VS = D / 16, DW = D / 64;
+    static constexpr int PS = D * 16 + 64, TILE = 4 * PS;      // plane and tile in LDS
+    static constexpr int G = 4 / DW, SLOTS = 4 * G;            // tiles per chunk, of the ring
+    static constexpr int TILES = 8 * (RS * (RS + 1) / 2);
+    static constexpr int LDS_BYTES = SLOTS * TILE;
+    static_assert(LDS_BYTES <= 81920 && TILES % G == 0, "two workgroups per CU");
+    static constexpr int first_tile(int s0) { return s0 == 0 ? 0 : first_tile(s0 - 1) + 8 * (RS - s0 + 1); }
+    static constexpr int range_of(int it)
+    {
+        int s0 = 0;
+        while (s0 + 1 < RS && it >= first_tile(s0 + 1)) ++s0;
+        return s0;
+    }
+    static constexpr int pair_of(int it) { return (it - first_tile(range_of(it))) / (RS - range_of(it)); }
+    static constexpr int beta_of(int it) { return range_of(it) + (it - first_tile(range_of(it))) % (RS - range_of(it)); }
+
+    struct Ring {
+        const unsigned char *from;                             // this wave's plane of the first tile
+        uint32_t to, lane16;
+        __device__ __forceinline__ Ring(const bf16_t *__restrict__ Z, const unsigned char *lds)
+        {
+            const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+            from = (const unsigned char *)Z + (size_t)(4 * (wave / 2) * (R / 8) + wave % 2) * D * 16;
+            to = lds_address(lds) + wave * PS;
+            lane16 = (uint32_t)lane * 16;
+        }
+        // this wave's plane of tile IT
+        template <int IT>
+        __device__ __forceinline__ void stage() const
+        {
+            constexpr int P = pair_of(IT), A = 16 * range_of(IT) + 8 * (P / 4) + P % 4;
+            constexpr int FROM = (A * (R / 8) + 2 * beta_of(IT)) * D * 16, TO = IT % SLOTS * TILE;
+#pragma unroll
+            for (int dw = 0; dw < DW; ++dw) dma16_sbase(from + FROM + dw * 1024, lane16, to + TO + dw * 1024);
+        }
+        // the ring's first tiles
+        __device__ __forceinline__ void fill() const
+        {
+            static_for<SLOTS>([&](auto it) { this->template stage<decltype(it)::value>(); });
+        }
+        // all but the youngest LEFT copies of every wave have landed, and nobody reads the chunk before any more
+        template <int LEFT>
+        static __device__ __forceinline__ void next_chunk()
+        {
+            wait_vmem_le<LEFT>();
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
+        // before the first tile's operands are read (after fill())
+        __device__ __forceinline__ void start() const { next_chunk<(SLOTS - G) * DW>(); }
+        // at the top of tile IT, whose operands have been asked for: from its last tile on a chunk makes room
+        template <int IT>
+        __device__ __forceinline__ void advance() const
+        {
+            if constexpr (IT % G == G - 1 && IT + 1 < TILES) {
+                constexpr int ISSUED = IT + 3 * G + 1 < SLOTS ? SLOTS : (IT + 3 * G + 1 < TILES ? IT + 3 * G + 1 : TILES);
+                constexpr int LEFT = ISSUED - (IT + 1 + G);
+                next_chunk<(LEFT > 0 ? LEFT : 0) * DW>();
+            }
+            constexpr int COPY = IT + 3 * G + 1;
+            if constexpr (COPY >= SLOTS && COPY < TILES) this->template stage<COPY>();
+        }
+    };
+};
+
+// out^T[c][token] += sum_{a <= b'} m[a] m[b'] Zs[a][b'][c] for 32 TT tokens a wave: the features m[a] m[b'] are
+// expanded in registers as the B operand (12 vector instructions per fragment of 16 b', which feeds D / 32 products), the
+// A operand is a fragment of the tile.  vec: m of the lane's token as fp32, entry e of step s = index 16 s + 8 h + e.
+template <int R, int D, int TT>
+struct FeaturesTimesState : StateTiles<R, D> {
+    using Base = StateTiles<R, D>;
+    static constexpr int CT = D / 32;
+    // The ring's first tiles are on their way (Ring::fill).
+    static __device__ __forceinline__ void run(const bf16_t *__restrict__ Z, const f32x8 (&vec)[TT][Base::RS],
+                                               f32x16 (&out)[TT][CT], unsigned char *lds)
+    {
+        constexpr int SLOTS = Base::SLOTS, TILE = Base::TILE, TILES = Base::TILES, PS = Base::PS;
+        const int lane = threadIdx.x & 63, x = lane & 31, h = lane >> 5;
+        const typename Base::Ring ring(Z, lds);
+        // (offsets of a read reach 64 KB: a base for each half of the ring)
+        const unsigned char *const lane_lo = lds + h * PS + x * 16, *const lane_hi = lane_lo + SLOTS / 2 * TILE;
+        bf16x8 zf[2][2][CT];                                   // [tile parity][row a, a + 4][column tile]
+        auto load = [&](auto it_tag) {
+            constexpr int IT = decltype(it_tag)::value, SLOT = IT % SLOTS;
+            const unsigned char *base = SLOT < SLOTS / 2 ? lane_lo + SLOT * TILE : lane_hi + (SLOT - SLOTS / 2) * TILE;
+#pragma unroll
+            for (int w = 0; w < 2; ++w)
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) zf[IT & 1][w][ct] = *(const bf16x8 *)(base + 2 * w * PS + ct * 512);
+        };
+        float ma[2][TT];                                       // m[a], m[a + 4] of the lane's tokens
+        auto rows = [&](auto it_tag) {                         // where a tile starts a row pair
+            constexpr int IT = decltype(it_tag)::value, S0 = Base::range_of(IT), P = Base::pair_of(IT);
+            if constexpr (Base::beta_of(IT) == S0) {
+#pragma unroll
+                for (int w = 0; w < 2; ++w)
+#pragma unroll
+                    for (int tt = 0; tt < TT; ++tt) {
+                        const uint32_t v = __float_as_uint(vec[tt][S0][P % 4 + 4 * w]);
+                        ma[w][tt] = __uint_as_float(__builtin_amdgcn_permlane32_swap(v, v, false, false)[P / 4]);
+                    }
+            }
+        };
+        // fragment q = (row w, token tile tt) of tile IT
+        auto gen = [&](auto it_tag, int w, int tt) {
+            constexpr int BETA = Base::beta_of(decltype(it_tag)::value);
+            f32x8 pr;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) pr[e] = ma[w][tt] * vec[tt][BETA][e];
+            return cvt8(pr);
+        };
+        constexpr std::integral_constant<int, 0> first{};
+        ring.start();
+        load(first);
+        rows(first);
+        bf16x8 frag = gen(first, 0, 0);
+        static_for<TILES>([&](auto it_tag) {
+            constexpr int IT = decltype(it_tag)::value;
+            ring.template advance<IT>();
+            static_for<2 * TT>([&](auto q_tag) {
+                constexpr int q = decltype(q_tag)::value, w = q / TT, tt = q % TT, qn = q + 1;
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (q == 0 && IT + 1 < TILES) load(std::integral_constant<int, IT + 1>{});
+                bf16x8 nxt = frag;
+                if constexpr (qn < 2 * TT) {
+                    nxt = gen(it_tag, qn / TT, qn % TT);
+                } else if constexpr (IT + 1 < TILES) {
+                    constexpr std::integral_constant<int, IT + 1> next{};
+                    rows(next);
+                    nxt = gen(next, 0, 0);
+                }
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) out[tt][ct] = mfma32(zf[IT & 1][w][ct], frag, out[tt][ct]);
+                if constexpr (q == 0 && IT + 1 < TILES) __builtin_amdgcn_sched_group_barrier(0x100, 2 * CT, 0);
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 12 / CT, 0);
+                }
+                frag = nxt;
+            });
+        });
+    }
+};
+
+// ------------------------------------------------------------------------------------
 // Output kernel.  Workgroup = 128*TT consecutive tokens of one block; wave = TT tiles of 32
 // tokens.  All accumulators are D^T-oriented: lane = token, registers = value columns.
 // Both phases are software-pipelined inside a wave so that the MFMAs of the next 32x32 item
@@ -1397,10 +1554,9 @@ constexpr int kKeyTilesInFlight = 4;
 template <int R, int D, int TT, bool LS, int PART>
 constexpr int out_lds_bytes()
 {
-    constexpr int KD = LS ? R : D, TOK_WAVE = 32 * TT, TOK_WG = 4 * TOK_WAVE;
+    constexpr int KD = LS ? R : D, TOK_WAVE = 32 * TT;
     constexpr int KV = TOK_WAVE * KD * 2 + TOK_WAVE * D * 2;
-    constexpr int ZA = 16384 / (R * D);
-    constexpr int CROSS = 2 * (ZA * R * D * 2) + 16 * TOK_WG * 2;
+    constexpr int CROSS = StateTiles<R, D>::LDS_BYTES;
     constexpr int INB = kKeyTilesInFlight * KV;
     return PART == 1 ? INB : (PART == 2 ? CROSS : (CROSS > INB ? CROSS : INB));
 }
@@ -1426,10 +1582,6 @@ __device__ __forceinline__ void out_workgroup(const bf16_t *__restrict__ Q, cons
     constexpr int KV_BYTES = K_BYTES + V_BYTES;           // staged K tile + V tile (16 KB)
     constexpr int NKV = kKeyTilesInFlight;                // key tiles in flight
     constexpr int DMA_KV = KV_BYTES / 16 / kWg;           // copies per thread and tile
-    constexpr int ZA = 16384 / (R * D);                   // sketch rows a per staged Z chunk
-    constexpr int Z_PER_A = R * D;                        // bf16 elements of Z for one a
-    constexpr int Z_CHUNK_BYTES = ZA * Z_PER_A * 2;       // 32 KB
-    constexpr int MQ_STEP_BYTES = 16 * TOK_WG * 2;        // m_i[a] of one 16-wide step of a, bf16 [16][TOK_WG]
     static_assert(K_BYTES % (16 * kWg) == 0 && V_BYTES % (16 * kWg) == 0, "whole copies");
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1685,10 +1837,7 @@ __device__ __forceinline__ void out_workgroup(const bf16_t *__restrict__ Q, cons
             for (int s = 0; s < RS; ++s)
                 mfr[tt][s] = *(const bf16x8 *)&MQ[(urow + tok_w0 + 32 * tt + x) * R + 16 * s + 8 * h];
 
-        // numerator: phi'(q_i)^T Z_l with phi'(q_i) = m_i (x) m_i expanded in registers.  For
-        // sketch row a and 16-wide step s the B operand is B[k = b'][j = token] = m_i[a] * m_i[b']
-        // (12 VALU operations per fragment, each feeding CT MFMAs that accumulate straight into
-        // `out`), the A operand a fragment of Z_l[a] read from LDS.
+        // numerator: phi'(q_i)^T Z_l, see FeaturesTimesState; its first tiles are on their way under the denominators
         f32x8 mb[TT][RS];
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt)
@@ -1698,55 +1847,8 @@ __device__ __forceinline__ void out_workgroup(const bf16_t *__restrict__ Q, cons
                 for (int e = 0; e < 8; ++e) mb[tt][s][e] = (float)mfr[tt][s][e];
 
         const bf16_t *zsrc = Zg + ((size_t)u * (t - 1) + (NONCAUSAL ? 0 : l - 1)) * R * R * D;
-        const uint32_t stage0 = lds_address(stage);
-        constexpr int NCHUNK = R / ZA;
-        constexpr int BUF_BYTES = Z_CHUNK_BYTES;
-        static_assert(PART == 1 || 2 * BUF_BYTES + MQ_STEP_BYTES <= out_lds_bytes<R, D, TT, LS, PART>(), "stage size");
-        // m_i[a] for the 16 sketch rows a of one 16-wide step, bf16 [16][TOK_WG] behind the two Z
-        // buffers, written from the fp32 copies of the B operands when the chunks reach the step:
-        // lane (x, h) holds entries a % 16 = 8 h + e of its tokens.  Every wave writes and reads
-        // only its own tokens, in program order: no barrier is involved.  (A second read of
-        // m(Q) from memory, 8 bytes of every row per chunk, cost an L1 access per lane and chunk:
-        // a tenth of this kernel's time.)
-        constexpr int PER = 16 / ZA;                         // chunks per step
-        static_assert(16 % ZA == 0, "whole chunks per step");
-        uint16_t *mq_step = (uint16_t *)(stage + 2 * BUF_BYTES);
-        // Z is stored with the symmetry weights baked in (see k_state): for sketch row a only
-        // b' >= 16 * (a / 16) contributes, i.e. 16-wide steps s >= s0 = a / 16 and octets >= 2 s0.
-        // All rows of a chunk share s0.
-        static_assert(16 % ZA == 0, "one s0 per chunk");
-        // The needed part of a chunk is copied in 1 KB pieces (one per wave and copy): piece c
-        // covers columns 64 * (c % DW).. of octet 2 s0 + c / (DW * ZA) of row (c / DW) % ZA;
-        // wave w issues the pieces w, w + 4, ...
-        constexpr int DW = D / 64;
-        constexpr int KPA = R * D / 2048;                    // copies per wave and row a, at most
-        static_assert(DW >= 1 && KPA >= 1 && (ZA * DW) % 2 == 0, "piece enumeration");
-        auto z_ncopy = [&](int chunk) { return (R / 8 - 2 * (chunk * ZA / 16)) * ZA * DW / 4; };
-        auto stage_z_k = [&](int buf, int chunk, int k) {
-            const int c = wave + 4 * k;
-            const int off = (((c / DW) % ZA) * (R / 8) + 2 * (chunk * ZA / 16) + c / (DW * ZA)) * D +
-                            (c % DW) * 64;                   // 16-byte units inside the chunk
-            dma16_sbase(zsrc + (size_t)chunk * ZA * Z_PER_A + (size_t)off * 8, (uint32_t)lane * 16,
-                        stage0 + buf * BUF_BYTES + off * 16);
-        };
-        auto store_mq = [&](auto s_tag) {
-            constexpr int S = decltype(s_tag)::value;
-            if constexpr (S < RS) {
-#pragma unroll
-                for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        mq_step[(8 * h + e) * TOK_WG + wave * TOK_WAVE + 32 * tt + x] =
-                            (uint16_t)(__float_as_uint(mb[tt][S][e]) >> 16);      // exact: mb holds bf16 values
-            }
-        };
-        auto gen = [&](float ma, const f32x8 &mbv) {
-            f32x8 pr;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) pr[e] = ma * mbv[e];
-            return cvt8(pr);
-        };
-        for (int k = 0; k < z_ncopy(0); ++k) stage_z_k(0, 0, k);
+        using Features = FeaturesTimesState<R, D, TT>;
+        typename Features::Ring(zsrc, stage).fill();
         // denominator: m_i^T S m_i with S = prefix of m_j m_j^T, hi + lo operands
         {
             const size_t sbase = ((size_t)u * (t - 1) + (NONCAUSAL ? 0 : l - 1)) * R * R;
@@ -1789,74 +1891,7 @@ __device__ __forceinline__ void out_workgroup(const bf16_t *__restrict__ Q, cons
             }
         }
 
-        store_mq(std::integral_constant<int, 0>{});
-        wait_all_memory();
-        __syncthreads();
-        auto chunk_iter = [&](auto s0_tag, int chunk) {
-            const int buf = chunk & 1;
-            // the next chunk's copies are issued a few per row a inside the loop below: issued
-            // back to back they stall this wave on the memory pipeline's queue
-            const int n_copies = chunk + 1 < NCHUNK ? z_ncopy(chunk + 1) : 0;
-            const bf16_t *zc = (const bf16_t *)(stage + buf * BUF_BYTES);
-            const uint16_t *mqs = mq_step + (chunk % PER) * ZA * TOK_WG;
-            auto run_chunk = [&](auto s0_tag) {
-                constexpr int S0 = decltype(s0_tag)::value;  // first 16-wide step with b' >= a
-                constexpr int NS = RS - S0;
-                bf16x8 zf[2][CT][RS];                        // fragments of Z[a], ping-pong over a
-                float ma[2][TT];                             // m_i[a] of this lane's tokens
-                auto load_a = [&](int ai) {
-                    const bf16_t *za = zc + ai * Z_PER_A;
-#pragma unroll
-                    for (int s = S0; s < RS; ++s)
-#pragma unroll
-                        for (int ct = 0; ct < CT; ++ct)
-                            zf[ai & 1][ct][s] = *(const bf16x8 *)&za[((2 * s + h) * D + 32 * ct + x) * 8];
-#pragma unroll
-                    for (int tt = 0; tt < TT; ++tt)
-                        ma[ai & 1][tt] =
-                            __uint_as_float((uint32_t)mqs[ai * TOK_WG + wave * TOK_WAVE + 32 * tt + x] << 16);
-                };
-                load_a(0);
-                bf16x8 frag = gen(ma[0][0], mb[0][S0]);
-#pragma unroll
-                for (int ai = 0; ai < ZA; ++ai) {
-#pragma unroll
-                    for (int c = 0; c < KPA; ++c)
-                        if (ai * KPA + c < n_copies) stage_z_k(buf ^ 1, chunk + 1, ai * KPA + c);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (ai + 1 < ZA) load_a(ai + 1);
-#pragma unroll
-                    for (int it = 0; it < NS * TT; ++it) {
-                        const int s = S0 + it / TT, tt = it % TT, itn = it + 1;
-                        bf16x8 nxt = frag;
-                        if (itn < NS * TT) nxt = gen(ma[ai & 1][itn % TT], mb[itn % TT][S0 + itn / TT]);
-                        else if (ai + 1 < ZA) nxt = gen(ma[(ai + 1) & 1][0], mb[0][S0]);
-#pragma unroll
-                        for (int ct = 0; ct < CT; ++ct)
-                            out[tt][ct] = mfma32(zf[ai & 1][ct][s], frag, out[tt][ct]);
-#pragma unroll
-                        for (int ct = 0; ct < CT; ++ct) {
-                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                            __builtin_amdgcn_sched_group_barrier(0x002, 12 / CT, 0);
-                        }
-                        frag = nxt;
-                    }
-                }
-            };
-            run_chunk(s0_tag);
-            wait_all_memory();
-            __syncthreads();
-        };
-        // one loop per step (the chunks come in the order of their first step s0), each with a
-        // single body, so that the accumulators are carried by simple loops; between two of them
-        // the next step's m_i[a] go to the table
-        static_assert(NCHUNK == RS * PER, "chunks per step");
-        static_for<RS>([&](auto s0_tag) {
-            constexpr int S0 = decltype(s0_tag)::value;
-#pragma unroll 1
-            for (int chunk = S0 * PER; chunk < (S0 + 1) * PER; ++chunk) chunk_iter(s0_tag, chunk);
-            store_mq(std::integral_constant<int, S0 + 1>{});
-        });
+        Features::run(zsrc, mb, out, stage);
     }
 
     if constexpr (PART == 2) {

@@ -380,88 +380,6 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_sketch_rows(const bf16_t *__rest
     }
 }
 
-// ---- generic cross-block contraction ---------------------------------------------------------
-// out^T[o][token] += sum_{a < NS} sum_{k < NV} (sc_token[a] * vec_token[k]) * Z[a][k][o],  Z stored
-// [NS][NV/8][NO][8] bf16 (k octets innermost: 16-byte A fragments with rows o).  The B operand
-// (the products) is generated in registers from the token's scalar sc[a] and its vector vec[.],
-// which the caller holds as fp32 in contraction order (element e of step s = index 16 s + 8 h + e).
-// SYM: Z carries the symmetry weights of the state kernel, steps below 16 (a / 16) are skipped.
-// Workgroup = 128 TT tokens; rows of Z stream through LDS in chunks of ZA, double buffered.
-template <int NS, int NV, int NO, bool SYM, int TT>
-struct Cross {
-    static constexpr int CT = NO / 32, VS = NV / 16;
-    static constexpr int Z_PER = NV * NO;                      // bf16 elements per scalar index
-    static constexpr int ZA = 16384 / Z_PER;                   // scalar indices per chunk (32 KB)
-    static constexpr int CHUNK_BYTES = ZA * Z_PER * 2;
-    static constexpr int NCHUNK = NS / ZA;
-    static constexpr int LDS_BYTES = 2 * CHUNK_BYTES;
-    static constexpr int DMA = CHUNK_BYTES / 16 / kWg;
-    static_assert(ZA >= 1 && ZA <= 8 && 16 % ZA == 0 && NS % ZA == 0, "chunking");
-    typedef __bf16 scvec __attribute__((ext_vector_type(ZA)));
-
-    // sc_rows: bf16 rows [tokens][NS] of the workgroup's first token
-    static __device__ __forceinline__ void run(const bf16_t *__restrict__ sc_rows, const f32x8 (&vec)[TT][VS],
-                                               const bf16_t *__restrict__ Z, f32x16 (&out)[TT][CT],
-                                               unsigned char *stage)
-    {
-        const int tid = threadIdx.x, lane = tid & 63;
-        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-        const int x = lane & 31, h = lane >> 5;
-        auto copy_chunk = [&](int buf, int chunk) {
-            const bf16_t *src = Z + (size_t)chunk * ZA * Z_PER;
-#pragma unroll
-            for (int q = 0; q < DMA; ++q)
-                dma16(src + (size_t)(q * kWg + tid) * 8, stage + buf * CHUNK_BYTES + (size_t)(q * kWg + wave * 64) * 16);
-        };
-        auto load_sc = [&](int chunk, scvec (&dst)[TT]) {
-#pragma unroll
-            for (int tt = 0; tt < TT; ++tt)
-                dst[tt] = *(const scvec *)&sc_rows[(size_t)(wave * 32 * TT + 32 * tt + x) * NS + chunk * ZA];
-        };
-        scvec sc[TT], sc_next[TT];
-        copy_chunk(0, 0);
-        load_sc(0, sc);
-#pragma unroll 1
-        for (int chunk = 0; chunk < NCHUNK; ++chunk) {
-            const int buf = chunk & 1;
-            wait_vmem_le<0>();
-            __syncthreads();                               // chunk landed; the other buffer is free
-            if (chunk + 1 < NCHUNK) {
-                copy_chunk(buf ^ 1, chunk + 1);
-                load_sc(chunk + 1, sc_next);
-            }
-            const bf16_t *zc = (const bf16_t *)(stage + buf * CHUNK_BYTES);
-            const int s0 = SYM ? (chunk * ZA) / 16 : 0;
-#pragma unroll
-            for (int ai = 0; ai < ZA; ++ai) {
-                const bf16_t *za = zc + ai * Z_PER;
-#pragma unroll
-                for (int s = 0; s < VS; ++s) {
-                    if (s < s0) continue;
-                    bf16x8 zf[CT];
-#pragma unroll
-                    for (int ct = 0; ct < CT; ++ct) zf[ct] = *(const bf16x8 *)&za[((2 * s + h) * NO + 32 * ct + x) * 8];
-#pragma unroll
-                    for (int tt = 0; tt < TT; ++tt) {
-                        const float ma = (float)sc[tt][ai];
-                        f32x8 pr;
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) pr[e] = ma * vec[tt][s][e];
-                        const bf16x8 frag = cvt8(pr);
-#pragma unroll
-                        for (int ct = 0; ct < CT; ++ct) out[tt][ct] = mfma32(zf[ct], frag, out[tt][ct]);
-                    }
-                }
-            }
-            if (chunk + 1 < NCHUNK) {
-#pragma unroll
-                for (int tt = 0; tt < TT; ++tt) sc[tt] = sc_next[tt];
-            }
-        }
-        __syncthreads();                                   // the caller may reuse the stage
-    }
-};
-
 // ---- contraction of the states with a row's gradient (or value) --------------------------------
 // dm[e] = sum_b 2 Z[e][b][.] . vec  m[b] for 32 TT tokens a wave, from the snapshots as the state kernel writes
 // them ([a][b'/8][c][8]: b' > a doubled, b' = a once, b' < a zero).  With T[a][b'] = sum_c Zs[a][b'][c] vec[c]:
@@ -477,48 +395,19 @@ struct Cross {
 // and the two halves' sums for a and a + 4 change places with one swap.  Its four planes (octets 2 beta, 2 beta + 1
 // of both rows, one per wave of the copy) lie 64 bytes apart modulo 256, so that the 16-lane groups of a
 // transposed read meet different banks.
-// The tiles stream through a ring of four chunks of G tiles, three of them in flight: with two chunks of 32 KB the
-// waves spent two fifths of their time waiting for the copies.
 template <int R, int D, int TT>
-struct StateTimesRow {
-    static constexpr int RS = R / 16, VS = D / 16, DW = D / 64;
-    static constexpr int PS = D * 16 + 64, TILE = 4 * PS;      // plane and tile in LDS
-    static constexpr int G = 4 / DW, SLOTS = 4 * G;            // tiles per chunk, of the ring
-    static constexpr int TILES = 8 * (RS * (RS + 1) / 2);
-    static constexpr int LDS_BYTES = SLOTS * TILE;
-    static_assert(LDS_BYTES <= 81920 && TILES % G == 0, "two workgroups per CU");
-    // tile it: ranges s0 of the rows in order, in each its 8 row pairs, for each the ranges beta >= s0
-    static constexpr int first_tile(int s0) { return s0 == 0 ? 0 : first_tile(s0 - 1) + 8 * (RS - s0 + 1); }
-    static constexpr int range_of(int it)
-    {
-        int s0 = 0;
-        while (s0 + 1 < RS && it >= first_tile(s0 + 1)) ++s0;
-        return s0;
-    }
-    static constexpr int pair_of(int it) { return (it - first_tile(range_of(it))) / (RS - range_of(it)); }
-    static constexpr int beta_of(int it) { return range_of(it) + (it - first_tile(range_of(it))) % (RS - range_of(it)); }
+struct StateTimesRow : StateTiles<R, D> {
+    using Base = StateTiles<R, D>;
+    using Base::RS;
+    using Base::VS;
+    using Base::PS;
+    using Base::TILE;
+    using Base::TILES;
+    using Base::SLOTS;
+    using Base::range_of;
+    using Base::pair_of;
+    using Base::beta_of;
 
-    // this wave's plane of tile IT
-    template <int IT>
-    static __device__ __forceinline__ void stage(const unsigned char *__restrict__ z_wave, uint32_t lds_wave, uint32_t lane16)
-    {
-        constexpr int P = pair_of(IT), A = 16 * range_of(IT) + 8 * (P / 4) + P % 4;
-        constexpr int FROM = (A * (R / 8) + 2 * beta_of(IT)) * D * 16, TO = IT % SLOTS * TILE;
-#pragma unroll
-        for (int dw = 0; dw < DW; ++dw) dma16_sbase(z_wave + FROM + dw * 1024, lane16, lds_wave + TO + dw * 1024);
-    }
-    // where a wave's planes come from and go to
-    static __device__ __forceinline__ const unsigned char *source(const bf16_t *__restrict__ Z, int wave)
-    {
-        return (const unsigned char *)Z + (size_t)(4 * (wave / 2) * (R / 8) + wave % 2) * D * 16;
-    }
-    static __device__ __forceinline__ void stage_first(const bf16_t *__restrict__ Z, unsigned char *lds)
-    {
-        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        static_for<SLOTS>([&](auto it) {
-            stage<decltype(it)::value>(source(Z, wave), lds_address(lds) + wave * PS, (uint32_t)lane * 16);
-        });
-    }
     // the products of tile IT with the row: m, dm in the order of the accumulators (index 8 range + i)
     template <int IT>
     static __device__ __forceinline__ void consume(const f32x16 &T, const float (&m)[8 * RS], float (&dm)[8 * RS],
@@ -548,10 +437,8 @@ struct StateTimesRow {
     static __device__ __forceinline__ void run(const bf16_t *__restrict__ Z, const bf16x8 (&vec)[TT][VS],
                                                const float (&m)[TT][8 * RS], float (&dm)[TT][8 * RS], unsigned char *lds)
     {
-        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        const int h = lane >> 5, s16 = lane & 15;
-        const unsigned char *const z_wave = source(Z, wave);
-        const uint32_t lds_wave = lds_address(lds) + wave * PS, lane16 = (uint32_t)lane * 16;
+        const int lane = threadIdx.x & 63, h = lane >> 5, s16 = lane & 15;
+        const typename Base::Ring ring(Z, lds);
         // (offsets of a read reach 64 KB: a base for each half of the ring)
         const unsigned char *const lane_lo =
             lds + (2 * ((lane >> 4) & 1) + ((s16 & 3) >> 1)) * PS + (8 * h + (s16 >> 2)) * 16 + (s16 & 1) * 8;
@@ -563,26 +450,13 @@ struct StateTimesRow {
 #pragma unroll
             for (int s = 0; s < VS; ++s) af[IT & 1][s] = read_turned(base + s * 256, base + s * 256 + 64);
         };
-        // chunk c has landed for every wave, and nobody reads the chunk before it any more
-        auto next_chunk = [&](auto left_tag) {
-            wait_vmem_le<decltype(left_tag)::value>();
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-        };
-        next_chunk(std::integral_constant<int, (SLOTS - G) * DW>{});
+        ring.start();
         load(std::integral_constant<int, 0>{});
         float ma[TT], mb[TT], sa[TT], sb[TT];
         f32x16 T[2];
         static_for<TILES>([&](auto it_tag) {
             constexpr int IT = decltype(it_tag)::value;
-            if constexpr (IT % G == G - 1 && IT + 1 < TILES) {
-                constexpr int ISSUED = IT + 3 * G + 1 < SLOTS ? SLOTS : (IT + 3 * G + 1 < TILES ? IT + 3 * G + 1 : TILES);
-                constexpr int LEFT = ISSUED - (IT + 1 + G);
-                next_chunk(std::integral_constant<int, (LEFT > 0 ? LEFT : 0) * DW>{});
-            }
-            constexpr int COPY = IT + 3 * G + 1;               // the slot this tile's chunk before left
-            if constexpr (COPY >= SLOTS && COPY < TILES) stage<COPY>(z_wave, lds_wave, lane16);
+            ring.template advance<IT>();
             static_for<TT>([&](auto tt_tag) {
                 constexpr int tt = decltype(tt_tag)::value, Q = IT * TT + tt;
                 __builtin_amdgcn_sched_barrier(0);
@@ -648,7 +522,7 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_dm(const bf16_t *__restrict__ M,
         for (int at = 0; at < AT; ++at) out[tt][at] = f32x16{0};
     if (has) {
         const bf16_t *z = Zs + ((size_t)u * (t - 1) + slot) * R * R * D;
-        X::stage_first(z, stage);
+        typename X::Ring(z, stage).fill();
         // ones column: (S m)[a] per token with S as hi + lo A operands [b'/8][a][8]
         bf16x8 mfr[TT][RS];
 #pragma unroll
@@ -753,7 +627,7 @@ template <int R, int D, int TT>
 __global__ __launch_bounds__(kWg, 2) void k_bwd_dvc(const bf16_t *__restrict__ MK, const bf16_t *__restrict__ Rg,
                                                    float *__restrict__ dVc, int n, int b, int t)
 {
-    using X = Cross<R, R, D, true, TT>;
+    using X = FeaturesTimesState<R, D, TT>;
     constexpr int CT = D / 32, RS = R / 16, TOK_WG = 128 * TT;
     __shared__ __attribute__((aligned(16))) unsigned char stage[X::LDS_BYTES];
     const int tid = threadIdx.x, lane = tid & 63, x = lane & 31, h = lane >> 5;
@@ -770,6 +644,8 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_dvc(const bf16_t *__restrict__ M
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) out[tt][ct] = f32x16{0};
     if (l < t - 1) {
+        const bf16_t *r = Rg + ((size_t)u * (t - 1) + (t - 2 - l)) * R * R * D;
+        typename X::Ring(r, stage).fill();
         f32x8 vec[TT][RS];
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt)
@@ -779,7 +655,7 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_dvc(const bf16_t *__restrict__ M
 #pragma unroll
                 for (int e = 0; e < 8; ++e) vec[tt][s][e] = (float)raw[e];
             }
-        X::run(MK + (urow + i0) * R, vec, Rg + ((size_t)u * (t - 1) + (t - 2 - l)) * R * R * D, out, stage);
+        X::run(r, vec, out, stage);
     }
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
