@@ -42,8 +42,11 @@ psf_status f32_sketch_pair(const Problem &pb, const void *X1, const void *X2, co
 psf_status f32_sketch_rows(const Problem &pb, const void *X, size_t x_unit, const void *G, float *M, size_t m_unit,
                            hipStream_t s);
 psf_status f32_key_states(const Problem &pb, const F32Plan &pl, const float *MK, const void *V, float *Z, hipStream_t s);
+// share, part: key tiles a workgroup takes where the rows' keys are shared out (0: they are not), and room for the sums
 psf_status f32_rows(const Problem &pb, const F32Plan &pl, const float *MQ, const float *MK, const void *Q,
-                    const void *K, const void *V, const float *Z, void *O, hipStream_t s);
+                    const void *K, const void *V, const float *Z, void *O, hipStream_t s, int share, float *part);
+constexpr int kSlotFloats = 16 * 65;         // sums of a slice: 16 rows of 64 columns and a denominator
+int f32_row_share(const Problem &pb, const F32Plan &pl, size_t part_floats);
 
 // backward pass: G_i as GV [rows][dv] and gden [rows]
 psf_status f32_rows_grad(const Problem &pb, const F32Plan &pl, const float *MQ, const float *MK, const void *Q,

@@ -285,6 +285,8 @@ __device__ __forceinline__ void finish_row(const f4 (&acc)[VT], float D, bool th
 //   WR 1, WK 4: four times the workgroups
 // The sums of a staged tile are formed apart and then added to the total.
 // GRAD: instead of the output, G_i = [dO_i / D_i | -<dO_i, o_i> / D_i] for the backward pass.
+// SPLIT: up to gridDim.z workgroups share the key tiles of the same rows, `share` each, and leave their sums in slots of
+// `part`, in the order of the registers, for f32_rows_sum_kernel (see f32_row_share).
 template <int DT, int RT, int WR, int WK, typename T>
 struct RowsLds {
     static constexpr int P = parts_of<T>(), MT = RT < 2 ? 2 : RT, OP = pitch_of<RT>(), ROWS = 16 * WR;
@@ -304,11 +306,11 @@ struct RowsLds {
     static constexpr int kPlaces = most(most(KT * kRow, kBuffers * WK * kPiece + kOwn), most(kBack, kSums));
 };
 
-template <int DT, int RT, int WR, int WK, bool GRAD, typename T>
+template <int DT, int RT, int WR, int WK, bool GRAD, bool SPLIT, typename T>
 __global__ __launch_bounds__((RowsLds<DT, RT, WR, WK, T>::kThreads), WK == 1 && DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void f32_rows_kernel(
     const float *__restrict__ MQ, const float *__restrict__ MK, const T *__restrict__ Q, const T *__restrict__ K,
     const T *__restrict__ V, const float *__restrict__ Z, T *__restrict__ O, const T *__restrict__ dO,
-    float *__restrict__ GV, float *__restrict__ gden, F32Shape sh)
+    float *__restrict__ GV, float *__restrict__ gden, F32Shape sh, int share, float *__restrict__ part)
 {
     using L = RowsLds<DT, RT, WR, WK, T>;
     constexpr int VT = DT, ROWS = L::ROWS, KT = L::KT, P = L::P, MT = L::MT, KP = L::KP, VP = L::VP, MP = L::MP;
@@ -325,6 +327,10 @@ __global__ __launch_bounds__((RowsLds<DT, RT, WR, WK, T>::kThreads), WK == 1 && 
     const int s_begin = span * sh.span, s_end = min(sh.n, s_begin + sh.span);
     const int i0 = s_begin + (per_span - 1 - at_rows.k) * ROWS;
     if (i0 >= s_end) return;
+    if constexpr (SPLIT) {
+        static_assert(WR == 1 && WK == 4 && DT == 4 && !GRAD, "blocks of 16 rows, tiles of 128 keys, slots");
+        if ((int)blockIdx.z >= row_slices(i0 / 16, sh.n, share, !sh.noncausal)) return;
+    }
     const int wr = wave % WR, wk = wave / WR, iw = i0 + 16 * wr, i = iw + li;
     const int i_last = min(i0 + ROWS, s_end) - 1, iw_last = min(iw + 15, s_end - 1);
     const bool there = i < s_end;
@@ -488,7 +494,10 @@ __global__ __launch_bounds__((RowsLds<DT, RT, WR, WK, T>::kThreads), WK == 1 && 
             if (j0 + KT > bs_wg && sh.vec_x) kt.load(K + (urow + j0) * sh.d, sh.d, nv, sh.d);
             if (j0 < bs_wg_last && sh.vec_m) mt.load(MK + (urow + j0) * sh.mcols, sh.mcols, nv, sh.mcols);
         };
-        const int j_begin = sh.noncausal ? 0 : s_begin;
+        // this workgroup's share of the key tiles
+        const int j_first = sh.noncausal ? 0 : s_begin;
+        const int j_begin = SPLIT ? j_first + (int)blockIdx.z * share * KT : j_first;
+        const int j_stop = SPLIT ? min(j_end, j_begin + share * KT) : j_end;
         fetch(j_begin);
         Parts<P> qf[DT / 2];
         Parts<3> mf[MT / 2];
@@ -500,7 +509,7 @@ __global__ __launch_bounds__((RowsLds<DT, RT, WR, WK, T>::kThreads), WK == 1 && 
             if (sh.local_exact) q_row.parts(qf, sh.d, g);
             m_row.parts(mf, sh.mcols, g);
         }
-        for (int j0 = j_begin; j0 < j_end; j0 += KT, turn ^= 1) {
+        for (int j0 = j_begin; j0 < j_stop; j0 += KT, turn ^= 1) {
             const int nv = min(KT, j_end - j0);
             const bool exact_g = j0 + KT > bs_wg, cross_g = j0 < bs_wg_last;
             __syncthreads();
@@ -519,10 +528,10 @@ __global__ __launch_bounds__((RowsLds<DT, RT, WR, WK, T>::kThreads), WK == 1 && 
             __syncthreads();
             odd = odd_tile[turn] != 0;
             if (threadIdx.x == 0) odd_tile[turn ^ 1] = 0;   // (read for the last time before the barrier above)
-            if (j0 + KT < j_end) fetch(j0 + KT);
-            f4 part[VT];                                    // this tile's sums (two levels of summation)
+            if (j0 + KT < j_stop) fetch(j0 + KT);
+            f4 tile[VT];                                    // this tile's sums (two levels of summation)
             float dpart = 0.f;
-            clear(part);
+            clear(tile);
             for (int sub = wk; sub < KT / 32; sub += WK) {
                 const int js = j0 + 32 * sub;
                 if (js >= j_end || (!sh.noncausal && js > iw_last)) break;
@@ -555,17 +564,17 @@ __global__ __launch_bounds__((RowsLds<DT, RT, WR, WK, T>::kThreads), WK == 1 && 
                 const float flat_w[8] = {w[0][0], w[0][1], w[0][2], w[0][3], w[1][0], w[1][1], w[1][2], w[1][3]};
                 if (odd) {
                     const int vis = j_max - js;             // tile rows 0 .. vis count
-                    add_parts_odd<VT, P>(vs + 32 * sub * VP, KT * VP, VP, flat_w, part, lane,
+                    add_parts_odd<VT, P>(vs + 32 * sub * VP, KT * VP, VP, flat_w, tile, lane,
                                          vis < 0 ? 0u : vis >= 31 ? 0xffffffffu : (2u << vis) - 1u);
                 } else {
                     Parts<3> wp;
                     split8(flat_w, wp);
-                    add_parts<VT, P>(vs + 32 * sub * VP, KT * VP, VP, wp, part, lane);
+                    add_parts<VT, P>(vs + 32 * sub * VP, KT * VP, VP, wp, tile, lane);
                 }
                 settle_parts();
             }
             den += dpart;
-            add_settled(acc, part);
+            add_settled(acc, tile);
         }
     }
 
@@ -593,9 +602,44 @@ __global__ __launch_bounds__((RowsLds<DT, RT, WR, WK, T>::kThreads), WK == 1 && 
             den += from[4 * VT * 64];
         }
     }
+    if constexpr (SPLIT) {
+        const int block = i0 / 16, slices = row_slices(block, sh.n, share, !sh.noncausal);
+        if (slices > 1) {
+            const int before = row_slots_before(block, sh.n, share, !sh.noncausal);
+            const int unit_slots = row_slots_before((sh.n + 15) / 16, sh.n, share, !sh.noncausal);
+            float *const to = part + ((size_t)u * unit_slots + before + blockIdx.z) * kSlotFloats;
+#pragma unroll
+            for (int ct = 0; ct < VT; ++ct) *(f4 *)&to[(ct * 64 + lane) * 4] = acc[ct];
+            if (g == 0) to[1024 + li] = den;
+            return;
+        }
+    }
     if (!there && !GRAD) return;
     const float D = 1.f + den;
     finish_row<VT, GRAD>(acc, D, there, li, g, urow + i, O, dO, GV, gden, sh);
+}
+
+// Adds up what the slices of a block of 16 rows left, in their order, and finishes the rows: a wave a block.
+template <typename T>
+__global__ __launch_bounds__(64) void f32_rows_sum_kernel(const float *__restrict__ part, int share, T *__restrict__ O, F32Shape sh)
+{
+    constexpr int VT = 4;
+    const int lane = threadIdx.x, li = lane & 15, g = lane >> 4, blocks = (sh.n + 15) / 16;
+    const int u = blockIdx.x / blocks, block = blockIdx.x % blocks, i = 16 * block + li, causal = !sh.noncausal;
+    const int slices = row_slices(block, sh.n, share, causal);
+    if (slices < 2) return;
+    const float *from = part + ((size_t)u * row_slots_before(blocks, sh.n, share, causal) +
+                                row_slots_before(block, sh.n, share, causal)) * kSlotFloats;
+    f4 acc[VT];
+    float den = 0.f;
+    clear(acc);
+    for (int sl = 0; sl < slices; ++sl, from += kSlotFloats) {
+#pragma unroll
+        for (int ct = 0; ct < VT; ++ct) acc[ct] += *(const f4 *)&from[(ct * 64 + lane) * 4];
+        den += from[1024 + li];
+    }
+    if (i < sh.n)
+        finish_row<VT, false>(acc, 1.f + den, true, li, g, (size_t)u * sh.n + i, O, (const T *)nullptr, nullptr, nullptr, sh);
 }
 
 template <typename S>
@@ -619,10 +663,13 @@ psf_status states(const Problem &pb, const F32Plan &pl, const float *M, const S 
     });
 }
 
+// `few` of f32_deal for the rows
+constexpr int rows_few(int rt, bool bf16) { return rt == 4 && !bf16 ? 50 : bf16 && rt <= 2 ? 110 : 70; }
+
 template <typename T, bool GRAD>
 psf_status rows_launch(const Problem &pb, const F32Plan &pl, const float *MQ, const float *MK, const void *Q,
                        const void *K, const void *V, const float *Z, void *O, const void *dO, float *GV, float *gden,
-                       hipStream_t s)
+                       hipStream_t s, int share = 0, float *part = nullptr)
 {
     F32Shape sh = f32_shape(pb, pl);
     sh.vec_x = pieces_ok<T>(pb.d, {Q, K});
@@ -635,17 +682,60 @@ psf_status rows_launch(const Problem &pb, const F32Plan &pl, const float *MQ, co
             using L = RowsLds<DT, RT, WR, WK, T>;
             const int per_span = ((pl.span < pb.n ? pl.span : pb.n) + L::ROWS - 1) / L::ROWS;
             const FlatGrid grid = flat_grid(row_groups(pb.units, pl.spans, per_span));
-            hipLaunchKernelGGL((f32_rows_kernel<DT, RT, WR, WK, GRAD, T>), dim3(grid.x, grid.y), dim3(L::kThreads), 0, s,
-                               MQ, MK, (const T *)Q, (const T *)K, (const T *)V, Z, (T *)O, (const T *)dO, GV, gden, sh);
+            auto launch = [&](auto split, unsigned slices) {
+                hipLaunchKernelGGL((f32_rows_kernel<DT, RT, WR, WK, GRAD, decltype(split)::value, T>), dim3(grid.x, grid.y, slices),
+                                   dim3(L::kThreads), 0, s, MQ, MK, (const T *)Q, (const T *)K, (const T *)V, Z, (T *)O,
+                                   (const T *)dO, GV, gden, sh, share, part);
+            };
+            if constexpr (DT == 4 && WR == 1 && WK == 4 && !GRAD) {
+                if (share > 0) {
+                    const int blocks = (pb.n + 15) / 16;
+                    launch(std::true_type{}, (unsigned)row_slices(blocks - 1, pb.n, share, !pl.noncausal));
+                    PSF_LAUNCH_CHECK();
+                    hipLaunchKernelGGL((f32_rows_sum_kernel<T>), dim3((unsigned)(pb.units * blocks)), dim3(64), 0, s, part, share,
+                                       (T *)O, sh);
+                    PSF_LAUNCH_CHECK();
+                    return PSF_OK;
+                }
+            }
+            launch(std::false_type{}, 1u);
             PSF_LAUNCH_CHECK();
             return PSF_OK;
         };
-        constexpr bool PARTS4 = RT == 4 && sizeof(T) == 4;
-        return f32_deal<DT, true, !PARTS4>(pb, pl, RT, PARTS4 ? 50 : sizeof(T) == 2 && RT <= 2 ? 110 : 70, go);
+        return f32_deal<DT, true, !(RT == 4 && sizeof(T) == 4)>(pb, pl, RT, rows_few(RT, sizeof(T) == 2), go);
     });
 }
 
 }  // namespace
+
+// Rows so few that even 16 of them a workgroup leave CUs idle, in a call that keeps no states: the key tiles of the
+// same rows are shared out, as few a workgroup as leave no more than kShareWorkgroups of them (one fills a CU's LDS)
+// and as many slots for their sums as the room of the state records, which such a call does not use, holds.
+// A tile of 128 keys is 3.4 us of a workgroup's chain, the launch that adds the sums 3: at least two tiles shorter.
+// us a call: 1 unit of 1024 tokens, fp32 storage, r = 16 32.5 -> 22.8, r = 64 37.1 -> 27.0; no mask, r = 16 31.0 -> 23.2; 2 units,
+// r = 32 32.8 -> 23.5.  (Room for one tile fewer a workgroup would take the first to 18.)
+constexpr long long kShareWorkgroups = 288;
+int f32_row_share(const Problem &pb, const F32Plan &pl, size_t part_floats)
+{
+    if (pl.states || pl.spans != 1) return 0;
+    bool sixteen = false;
+    with_tiles(pb, [&](auto dt, auto rt) -> psf_status {
+        constexpr int DT = decltype(dt)::value, RT = decltype(rt)::value;
+        return f32_deal<DT, true, true>(pb, pl, RT, rows_few(RT, pb.bf16), [&](auto wr, auto wk) -> psf_status {
+            sixteen = DT == 4 && decltype(wr)::value == 1 && decltype(wk)::value == 4;
+            return PSF_OK;
+        });
+    });
+    if (!sixteen) return 0;
+    const int tiles = (pb.n + 127) / 128, blocks = (pb.n + 15) / 16, causal = !pl.noncausal;
+    for (int share = 1; share + 2 <= tiles; ++share) {
+        const long long slots = row_slots_before(blocks, pb.n, share, causal);
+        const long long whole = causal ? (blocks < 8 * share ? blocks : 8 * share) : 0;
+        if (pb.units * (whole + slots) <= kShareWorkgroups && (size_t)(pb.units * slots) * kSlotFloats <= part_floats)
+            return share;
+    }
+    return 0;
+}
 
 bool f32_supported(const Problem &pb)
 {
@@ -791,10 +881,10 @@ psf_status f32_mirror_states(const Problem &pb, const F32Plan &pl, const float *
 }
 
 psf_status f32_rows(const Problem &pb, const F32Plan &pl, const float *MQ, const float *MK, const void *Q,
-                    const void *K, const void *V, const float *Z, void *O, hipStream_t s)
+                    const void *K, const void *V, const float *Z, void *O, hipStream_t s, int share, float *part)
 {
-    return pb.bf16 ? rows_launch<bf16_t, false>(pb, pl, MQ, MK, Q, K, V, Z, O, nullptr, nullptr, nullptr, s)
-                   : rows_launch<float, false>(pb, pl, MQ, MK, Q, K, V, Z, O, nullptr, nullptr, nullptr, s);
+    return pb.bf16 ? rows_launch<bf16_t, false>(pb, pl, MQ, MK, Q, K, V, Z, O, nullptr, nullptr, nullptr, s, share, part)
+                   : rows_launch<float, false>(pb, pl, MQ, MK, Q, K, V, Z, O, nullptr, nullptr, nullptr, s, share, part);
 }
 
 psf_status f32_rows_grad(const Problem &pb, const F32Plan &pl, const float *MQ, const float *MK, const void *Q,

@@ -79,5 +79,23 @@ PSF_HD double row_walks(int units, int spans, int per_span, int causal, double s
     return causal ? blocks * ((per_span + 1) / 2.0 + state_walk) / (per_span + state_walk) : blocks;
 }
 
+// Rows whose keys several workgroups share (see f32_row_share): a block of 16 rows walks `tiles` tiles of 128 keys of
+// its unit, `share` of them a workgroup.  A block of one workgroup finishes its rows itself; the others leave
+// their sums in slots, numbered unit by unit, block by block, slice by slice.
+PSF_HD int row_slices(int block, int n, int share, int causal)
+{
+    const int tiles = causal ? block / 8 + 1 : (n + 127) / 128;
+    return (tiles + share - 1) / share;
+}
+PSF_HD int row_slots_before(int block, int n, int share, int causal)    // of the blocks 0 .. block - 1 of a unit
+{
+    if (!causal) {
+        const int s = row_slices(0, n, share, 0);
+        return s > 1 ? block * s : 0;
+    }
+    const int per = 8 * share, q = block / per;                         // blocks of q + 1 slices come `per` together
+    return q < 1 ? 0 : per * ((q - 1) * (q + 2) / 2) + (block - q * per) * (q + 1);
+}
+
 }  // namespace psf
 #endif

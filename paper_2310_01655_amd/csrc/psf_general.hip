@@ -448,7 +448,7 @@ psf_status attn_launch(const Problem &pb, const void *Q, const void *K, const vo
             if (st != PSF_OK) return st;
         }
         if (tm) { tm->mark(); tm->mark(); }             // states and their scan
-        st = f32_rows(pb, pl, w.MQ, w.MK, Q, K, V, w.Z, O, s);
+        st = f32_rows(pb, pl, w.MQ, w.MK, Q, K, V, w.Z, O, s, f32_row_share(pb, pl, w.f32.z_floats), w.Z);
         if (tm) tm->mark();
         return st;
     }

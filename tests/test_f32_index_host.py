@@ -79,3 +79,36 @@ def run_host(tmp_path, program):
 
 def test_state_kernel_loads_stay_inside_the_values(tmp_path):
     run_host(tmp_path, PROGRAM)
+
+
+SLOTS = r"""
+#include <cstdio>
+#include "psf_f32_index.h"
+using namespace psf;
+int main()
+{
+    int bad = 0;
+    for (int causal = 0; causal < 2; ++causal)
+        for (int n = 1; n <= 2100; n += n < 300 ? 1 : 37)
+            for (int share = 1; share <= 17; ++share) {
+                int slots = 0, blocks = (n + 15) / 16;
+                for (int block = 0; block <= blocks; ++block) {
+                    if (row_slots_before(block, n, share, causal) != slots && bad++ < 4)
+                        printf("causal %d n %d share %d block %d: %d, not %d\n", causal, n, share, block,
+                               row_slots_before(block, n, share, causal), slots);
+                    const int last = 16 * block + 15 < n ? 16 * block + 15 : n - 1;
+                    const int tiles = causal ? last / 128 + 1 : (n + 127) / 128, s = (tiles + share - 1) / share;
+                    if (block < blocks && row_slices(block, n, share, causal) != s && bad++ < 4)
+                        printf("causal %d n %d share %d block %d: %d slices, not %d\n", causal, n, share, block,
+                               row_slices(block, n, share, causal), s);
+                    slots += s > 1 ? s : 0;
+                }
+            }
+    return bad;
+}
+"""
+
+
+def test_slots_of_shared_rows_are_counted_through(tmp_path):
+    """Where the workgroups that share a block's keys leave their sums, against counting them."""
+    run_host(tmp_path, SLOTS)
