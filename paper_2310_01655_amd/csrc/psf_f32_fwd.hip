@@ -307,10 +307,10 @@ struct RowsLds {
 };
 
 template <int DT, int RT, int WR, int WK, bool GRAD, bool SPLIT, typename T>
-__global__ __launch_bounds__((RowsLds<DT, RT, WR, WK, T>::kThreads), WK == 1 && DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void f32_rows_kernel(
+__device__ __forceinline__ void rows_workgroup(
     const float *__restrict__ MQ, const float *__restrict__ MK, const T *__restrict__ Q, const T *__restrict__ K,
     const T *__restrict__ V, const float *__restrict__ Z, T *__restrict__ O, const T *__restrict__ dO,
-    float *__restrict__ GV, float *__restrict__ gden, F32Shape sh, int share, float *__restrict__ part)
+    float *__restrict__ GV, float *__restrict__ gden, const F32Shape &sh, int share, float *__restrict__ part)
 {
     using L = RowsLds<DT, RT, WR, WK, T>;
     constexpr int VT = DT, ROWS = L::ROWS, KT = L::KT, P = L::P, MT = L::MT, KP = L::KP, VP = L::VP, MP = L::MP;
@@ -619,6 +619,23 @@ __global__ __launch_bounds__((RowsLds<DT, RT, WR, WK, T>::kThreads), WK == 1 && 
     finish_row<VT, GRAD>(acc, D, there, li, g, urow + i, O, dO, GV, gden, sh);
 }
 
+template <int DT, int RT, int WR, int WK, bool GRAD, typename T>
+__global__ __launch_bounds__((RowsLds<DT, RT, WR, WK, T>::kThreads), WK == 1 && DT == 4 ? (RT <= 2 ? 3 : 2) : 1) void f32_rows_kernel(
+    const float *__restrict__ MQ, const float *__restrict__ MK, const T *__restrict__ Q, const T *__restrict__ K,
+    const T *__restrict__ V, const float *__restrict__ Z, T *__restrict__ O, const T *__restrict__ dO,
+    float *__restrict__ GV, float *__restrict__ gden, F32Shape sh)
+{
+    rows_workgroup<DT, RT, WR, WK, GRAD, false, T>(MQ, MK, Q, K, V, Z, O, dO, GV, gden, sh, 0, nullptr);
+}
+
+template <int RT, typename T>
+__global__ __launch_bounds__((RowsLds<4, RT, 1, 4, T>::kThreads), 1) void f32_shared_rows_kernel(
+    const float *__restrict__ MQ, const float *__restrict__ MK, const T *__restrict__ Q, const T *__restrict__ K,
+    const T *__restrict__ V, T *__restrict__ O, F32Shape sh, int share, float *__restrict__ part)
+{
+    rows_workgroup<4, RT, 1, 4, false, true, T>(MQ, MK, Q, K, V, nullptr, O, nullptr, nullptr, nullptr, sh, share, part);
+}
+
 // Adds up what the slices of a block of 16 rows left, in their order, and finishes the rows: a wave a block.
 template <typename T>
 __global__ __launch_bounds__(64) void f32_rows_sum_kernel(const float *__restrict__ part, int share, T *__restrict__ O, F32Shape sh)
@@ -682,15 +699,12 @@ psf_status rows_launch(const Problem &pb, const F32Plan &pl, const float *MQ, co
             using L = RowsLds<DT, RT, WR, WK, T>;
             const int per_span = ((pl.span < pb.n ? pl.span : pb.n) + L::ROWS - 1) / L::ROWS;
             const FlatGrid grid = flat_grid(row_groups(pb.units, pl.spans, per_span));
-            auto launch = [&](auto split, unsigned slices) {
-                hipLaunchKernelGGL((f32_rows_kernel<DT, RT, WR, WK, GRAD, decltype(split)::value, T>), dim3(grid.x, grid.y, slices),
-                                   dim3(L::kThreads), 0, s, MQ, MK, (const T *)Q, (const T *)K, (const T *)V, Z, (T *)O,
-                                   (const T *)dO, GV, gden, sh, share, part);
-            };
             if constexpr (DT == 4 && WR == 1 && WK == 4 && !GRAD) {
                 if (share > 0) {
                     const int blocks = (pb.n + 15) / 16;
-                    launch(std::true_type{}, (unsigned)row_slices(blocks - 1, pb.n, share, !pl.noncausal));
+                    const unsigned slices = (unsigned)row_slices(blocks - 1, pb.n, share, !pl.noncausal);
+                    hipLaunchKernelGGL((f32_shared_rows_kernel<RT, T>), dim3(grid.x, grid.y, slices), dim3(L::kThreads), 0, s, MQ,
+                                       MK, (const T *)Q, (const T *)K, (const T *)V, (T *)O, sh, share, part);
                     PSF_LAUNCH_CHECK();
                     hipLaunchKernelGGL((f32_rows_sum_kernel<T>), dim3((unsigned)(pb.units * blocks)), dim3(64), 0, s, part, share,
                                        (T *)O, sh);
@@ -698,7 +712,8 @@ psf_status rows_launch(const Problem &pb, const F32Plan &pl, const float *MQ, co
                     return PSF_OK;
                 }
             }
-            launch(std::false_type{}, 1u);
+            hipLaunchKernelGGL((f32_rows_kernel<DT, RT, WR, WK, GRAD, T>), dim3(grid.x, grid.y), dim3(L::kThreads), 0, s,
+                               MQ, MK, (const T *)Q, (const T *)K, (const T *)V, Z, (T *)O, (const T *)dO, GV, gden, sh);
             PSF_LAUNCH_CHECK();
             return PSF_OK;
         };
