@@ -3,14 +3,14 @@
 //
 // Kernels (R = sketch size r, D = head size d = dv, b = block size, t = n/b):
 //   k_prep         degree 4 with Gaussian sketches: Algorithm 1 on bf16 MFMA for the query rows
-//                  (m(Q) row-major bf16), for the key rows (m(K) as "token octets", see below, and
+//                  (m(Q) row-major bf16) and for the key rows (m(K) as "token octets", see below, and
 //                  the partial sums S = m(K)^T m(K) per workgroup: the "ones" column of
-//                  H_l = phi'(K_l)^T [V_l | 1], because phi' = m (x) m) and V -> [n/8][D][8] bf16,
-//                  as roles of two launches (queries + values at four workgroups per CU, keys
-//                  at two); the sketch matrices are transposed on their way into LDS.  m(K) is
-//                  stored as fp32 octets [n/8][2][R][4], or, for the half-precision state
-//                  kernel, as fp16 octets [n/8][R][8] scaled by a power of two per 128 tokens.
-//   k_transpose_g, k_sketch, k_v_octets
+//                  H_l = phi'(K_l)^T [V_l | 1], because phi' = m (x) m), as one launch or, with many
+//                  parts, as two (queries at four workgroups per CU, keys at two); the sketch
+//                  matrices are transposed on their way into LDS.  m(K) is stored as fp32 octets
+//                  [n/8][2][R][4], or, for the half-precision state kernel, as fp16 octets
+//                  [n/8][R][8] scaled by a power of two per 128 tokens, and V as [n/8][D][8] beside it.
+//   k_transpose_g, k_sketch
 //                  the same steps as separate launches: degree 8 (two levels, the first level's
 //                  accumulators are the second level's operands) and the backward pass.
 //   den_scan_role  prefix of the S partials over blocks, stored as bf16 hi + lo MFMA operands: the last
@@ -162,6 +162,36 @@ __device__ __forceinline__ void wait_vmem_le()
 {
     static_assert(N >= 0 && N < 64, "vmcnt is 6 bits");
     __builtin_amdgcn_s_waitcnt((N & 0xF) | (0x7 << 4) | (0xF << 8) | ((N >> 4) << 14));
+}
+
+// Rows of D 16-bit values staged in LDS as they lie in memory: the 16-byte piece p of row j at p ^ row_swz(j).  Plain
+// reads (one piece of 16 consecutive rows) and transposed ones (two neighbouring pieces of 4 consecutive
+// rows a 16-lane group, four pieces two groups) meet every bank once, with 32 banks as with 64.  Period: 16 rows.
+// With it values are read where the caller has them; a pass that laid them out first, at the rate of a copy, cost
+// (us a call, with and without): 60 units of 4096, no mask 97, 87; gradients of 96 units of 4096, d = 64 838, 778, 16 units of
+// 16384, d = 128 2238, 2048; causal, 24 units of 32768 807, 768.
+template <int D>
+__device__ __forceinline__ int row_swz(int j)
+{
+    static_assert(D == 64 || D == 128, "8 or 16 pieces");
+    if constexpr (D == 64) return ((j & 3) << 1) ^ ((j >> 2) & 1) ^ ((j >> 2) & 2);
+    else return ((j & 1) * 10) ^ ((j & 2) << 1) ^ ((j >> 2) & 1) ^ (j & 8);
+}
+// Where lane `lane` of a copy that moves rows of D values, 16 bytes a lane, takes its piece from.
+template <int D>
+__device__ __forceinline__ uint32_t row_copy_offset(int lane)
+{
+    constexpr int PIECES = D / 8;
+    const int row = lane / PIECES;
+    return (uint32_t)((row * PIECES + (lane % PIECES ^ row_swz<D>(row))) * 16);
+}
+// Byte offset of this lane's read for a transposed fragment of staged rows: columns 32 ct .. of the four rows that
+// start at row j0 (a multiple of four) of the lane's 16-lane group.
+template <int D>
+__device__ __forceinline__ uint32_t row_turned_offset(int lane, int j0, int ct)
+{
+    const int s16 = lane & 15, j = j0 + s16 / 4, p = 4 * ct + 2 * ((lane >> 4) & 1) + (s16 % 4) / 2;
+    return (uint32_t)((j * (D / 8) + (p ^ row_swz<D>(j))) * 16 + (s16 & 1) * 8);
 }
 
 // ------------------------------------------------------------------------------------
@@ -401,29 +431,6 @@ __global__ __launch_bounds__(kWg) void k_sketch(const bf16_t *__restrict__ X,
                 }
             }
     }
-}
-
-// V [rows][D] -> V8 [rows/8][D][8] (bf16 bits moved, not converted)
-template <int D>
-__global__ __launch_bounds__(kWg) void k_v_octets(const bf16_t *__restrict__ V,
-                                                  bf16_t *__restrict__ V8, size_t octets,
-                                                  unsigned oct_per_unit, unsigned gap)
-{
-    // oct_per_unit != 0: `gap` more rows of V follow the ones taken of every unit
-    const size_t idx = (size_t)blockIdx.x * kWg + threadIdx.x;
-    if (idx >= octets * D) return;
-    const size_t oct = idx / D;
-    const int c = (int)(idx % D);
-    const size_t row = oct * 8 + (oct_per_unit ? (size_t)((unsigned)oct / oct_per_unit) * gap : 0);
-    uint16_t tmp[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) tmp[j] = V[(row + j) * D + c];
-    uint4 pk;
-    pk.x = tmp[0] | ((uint32_t)tmp[1] << 16);
-    pk.y = tmp[2] | ((uint32_t)tmp[3] << 16);
-    pk.z = tmp[4] | ((uint32_t)tmp[5] << 16);
-    pk.w = tmp[6] | ((uint32_t)tmp[7] << 16);
-    *(uint4 *)&V8[idx * 8] = pk;
 }
 
 // ------------------------------------------------------------------------------------
@@ -690,12 +697,12 @@ __device__ __forceinline__ void prep_keys_f16_role(PrepLds<D, R> &lds, const bf1
         }
 }
 
-// KEYS = false: roles 0 and 2 alternate (few registers, four workgroups per CU); KEYS = true: role 1
-// alone (its S accumulators make it the register-heavy one; as one launch with the others it
+// KEYS = false: the queries' sketch and, with F16, the values (few registers, four workgroups per CU); KEYS = true:
+// the keys alone (their S accumulators make that role the register-heavy one; as one launch with the others it
 // would pull them down to its occupancy).
 // F16: for the half-precision state kernel -- role 1 writes fp16 key sketches and their scale
-// (prep_keys_f16_role; MK8 then points to them, Kscale gets one float per 128-token tile), role 2 also
-// writes the value rows as fp16 token octets (V8h; magnitudes beyond the fp16 range saturate).
+// (prep_keys_f16_role; MK8 then points to them, Kscale gets one float per 128-token tile), role 2 the value rows as
+// fp16 token octets (V8h; magnitudes beyond the fp16 range saturate).
 // ALL (with KEYS): all roles in turn in one launch, see kOnePrepParts.
 template <int D, int R, bool KEYS, bool F16 = false, bool ROWS = false, bool ALL = false>
 __global__ __launch_bounds__(kWg, KEYS ? 2 : 4) void k_prep(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
@@ -703,51 +710,45 @@ __global__ __launch_bounds__(kWg, KEYS ? 2 : 4) void k_prep(const bf16_t *__rest
                                               int n, int heads, int per_head, size_t g_len, int tiles_per_wg,
                                               bf16_t *__restrict__ MQ, float *__restrict__ MK8,
                                               bf16_t *__restrict__ MK_rm, float *__restrict__ Spart,
-                                              bf16_t *__restrict__ V8, int with_q,
-                                              float *__restrict__ Kscale, _Float16 *__restrict__ V8h)
+                                              int with_q, float *__restrict__ Kscale, _Float16 *__restrict__ V8h)
 {
-    // (with_q == 0: the query rows are sketched elsewhere; every workgroup takes role 2)
+    // (with_q == 0: the query rows are sketched elsewhere)
     __shared__ __attribute__((aligned(16))) PrepLds<D, R> lds;
     static_assert(!ALL || KEYS, "the registers of the key role");
-    const int roles = with_q ? 3 : 2;                                   // ALL: keys, values, queries
-    const int role = ALL ? (int)(blockIdx.x % roles + 1) % 3 : KEYS ? 1 : (with_q ? 2 * (int)(blockIdx.x % 2) : 2);
-    const size_t part = ALL ? blockIdx.x / roles : (KEYS || !with_q) ? blockIdx.x : blockIdx.x / 2;
+    // the roles of the launch, in turn: keys (1), values (2), queries (0), those it has of them
+    const int values = F16 && (!KEYS || ALL) ? 1 : 0, queries = with_q && (!KEYS || ALL) ? 1 : 0, roles = (KEYS ? 1 : 0) + values + queries;
+    const int turn = (int)(blockIdx.x % roles) + (KEYS ? 0 : 1);
+    const int role = turn == 0 ? 1 : turn == 1 && values ? 2 : 0;
+    const size_t part = blockIdx.x / roles;
     const size_t tok_wg0 = part * (size_t)tiles_per_wg * 128;           // first row of the part (all units)
-    if ((!KEYS || ALL) && role == 2) {
-        // value rows -> token octets [rows/8][D][8]: one 16-byte store per thread and step
-        // (UN outputs per thread and step, all their loads issued before the first is used: the
-        // role is bound by memory latency otherwise)
-        constexpr int UN = 4;
-        const size_t first = tok_wg0 / 8 * D, count = (size_t)tiles_per_wg * 16 * D;   // count % (UN * kWg) == 0
-        static_assert((16 * D) % (UN * kWg) == 0, "whole steps per 128-token tile");
-        for (size_t i0 = threadIdx.x; i0 < count; i0 += UN * kWg) {
-            uint16_t tmp[UN][8];
+    if constexpr (F16 && (!KEYS || ALL)) {
+        if (role == 2) {
+            // value rows -> fp16 token octets [rows/8][D][8]: one 16-byte store per thread and step
+            // (UN outputs per thread and step, all their loads issued before the first is used: the
+            // role is bound by memory latency otherwise)
+            constexpr int UN = 4;
+            const size_t first = tok_wg0 / 8 * D, count = (size_t)tiles_per_wg * 16 * D;   // count % (UN * kWg) == 0
+            static_assert((16 * D) % (UN * kWg) == 0, "whole steps per 128-token tile");
+            for (size_t i0 = threadIdx.x; i0 < count; i0 += UN * kWg) {
+                uint16_t tmp[UN][8];
 #pragma unroll
-            for (int q = 0; q < UN; ++q) {
-                const size_t idx = first + i0 + (size_t)q * kWg, oct = idx / D;
-                const int c = (int)(idx % D);
+                for (int q = 0; q < UN; ++q) {
+                    const size_t idx = first + i0 + (size_t)q * kWg, oct = idx / D;
+                    const int c = (int)(idx % D);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) tmp[q][j] = V[(oct * 8 + j) * D + c];
-            }
+                    for (int j = 0; j < 8; ++j) tmp[q][j] = V[(oct * 8 + j) * D + c];
+                }
 #pragma unroll
-            for (int q = 0; q < UN; ++q) {
-                const size_t idx = first + i0 + (size_t)q * kWg;
-                uint4 pk;
-                pk.x = tmp[q][0] | ((uint32_t)tmp[q][1] << 16);
-                pk.y = tmp[q][2] | ((uint32_t)tmp[q][3] << 16);
-                pk.z = tmp[q][4] | ((uint32_t)tmp[q][5] << 16);
-                pk.w = tmp[q][6] | ((uint32_t)tmp[q][7] << 16);
-                *(uint4 *)&V8[idx * 8] = pk;
-                if constexpr (F16) {
+                for (int q = 0; q < UN; ++q) {
                     f16x8 hv;
 #pragma unroll
                     for (int j = 0; j < 8; ++j)
                         hv[j] = (_Float16)fminf(fmaxf(bf16_to_f32(tmp[q][j]), -65504.f), 65504.f);
-                    *(f16x8 *)&V8h[idx * 8] = hv;
+                    *(f16x8 *)&V8h[(first + i0 + (size_t)q * kWg) * 8] = hv;
                 }
             }
+            return;
         }
-        return;
     }
     const int u = (int)(tok_wg0 / n);
     const bf16_t *g = G + (per_head ? (size_t)(u % heads) * g_len : 0);
@@ -909,8 +910,8 @@ struct StateLds {
 // run under the other wave's MFMAs; at a block boundary the two exchange partial sums through
 // LDS so that each holds (and stores) the whole of one of the two tiles.
 template <int R, int D, int NA, bool SYM, int TC, int NG>
-__device__ __forceinline__ void state_body(const float *__restrict__ M8, const bf16_t *__restrict__ V8,
-                                           bf16_t *__restrict__ Zg, int n, int b, int t, int u, int grp,
+__device__ __forceinline__ void state_body(const float *__restrict__ M8, const bf16_t *__restrict__ V, size_t v_unit,
+                                           int v_mirror, bf16_t *__restrict__ Zg, int n, int b, int t, int u, int grp,
                                            unsigned char *lds_base)
 {
     constexpr int NB = R / 32;                 // 32-wide b' ranges
@@ -956,17 +957,27 @@ __device__ __forceinline__ void state_body(const float *__restrict__ M8, const b
         for (int j = 0; j < CT; ++j) acc[i][j] = f32x16{0};
 
     const float *gm = M8 + (size_t)u * n * R;
-    const bf16_t *gv = V8 + (size_t)u * n * D;
-    const int chunks = (t - 1) * (b / TC), chunks_per_block = b / TC;
+    const bf16_t *gv = V + (size_t)u * v_unit;
+    const int chunks_per_block = b / TC;
 
     // Ring slots are compile-time constants (the chunk loop dispatches on the slot), so every
     // LDS address below is a per-lane base plus an immediate and the copies take a scalar base.
     const uint32_t copy_off = (uint32_t)(tid & 255) * 16;     // lane's byte offset inside a 4 KB piece
+    const uint32_t copy_off_v = row_copy_offset<D>(tid & 255);
     const uint32_t lds0 = lds_address(lds_base);
-    auto stage = [&](auto slot_tag, int chunk) {              // straight copies: global layout == LDS layout
+    // chunk r of block l, the last chunk past the end; r < 2 chunks_per_block
+    auto stage = [&](auto slot_tag, int l, int r) {           // straight copies: global layout == LDS layout but for the swizzle of V
         constexpr int SLOT = decltype(slot_tag)::value;
+        if (r >= chunks_per_block) {
+            r -= chunks_per_block;
+            if (++l > t - 2) {
+                l = t - 2;
+                r = chunks_per_block - 1;
+            }
+        }
+        const int chunk = l * chunks_per_block + r, chunk_v = v_mirror ? (t - 1 - l) * chunks_per_block + r : chunk;
         const unsigned char *sm = (const unsigned char *)(gm + (size_t)chunk * TC * R);
-        const unsigned char *sv = (const unsigned char *)(gv + (size_t)chunk * TC * D);
+        const unsigned char *sv = (const unsigned char *)(gv + (size_t)chunk_v * TC * D);
         const uint32_t dst = lds0 + SLOT * BUF_BYTES;
         // (the wave groups share the pieces: group g copies pieces g, g + NG, ...)
 #pragma unroll
@@ -977,13 +988,18 @@ __device__ __forceinline__ void state_body(const float *__restrict__ M8, const b
 #pragma unroll
         for (int qq = 0; qq < V_BYTES / 4096 / NG; ++qq) {
             const int q = qq * NG + wg2;
-            dma16_sbase(sv + q * 4096, copy_off, dst + M_LDS + q * 4096 + wave * 1024);
+            dma16_sbase(sv + q * 4096, copy_off_v, dst + M_LDS + q * 4096 + wave * 1024);
         }
     };
     // step S of this wave is step NG * S + wg2 of the chunk: the parity sits in the lane bases
     const unsigned char *lane_b = lds_base + (h * 2 * PS + bcol * 16) + wg2 * 4 * PS;
     const unsigned char *lane_a = lds_base + ((h * 2 + q_src) * PS + a_src * 16) + wg2 * 4 * PS;
-    const unsigned char *lane_v = lds_base + M_LDS + ((h * D + x) * 16) + wg2 * 2 * D * 16;
+    const unsigned char *lane_v[2][CT];                       // tokens 8 h + 0..3 and + 4..7 of the step
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+            lane_v[e][ct] = lds_base + M_LDS + wg2 * 2 * D * 16 + row_turned_offset<D>(lane, 8 * h + 4 * e, ct);
     auto load_ops = [&](auto slot_tag, auto step_tag) {
         constexpr int OFF = decltype(slot_tag)::value * BUF_BYTES;
         constexpr int S = decltype(step_tag)::value * NG;     // octet 2 (S + wg2) + h
@@ -994,7 +1010,8 @@ __device__ __forceinline__ void state_body(const float *__restrict__ M8, const b
         for (int e = 0; e < 4; ++e) { o.bfv[e] = b_lo[e]; o.bfv[4 + e] = b_hi[e]; }
         o.af = *(const f32x4 *)(lane_a + OFF + S * 4 * PS);
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) o.vf[ct] = *(const bf16x8 *)(lane_v + OFF + S * 2 * D * 16 + ct * 32 * 16);
+        for (int ct = 0; ct < CT; ++ct)
+            o.vf[ct] = read_turned(lane_v[0][ct] + OFF + S * 2 * D * 16, lane_v[1][ct] + OFF + S * 2 * D * 16);
         return o;
     };
     auto snapshot = [&](int l) {
@@ -1071,9 +1088,9 @@ __device__ __forceinline__ void state_body(const float *__restrict__ M8, const b
     // Before the last step the next chunk must have landed for every wave (wait + barrier);
     // after that barrier nobody reads this chunk's buffer again, so the next iteration may
     // refill it.
-    auto run_chunk = [&](auto slot_tag, int chunk) {
+    auto run_chunk = [&](auto slot_tag, int l, int cb) {
         constexpr int SLOT = decltype(slot_tag)::value;
-        stage(std::integral_constant<int, (SLOT + NBUF - 1) % NBUF>{}, min(chunk + NBUF - 1, chunks - 1));
+        stage(std::integral_constant<int, (SLOT + NBUF - 1) % NBUF>{}, l, cb + SLOT + NBUF - 1);
         static_for<STEPS>([&](auto s_tag) {
             constexpr int s = decltype(s_tag)::value;
             if (s == STEPS - 1) {
@@ -1088,18 +1105,17 @@ __device__ __forceinline__ void state_body(const float *__restrict__ M8, const b
             else
                 ops[(s + 1) & 1] = load_ops(std::integral_constant<int, (SLOT + 1) % NBUF>{},
                                             std::integral_constant<int, 0>{});
-            __builtin_amdgcn_sched_group_barrier(0x100, 3 + CT, 0);   // LDS reads first
+            __builtin_amdgcn_sched_group_barrier(0x100, 3 + 2 * CT, 0);   // LDS reads first
             StateStep<NA, CT, 0>::run(ops[s & 1], ops[(s + 1) & 1], frag, acc);
         });
     };
     // The slots follow each other inside one loop body (a block holds a multiple of NBUF
     // chunks), so the accumulators stay in place from chunk to chunk.
-    int chunk = 0;
 #pragma unroll 1
     for (int l = 0; l < t - 1; ++l) {
 #pragma unroll 1
-        for (int cb = 0; cb < chunks_per_block; cb += NBUF, chunk += NBUF)
-            static_for<NBUF>([&](auto slot_tag) { run_chunk(slot_tag, chunk + decltype(slot_tag)::value); });
+        for (int cb = 0; cb < chunks_per_block; cb += NBUF)
+            static_for<NBUF>([&](auto slot_tag) { run_chunk(slot_tag, l, cb); });
         snapshot(l);
     }
 }
@@ -1115,8 +1131,8 @@ constexpr int state_lds_bytes() { return kStateRing * StateLds<R, D, TC>::BUF + 
 // lds: state_lds_bytes() of workgroup memory, 16-byte aligned; (bid, nblk): this workgroup's
 // index among the nblk state workgroups of the launch (dispatch order).
 template <int R, int D, int NA, bool SYM, int TC, int NG>
-__device__ __forceinline__ void state_workgroup(const float *__restrict__ M8, const bf16_t *__restrict__ V8,
-                                                bf16_t *__restrict__ Zg, int n, int b, int t, int units,
+__device__ __forceinline__ void state_workgroup(const float *__restrict__ M8, const bf16_t *__restrict__ V, size_t v_unit,
+                                                int v_mirror, bf16_t *__restrict__ Zg, int n, int b, int t, int units,
                                                 unsigned char *lds, int bid, int nblk)
 {
     constexpr int NBUF = kStateRing;
@@ -1140,12 +1156,11 @@ __device__ __forceinline__ void state_workgroup(const float *__restrict__ M8, co
     {
         const int tid = threadIdx.x & 255, wave = tid >> 6;
         const int wg2 = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
-        const int chunks = (t - 1) * (b / TC);
         const float *gm = M8 + (size_t)u * n * R;
-        const bf16_t *gv = V8 + (size_t)u * n * D;
+        const bf16_t *gv = V + (size_t)u * v_unit + (v_mirror ? (size_t)(t - 1) * b * D : 0);
 #pragma unroll
         for (int c = 0; c < NBUF - 1; ++c) {
-            const int chunk = min(c, chunks - 1);
+            const int chunk = c;                           // (a block holds a multiple of NBUF chunks)
             unsigned char *dst = lds + c * BUF_BYTES;
 #pragma unroll
             for (int qq = 0; qq < TC * R * 4 / 4096 / NG; ++qq) {
@@ -1156,14 +1171,14 @@ __device__ __forceinline__ void state_workgroup(const float *__restrict__ M8, co
 #pragma unroll
             for (int qq = 0; qq < TC * D * 2 / 4096 / NG; ++qq) {
                 const int q = qq * NG + wg2;
-                dma16(gv + (size_t)chunk * TC * D + (size_t)(q * kWg + tid) * 8,
+                dma16((const unsigned char *)(gv + (size_t)chunk * TC * D + (size_t)q * kWg * 8) + row_copy_offset<D>(tid),
                       dst + M_LDS + (size_t)(q * kWg + wave * 64) * 16);
             }
         }
         wait_vmem_le<(NBUF - 2) * DMA_PER_CHUNK>();
         __syncthreads();
     }
-    state_body<R, D, NA, SYM, TC, NG>(M8, V8, Zg, n, b, t, u, grp, lds);
+    state_body<R, D, NA, SYM, TC, NG>(M8, V, v_unit, v_mirror, Zg, n, b, t, u, grp, lds);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1340,25 +1355,25 @@ __device__ __forceinline__ void state_f16_workgroup(const _Float16 *__restrict__
 
 template <int R, int D, int NA, bool SYM, int TC, int OCC>
 __global__ __launch_bounds__(kWg, OCC) void k_state(const float *__restrict__ M8,
-                                               const bf16_t *__restrict__ V8,
+                                               const bf16_t *__restrict__ V, size_t v_unit, int v_mirror,
                                                bf16_t *__restrict__ Zg, int n, int b, int t,
                                                int units, DenScan den)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[state_lds_bytes<R, D, TC, 1>()];
     if (den_scan_role<R, kWg>(den, t, lds)) return;
-    state_workgroup<R, D, NA, SYM, TC, 1>(M8, V8, Zg, n, b, t, units, lds, blockIdx.x, den.n_main);
+    state_workgroup<R, D, NA, SYM, TC, 1>(M8, V, v_unit, v_mirror, Zg, n, b, t, units, lds, blockIdx.x, den.n_main);
 }
 
 // The symmetric deal with eight waves, two per SIMD (see state_body), one workgroup per CU.
 template <int R, int D, int TC>
 __global__ __launch_bounds__(2 * kWg, 1) void k_state_two_waves(const float *__restrict__ M8,
-                                                                 const bf16_t *__restrict__ V8,
+                                                                 const bf16_t *__restrict__ V, size_t v_unit, int v_mirror,
                                                                  bf16_t *__restrict__ Zg, int n, int b, int t,
                                                                  int units, DenScan den)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[state_lds_bytes<R, D, TC, 2>()];
     if (den_scan_role<R, 2 * kWg>(den, t, lds)) return;
-    state_workgroup<R, D, 2, true, TC, 2>(M8, V8, Zg, n, b, t, units, lds, blockIdx.x, den.n_main);
+    state_workgroup<R, D, 2, true, TC, 2>(M8, V, v_unit, v_mirror, Zg, n, b, t, units, lds, blockIdx.x, den.n_main);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1565,7 +1580,7 @@ constexpr int out_lds_bytes()
 // index among the nblk output workgroups of the launch (dispatch order).
 template <int R, int D, int P, int TT, bool DEN, bool NONCAUSAL, bool LS, int PART>
 __device__ __forceinline__ void out_workgroup(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
-                                              const bf16_t *__restrict__ V8, const bf16_t *__restrict__ MQ,
+                                              const bf16_t *__restrict__ V, const bf16_t *__restrict__ MQ,
                                               const bf16_t *__restrict__ Zg, const bf16_t *__restrict__ Shi,
                                               const bf16_t *__restrict__ Slo, bf16_t *__restrict__ O,
                                               float *__restrict__ Den, float *__restrict__ Pnum,
@@ -1633,8 +1648,8 @@ __device__ __forceinline__ void out_workgroup(const bf16_t *__restrict__ Q, cons
         // K tile in LDS row by row as in memory, [KEYT keys][KD/8 pieces of 8], so that a copy
         // instruction reads whole rows (a lane per 16-byte piece: 16 cache lines per instruction;
         // one key row per lane would be 64), with the pieces of key j stored at piece ^ swz(j): the
-        // A fragments of 8 consecutive keys then fall into different banks.  V tile as
-        // [KEYT/8 octets][D][8].  Both filled by direct global->LDS copies.
+        // A fragments of 8 consecutive keys then fall into different banks.  V tile alike, swizzled for its transposed
+        // reads (row_swz).  Both filled by direct global->LDS copies.
         constexpr int P8 = KD / 8;                               // 16-byte pieces per key row
         static_assert(P8 == 4 || P8 == 8 || P8 == 16, "swizzle");
         auto swz = [](int key) { return P8 >= 8 ? (key & 7) : ((key >> 1) & 3); };
@@ -1645,12 +1660,18 @@ __device__ __forceinline__ void out_workgroup(const bf16_t *__restrict__ Q, cons
         const uint32_t stage0 = lds_address(stage);
         // copy slot q * kWg + tid = (key q * kWg / P8 + tid / P8, piece tid % P8)
         const uint32_t k_lane = (uint32_t)(((tid / P8) * KD + 8 * ((tid % P8) ^ swz(tid / P8))) * 2);
-        const uint32_t v_lane = (uint32_t)tid * 16;
+        const uint32_t v_lane = row_copy_offset<D>(tid);
+        // V^T fragments: columns 32 ct + x, keys in the order of the score registers (16 sp + 8 (e / 4) + 4 h + e % 4)
+        uint32_t v_turned[2][CT];
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) v_turned[e][ct] = row_turned_offset<D>(lane, 8 * e + 4 * h, ct);
         auto stage_kv = [&](int kt) {
             const int ktc = min(kt, ntiles_wg - 1);              // clamped: keeps the copy count uniform
             const uint32_t dst = stage0 + (kt % NKV) * KV_BYTES + wave * 1024;
             const size_t j0 = urow + jb + (size_t)ktc * KEYT;
-            const bf16_t *ksrc = K + j0 * KD, *vsrc = V8 + j0 * D;
+            const bf16_t *ksrc = K + j0 * KD, *vsrc = V + j0 * D;
 #pragma unroll
             for (int q = 0; q < K_BYTES / 16 / kWg; ++q)
                 dma16_sbase(ksrc + q * (kWg / P8) * KD, k_lane, dst + q * 4096);
@@ -1688,13 +1709,13 @@ __device__ __forceinline__ void out_workgroup(const bf16_t *__restrict__ Q, cons
         };
         // out^T += V^T P^T for item q with the packed weights pw
         auto apply_pv = [&](int q, int jsub, int jtt, const bf16x8 *pw) {
-            const bf16_t *vs = (const bf16_t *)(stage + ((q / IPT) % NKV) * KV_BYTES) + KEYT * KD;
+            const unsigned char *vs = stage + ((q / IPT) % NKV) * KV_BYTES + K_BYTES + 32 * jsub * D * 2;
             if (jtt == 0) {                               // fragments serve all token tiles of the sub-tile
 #pragma unroll
                 for (int sp = 0; sp < 2; ++sp)
 #pragma unroll
                     for (int ct = 0; ct < CT; ++ct)
-                        vfr[sp][ct] = *(const bf16x8 *)&vs[((4 * jsub + 2 * sp + h) * D + 32 * ct + x) * 8];
+                        vfr[sp][ct] = read_turned(vs + 16 * sp * D * 2 + v_turned[0][ct], vs + 16 * sp * D * 2 + v_turned[1][ct]);
             }
 #pragma unroll
             for (int sp = 0; sp < 2; ++sp)
@@ -1703,8 +1724,7 @@ __device__ __forceinline__ void out_workgroup(const bf16_t *__restrict__ Q, cons
         };
         // weights of one item: x^p, causal mask (diagonal tile only), bf16 pack, row sums of the
         // packed values.  The score registers give lane (token, h) the keys
-        // 16sp + 8*(e/4) + 4h + e%4; one half-wave swap per register pair turns that into keys
-        // 16sp + 8h + e, so that V^T fragments are whole token octets.
+        // 16sp + 8*(e/4) + 4h + e%4, the order in which the V^T fragments are read.
         auto weights = [&](auto diag_tag, f32x16 &scv, int jtt, int key0, int tok0, bf16x8 *pw) {
             constexpr bool DIAG = decltype(diag_tag)::value;
             const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
@@ -1725,9 +1745,6 @@ __device__ __forceinline__ void out_workgroup(const bf16_t *__restrict__ Q, cons
                 dsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w.y), ones, dsum, false);
                 dsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w.z), ones, dsum, false);
                 dsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w.w), ones, dsum, false);
-                const auto s0 = __builtin_amdgcn_permlane32_swap(w.x, w.z, false, false);
-                const auto s1 = __builtin_amdgcn_permlane32_swap(w.y, w.w, false, false);
-                w.x = s0[0]; w.z = s0[1]; w.y = s1[0]; w.w = s1[1];
                 pw[sp] = __builtin_bit_cast(bf16x8, w);
             }
             den[jtt] = dsum;
@@ -1738,7 +1755,7 @@ __device__ __forceinline__ void out_workgroup(const bf16_t *__restrict__ Q, cons
             constexpr int jn = (j + 1) % IPT, jp = (j + IPT - 1) % IPT;
             constexpr int cur = PAR * (j & 1), nxt = PAR * ((j + 1) & 1);
             constexpr int NM = KS + 2 * CT;                       // MFMAs of one step
-            constexpr int NV = (P == 8 ? 68 : 52) + (decltype(diag_tag)::value ? 48 : 0);
+            constexpr int NV = (P == 8 ? 64 : 48) + (decltype(diag_tag)::value ? 48 : 0);
             const int q = kt * IPT + j;
             __builtin_amdgcn_sched_barrier(0);
             f32x16 sn = score(q + 1, jn / TT, jn % TT);           // garbage past the end, unused
@@ -1747,7 +1764,7 @@ __device__ __forceinline__ void out_workgroup(const bf16_t *__restrict__ Q, cons
             weights(diag_tag, sc[cur], j % TT, jb + kt * KEYT + 32 * (j / TT), tok_w0 + 32 * (j % TT), pw);
             // LDS reads first, a few VALU operations to cover their latency, then one MFMA per
             // share of the remaining VALU work
-            __builtin_amdgcn_sched_group_barrier(0x100, (jn % TT == 0 ? KS : 0) + (jp % TT == 0 ? 2 * CT : 0), 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, (jn % TT == 0 ? KS : 0) + (jp % TT == 0 ? 4 * CT : 0), 0);
             __builtin_amdgcn_sched_group_barrier(0x002, NV / (NM + 1), 0);
 #pragma unroll
             for (int m = 0; m < NM; ++m) {
@@ -1927,7 +1944,7 @@ __device__ __forceinline__ void out_workgroup(const bf16_t *__restrict__ Q, cons
 
 template <int R, int D, int P, int TT, bool DEN, bool NONCAUSAL = false, bool LS = false, int PART = 0>
 __global__ __launch_bounds__(kWg, 2) void k_out(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
-                                                const bf16_t *__restrict__ V8,
+                                                const bf16_t *__restrict__ V,
                                                 const bf16_t *__restrict__ MQ,
                                                 const bf16_t *__restrict__ Zg,
                                                 const bf16_t *__restrict__ Shi,
@@ -1936,7 +1953,7 @@ __global__ __launch_bounds__(kWg, 2) void k_out(const bf16_t *__restrict__ Q, co
                                                 float *__restrict__ Pden, int n, int b, int t)
 {
     __shared__ __attribute__((aligned(16))) unsigned char stage[out_lds_bytes<R, D, TT, LS, PART>()];
-    out_workgroup<R, D, P, TT, DEN, NONCAUSAL, LS, PART>(Q, K, V8, MQ, Zg, Shi, Slo, O, Den, Pnum, Pden, n, b, t,
+    out_workgroup<R, D, P, TT, DEN, NONCAUSAL, LS, PART>(Q, K, V, MQ, Zg, Shi, Slo, O, Den, Pnum, Pden, n, b, t,
                                                          stage, blockIdx.x, gridDim.x);
 }
 
@@ -1965,7 +1982,7 @@ struct BesideStates {
 // F16: the state role runs state_f16_workgroup (M8 then holds the fp16 key sketches).
 template <int R, int D, int P, int TT, bool F16>
 __global__ __launch_bounds__(kWg, 2) void k_state_and_in_block(const float *__restrict__ M8,
-                                                               const bf16_t *__restrict__ V8,
+                                                               const bf16_t *__restrict__ V,
                                                                bf16_t *__restrict__ Zg, int units, int n, int b,
                                                                int t, BesideStates a)
 {
@@ -1980,7 +1997,7 @@ __global__ __launch_bounds__(kWg, 2) void k_state_and_in_block(const float *__re
         if constexpr (F16)
             state_f16_workgroup<R, D>((const _Float16 *)M8, a.V8h, a.Kscale, Zg, n, b, t, units, lds, bid, a.n_state);
         else
-            state_workgroup<R, D, 2, true, TC, 1>(M8, V8, Zg, n, b, t, units, lds, bid, a.n_state);
+            state_workgroup<R, D, 2, true, TC, 1>(M8, V, (size_t)n * D, 0, Zg, n, b, t, units, lds, bid, a.n_state);
         return;
     }
     bid -= a.n_state;
@@ -1999,7 +2016,7 @@ __global__ __launch_bounds__(kWg, 2) void k_state_and_in_block(const float *__re
         prep_sketch_role<D, R, true>(*reinterpret_cast<PrepLds<D, R> *>(lds), a.Q, g, tok_wg0, a.tiles_per_wg, a.MQ,
                                      nullptr, nullptr);
     } else {
-        out_workgroup<R, D, P, TT, false, false, false, 1>(a.Q, a.K, V8, nullptr, nullptr, nullptr, nullptr, nullptr,
+        out_workgroup<R, D, P, TT, false, false, false, 1>(a.Q, a.K, V, nullptr, nullptr, nullptr, nullptr, nullptr,
                                                            nullptr, a.Pnum, a.Pden, n, b, t, lds,
                                                            (bid / period) * a.ratio + bid % period, a.n_tiles);
     }
@@ -2606,7 +2623,7 @@ __global__ __launch_bounds__(512 / TT, 1) void k_learned_sketch(const bf16_t *__
 
 
 struct MfmaWs {
-    bf16_t *Gt; bf16_t *MQ; float *MK8; bf16_t *V8; bf16_t *Zg; float *Spart; bf16_t *Shi, *Slo;
+    bf16_t *Gt; bf16_t *MQ; float *MK8; bf16_t *Zg; float *Spart; bf16_t *Shi, *Slo;
     float *Pnum, *Pden;                          // in-block part of the rows (two-launch output, see k_out)
     _Float16 *V8h; float *Kscale;                // half-precision state kernel: value octets, key scales per part
     float *M32;                                  // learned sketches only: m(x) as fp32 rows
@@ -2693,7 +2710,6 @@ MfmaWs carve(const Problem &pb, void *ws, int tiles)
     w.Gt = (bf16_t *)take(pb.learned ? 0 : sets * pb.g_len * 2);
     w.MQ = (bf16_t *)take(pb.p == 2 ? 0 : rows * R * 2);     // p = 2: m(Q) = Q itself
     w.MK8 = (float *)take(rows * R * 4);
-    w.V8 = (bf16_t *)take(rows * D * 2);
     w.Zg = (bf16_t *)take((size_t)pb.units * tb * R * R * D * 2);
     w.Spart = (float *)take(parts * R * R * 4);
     w.Shi = (bf16_t *)take((size_t)pb.units * tb * R * R * 2);
@@ -2741,7 +2757,8 @@ psf_status launch_sketch(const Problem &pb, const void *X, const bf16_t *Gt, boo
     return PSF_OK;
 }
 
-// Running prefix states of (M8, V8) for every unit, snapshots into Zg.
+// Running prefix states of (M8, V) for every unit, snapshots into Zg.  V: rows as they lie, v_unit values from one unit to
+// the next, v_mirror: its blocks in reverse order (M8's are laid so already).
 //
 // Which form: a workgroup walks its unit's tokens in series, a step takes longer the more tiles a wave holds, and all
 // workgroups of a unit stage the same tokens.  us of a whole call of 4096 tokens, no mask unless said:
@@ -2755,7 +2772,8 @@ psf_status launch_sketch(const Problem &pb, const void *X, const bf16_t *Gt, boo
 //   d = 64, r = 64: two tiles a wave, from 80 units on four (below);
 //   d = 128: two tiles a wave of the symmetric deal (config 5: 0.285 -> 0.254 ms for the state stage against full tiles).
 template <int D, int R>
-psf_status launch_state(const Problem &pb, const float *M8, const bf16_t *V8, bf16_t *Zg, hipStream_t s, DenScan den = {})
+psf_status launch_state(const Problem &pb, const float *M8, const bf16_t *V, size_t v_unit, int v_mirror, bf16_t *Zg,
+                        hipStream_t s, DenScan den = {})
 {
     // (the scan of the denominators, where the caller has one: its workgroups fill CUs that the states leave, and
     // come last, so that they never hold one back)
@@ -2767,16 +2785,16 @@ psf_status launch_state(const Problem &pb, const float *M8, const bf16_t *V8, bf
 #define PSF_STATE(NA_, SYM_, TC_, OCC_, WGS)                                                                          \
     do {                                                                                                              \
         den.n_main = (int)(WGS);                                                                                      \
-        hipLaunchKernelGGL((k_state<R, D, NA_, SYM_, TC_, OCC_>), dim3((WGS) + scan), dim3(kWg), 0, s, M8, V8, Zg, pb.n, \
-                           pb.b, pb.t, pb.units, den);                                                                \
+        hipLaunchKernelGGL((k_state<R, D, NA_, SYM_, TC_, OCC_>), dim3((WGS) + scan), dim3(kWg), 0, s, M8, V, v_unit, \
+                           v_mirror, Zg, pb.n, pb.b, pb.t, pb.units, den);                                                                \
     } while (0)
     if constexpr (D == 64) {
         // One block only: eight waves, two per SIMD, that split the tokens' steps, 8 % faster per token at r = 64; with a
         // snapshot every block the exchange and the stalled ring after the stores cost more than that.
         if (one_block && grid_sym <= 256 && (R == 64 || 2 * grid_sym > 256)) {
             den.n_main = (int)grid_sym;
-            hipLaunchKernelGGL((k_state_two_waves<R, D, 64>), dim3(grid_sym + scan / 2), dim3(2 * kWg), 0, s, M8, V8, Zg,
-                               pb.n, pb.b, pb.t, pb.units, den);
+            hipLaunchKernelGGL((k_state_two_waves<R, D, 64>), dim3(grid_sym + scan / 2), dim3(2 * kWg), 0, s, M8, V, v_unit,
+                               v_mirror, Zg, pb.n, pb.b, pb.t, pb.units, den);
             PSF_LAUNCH_CHECK();
             return PSF_OK;
         }
@@ -2821,7 +2839,6 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
     MfmaWs w = carve(pb, ws);
     const int tiles = sketch_tiles_per_wg(pb);
     psf_status st;
-    bool v_done = false;                         // value octets already written by the sketch launch
     // the state kernel's launch also runs the in-block part of the output, the denominator scan
     // and, with Gaussian sketches of degree 4, the sketch of the query rows
     // (the backward pass's forward, which also wants the denominators: Gaussian sketches of degree 4 only)
@@ -2892,11 +2909,11 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
             hipLaunchKernelGGL((k_prep<D, R, decltype(keys)::value, decltype(half)::value, decltype(rows)::value, decltype(all)::value>),
                                dim3(wgs), dim3(kWg), 0, s, (const bf16_t *)Q, (const bf16_t *)K, (const bf16_t *)V,
                                (const bf16_t *)G, pb.n, pb.heads, pb.per_head ? 1 : 0, pb.g_len, tiles, w.MQ, w.MK8, mk_rows,
-                               w.Spart, w.V8, with_q, w.Kscale, w.V8h);
+                               w.Spart, with_q, w.Kscale, w.V8h);
         };
         constexpr std::true_type yes{};
         constexpr std::false_type no{};
-        const unsigned all_wgs = (2 + with_q) * parts;
+        const unsigned all_wgs = (1 + (f16 ? 1 : 0) + with_q) * parts;
         if (f16) {
             if constexpr (D == 64 && R == 64) {
                 if (!one) prep(no, yes, no, no, (1 + with_q) * parts);
@@ -2906,12 +2923,11 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
                 else prep(yes, yes, no, no, parts);
             }
         } else {
-            if (!one) prep(no, no, no, no, 2 * parts);
+            if (!one) prep(no, no, no, no, parts);
             if (one) prep(yes, no, no, yes, all_wgs);
             else prep(yes, no, no, no, parts);
         }
         PSF_LAUNCH_CHECK();
-        v_done = true;
       }
     } else {
         st = launch_transpose_g(pb, G, w.Gt, s);
@@ -2921,12 +2937,6 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
         st = launch_sketch<D, R, P>(pb, K, w.Gt, false, MK_rm ? MK_rm : (pb.local_exact ? nullptr : w.MKrm), w.MK8,
                                     w.Spart, tiles, s);
         if (st != PSF_OK) return st;
-    }
-    if (!v_done) {
-        const size_t octets = (size_t)pb.units * pb.n / 8;
-        hipLaunchKernelGGL((k_v_octets<D>), dim3((unsigned)((octets * D + kWg - 1) / kWg)), dim3(kWg), 0,
-                           s, (const bf16_t *)V, w.V8, octets, 0u, 0u);
-        PSF_LAUNCH_CHECK();
     }
     if (tm) tm->mark();
     const DenScan den = {w.Spart, w.Shi, w.Slo, pb.b / part_tokens(pb), pb.n / part_tokens(pb), 0};
@@ -2949,20 +2959,20 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
             a.V8h = w.V8h; a.Kscale = w.Kscale;
             const dim3 grid((unsigned)(a.n_state + a.n_den + n_tiles + n_q));
             if (q_beside)
-                hipLaunchKernelGGL((k_state_and_in_block<R, D, P, TT, true>), grid, dim3(kWg), 0, s, w.MK8, w.V8, w.Zg,
+                hipLaunchKernelGGL((k_state_and_in_block<R, D, P, TT, true>), grid, dim3(kWg), 0, s, w.MK8, (const bf16_t *)V, w.Zg,
                                    pb.units, pb.n, pb.b, pb.t, a);
             else
-                hipLaunchKernelGGL((k_state_and_in_block<R, D, P, TT, false>), grid, dim3(kWg), 0, s, w.MK8, w.V8, w.Zg,
+                hipLaunchKernelGGL((k_state_and_in_block<R, D, P, TT, false>), grid, dim3(kWg), 0, s, w.MK8, (const bf16_t *)V, w.Zg,
                                    pb.units, pb.n, pb.b, pb.t, a);
             PSF_LAUNCH_CHECK();
             if (tm) tm->mark();
             if (Den)
                 hipLaunchKernelGGL((k_out<R, D, P, TT, true, false, false, 2>), dim3((unsigned)n_tiles), dim3(kWg), 0, s,
-                                   (const bf16_t *)Q, (const bf16_t *)K, w.V8, w.MQ, w.Zg, w.Shi, w.Slo, (bf16_t *)O,
+                                   (const bf16_t *)Q, (const bf16_t *)K, (const bf16_t *)V, w.MQ, w.Zg, w.Shi, w.Slo, (bf16_t *)O,
                                    Den, w.Pnum, w.Pden, pb.n, pb.b, pb.t);
             else
                 hipLaunchKernelGGL((k_out<R, D, P, TT, false, false, false, 2>), dim3((unsigned)n_tiles), dim3(kWg), 0, s,
-                                   (const bf16_t *)Q, (const bf16_t *)K, w.V8, w.MQ, w.Zg, w.Shi, w.Slo, (bf16_t *)O,
+                                   (const bf16_t *)Q, (const bf16_t *)K, (const bf16_t *)V, w.MQ, w.Zg, w.Shi, w.Slo, (bf16_t *)O,
                                    nullptr, w.Pnum, w.Pden, pb.n, pb.b, pb.t);
             PSF_LAUNCH_CHECK();
             if (tm) tm->mark();
@@ -2978,7 +2988,7 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
             PSF_LAUNCH_CHECK();
         }
     } else if (pb.t > 1) {
-        st = launch_state<D, R>(pb, w.MK8, w.V8, w.Zg, s, den);
+        st = launch_state<D, R>(pb, w.MK8, (const bf16_t *)V, (size_t)pb.n * D, 0, w.Zg, s, den);
         if (st != PSF_OK) return st;
     }
     if (tm) tm->mark();
@@ -2996,12 +3006,12 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
                     // the backward pass's forward: only where the backward kernels exist
                     if constexpr (D == 64 && R == 64 && P == 4)
                         hipLaunchKernelGGL((k_out<R, D, P, TT, true, false, true>), dim3(grid), dim3(kWg), 0, s, w.MQ,
-                                           mk_rows, w.V8, w.MQ, w.Zg, w.Shi, w.Slo, (bf16_t *)O, Den, nullptr, nullptr, pb.n, pb.b, pb.t);
+                                           mk_rows, (const bf16_t *)V, w.MQ, w.Zg, w.Shi, w.Slo, (bf16_t *)O, Den, nullptr, nullptr, pb.n, pb.b, pb.t);
                     else
                         return PSF_ERR_UNSUPPORTED;
                 } else {
                     hipLaunchKernelGGL((k_out<R, D, P, TT, false, false, true>), dim3(grid), dim3(kWg), 0, s, w.MQ,
-                                       mk_rows, w.V8, w.MQ, w.Zg, w.Shi, w.Slo, (bf16_t *)O, Den, nullptr, nullptr, pb.n, pb.b, pb.t);
+                                       mk_rows, (const bf16_t *)V, w.MQ, w.Zg, w.Shi, w.Slo, (bf16_t *)O, Den, nullptr, nullptr, pb.n, pb.b, pb.t);
                 }
             } else {
                 return PSF_ERR_UNSUPPORTED;
@@ -3010,15 +3020,15 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
             auto launch = [&](auto tt) {
                 constexpr int T = decltype(tt)::value;
                 const dim3 wgs((unsigned)((size_t)pb.units * (pb.n / (128 * T))));
-                const bf16_t *q = (const bf16_t *)Q, *k = (const bf16_t *)K;
+                const bf16_t *q = (const bf16_t *)Q, *k = (const bf16_t *)K, *v = (const bf16_t *)V;
                 if (noncausal)
-                    hipLaunchKernelGGL((k_out<R, D, P, T, false, true>), wgs, dim3(kWg), 0, s, q, k, w.V8, w.MQ, w.Zg,
+                    hipLaunchKernelGGL((k_out<R, D, P, T, false, true>), wgs, dim3(kWg), 0, s, q, k, v, w.MQ, w.Zg,
                                        w.Shi, w.Slo, (bf16_t *)O, Den, nullptr, nullptr, pb.n, pb.b, pb.t);
                 else if (Den)
-                    hipLaunchKernelGGL((k_out<R, D, P, T, true>), wgs, dim3(kWg), 0, s, q, k, w.V8, w.MQ, w.Zg, w.Shi,
+                    hipLaunchKernelGGL((k_out<R, D, P, T, true>), wgs, dim3(kWg), 0, s, q, k, v, w.MQ, w.Zg, w.Shi,
                                        w.Slo, (bf16_t *)O, Den, nullptr, nullptr, pb.n, pb.b, pb.t);
                 else
-                    hipLaunchKernelGGL((k_out<R, D, P, T, false>), wgs, dim3(kWg), 0, s, q, k, w.V8, w.MQ, w.Zg, w.Shi,
+                    hipLaunchKernelGGL((k_out<R, D, P, T, false>), wgs, dim3(kWg), 0, s, q, k, v, w.MQ, w.Zg, w.Shi,
                                        w.Slo, (bf16_t *)O, Den, nullptr, nullptr, pb.n, pb.b, pb.t);
             };
             if (TT == 2 && grid <= kSmallOutGrid)
@@ -3152,7 +3162,7 @@ psf_status mfma_attn(const Problem &pb0, const void *Q, const void *K, const voi
 // non-causal entry point does).  Zg: [units][a][b'/8][c][8] bf16 with the symmetry weights of
 // k_state (b' > a doubled, b' < a zero); Spart: [units][parts][r][r] fp32 partial m^T m.
 struct TotalWs {
-    bf16_t *Gt; float *MK8; bf16_t *V8; bf16_t *Zg; float *Spart;
+    bf16_t *Gt; float *MK8; bf16_t *Zg; float *Spart;
     bf16_t *LW; float *C1, *LVp;                 // learned sketches: arranged weights (see k_learned_prep)
     size_t total;
 };
@@ -3177,13 +3187,13 @@ static TotalWs carve_total(const Problem &pb, void *ws)
     auto take = [&](size_t bytes) { char *q = base + off; off += align_up(bytes, 256); return q; };
     w.Gt = (bf16_t *)take(pb.learned ? 0 : sets * pb.g_len * 2);
     w.MK8 = (float *)take(rows * R * 4);
-    w.V8 = (bf16_t *)take(rows * D * 2);
     w.Zg = (bf16_t *)take((size_t)pb.units * R * R * D * 2);
     w.Spart = (float *)take(parts * R * R * 4);
     const size_t nch = R / 4;
     w.LW = (bf16_t *)take(pb.learned ? sets * 4 * nch * kLsSlotBytes : 0);
     w.C1 = (float *)take(pb.learned ? sets * 2 * nch * 32 * 4 : 0);
     w.LVp = (float *)take(pb.learned ? sets * 2 * nch * 2 * R * 4 : 0);
+    off += align_up(rows * D * 2, 256);              // (the least size callers budget with: it held a layout of V)
     w.total = off;
     return w;
 }
@@ -3226,12 +3236,7 @@ psf_status total_state_impl(const Problem &pb, int src_n, const void *K, const v
         st = launch_sketch<D, R, P>(pb, K, w.Gt, false, nullptr, w.MK8, w.Spart, sketch_tiles_per_wg(pb), s, src_n);
         if (st != PSF_OK) return st;
     }
-    const size_t octets = (size_t)pb.units * pb.n / 8;
-    hipLaunchKernelGGL((k_v_octets<D>), dim3((unsigned)((octets * D + kWg - 1) / kWg)), dim3(kWg), 0, s,
-                       (const bf16_t *)V, w.V8, octets, src_n > pb.n ? (unsigned)(pb.n / 8) : 0u,
-                       (unsigned)(src_n - pb.n));
-    PSF_LAUNCH_CHECK();
-    return launch_state<D, R>(pb, w.MK8, w.V8, w.Zg, s);
+    return launch_state<D, R>(pb, w.MK8, (const bf16_t *)V, (size_t)src_n * D, 0, w.Zg, s);
 }
 }  // namespace
 

@@ -26,52 +26,39 @@ __device__ __forceinline__ float pow_n(float x)
 }
 
 // ---- g, c and the layouts of g ------------------------------------------------------------
-// One wave per token octet, lane = value column.  G_rm: g as bf16 rows; G8r: octets [rows/8][D][8]
-// with the blocks of every unit in reverse order (input of the mirror state kernel, which then is the
-// forward state kernel unchanged); Cc: c as fp32.
+// A group of D / 8 lanes per row, eight columns a lane.  G_rm: g as bf16 rows; Cc: c as fp32.
 template <int D>
 __global__ __launch_bounds__(kWg) void k_bwd_prep(const bf16_t *__restrict__ dO, const bf16_t *__restrict__ O,
                                                   const float *__restrict__ Den, bf16_t *__restrict__ G_rm,
-                                                  bf16_t *__restrict__ G8r,
-                                                  float *__restrict__ Cc, int n, int b, int t)
+                                                  float *__restrict__ Cc)
 {
-    static_assert(D % 64 == 0, "D / 64 value columns per lane");
-    constexpr int CL = D / 64;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const size_t oct = (size_t)blockIdx.x * 4 + wave, row0 = oct * 8;
-    uint16_t gb[CL][8];
-    float dot[8];
+    constexpr int LANES = D / 8, ROWS = kWg / LANES, U = 4;    // rows a pass; passes, all their loads first
+    const int li = threadIdx.x % LANES;
+    const size_t row0 = (size_t)blockIdx.x * (ROWS * U) + threadIdx.x / LANES;
+    bf16x8 d_o[U], o[U];
+    float inv[U];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const float inv = 1.0f / Den[row0 + j];
-        dot[j] = 0.f;
+    for (int i = 0; i < U; ++i) {
+        const size_t row = row0 + (size_t)i * ROWS;
+        d_o[i] = *(const bf16x8 *)&dO[row * D + 8 * li];
+        o[i] = *(const bf16x8 *)&O[row * D + 8 * li];
+        inv[i] = Den[row];
+    }
 #pragma unroll
-        for (int cl = 0; cl < CL; ++cl) {
-            const int col = 64 * cl + lane;
-            const float d_o = bf16_to_f32(dO[(row0 + j) * D + col]);
-            const float o = bf16_to_f32(O[(row0 + j) * D + col]);
-            gb[cl][j] = f32_to_bf16(d_o * inv);
-            dot[j] += d_o * o * inv;
-            G_rm[(row0 + j) * D + col] = gb[cl][j];
+    for (int i = 0; i < U; ++i) {
+        const size_t row = row0 + (size_t)i * ROWS;
+        inv[i] = 1.0f / inv[i];
+        f32x8 g;
+        float dot = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            g[e] = (float)d_o[i][e] * inv[i];
+            dot += (float)d_o[i][e] * (float)o[i][e] * inv[i];
         }
-    }
+        *(bf16x8 *)&G_rm[row * D + 8 * li] = cvt8(g);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) dot[j] += __shfl_xor(dot[j], m);
-        if (lane == j) Cc[row0 + j] = -dot[j];
-    }
-    const size_t u = row0 / n, pos = row0 % n;
-    const size_t rpos = (size_t)(t - 1 - (int)(pos / b)) * b + pos % b;
-#pragma unroll
-    for (int cl = 0; cl < CL; ++cl) {
-        const int col = 64 * cl + lane;
-        uint4 pk;
-        pk.x = gb[cl][0] | ((uint32_t)gb[cl][1] << 16);
-        pk.y = gb[cl][2] | ((uint32_t)gb[cl][3] << 16);
-        pk.z = gb[cl][4] | ((uint32_t)gb[cl][5] << 16);
-        pk.w = gb[cl][6] | ((uint32_t)gb[cl][7] << 16);
-        *(uint4 *)&G8r[(((u * n + rpos) >> 3) * D + col) * 8] = pk;
+        for (int m = LANES / 2; m >= 1; m >>= 1) dot += __shfl_xor(dot, m);
+        if (li == 0) Cc[row] = -dot;
     }
 }
 
@@ -684,35 +671,24 @@ struct LocTile {
     static constexpr int BYTES = kLocT * D * 2, PIECES = D / 8, KS = D / 16, CT = D / 32;
     static constexpr int ROWS_PER_COPY = NTHR / PIECES;     // rows one copy instruction of the workgroup moves
     static_assert(ROWS_PER_COPY % 16 == 0 && kLocT % ROWS_PER_COPY == 0, "whole swizzle periods per copy");
-    // The 16-byte piece p of row j lies at p ^ swz(j).  Plain reads (one piece of 16 consecutive rows) and transposed
-    // ones (two neighbouring pieces of 4 consecutive rows a 16-lane group, four pieces two groups) meet every bank
-    // once, with 32 banks as with 64.
-    static __device__ __forceinline__ int swz(int j)
-    {
-        if constexpr (D == 64) return ((j & 3) << 1) ^ ((j >> 2) & 1) ^ ((j >> 2) & 2);
-        else return ((j & 1) * 10) ^ ((j & 2) << 1) ^ ((j >> 2) & 1) ^ (j & 8);
-    }
+    static __device__ __forceinline__ int swz(int j) { return row_swz<D>(j); }
     int x, h, tid, wave;
     uint32_t copy_off;                                      // lane's place in a copy's source
     uint32_t plain[KS], turned[2][CT];                      // lane's byte offsets of fragments, see rows() and columns()
     __device__ __forceinline__ LocTile()
     {
         tid = threadIdx.x;
-        const int lane = tid & 63, s16 = lane & 15;
+        const int lane = tid & 63;
         x = lane & 31;
         h = lane >> 5;
         wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-        const int row = tid / PIECES;
-        copy_off = (uint32_t)((row * PIECES + (tid % PIECES ^ swz(row))) * 16);
+        copy_off = row_copy_offset<D>(tid);
 #pragma unroll
         for (int s = 0; s < KS; ++s) plain[s] = (uint32_t)((x * PIECES + ((2 * s + h) ^ swz(x))) * 16);
 #pragma unroll
         for (int hi = 0; hi < 2; ++hi)
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) {
-                const int j = 8 * hi + 4 * h + s16 / 4, p = 4 * ct + 2 * ((lane >> 4) & 1) + (s16 % 4) / 2;
-                turned[hi][ct] = (uint32_t)((j * PIECES + (p ^ swz(j))) * 16 + (s16 & 1) * 8);
-            }
+            for (int ct = 0; ct < CT; ++ct) turned[hi][ct] = row_turned_offset<D>(lane, 8 * hi + 4 * h, ct);
     }
     // rows [j0, j0 + 64) of X -> LDS
     __device__ __forceinline__ void stage(const bf16_t *__restrict__ X, size_t j0, uint32_t dst) const
@@ -951,7 +927,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_k(const 
 // ---- host ---------------------------------------------------------------------------------------
 struct MfmaBwdWs {
     void *fwd;                                               // the forward workspace
-    bf16_t *O, *MK, *G_rm, *G8r, *Rg, *Rchi, *Rclo;
+    bf16_t *O, *MK, *G_rm, *Rg, *Rchi, *Rclo;
     float *Den, *Cc, *M8r, *ScPart, *dVc, *dQacc, *dKacc;
     // learned sketches: backward weight stream, what the row kernel leaves for the parameter
     // kernel (one side at a time), its workgroup sums, the per-unit parameter sums of both sides
@@ -973,7 +949,6 @@ MfmaBwdWs carve_bwd(const Problem &pb, void *ws)
     w.O = (bf16_t *)take(rows * D * 2);
     w.MK = (bf16_t *)take(rows * R * 2);
     w.G_rm = (bf16_t *)take(rows * D * 2);
-    w.G8r = (bf16_t *)take(rows * D * 2);
     w.Rg = (bf16_t *)take(snaps * R * R * D * 2);
     w.Rchi = (bf16_t *)take(snaps * R * R * 2);
     w.Rclo = (bf16_t *)take(snaps * R * R * 2);
@@ -1074,8 +1049,8 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
     if (tm) tm->mark();
     const bf16_t *rq = ls ? f.MQ : q, *rk = ls ? w.MK : k;  // the rows the in-block weights are made of
     // g, c, layouts
-    hipLaunchKernelGGL((k_bwd_prep<D>), dim3((unsigned)(rows / 32)), dim3(kWg), 0, s, (const bf16_t *)dO, w.O,
-                       w.Den, w.G_rm, w.G8r, w.Cc, pb.n, pb.b, pb.t);
+    hipLaunchKernelGGL((k_bwd_prep<D>), dim3((unsigned)(rows / (kWg / (D / 8) * 4))), dim3(kWg), 0, s, (const bf16_t *)dO,
+                       w.O, w.Den, w.G_rm, w.Cc);
     PSF_LAUNCH_CHECK();
     if (tm) tm->mark();
     // mirror states R_l (the forward state kernel on block-reversed inputs)
@@ -1083,7 +1058,7 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
         hipLaunchKernelGGL((k_bwd_qoct<R>), dim3((unsigned)(rows / 256)), dim3(kWg), 0, s, f.MQ, w.Cc, w.M8r,
                            w.ScPart, pb.n, pb.b, pb.t);
         PSF_LAUNCH_CHECK();
-        st = launch_state<D, R>(pb, w.M8r, w.G8r, w.Rg, s);
+        st = launch_state<D, R>(pb, w.M8r, w.G_rm, (size_t)pb.n * D, 1, w.Rg, s);
         if (st != PSF_OK) return st;
     }
     if (tm) tm->mark();
