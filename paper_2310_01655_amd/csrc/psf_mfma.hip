@@ -3042,6 +3042,17 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
     return PSF_OK;
 }
 
+// Rows of W fp32 values that one kernel leaves for another lie in the order of the accumulators both hold them in: tile of 32
+// rows, column tile, register quad, lane, the four columns 32 ct + 8 gq + 4 h + 0..3 of row x.  A quad is 1 KB in one
+// piece; as rows, every access of a wave touched 32 bytes of 32 of them (96 units of 4096, r = 32, us: k_bwd_local_q 80, k_bwd_local_k 108,
+// k_bwd_dvc 67, k_bwd_dm 119 and 111; so 71, 100, 60, 114 and 107).
+// row: lane x's row, the tile's first one a multiple of 32.
+template <int W>
+__device__ __forceinline__ size_t held_quad(size_t row, int x, int h, int ct, int gq)
+{
+    return (row - x) * W + (size_t)(((ct * 4 + gq) * 64 + 32 * h + x) * 4);
+}
+
 #include "psf_mfma_learned_bwd.inl"
 #include "psf_mfma_bwd.inl"
 

@@ -189,7 +189,7 @@ __device__ __forceinline__ void sketch_grad_tile(const SketchLds<D, R> &lds, con
             const size_t off = row * D + 32 * dt + 8 * gq + 4 * h;
             f32x4 q4 = {acc[4 * gq], acc[4 * gq + 1], acc[4 * gq + 2], acc[4 * gq + 3]};
             if constexpr (ADD_BASE) {
-                const f32x4 base = *(const f32x4 *)&dXacc[off];
+                const f32x4 base = *(const f32x4 *)&dXacc[held_quad<D>(row, x, h, dt, gq)];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) q4[j] += base[j];
             }
@@ -214,7 +214,7 @@ __device__ __forceinline__ void sketch_grad_stage(SketchLds<D, R> &lds, bf16_t *
 
 // ---- through Algorithm 1 as a pass of its own (d = 128 or degree 8) ---------------------------
 // dX = bf16(dXacc + J_m(x)^T dm) for 128 rows per workgroup (one 32-row tile per wave, lane = row), dm
-// given as fp32 rows.  Degree 4: sketch_grad_tile.  Degree 8, with u_k = x G_k (k < 4),
+// given as fp32 rows (held_quad).  Degree 4: sketch_grad_tile.  Degree 8, with u_k = x G_k (k < 4),
 // n1 = s u0 * u1, n2 = s u2 * u3, w1 = n1 G4, w2 = n2 G5, m = s w1 * w2, s = sqrt(1/r):
 //     dw1 = s dm * w2, dw2 = s dm * w1;  dn1 = dw1 G4^T, dn2 = dw2 G5^T;
 //     du0 = s dn1 * u1, du1 = s dn1 * u0, du2 = s dn2 * u3, du3 = s dn2 * u2;  dx = sum_k du_k G_k^T.
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_sketch_rows(const bf16_t *__rest
     for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
         for (int gq = 0; gq < 4; ++gq) {
-            const f32x4 d4 = *(const f32x4 *)&dM[row * R + 32 * ct + 8 * gq + 4 * h];
+            const f32x4 d4 = *(const f32x4 *)&dM[held_quad<R>(row, x, h, ct, gq)];
 #pragma unroll
             for (int j = 0; j < 4; ++j) dm[ct][4 * gq + j] = d4[j];
         }
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_sketch_rows(const bf16_t *__rest
 #pragma unroll
             for (int gq = 0; gq < 4; ++gq) {
                 const size_t off = row * D + 32 * dt + 8 * gq + 4 * h;
-                const f32x4 base = *(const f32x4 *)&dXacc[off];
+                const f32x4 base = *(const f32x4 *)&dXacc[held_quad<D>(row, x, h, dt, gq)];
                 const f32x4 q4 = {dx[dt][4 * gq] + base[0], dx[dt][4 * gq + 1] + base[1], dx[dt][4 * gq + 2] + base[2],
                                   dx[dt][4 * gq + 3] + base[3]};
                 *(bf16x4 *)&dX[off] = cvt4(q4);
@@ -477,7 +477,7 @@ struct StateTimesRow : StateTiles<R, D> {
 // LS (in-block rule of Section 3.1, R == D): the in-block weights are functions of the sketches
 // too, so dXacc holds the in-block part of dm ([rows][R] fp32), which joins dm before the sketch:
 // dX = bf16(J_m(x)^T (dm + dXacc)).
-// RAW (learned sketches): dm itself is the result, fp32 rows [rows][R] in dMout (no sketch matrices).
+// RAW (learned sketches, and those with a pass of their own): dm itself is the result, fp32 rows (held_quad) in dMout.
 template <int R, int D, bool QSIDE, int TT, bool LS = false, bool RAW = false>
 __global__ __launch_bounds__(kWg, 2) void k_bwd_dm(const bf16_t *__restrict__ M, const bf16_t *__restrict__ Vec,
                                                   const float *__restrict__ Cc, const bf16_t *__restrict__ Zs,
@@ -578,7 +578,7 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_dm(const bf16_t *__restrict__ M,
                 for (int gq = 0; gq < 4; ++gq) {
                     const f32x4 o4 = {out[tt][at][4 * gq], out[tt][at][4 * gq + 1], out[tt][at][4 * gq + 2],
                                       out[tt][at][4 * gq + 3]};
-                    *(f32x4 *)&dMout[(urow + i0 + wave * 32 * TT + 32 * tt + x) * R + 32 * at + 8 * gq + 4 * h] = o4;
+                    *(f32x4 *)&dMout[held_quad<R>(urow + i0 + wave * 32 * TT + 32 * tt + x, x, h, at, gq)] = o4;
                 }
         return;
     }
@@ -597,8 +597,8 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_dm(const bf16_t *__restrict__ M,
 #pragma unroll
                 for (int gq = 0; gq < 4; ++gq) {
                     // register v of out[tt][at]: sketch column 32 at + 8 (v / 4) + 4 h + v % 4
-                    const f32x4 a4 = *(const f32x4 *)&dXacc[(urow + i0 + wave * 32 * TT + 32 * tt + x) * R + 32 * at +
-                                                            8 * gq + 4 * h];
+                    const f32x4 a4 = *(const f32x4 *)&dXacc[held_quad<R>(urow + i0 + wave * 32 * TT + 32 * tt + x, x, h,
+                                                                         at, gq)];
 #pragma unroll
                     for (int j = 0; j < 4; ++j) out[tt][at][4 * gq + j] += a4[j];
                 }
@@ -653,7 +653,7 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_dvc(const bf16_t *__restrict__ M
             for (int gq = 0; gq < 4; ++gq) {
                 const f32x4 q4 = {out[tt][ct][4 * gq], out[tt][ct][4 * gq + 1], out[tt][ct][4 * gq + 2],
                                   out[tt][ct][4 * gq + 3]};
-                *(f32x4 *)&dVc[row * D + 32 * ct + 8 * gq + 4 * h] = q4;
+                *(f32x4 *)&dVc[held_quad<D>(row, x, h, ct, gq)] = q4;
             }
     }
 }
@@ -807,13 +807,13 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_q(const 
             // (the p of p s^(p-1): a power of two, exact)
             const f32x4 q4 = {(float)P * dq[ct][4 * gq], (float)P * dq[ct][4 * gq + 1], (float)P * dq[ct][4 * gq + 2],
                               (float)P * dq[ct][4 * gq + 3]};
-            *(f32x4 *)&dQacc[(urow + tok) * D + 32 * ct + 8 * gq + 4 * h] = q4;
+            *(f32x4 *)&dQacc[held_quad<D>(urow + tok, x, h, ct, gq)] = q4;
         }
 }
 
 // dK (in-block) and dV (in-block + the cross-block part already in dVc): own rows = keys,
 // streamed = queries of the same block from the diagonal on.
-//   dk_j = sum_{i >= j} (<g_i, v_j> + c_i) p <q_i, k_j>^(p-1) q_i   -> dKacc fp32 rows
+//   dk_j = sum_{i >= j} (<g_i, v_j> + c_i) p <q_i, k_j>^(p-1) q_i   -> dKacc fp32 rows (held_quad)
 //   dv_j = sum_{i >= j} <q_i, k_j>^p g_i + dVc_j                     -> dV bf16 rows
 template <int P, int NW, int D = 64>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_k(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
@@ -912,12 +912,12 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_k(const 
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
         for (int gq = 0; gq < 4; ++gq) {
-            const size_t off = (urow + key) * D + 32 * ct + 8 * gq + 4 * h;
+            const size_t off = (urow + key) * D + 32 * ct + 8 * gq + 4 * h, held = held_quad<D>(urow + key, x, h, ct, gq);
             // (the p of p s^(p-1): a power of two, exact)
             const f32x4 k4 = {(float)P * dk[ct][4 * gq], (float)P * dk[ct][4 * gq + 1], (float)P * dk[ct][4 * gq + 2],
                               (float)P * dk[ct][4 * gq + 3]};
-            *(f32x4 *)&dKacc[off] = k4;
-            const f32x4 c4 = *(const f32x4 *)&dVc[off];
+            *(f32x4 *)&dKacc[held] = k4;
+            const f32x4 c4 = *(const f32x4 *)&dVc[held];
             const f32x4 v4 = {dv[ct][4 * gq] + c4[0], dv[ct][4 * gq + 1] + c4[1], dv[ct][4 * gq + 2] + c4[2],
                               dv[ct][4 * gq + 3] + c4[3]};
             *(bf16x4 *)&dV[off] = cvt4(v4);

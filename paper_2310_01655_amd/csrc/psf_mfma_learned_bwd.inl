@@ -127,8 +127,8 @@ struct LbStage {
     size_t rows;
 };
 
-// dM: dL/dm of the rows as fp32 [rows][R]; dXacc: the direct term of the exact in-block weights
-// (fp32 [rows][64]); LW, C1, LVp: the forward weight stream of k_learned_prep; LB: the backward
+// dM: dL/dm of the rows as fp32 (held_quad); dXacc: the direct term of the exact in-block weights
+// (likewise); LW, C1, LVp: the forward weight stream of k_learned_prep; LB: the backward
 // stream; P: the parameter blobs (for g1).  GB1: [workgroup][net][2][64] fp32, the workgroup's sums
 // for dg1 and db1.  STAGE = false: row gradient only (parameters as constants).
 template <int R, bool STAGE>
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(512, 1) void k_learned_bwd_rows(const bf16_t *__res
             f32x16 d0, d1;
 #pragma unroll
             for (int g4 = 0; g4 < 4; ++g4) {
-                const f32x4 dm4 = *(const f32x4 *)&dM[row * R + 32 * ot + 8 * g4 + 4 * h];
+                const f32x4 dm4 = *(const f32x4 *)&dM[held_quad<R>(row, x, h, ot, g4)];
 #pragma unroll
                 for (int j2 = 0; j2 < 4; ++j2) {
                     const int v = 4 * g4 + j2;
@@ -524,7 +524,7 @@ __global__ __launch_bounds__(512, 1) void k_learned_bwd_rows(const bf16_t *__res
         for (int g4 = 0; g4 < 4; ++g4) {
             const size_t off = row * D + 32 * dt + 8 * g4 + 4 * h;
             f32x4 o4 = {dxs[dt][4 * g4], dxs[dt][4 * g4 + 1], dxs[dt][4 * g4 + 2], dxs[dt][4 * g4 + 3]};
-            const f32x4 base = *(const f32x4 *)&dXacc[off];
+            const f32x4 base = *(const f32x4 *)&dXacc[held_quad<D>(row, x, h, dt, g4)];
 #pragma unroll
             for (int j2 = 0; j2 < 4; ++j2) o4[j2] += base[j2];
             *(bf16x4 *)&dX[off] = cvt4(o4);
