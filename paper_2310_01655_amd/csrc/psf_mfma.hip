@@ -1565,6 +1565,35 @@ __global__ __launch_bounds__(kWg, 2) void k_state_f16(const _Float16 *__restrict
     state_f16_workgroup<R, D>(MKh, V8h, Kscale, Zg, n, b, t, units, lds, blockIdx.x, den.n_main);
 }
 
+// A wave's 32 result rows of D 16-bit values on their way to memory (lane = row x, quad gq of column tile ct = columns
+// 32 ct + 8 gq + 4 h + 0..3).  They are turned through LDS of the wave's own, so that a store writes whole rows, 1 KB in
+// one piece; stored as they stand, every instruction wrote 16 bytes of each of 32 rows (us a call, before and so: causal, 24
+// units of 32768 767, 761, 12 of 512 19.3, 18.6; gradients of 96 units of 4096 778, 754, with d = 128, 16 of 16384 2115, 2067).
+template <int D>
+struct RowsOut {
+    static constexpr int PITCH = D + 8, BYTES = 32 * PITCH * 2;    // of a wave
+    bf16_t *tile;
+    int lane;
+    __device__ __forceinline__ RowsOut(unsigned char *lds, int wave, int lane_)
+        : tile((bf16_t *)(lds + wave * BYTES)), lane(lane_)
+    {
+    }
+    __device__ __forceinline__ void put(int ct, int gq, f32x4 q) const
+    {
+        *(bf16x4 *)&tile[(lane & 31) * PITCH + 32 * ct + 8 * gq + 4 * (lane >> 5)] = cvt4(q);
+    }
+    __device__ __forceinline__ void store(bf16_t *dst) const        // dst: the tile's first row
+    {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // the wave's own writes
+#pragma unroll
+        for (int i = 0; i < 32 * D / 8 / 64; ++i) {
+            const int w = i * 64 + lane, row = w / (D / 8), piece = w % (D / 8);
+            *(uint4 *)&dst[row * D + 8 * piece] = *(const uint4 *)&tile[row * PITCH + 8 * piece];
+        }
+        asm volatile("" ::: "memory");                              // (the next tile's writes come after these reads)
+    }
+};
+
 constexpr int kKeyTilesInFlight = 4;
 template <int R, int D, int TT, bool LS, int PART>
 constexpr int out_lds_bytes()
@@ -1925,6 +1954,10 @@ __device__ __forceinline__ void out_workgroup(const bf16_t *__restrict__ Q, cons
                 }
     }
     // ---------------- normalise and store (Section 3: divide by 1 + sum of weights) ----------------
+    static_assert(4 * RowsOut<D>::BYTES <= out_lds_bytes<R, D, TT, LS, PART>(), "the rows reuse the stage");
+    wait_vmem_le<0>();                                     // copies past the end of the last key tile
+    __syncthreads();
+    const RowsOut<D> rows_out(stage, wave, lane);
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
         const float total = den[tt] + __shfl_xor(den[tt], 32);   // the two halves hold different keys / rows
@@ -1937,8 +1970,9 @@ __device__ __forceinline__ void out_workgroup(const bf16_t *__restrict__ Q, cons
             for (int gq = 0; gq < 4; ++gq) {
                 f32x4 q4 = {out[tt][ct][4 * gq] * inv, out[tt][ct][4 * gq + 1] * inv,
                             out[tt][ct][4 * gq + 2] * inv, out[tt][ct][4 * gq + 3] * inv};
-                *(bf16x4 *)&O[row * D + 32 * ct + 8 * gq + 4 * h] = cvt4(q4);
+                rows_out.put(ct, gq, q4);
             }
+        rows_out.store(O + (urow + tok_w0 + 32 * tt) * D);
     }
 }
 
@@ -3044,8 +3078,8 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
 
 // Rows of W fp32 values that one kernel leaves for another lie in the order of the accumulators both hold them in: tile of 32
 // rows, column tile, register quad, lane, the four columns 32 ct + 8 gq + 4 h + 0..3 of row x.  A quad is 1 KB in one
-// piece; as rows, every access of a wave touched 32 bytes of 32 of them (96 units of 4096, r = 32, us: k_bwd_local_q 80, k_bwd_local_k 108,
-// k_bwd_dvc 67, k_bwd_dm 119 and 111; so 71, 100, 60, 114 and 107).
+// piece; as rows, every access of a wave touched 32 bytes of 32 of them (96 units of 4096, r = 32, us: k_bwd_local_q 80,
+// k_bwd_local_k 108, k_bwd_dvc 67, k_bwd_dm 119 and 111; so 71, 100, 60, 114 and 107).
 // row: lane x's row, the tile's first one a multiple of 32.
 template <int W>
 __device__ __forceinline__ size_t held_quad(size_t row, int x, int h, int ct, int gq)

@@ -135,6 +135,31 @@ __global__ __launch_bounds__(kWg) void k_bwd_qoct(const bf16_t *__restrict__ MQ,
 }
 
 // ---- through Algorithm 1 (p = 4), one 32-token tile of a wave --------------------------------
+template <int D>
+__device__ __forceinline__ void add_held(f32x16 (&dx)[D / 32], const float *__restrict__ held, size_t row, int x, int h)
+{
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq) {
+            const f32x4 base = *(const f32x4 *)&held[held_quad<D>(row, x, h, dt, gq)];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) dx[dt][4 * gq + j] += base[j];
+        }
+}
+
+// dst: the first of the wave's 32 rows
+template <int D>
+__device__ __forceinline__ void store_rows(const RowsOut<D> &out, const f32x16 (&dx)[D / 32], bf16_t *__restrict__ dst)
+{
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq)
+            out.put(dt, gq, f32x4{dx[dt][4 * gq], dx[dt][4 * gq + 1], dx[dt][4 * gq + 2], dx[dt][4 * gq + 3]});
+    out.store(dst);
+}
+
 // dx = dXacc (if ADD_BASE) + sqrt(1/r) [(dm * (x G2)) G1^T + (dm * (x G1)) G2^T].  lds: the transposed sketch
 // matrices as the forward sketch kernel stages them (for the recomputed projections); go: G1,
 // G2 as given, rows [d][r] padded to GP (for the transposed products, whose A fragments are read
@@ -143,8 +168,8 @@ __global__ __launch_bounds__(kWg) void k_bwd_qoct(const bf16_t *__restrict__ MQ,
 template <int D, int R, bool ADD_BASE = true>
 __device__ __forceinline__ void sketch_grad_tile(const SketchLds<D, R> &lds, const bf16_t *go,
                                                  const bf16_t *__restrict__ X, const f32x16 *dm,
-                                                 const float *__restrict__ dXacc, bf16_t *__restrict__ dX,
-                                                 size_t row, int x, int h)
+                                                 const float *__restrict__ dXacc, size_t row, int x, int h,
+                                                 f32x16 (&dx)[D / 32])
 {
     constexpr int KS = D / 16, NT = R / 32, DT = D / 32, GP = R + 8;
     const float scale = sqrtf(1.0f / (float)R);
@@ -184,18 +209,9 @@ __device__ __forceinline__ void sketch_grad_tile(const SketchLds<D, R> &lds, con
             acc = mfma32(f1, d0[ks], acc);
             acc = mfma32(f2, d1[ks], acc);
         }
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-            const size_t off = row * D + 32 * dt + 8 * gq + 4 * h;
-            f32x4 q4 = {acc[4 * gq], acc[4 * gq + 1], acc[4 * gq + 2], acc[4 * gq + 3]};
-            if constexpr (ADD_BASE) {
-                const f32x4 base = *(const f32x4 *)&dXacc[held_quad<D>(row, x, h, dt, gq)];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) q4[j] += base[j];
-            }
-            *(bf16x4 *)&dX[off] = cvt4(q4);
-        }
+        dx[dt] = acc;
     }
+    if constexpr (ADD_BASE) add_held<D>(dx, dXacc, row, x, h);
 }
 
 // Both sets of sketch matrices of one parameter set into LDS (see sketch_grad_tile).
@@ -227,8 +243,11 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_sketch_rows(const bf16_t *__rest
                                                            int n, int heads, int per_head, size_t g_len)
 {
     constexpr int KS = D / 16, NT = R / 32, RS = R / 16, DT = D / 32, GP = R + 8;
-    __shared__ __attribute__((aligned(16))) SketchLds<D, R> lds;
-    __shared__ __attribute__((aligned(16))) bf16_t go[2 * D * GP];
+    constexpr int LDS_BYTES = sizeof(SketchLds<D, R>) + 2 * D * GP * 2;
+    static_assert(4 * RowsOut<D>::BYTES <= LDS_BYTES, "the rows reuse the matrices' room");
+    __shared__ __attribute__((aligned(16))) unsigned char stage[LDS_BYTES];
+    SketchLds<D, R> &lds = *(SketchLds<D, R> *)stage;
+    bf16_t *go = (bf16_t *)(stage + sizeof(SketchLds<D, R>));
     const int tid = threadIdx.x, lane = tid & 63, x = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const size_t row0 = (size_t)blockIdx.x * 128, row = row0 + wave * 32 + x;
@@ -244,10 +263,11 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_sketch_rows(const bf16_t *__rest
 #pragma unroll
             for (int j = 0; j < 4; ++j) dm[ct][4 * gq + j] = d4[j];
         }
+    f32x16 dx[DT];
     if constexpr (P == 4) {
         sketch_grad_stage<D, R>(lds, go, gt, g);
         __syncthreads();
-        sketch_grad_tile<D, R, true>(lds, go, X, dm, dXacc, dX, row, x, h);
+        sketch_grad_tile<D, R, true>(lds, go, X, dm, dXacc, row, x, h, dx);
     } else {
         static_assert(P == 8, "degree 4 or 8");
         const float scale = sqrtf(1.0f / (float)R);
@@ -339,7 +359,6 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_sketch_rows(const bf16_t *__rest
             to_frags(d1, duf[2]);
             to_frags(d2, duf[3]);
         }
-        f32x16 dx[DT];
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) dx[dt] = f32x16{0};
 #pragma unroll
@@ -354,17 +373,10 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_sketch_rows(const bf16_t *__rest
                 dx[dt] = times_rows(1, dt, duf[2 * pair + 1], dx[dt]);
             }
         }
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int gq = 0; gq < 4; ++gq) {
-                const size_t off = row * D + 32 * dt + 8 * gq + 4 * h;
-                const f32x4 base = *(const f32x4 *)&dXacc[held_quad<D>(row, x, h, dt, gq)];
-                const f32x4 q4 = {dx[dt][4 * gq] + base[0], dx[dt][4 * gq + 1] + base[1], dx[dt][4 * gq + 2] + base[2],
-                                  dx[dt][4 * gq + 3] + base[3]};
-                *(bf16x4 *)&dX[off] = cvt4(q4);
-            }
+        add_held<D>(dx, dXacc, row, x, h);
     }
+    __syncthreads();                                        // every wave is done with the matrices
+    store_rows<D>(RowsOut<D>(stage, wave, lane), dx, dX + (row0 + wave * 32) * D);
 }
 
 // ---- contraction of the states with a row's gradient (or value) --------------------------------
@@ -488,7 +500,8 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_dm(const bf16_t *__restrict__ M,
                                                   int per_head, size_t g_len, float *__restrict__ dMout = nullptr)
 {
     using X = StateTimesRow<R, D, TT>;
-    static_assert(RAW || sizeof(SketchLds<D, R>) + 2 * D * (R + 8) * 2 <= X::LDS_BYTES, "the sketch matrices reuse the stage");
+    constexpr int MATS = sizeof(SketchLds<D, R>) + 2 * D * (R + 8) * 2;
+    static_assert(RAW || MATS + 4 * RowsOut<D>::BYTES <= X::LDS_BYTES, "the sketch matrices and the result rows reuse the stage");
     constexpr int AT = R / 32, RS = R / 16, VS = D / 16, TOK_WG = 128 * TT;
     __shared__ __attribute__((aligned(16))) unsigned char stage[X::LDS_BYTES];
     const int tid = threadIdx.x, lane = tid & 63, x = lane & 31, h = lane >> 5;
@@ -604,9 +617,12 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_dm(const bf16_t *__restrict__ M,
                 }
     }
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt)
-        sketch_grad_tile<D, R, !LS>(lds, go, Xrows, out[tt], dXacc, dX, urow + i0 + wave * 32 * TT + 32 * tt + x, x,
-                                    h);
+    for (int tt = 0; tt < TT; ++tt) {
+        const size_t row = urow + i0 + wave * 32 * TT + 32 * tt;
+        f32x16 dx[D / 32];
+        sketch_grad_tile<D, R, !LS>(lds, go, Xrows, out[tt], dXacc, row + x, x, h, dx);
+        store_rows<D>(RowsOut<D>(stage + MATS, wave, lane), dx, dX + row * D);
+    }
 }
 
 // ---- dV: cross-block part = phi'(k_j)^T R_l (value columns) ----------------------------------
@@ -908,11 +924,14 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_k(const 
         tile(std::false_type{}, qt);
         branch_wait();
     }
+    static_assert(NW * RowsOut<D>::BYTES <= 2 * BUF, "the rows reuse the stage");
+    __syncthreads();                                        // every wave is done with the last tile
+    const RowsOut<D> rows_out(stage, T.wave, T.tid & 63);
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
         for (int gq = 0; gq < 4; ++gq) {
-            const size_t off = (urow + key) * D + 32 * ct + 8 * gq + 4 * h, held = held_quad<D>(urow + key, x, h, ct, gq);
+            const size_t held = held_quad<D>(urow + key, x, h, ct, gq);
             // (the p of p s^(p-1): a power of two, exact)
             const f32x4 k4 = {(float)P * dk[ct][4 * gq], (float)P * dk[ct][4 * gq + 1], (float)P * dk[ct][4 * gq + 2],
                               (float)P * dk[ct][4 * gq + 3]};
@@ -920,8 +939,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_k(const 
             const f32x4 c4 = *(const f32x4 *)&dVc[held];
             const f32x4 v4 = {dv[ct][4 * gq] + c4[0], dv[ct][4 * gq + 1] + c4[1], dv[ct][4 * gq + 2] + c4[2],
                               dv[ct][4 * gq + 3] + c4[3]};
-            *(bf16x4 *)&dV[off] = cvt4(v4);
+            rows_out.put(ct, gq, v4);
         }
+    rows_out.store(dV + (urow + key - x) * D);
 }
 
 // ---- host ---------------------------------------------------------------------------------------

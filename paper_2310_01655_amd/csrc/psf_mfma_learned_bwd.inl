@@ -517,20 +517,22 @@ __global__ __launch_bounds__(512, 1) void k_learned_bwd_rows(const bf16_t *__res
             for (int v = 0; v < 16; ++v) dxs[dt][v] += inv1 * (dxh[dt][v] - mA - xh[dt][v] * mB);
     }
     wait_vmem_le<0>();                                     // drain the clamped copies
+    __syncthreads();                                       // every wave is done with the ring, and its copies are in
+    static_assert(NTHR / 64 * RowsOut<D>::BYTES <= kLbRing * kLbSlot, "the rows reuse the ring");
+    const RowsOut<D> rows_out(ring, wave, lane);
 
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int g4 = 0; g4 < 4; ++g4) {
-            const size_t off = row * D + 32 * dt + 8 * g4 + 4 * h;
             f32x4 o4 = {dxs[dt][4 * g4], dxs[dt][4 * g4 + 1], dxs[dt][4 * g4 + 2], dxs[dt][4 * g4 + 3]};
             const f32x4 base = *(const f32x4 *)&dXacc[held_quad<D>(row, x, h, dt, g4)];
 #pragma unroll
             for (int j2 = 0; j2 < 4; ++j2) o4[j2] += base[j2];
-            *(bf16x4 *)&dX[off] = cvt4(o4);
+            rows_out.put(dt, g4, o4);
         }
+    rows_out.store(dX + (row - x) * D);
     if constexpr (STAGE) {
-        __syncthreads();
         if (tid < NETS * 2 * D) {
             float sum = 0.f;
 #pragma unroll
