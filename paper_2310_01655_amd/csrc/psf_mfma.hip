@@ -1389,10 +1389,13 @@ template <int R, int D>
 struct StateTiles {
     static constexpr int RS = R / 16, VS = D / 16, DW = D / 64;
     static constexpr int PS = D * 16 + 64, TILE = 4 * PS;      // plane and tile in LDS
-    static constexpr int G = 4 / DW, SLOTS = 4 * G;            // tiles per chunk, of the ring
+    // Workgroups per CU of the backward kernels around it.  They wait on memory most of the time: at r = 32 three, with 32
+    // rows a wave in k_bwd_dm, take 98.8 and 94.0 us for the two sides of 96 units of 4096, two with 64 rows 105.1 and 101.8.
+    static constexpr int OCC = R == 32 && D == 64 ? 3 : 2;
+    static constexpr int G = OCC == 3 ? 3 : 4 / DW, SLOTS = 4 * G;    // tiles per chunk, of the ring
     static constexpr int TILES = 8 * (RS * (RS + 1) / 2);
     static constexpr int LDS_BYTES = SLOTS * TILE;
-    static_assert(LDS_BYTES <= 81920 && TILES % G == 0, "two workgroups per CU");
+    static_assert(OCC * LDS_BYTES <= 163840 && TILES % G == 0, "workgroups per CU, whole chunks");
     static constexpr int first_tile(int s0) { return s0 == 0 ? 0 : first_tile(s0 - 1) + 8 * (RS - s0 + 1); }
     static constexpr int range_of(int it)
     {

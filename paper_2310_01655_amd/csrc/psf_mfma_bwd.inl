@@ -491,7 +491,7 @@ struct StateTimesRow : StateTiles<R, D> {
 // dX = bf16(J_m(x)^T (dm + dXacc)).
 // RAW (learned sketches, and those with a pass of their own): dm itself is the result, fp32 rows (held_quad) in dMout.
 template <int R, int D, bool QSIDE, int TT, bool LS = false, bool RAW = false>
-__global__ __launch_bounds__(kWg, 2) void k_bwd_dm(const bf16_t *__restrict__ M, const bf16_t *__restrict__ Vec,
+__global__ __launch_bounds__(kWg, (StateTiles<R, D>::OCC)) void k_bwd_dm(const bf16_t *__restrict__ M, const bf16_t *__restrict__ Vec,
                                                   const float *__restrict__ Cc, const bf16_t *__restrict__ Zs,
                                                   const bf16_t *__restrict__ Shi, const bf16_t *__restrict__ Slo,
                                                   const bf16_t *__restrict__ Xrows, const bf16_t *__restrict__ Gt,
@@ -627,7 +627,7 @@ __global__ __launch_bounds__(kWg, 2) void k_bwd_dm(const bf16_t *__restrict__ M,
 
 // ---- dV: cross-block part = phi'(k_j)^T R_l (value columns) ----------------------------------
 template <int R, int D, int TT>
-__global__ __launch_bounds__(kWg, 2) void k_bwd_dvc(const bf16_t *__restrict__ MK, const bf16_t *__restrict__ Rg,
+__global__ __launch_bounds__(kWg, (StateTiles<R, D>::OCC)) void k_bwd_dvc(const bf16_t *__restrict__ MK, const bf16_t *__restrict__ Rg,
                                                    float *__restrict__ dVc, int n, int b, int t)
 {
     using X = FeaturesTimesState<R, D, TT>;
@@ -1035,6 +1035,7 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
                          void *saved = nullptr, const void *O_saved = nullptr, float *dG = nullptr)
 {
     constexpr int TT = D == 64 ? 2 : 1;                     // 32-token tiles per wave in the cross-block kernels
+    constexpr int DT = D == 64 && R == 64 ? 2 : 1;          // the same in k_bwd_dm (see StateTiles::OCC)
     constexpr int NWL = 4;                                  // waves per in-block workgroup: 256 own rows share a streamed tile
     MfmaBwdWs w = carve_bwd(pb, ws);
     MfmaWs f = carve(pb, w.fwd);
@@ -1121,15 +1122,15 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
     if (tm) tm->mark();
     // cross-block parts of dm(q), dm(k), then through the sketch together with the in-block parts
     {
-        const unsigned grid = (unsigned)(rows / (128 * TT));
+        const unsigned grid = (unsigned)(rows / (128 * DT));
         const int ph = pb.per_head ? 1 : 0;
         if constexpr (R == D && P == 4) {
             if (ls) {
-                hipLaunchKernelGGL((k_bwd_dm<R, D, true, TT, true>), dim3(grid), dim3(kWg), 0, s, f.MQ, w.G_rm, w.Cc,
+                hipLaunchKernelGGL((k_bwd_dm<R, D, true, DT, true>), dim3(grid), dim3(kWg), 0, s, f.MQ, w.G_rm, w.Cc,
                                    f.Zg, f.Shi, f.Slo, q, f.Gt, (const bf16_t *)G, w.dQacc, (bf16_t *)dQ, pb.n, pb.b,
                                    pb.t, pb.heads, ph, pb.g_len);
                 PSF_LAUNCH_CHECK();
-                hipLaunchKernelGGL((k_bwd_dm<R, D, false, TT, true>), dim3(grid), dim3(kWg), 0, s, w.MK, v, w.Cc, w.Rg,
+                hipLaunchKernelGGL((k_bwd_dm<R, D, false, DT, true>), dim3(grid), dim3(kWg), 0, s, w.MK, v, w.Cc, w.Rg,
                                    w.Rchi, w.Rclo, k, f.Gt, (const bf16_t *)G, w.dKacc, (bf16_t *)dK, pb.n, pb.b, pb.t,
                                    pb.heads, ph, pb.g_len);
                 PSF_LAUNCH_CHECK();
@@ -1150,11 +1151,11 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
             PSF_LAUNCH_CHECK();
             for (int side = 0; side < 2; ++side) {
                 if (side == 0)
-                    hipLaunchKernelGGL((k_bwd_dm<R, D, true, TT, false, true>), dim3(grid), dim3(kWg), 0, s, f.MQ, w.G_rm,
+                    hipLaunchKernelGGL((k_bwd_dm<R, D, true, DT, false, true>), dim3(grid), dim3(kWg), 0, s, f.MQ, w.G_rm,
                                        w.Cc, f.Zg, f.Shi, f.Slo, q, nullptr, nullptr, nullptr, nullptr, pb.n, pb.b, pb.t,
                                        pb.heads, ph, pb.g_len, w.M8r);
                 else
-                    hipLaunchKernelGGL((k_bwd_dm<R, D, false, TT, false, true>), dim3(grid), dim3(kWg), 0, s, w.MK, v,
+                    hipLaunchKernelGGL((k_bwd_dm<R, D, false, DT, false, true>), dim3(grid), dim3(kWg), 0, s, w.MK, v,
                                        w.Cc, w.Rg, w.Rchi, w.Rclo, k, nullptr, nullptr, nullptr, nullptr, pb.n, pb.b, pb.t,
                                        pb.heads, ph, pb.g_len, w.M8r);
                 PSF_LAUNCH_CHECK();
@@ -1188,11 +1189,11 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
                 PSF_LAUNCH_CHECK();
             }
         } else if (!ls) {
-            hipLaunchKernelGGL((k_bwd_dm<R, D, true, TT>), dim3(grid), dim3(kWg), 0, s, f.MQ, w.G_rm, w.Cc, f.Zg, f.Shi,
+            hipLaunchKernelGGL((k_bwd_dm<R, D, true, DT>), dim3(grid), dim3(kWg), 0, s, f.MQ, w.G_rm, w.Cc, f.Zg, f.Shi,
                                f.Slo, q, f.Gt, (const bf16_t *)G, w.dQacc, (bf16_t *)dQ, pb.n, pb.b, pb.t, pb.heads, ph,
                                pb.g_len);
             PSF_LAUNCH_CHECK();
-            hipLaunchKernelGGL((k_bwd_dm<R, D, false, TT>), dim3(grid), dim3(kWg), 0, s, w.MK, v, w.Cc, w.Rg, w.Rchi,
+            hipLaunchKernelGGL((k_bwd_dm<R, D, false, DT>), dim3(grid), dim3(kWg), 0, s, w.MK, v, w.Cc, w.Rg, w.Rchi,
                                w.Rclo, k, f.Gt, (const bf16_t *)G, w.dKacc, (bf16_t *)dK, pb.n, pb.b, pb.t, pb.heads, ph,
                                pb.g_len);
             PSF_LAUNCH_CHECK();
@@ -1202,11 +1203,11 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
             // by now), then Algorithm 1's reverse as a pass of its own, one side after the other
             for (int side = 0; side < 2; ++side) {
                 if (side == 0)
-                    hipLaunchKernelGGL((k_bwd_dm<R, D, true, TT, false, true>), dim3(grid), dim3(kWg), 0, s, f.MQ, w.G_rm,
+                    hipLaunchKernelGGL((k_bwd_dm<R, D, true, DT, false, true>), dim3(grid), dim3(kWg), 0, s, f.MQ, w.G_rm,
                                        w.Cc, f.Zg, f.Shi, f.Slo, q, nullptr, nullptr, nullptr, nullptr, pb.n, pb.b, pb.t,
                                        pb.heads, ph, pb.g_len, w.M8r);
                 else
-                    hipLaunchKernelGGL((k_bwd_dm<R, D, false, TT, false, true>), dim3(grid), dim3(kWg), 0, s, w.MK, v,
+                    hipLaunchKernelGGL((k_bwd_dm<R, D, false, DT, false, true>), dim3(grid), dim3(kWg), 0, s, w.MK, v,
                                        w.Cc, w.Rg, w.Rchi, w.Rclo, k, nullptr, nullptr, nullptr, nullptr, pb.n, pb.b, pb.t,
                                        pb.heads, ph, pb.g_len, w.M8r);
                 PSF_LAUNCH_CHECK();
