@@ -481,41 +481,23 @@ struct StateTimesRow : StateTiles<R, D> {
 };
 
 // ---- dm(q) and dm(k): cross-block part -------------------------------------------------------
-// QSIDE: tokens of block l >= 1 with Z / S of slot l - 1, vec = g, coefficient c_i.
-// key side: tokens of block l <= t - 2 with R / Rc of the mirror slot t - 2 - l, vec = v,
-// coefficient 1.  Blocks without a cross-block term have dm = 0.  dm stays in registers and goes
-// straight through Algorithm 1 (sketch_grad_tile): dX = bf16(dXacc + J_m(x)^T dm), with dXacc the
-// in-block part, for the rows X (Q or K) of the workgroup.
-// LS (in-block rule of Section 3.1, R == D): the in-block weights are functions of the sketches
-// too, so dXacc holds the in-block part of dm ([rows][R] fp32), which joins dm before the sketch:
-// dX = bf16(J_m(x)^T (dm + dXacc)).
-// RAW (learned sketches, and those with a pass of their own): dm itself is the result, fp32 rows (held_quad) in dMout.
-template <int R, int D, bool QSIDE, int TT, bool LS = false, bool RAW = false>
-__global__ __launch_bounds__(kWg, (StateTiles<R, D>::OCC)) void k_bwd_dm(const bf16_t *__restrict__ M, const bf16_t *__restrict__ Vec,
-                                                  const float *__restrict__ Cc, const bf16_t *__restrict__ Zs,
-                                                  const bf16_t *__restrict__ Shi, const bf16_t *__restrict__ Slo,
-                                                  const bf16_t *__restrict__ Xrows, const bf16_t *__restrict__ Gt,
-                                                  const bf16_t *__restrict__ G, const float *__restrict__ dXacc,
-                                                  bf16_t *__restrict__ dX, int n, int b, int t, int heads,
-                                                  int per_head, size_t g_len, float *__restrict__ dMout = nullptr)
+// dm of the workgroup's 128 TT rows from i0 of unit u on; stage: StateTimesRow's room, free again at the end (of every wave
+// where there was a state, untouched where there was none: then false).
+template <int R, int D, bool QSIDE, int TT>
+__device__ __forceinline__ bool dm_rows(const bf16_t *__restrict__ M, const bf16_t *__restrict__ Vec,
+                                        const float *__restrict__ Cc, const bf16_t *__restrict__ Zs,
+                                        const bf16_t *__restrict__ Shi, const bf16_t *__restrict__ Slo, int u, int i0,
+                                        int n, int b, int t, unsigned char *stage, f32x16 (&out)[TT][R / 32])
 {
     using X = StateTimesRow<R, D, TT>;
-    constexpr int MATS = sizeof(SketchLds<D, R>) + 2 * D * (R + 8) * 2;
-    static_assert(RAW || MATS + 4 * RowsOut<D>::BYTES <= X::LDS_BYTES, "the sketch matrices and the result rows reuse the stage");
-    constexpr int AT = R / 32, RS = R / 16, VS = D / 16, TOK_WG = 128 * TT;
-    __shared__ __attribute__((aligned(16))) unsigned char stage[X::LDS_BYTES];
-    const int tid = threadIdx.x, lane = tid & 63, x = lane & 31, h = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tiles_per_unit = n / TOK_WG;
-    int wg = blockIdx.x;                                    // XCD-aware order: one state snapshot, one L2
-    if ((gridDim.x & 7) == 0) wg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    const int u = wg / tiles_per_unit, i0 = (wg % tiles_per_unit) * TOK_WG;
+    constexpr int AT = R / 32, RS = R / 16, VS = D / 16;
+    const int lane = threadIdx.x & 63, x = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l = i0 / b;
     const size_t urow = (size_t)u * n;
     const bool has = QSIDE ? l > 0 : l < t - 1;
     const int slot = QSIDE ? l - 1 : t - 2 - l;
 
-    f32x16 out[TT][AT];
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
@@ -581,6 +563,42 @@ __global__ __launch_bounds__(kWg, (StateTiles<R, D>::OCC)) void k_bwd_dm(const b
 #pragma unroll
                 for (int v = 0; v < 16; ++v) out[tt][at][v] = dm[tt][16 * at + v];
     }
+    return has;
+}
+
+// QSIDE: tokens of block l >= 1 with Z / S of slot l - 1, vec = g, coefficient c_i.
+// key side: tokens of block l <= t - 2 with R / Rc of the mirror slot t - 2 - l, vec = v,
+// coefficient 1.  Blocks without a cross-block term have dm = 0.  dm stays in registers and goes
+// straight through Algorithm 1 (sketch_grad_tile): dX = bf16(dXacc + J_m(x)^T dm), with dXacc the
+// in-block part, for the rows X (Q or K) of the workgroup.
+// LS (in-block rule of Section 3.1, R == D): the in-block weights are functions of the sketches
+// too, so dXacc holds the in-block part of dm ([rows][R] fp32), which joins dm before the sketch:
+// dX = bf16(J_m(x)^T (dm + dXacc)).
+// RAW (learned sketches, and those with a pass of their own): dm itself is the result, fp32 rows (held_quad) in dMout.
+template <int R, int D, bool QSIDE, int TT, bool LS = false, bool RAW = false>
+__global__ __launch_bounds__(kWg, (StateTiles<R, D>::OCC)) void k_bwd_dm(const bf16_t *__restrict__ M, const bf16_t *__restrict__ Vec,
+                                                  const float *__restrict__ Cc, const bf16_t *__restrict__ Zs,
+                                                  const bf16_t *__restrict__ Shi, const bf16_t *__restrict__ Slo,
+                                                  const bf16_t *__restrict__ Xrows, const bf16_t *__restrict__ Gt,
+                                                  const bf16_t *__restrict__ G, const float *__restrict__ dXacc,
+                                                  bf16_t *__restrict__ dX, int n, int b, int t, int heads,
+                                                  int per_head, size_t g_len, float *__restrict__ dMout = nullptr)
+{
+    using X = StateTimesRow<R, D, TT>;
+    constexpr int MATS = sizeof(SketchLds<D, R>) + 2 * D * (R + 8) * 2;
+    static_assert(RAW || MATS + 4 * RowsOut<D>::BYTES <= X::LDS_BYTES, "the sketch matrices and the result rows reuse the stage");
+    constexpr int AT = R / 32, TOK_WG = 128 * TT;
+    __shared__ __attribute__((aligned(16))) unsigned char stage[X::LDS_BYTES];
+    const int tid = threadIdx.x, lane = tid & 63, x = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tiles_per_unit = n / TOK_WG;
+    int wg = blockIdx.x;                                    // XCD-aware order: one state snapshot, one L2
+    if ((gridDim.x & 7) == 0) wg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const int u = wg / tiles_per_unit, i0 = (wg % tiles_per_unit) * TOK_WG;
+    const size_t urow = (size_t)u * n;
+
+    f32x16 out[TT][AT];
+    dm_rows<R, D, QSIDE, TT>(M, Vec, Cc, Zs, Shi, Slo, u, i0, n, b, t, stage, out);
     if constexpr (RAW) {
         // register v of out[tt][at]: sketch column 32 at + 8 (v / 4) + 4 h + v % 4
 #pragma unroll
@@ -626,12 +644,35 @@ __global__ __launch_bounds__(kWg, (StateTiles<R, D>::OCC)) void k_bwd_dm(const b
 }
 
 // ---- dV: cross-block part = phi'(k_j)^T R_l (value columns) ----------------------------------
+// 32 TT rows a wave of the 128 TT from i0 of unit u on; slot: the mirror state they take.
+template <int R, int D, int TT>
+__device__ __forceinline__ void dv_rows(const bf16_t *__restrict__ MK, const bf16_t *__restrict__ Rg, int u, int i0, int slot,
+                                        int n, int t, unsigned char *stage, f32x16 (&out)[TT][D / 32])
+{
+    using X = FeaturesTimesState<R, D, TT>;
+    constexpr int RS = R / 16;
+    const int lane = threadIdx.x & 63, x = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bf16_t *r = Rg + ((size_t)u * (t - 1) + slot) * R * R * D;
+    typename X::Ring(r, stage).fill();
+    f32x8 vec[TT][RS];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+        for (int s = 0; s < RS; ++s) {
+            const bf16x8 raw = *(const bf16x8 *)&MK[((size_t)u * n + i0 + wave * 32 * TT + 32 * tt + x) * R + 16 * s + 8 * h];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) vec[tt][s][e] = (float)raw[e];
+        }
+    X::run(r, vec, out, stage);
+}
+
 template <int R, int D, int TT>
 __global__ __launch_bounds__(kWg, (StateTiles<R, D>::OCC)) void k_bwd_dvc(const bf16_t *__restrict__ MK, const bf16_t *__restrict__ Rg,
                                                    float *__restrict__ dVc, int n, int b, int t)
 {
     using X = FeaturesTimesState<R, D, TT>;
-    constexpr int CT = D / 32, RS = R / 16, TOK_WG = 128 * TT;
+    constexpr int CT = D / 32, TOK_WG = 128 * TT;
     __shared__ __attribute__((aligned(16))) unsigned char stage[X::LDS_BYTES];
     const int tid = threadIdx.x, lane = tid & 63, x = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -646,20 +687,7 @@ __global__ __launch_bounds__(kWg, (StateTiles<R, D>::OCC)) void k_bwd_dvc(const 
     for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) out[tt][ct] = f32x16{0};
-    if (l < t - 1) {
-        const bf16_t *r = Rg + ((size_t)u * (t - 1) + (t - 2 - l)) * R * R * D;
-        typename X::Ring(r, stage).fill();
-        f32x8 vec[TT][RS];
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-            for (int s = 0; s < RS; ++s) {
-                const bf16x8 raw = *(const bf16x8 *)&MK[(urow + i0 + wave * 32 * TT + 32 * tt + x) * R + 16 * s + 8 * h];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) vec[tt][s][e] = (float)raw[e];
-            }
-        X::run(r, vec, out, stage);
-    }
+    if (l < t - 1) dv_rows<R, D, TT>(MK, Rg, u, i0, t - 2 - l, n, t, stage, out);
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
         const size_t row = urow + i0 + wave * 32 * TT + 32 * tt + x;
@@ -673,6 +701,48 @@ __global__ __launch_bounds__(kWg, (StateTiles<R, D>::OCC)) void k_bwd_dvc(const 
             }
     }
 }
+
+// The cross-block part of one side inside the in-block kernel of that side (degree 4, Gaussian sketches, r = 32): the
+// gradient through the states and the sketch is where the in-block accumulators start from, so that the fp32 rows
+// between the two kernels (one written and read for queries, two for keys) and the second read of the side's own rows
+// go away.  At r = 64 the contractions want 64 rows a wave, which the in-block part has no registers for.  96 units of
+// 4096, us, as kernels of their own and in one: queries 71 + 99 and 123, keys 93 + 94 + 60 and 169.
+struct CrossSide {
+    const bf16_t *M, *Zs, *Shi, *Slo, *Gt, *G;               // the side's sketches, states, matrices
+    bf16_t *dX;
+    int heads, per_head;
+    size_t g_len;
+
+    template <int R, int D>
+    static constexpr int mats_bytes() { return sizeof(SketchLds<D, R>) + 2 * D * (R + 8) * 2; }
+    template <int R, int D>
+    static constexpr int lds_bytes() { return std::max(StateTimesRow<R, D, 1>::LDS_BYTES, mats_bytes<R, D>()); }
+
+    // dx: 1 / P (a power of two) of the row's gradient, 128 rows from i0 of unit u on.  stage is free before and after.
+    template <int R, int D, int P, bool QSIDE>
+    __device__ __forceinline__ void rows(const bf16_t *__restrict__ Vec, const float *__restrict__ Cc,
+                                         const bf16_t *__restrict__ X, int u, int i0, int n, int b, int t,
+                                         unsigned char *stage, f32x16 (&dx)[D / 32]) const
+    {
+        const int lane = threadIdx.x & 63, x = lane & 31, h = lane >> 5;
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        f32x16 dm[1][R / 32];
+        if (!dm_rows<R, D, QSIDE, 1>(M, Vec, Cc, Zs, Shi, Slo, u, i0, n, b, t, stage, dm)) {
+#pragma unroll
+            for (int ct = 0; ct < D / 32; ++ct) dx[ct] = f32x16{0};
+            return;
+        }
+        SketchLds<D, R> &lds = *(SketchLds<D, R> *)stage;
+        bf16_t *go = (bf16_t *)(stage + sizeof(SketchLds<D, R>));
+        const size_t goff = per_head ? (size_t)(u % heads) * g_len : 0;
+        sketch_grad_stage<D, R>(lds, go, Gt + goff, G + goff);
+        __syncthreads();
+        sketch_grad_tile<D, R, false>(lds, go, X, dm[0], nullptr, (size_t)u * n + i0 + wave * 32 + x, x, h, dx);
+#pragma unroll
+        for (int ct = 0; ct < D / 32; ++ct) dx[ct] *= 1.0f / (float)P;
+        __syncthreads();
+    }
+};
 
 // ---- in-block pairs ---------------------------------------------------------------------------
 // Both kernels: workgroup = 32 NW "own" rows (wave = 32, held in registers as B operands), the other side streams
@@ -728,18 +798,19 @@ struct LocTile {
 
 // dQ (in-block): own rows = queries, streamed = keys of the same block up to the diagonal.
 //   dq_i = sum_{j <= i} (<g_i, v_j> + c_i) p <q_i, k_j>^(p-1) k_j          -> dQacc fp32 rows
+// CROSS: the cross-block part and Algorithm 1's reverse first, in the same workgroup, into the accumulators (see CrossSide).
 // The launch's last workgroups scan the mirror states' ones column (R: sketch width; DenScan::n_main others come first).
-template <int P, int NW, int D, int R>
+template <int P, int NW, int D, int R, bool CROSS = false>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_q(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                                          const bf16_t *__restrict__ V, const bf16_t *__restrict__ G_rm,
                                                                          const float *__restrict__ Cc, float *__restrict__ dQacc,
-                                                                         int n, int b, int t, DenScan den)
+                                                                         int n, int b, int t, DenScan den, CrossSide cx = {})
 {
     constexpr int KS = D / 16, CT = D / 32, NTHR = 64 * NW, OWN = 32 * NW;
     using Tile = LocTile<D, NTHR>;
     constexpr int BUF = 2 * Tile::BYTES;
     static_assert(NTHR == kWg, "the scan's workgroup");
-    __shared__ __attribute__((aligned(16))) unsigned char stage[2 * BUF];
+    __shared__ __attribute__((aligned(16))) unsigned char stage[CROSS ? std::max(2 * BUF, CrossSide::lds_bytes<R, D>()) : 2 * BUF];
     if (den_scan_role<R, NTHR>(den, t, stage)) return;
     const Tile T;
     const int x = T.x, h = T.h, tiles_per_unit = n / OWN;
@@ -751,6 +822,13 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_q(const 
     const int jb = (i0 / b) * b;
     const size_t urow = (size_t)u * n;
     const int tok0 = i0 + 32 * T.wave, tok = tok0 + x;
+    f32x16 dq[CT];
+    if constexpr (CROSS) {
+        cx.rows<R, D, P, true>(G_rm, Cc, Q, u, i0, n, b, t, stage, dq);
+    } else {
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) dq[ct] = f32x16{0};
+    }
     bf16x8 qfr[KS], gfr[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
@@ -758,9 +836,6 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_q(const 
         gfr[s] = *(const bf16x8 *)&G_rm[(urow + tok) * D + 16 * s + 8 * h];
     }
     const float c_me = Cc[urow + tok];
-    f32x16 dq[CT];
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) dq[ct] = f32x16{0};
     const int ntiles = (i0 + OWN - jb) / kLocT;
     const uint32_t stage0 = lds_address(stage);
     auto stage_tile = [&](int kt) {
@@ -816,6 +891,13 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_q(const 
     tile(std::true_type{}, diag);
 #pragma unroll 1
     for (int kt = diag + 1; kt < ntiles; ++kt) sync(kt);   // later tiles: only keep the barriers and copies going
+    if constexpr (CROSS) {
+        __syncthreads();                                    // every wave is done with the last tile
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) dq[ct] *= (float)P;
+        store_rows<D>(RowsOut<D>(stage, T.wave, T.tid & 63), dq, cx.dX + (urow + tok0) * D);
+        return;
+    }
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
@@ -831,17 +913,18 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_q(const 
 // streamed = queries of the same block from the diagonal on.
 //   dk_j = sum_{i >= j} (<g_i, v_j> + c_i) p <q_i, k_j>^(p-1) q_i   -> dKacc fp32 rows (held_quad)
 //   dv_j = sum_{i >= j} <q_i, k_j>^p g_i + dVc_j                     -> dV bf16 rows
-template <int P, int NW, int D = 64>
+// CROSS: the cross-block parts of both first, in the same workgroup, into the accumulators; dK as bf16 rows (see CrossSide).
+template <int P, int NW, int D, int R = 0, bool CROSS = false>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_k(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                                          const bf16_t *__restrict__ V, const bf16_t *__restrict__ G_rm,
                                                                          const float *__restrict__ Cc, const float *__restrict__ dVc,
                                                                          float *__restrict__ dKacc, bf16_t *__restrict__ dV,
-                                                                         int n, int b)
+                                                                         int n, int b, int t = 0, CrossSide cx = {})
 {
     constexpr int KS = D / 16, CT = D / 32, NTHR = 64 * NW, OWN = 32 * NW;
     using Tile = LocTile<D, NTHR>;
-    constexpr int BUF = 2 * Tile::BYTES + kLocT * 4;
-    __shared__ __attribute__((aligned(16))) unsigned char stage[2 * BUF];
+    constexpr int BUF = 2 * Tile::BYTES + kLocT * 4, RC = CROSS ? R : 32;
+    __shared__ __attribute__((aligned(16))) unsigned char stage[CROSS ? std::max(2 * BUF, CrossSide::lds_bytes<RC, D>()) : 2 * BUF];
     const Tile T;
     const int x = T.x, h = T.h, tiles_per_unit = n / OWN;
     int wg = blockIdx.x;                                    // XCD-aware order, as in k_bwd_local_q
@@ -850,15 +933,21 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_k(const 
     const int jb = (j0 / b) * b;
     const size_t urow = (size_t)u * n;
     const int key0 = j0 + 32 * T.wave, key = key0 + x;
+    f32x16 dk[CT], dv[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) dk[ct] = dv[ct] = f32x16{0};
+    if constexpr (CROSS) {
+        cx.rows<R, D, P, false>(V, nullptr, K, u, j0, n, b, t, stage, dk);
+        const int l = j0 / b;
+        if (l < t - 1) dv_rows<R, D, 1>(cx.M, cx.Zs, u, j0, t - 2 - l, n, t, stage, *(f32x16(*)[1][CT]) & dv);
+        __syncthreads();                                    // the stage is free
+    }
     bf16x8 kfr[KS], vfr[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
         kfr[s] = *(const bf16x8 *)&K[(urow + key) * D + 16 * s + 8 * h];
         vfr[s] = *(const bf16x8 *)&V[(urow + key) * D + 16 * s + 8 * h];
     }
-    f32x16 dk[CT], dv[CT];
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) dk[ct] = dv[ct] = f32x16{0};
     const int first = (j0 - jb) / kLocT, ntiles = b / kLocT;
     const uint32_t stage0 = lds_address(stage);
     auto stage_tile = [&](int qt) {
@@ -927,6 +1016,13 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_k(const 
     static_assert(NW * RowsOut<D>::BYTES <= 2 * BUF, "the rows reuse the stage");
     __syncthreads();                                        // every wave is done with the last tile
     const RowsOut<D> rows_out(stage, T.wave, T.tid & 63);
+    if constexpr (CROSS) {
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) dk[ct] *= (float)P;
+        store_rows<D>(rows_out, dk, cx.dX + (urow + key0) * D);
+        store_rows<D>(rows_out, dv, dV + (urow + key0) * D);
+        return;
+    }
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
@@ -1083,6 +1179,25 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
         if (st != PSF_OK) return st;
     }
     if (tm) tm->mark();
+    if constexpr (D == 64 && P == 4 && R == 32) {
+        if (!pb.learned) {
+            // both parts of a side in one kernel; the timed call's last two stages are the query and the key side
+            const unsigned main = (unsigned)(rows / (32 * NWL));
+            const DenScan den = {w.ScPart, w.Rchi, w.Rclo, pb.b / 256, pb.n / 256, (int)main};
+            const int ph = pb.per_head ? 1 : 0;
+            const CrossSide cq = {f.MQ, f.Zg, f.Shi, f.Slo, f.Gt, (const bf16_t *)G, (bf16_t *)dQ, pb.heads, ph, pb.g_len};
+            const CrossSide ck = {w.MK, w.Rg, w.Rchi, w.Rclo, f.Gt, (const bf16_t *)G, (bf16_t *)dK, pb.heads, ph, pb.g_len};
+            hipLaunchKernelGGL((k_bwd_local_q<P, NWL, D, R, true>), dim3(main + (pb.t > 1 ? (unsigned)(pb.units * (R * R / kWg)) : 0u)),
+                               dim3(64 * NWL), 0, s, q, k, v, w.G_rm, w.Cc, nullptr, pb.n, pb.b, pb.t, den, cq);
+            PSF_LAUNCH_CHECK();
+            if (tm) tm->mark();
+            hipLaunchKernelGGL((k_bwd_local_k<P, NWL, D, R, true>), dim3(main), dim3(64 * NWL), 0, s, q, k, v, w.G_rm, w.Cc,
+                               nullptr, nullptr, (bf16_t *)dV, pb.n, pb.b, pb.t, ck);
+            PSF_LAUNCH_CHECK();
+            if (tm) tm->mark();
+            return PSF_OK;
+        }
+    }
     // in-block parts
     {
         const unsigned main = (unsigned)(rows / (32 * NWL));
@@ -1188,7 +1303,8 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
                                    w.part, dG, pb.g_len, sl.units, sl.per_unit, pb.heads, ph);
                 PSF_LAUNCH_CHECK();
             }
-        } else if (!ls) {
+        } else if constexpr (R != 32) {                     // (r = 32: done above)
+            if (!ls) {
             hipLaunchKernelGGL((k_bwd_dm<R, D, true, DT>), dim3(grid), dim3(kWg), 0, s, f.MQ, w.G_rm, w.Cc, f.Zg, f.Shi,
                                f.Slo, q, f.Gt, (const bf16_t *)G, w.dQacc, (bf16_t *)dQ, pb.n, pb.b, pb.t, pb.heads, ph,
                                pb.g_len);
@@ -1197,6 +1313,7 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
                                w.Rclo, k, f.Gt, (const bf16_t *)G, w.dKacc, (bf16_t *)dK, pb.n, pb.b, pb.t, pb.heads, ph,
                                pb.g_len);
             PSF_LAUNCH_CHECK();
+            }
         }
         } else {
             // d = 128 or degree 8: dm as fp32 rows (in the buffer of the mirror-state octets, consumed
