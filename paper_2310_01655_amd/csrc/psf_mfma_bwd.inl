@@ -914,7 +914,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_q(const 
 //   dk_j = sum_{i >= j} (<g_i, v_j> + c_i) p <q_i, k_j>^(p-1) q_i   -> dKacc fp32 rows (held_quad)
 //   dv_j = sum_{i >= j} <q_i, k_j>^p g_i + dVc_j                     -> dV bf16 rows
 // CROSS: the cross-block parts of both first, in the same workgroup, into the accumulators; dK as bf16 rows (see CrossSide).
-template <int P, int NW, int D, int R = 0, bool CROSS = false>
+// CROSS_V: dV's alone, from the mirror states cx.Zs and m(K) in cx.M (48 units of 8192, r = 32: 172 us, with k_bwd_dvc and
+// its fp32 rows 154 + 44; a call of 16 units of 16384, d = 128: 2035, 2083).
+template <int P, int NW, int D, int R = 0, bool CROSS = false, bool CROSS_V = CROSS>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_k(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                                          const bf16_t *__restrict__ V, const bf16_t *__restrict__ G_rm,
                                                                          const float *__restrict__ Cc, const float *__restrict__ dVc,
@@ -923,8 +925,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_k(const 
 {
     constexpr int KS = D / 16, CT = D / 32, NTHR = 64 * NW, OWN = 32 * NW;
     using Tile = LocTile<D, NTHR>;
-    constexpr int BUF = 2 * Tile::BYTES + kLocT * 4, RC = CROSS ? R : 32;
-    __shared__ __attribute__((aligned(16))) unsigned char stage[CROSS ? std::max(2 * BUF, CrossSide::lds_bytes<RC, D>()) : 2 * BUF];
+    constexpr int BUF = 2 * Tile::BYTES + kLocT * 4, RC = CROSS_V ? R : 32;
+    constexpr int CROSS_LDS = CROSS ? CrossSide::lds_bytes<RC, D>() : CROSS_V ? StateTiles<RC, D>::LDS_BYTES : 0;
+    __shared__ __attribute__((aligned(16))) unsigned char stage[std::max(2 * BUF, CROSS_LDS)];
     const Tile T;
     const int x = T.x, h = T.h, tiles_per_unit = n / OWN;
     int wg = blockIdx.x;                                    // XCD-aware order, as in k_bwd_local_q
@@ -936,8 +939,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_k(const 
     f32x16 dk[CT], dv[CT];
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) dk[ct] = dv[ct] = f32x16{0};
-    if constexpr (CROSS) {
-        cx.rows<R, D, P, false>(V, nullptr, K, u, j0, n, b, t, stage, dk);
+    if constexpr (CROSS) cx.rows<R, D, P, false>(V, nullptr, K, u, j0, n, b, t, stage, dk);
+    if constexpr (CROSS_V) {
         const int l = j0 / b;
         if (l < t - 1) dv_rows<R, D, 1>(cx.M, cx.Zs, u, j0, t - 2 - l, n, t, stage, *(f32x16(*)[1][CT]) & dv);
         __syncthreads();                                    // the stage is free
@@ -1032,7 +1035,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void k_bwd_local_k(const 
             const f32x4 k4 = {(float)P * dk[ct][4 * gq], (float)P * dk[ct][4 * gq + 1], (float)P * dk[ct][4 * gq + 2],
                               (float)P * dk[ct][4 * gq + 3]};
             *(f32x4 *)&dKacc[held] = k4;
-            const f32x4 c4 = *(const f32x4 *)&dVc[held];
+            f32x4 c4 = {0.f, 0.f, 0.f, 0.f};                // (with CROSS_V the sums started from it)
+            if constexpr (!CROSS_V) c4 = *(const f32x4 *)&dVc[held];
             const f32x4 v4 = {dv[ct][4 * gq] + c4[0], dv[ct][4 * gq + 1] + c4[1], dv[ct][4 * gq + 2] + c4[2],
                               dv[ct][4 * gq + 3] + c4[3]};
             rows_out.put(ct, gq, v4);
@@ -1219,8 +1223,12 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
     {
         // dV: the cross-block part first, the in-block kernel adds to it
         const unsigned gridc = (unsigned)(rows / (128 * TT)), grid = (unsigned)(rows / (32 * NWL));
-        hipLaunchKernelGGL((k_bwd_dvc<R, D, TT>), dim3(gridc), dim3(kWg), 0, s, w.MK, w.Rg, w.dVc, pb.n, pb.b, pb.t);
-        PSF_LAUNCH_CHECK();
+        constexpr bool APART = D == 64 && R == 64;          // two row tiles a wave share a state's operands there
+        const CrossSide cv = {w.MK, w.Rg, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, 0};
+        if constexpr (APART) {
+            hipLaunchKernelGGL((k_bwd_dvc<R, D, TT>), dim3(gridc), dim3(kWg), 0, s, w.MK, w.Rg, w.dVc, pb.n, pb.b, pb.t);
+            PSF_LAUNCH_CHECK();
+        }
         if constexpr (R == D && P == 4) {
             if (ls) {
                 hipLaunchKernelGGL((k_bwd_local_k<2, NWL, D>), dim3(grid), dim3(64 * NWL), 0, s, rq, rk, v, w.G_rm, w.Cc,
@@ -1229,8 +1237,8 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
             }
         }
         if (!ls) {
-            hipLaunchKernelGGL((k_bwd_local_k<P, NWL, D>), dim3(grid), dim3(64 * NWL), 0, s, q, k, v, w.G_rm, w.Cc,
-                               w.dVc, w.dKacc, (bf16_t *)dV, pb.n, pb.b);
+            hipLaunchKernelGGL((k_bwd_local_k<P, NWL, D, R, false, !APART>), dim3(grid), dim3(64 * NWL), 0, s, q, k, v, w.G_rm,
+                               w.Cc, w.dVc, w.dKacc, (bf16_t *)dV, pb.n, pb.b, pb.t, cv);
             PSF_LAUNCH_CHECK();
         }
     }
@@ -1305,14 +1313,14 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
             }
         } else if constexpr (R != 32) {                     // (r = 32: done above)
             if (!ls) {
-            hipLaunchKernelGGL((k_bwd_dm<R, D, true, DT>), dim3(grid), dim3(kWg), 0, s, f.MQ, w.G_rm, w.Cc, f.Zg, f.Shi,
-                               f.Slo, q, f.Gt, (const bf16_t *)G, w.dQacc, (bf16_t *)dQ, pb.n, pb.b, pb.t, pb.heads, ph,
-                               pb.g_len);
-            PSF_LAUNCH_CHECK();
-            hipLaunchKernelGGL((k_bwd_dm<R, D, false, DT>), dim3(grid), dim3(kWg), 0, s, w.MK, v, w.Cc, w.Rg, w.Rchi,
-                               w.Rclo, k, f.Gt, (const bf16_t *)G, w.dKacc, (bf16_t *)dK, pb.n, pb.b, pb.t, pb.heads, ph,
-                               pb.g_len);
-            PSF_LAUNCH_CHECK();
+                hipLaunchKernelGGL((k_bwd_dm<R, D, true, DT>), dim3(grid), dim3(kWg), 0, s, f.MQ, w.G_rm, w.Cc, f.Zg, f.Shi,
+                                   f.Slo, q, f.Gt, (const bf16_t *)G, w.dQacc, (bf16_t *)dQ, pb.n, pb.b, pb.t, pb.heads, ph,
+                                   pb.g_len);
+                PSF_LAUNCH_CHECK();
+                hipLaunchKernelGGL((k_bwd_dm<R, D, false, DT>), dim3(grid), dim3(kWg), 0, s, w.MK, v, w.Cc, w.Rg, w.Rchi,
+                                   w.Rclo, k, f.Gt, (const bf16_t *)G, w.dKacc, (bf16_t *)dK, pb.n, pb.b, pb.t, pb.heads, ph,
+                                   pb.g_len);
+                PSF_LAUNCH_CHECK();
             }
         }
         } else {
