@@ -2803,7 +2803,7 @@ psf_status launch_sketch(const Problem &pb, const void *X, const bf16_t *Gt, boo
 //     full tiles, four a wave: 1 unit 72.5 -> 49.6, 12 81 -> 58, 40 105 -> 84, causal 12 93 -> 61; d = 128, r = 64, against
 //     two a wave: 1 unit 127 -> 108, 12 145 -> 131; d = 128, r = 32: 1 unit 80 -> 69, 40 151 -> 139 (one unit more than fit: slower);
 //   d = 64, r = 32, then two tiles a wave (3 workgroups a unit) while those fit: against full tiles, causal, 48 units 134 -> 110,
-//     80 200 -> 182; with one block the tokens' steps split over two waves: 48 units 105 -> 84, 80 148 -> 130;
+//     80 200 -> 182; one block, 48 units 105 -> 79, 80 148 -> 104;
 //     then full tiles, four a wave, while their two a unit fit (causal, 96 units 228 against 230, 128 283 against 293);
 //     beyond, two a wave again (160 units 379 -> 344);
 //   d = 64, r = 64: two tiles a wave, from 80 units on four (below);
@@ -2827,13 +2827,17 @@ psf_status launch_state(const Problem &pb, const float *M8, const bf16_t *V, siz
     } while (0)
     if constexpr (D == 64) {
         // One block only: eight waves, two per SIMD, that split the tokens' steps, 8 % faster per token at r = 64; with a
-        // snapshot every block the exchange and the stalled ring after the stores cost more than that.
-        if (one_block && grid_sym <= 256 && (R == 64 || 2 * grid_sym > 256)) {
-            den.n_main = (int)grid_sym;
-            hipLaunchKernelGGL((k_state_two_waves<R, D, 64>), dim3(grid_sym + scan / 2), dim3(2 * kWg), 0, s, M8, V, v_unit,
-                               v_mirror, Zg, pb.n, pb.b, pb.t, pb.units, den);
-            PSF_LAUNCH_CHECK();
-            return PSF_OK;
+        // snapshot every block the exchange and the stalled ring after the stores cost more than that.  Not at r = 32, where
+        // every form adds up the tokens in their order, so that a sequence's bits do not depend on the units beside it:
+        // there it would take 74 us instead of 79 (48 units of 4096) and 101 instead of 104 (80).
+        if constexpr (R == 64) {
+            if (one_block && grid_sym <= 256) {
+                den.n_main = (int)grid_sym;
+                hipLaunchKernelGGL((k_state_two_waves<R, D, 64>), dim3(grid_sym + scan / 2), dim3(2 * kWg), 0, s, M8, V,
+                                   v_unit, v_mirror, Zg, pb.n, pb.b, pb.t, pb.units, den);
+                PSF_LAUNCH_CHECK();
+                return PSF_OK;
+            }
         }
     }
     if (2 * grid_sym <= 256) {
