@@ -2676,34 +2676,20 @@ bool learned_on_mfma(const Problem &pb)
     return pb.learned && (pb.p == 4 || pb.p == 8) && (pb.d == 64 || pb.d == 128) && pb.b % 256 == 0;
 }
 
-struct MfmaWs;
-MfmaWs carve(const Problem &pb, void *ws, int tiles = 0);
-size_t carve_bytes(const Problem &pb, int tiles);
-bool in_block_beside_states(const Problem &pb);
-
 // 128-token tiles per sketch workgroup, which stays inside one block: eight, so that the matrices staged in LDS are
-// reused, and fewer where that would leave less than kFewParts workgroups a tensor, because a workgroup then is a
-// chain of tiles on an idle chip.  (Blocks that end after four tiles or fewer keep them together: little to gain, and
-// a row's denominator then does not depend on how many units a call has.)  us a call, eight tiles and by this rule: 2048 tokens of r = 32, b = 1024, 1 unit 36.0, 31.6, 12
-// 39.6, 35.2, 48 68.9, 65.9; degree 8 69.5, 41.7 and 73.5, 44.4.  (The partial sums of S that more workgroups leave cost 16
-// KB each at r = 64: not where they would take a call past the library's static scratch.)
-constexpr unsigned kFewParts = 128;
-int sketch_tiles_per_wg(const Problem &pb)
+// reused, or as many as divide a block.  A workgroup leaves one partial sum of S, so this may not go by the number of
+// units (a row's denominator would depend on what shares its call) nor by the length (the room for the sums would
+// fall where a longer call takes more tiles).  Finer parts where there are less than 128 of them would save small calls with b =
+// 1024 time: 2048 tokens, r = 32, 1 unit 36.0, 31.6 us, 12 39.6, 35.2; degree 8 69.5, 41.7 and 73.5, 44.4.
+int sketch_tiles_per_wg(int b)
 {
     int tiles = 8;
-    while (pb.b % (tiles * 128) != 0) tiles /= 2;
-    const size_t rows = (size_t)pb.units * pb.n;
-    int fine = tiles;
-    const int least = in_block_beside_states(pb) ? 2 : 1;   // (its launch deals a sketch part to one or more 256-token tiles)
-    const size_t few = pb.p == 8 ? 2 * kFewParts : kFewParts;   // (degree 8 has six matrices and stages them for every tile)
-    while (tiles == 8 && fine > least && rows / (128 * (size_t)fine) < few) fine /= 2;
-    if (fine != tiles && carve_bytes(pb, fine) > PSF_STATIC_SCRATCH_BYTES && carve_bytes(pb, tiles) <= PSF_STATIC_SCRATCH_BYTES)
-        return tiles;
-    return fine;
+    while (b % (tiles * 128) != 0) tiles /= 2;
+    return tiles;
 }
 
 // tokens per partial S = m^T m handed to the denominator scan
-int part_tokens(const Problem &pb) { return learned_on_mfma(pb) ? 256 : 128 * sketch_tiles_per_wg(pb); }
+int part_tokens(const Problem &pb) { return learned_on_mfma(pb) ? 256 : 128 * sketch_tiles_per_wg(pb.b); }
 
 // The causal call with exact in-block weights at d = r = 64 runs the in-block part of the output
 // beside the state kernel when the state kernel leaves room for it: at most one state
@@ -2735,12 +2721,12 @@ bool half_precision_states(const Problem &pb)
            pb.n / 128 <= kStateF16Tiles;
 }
 
-MfmaWs carve(const Problem &pb, void *ws, int tiles)
+MfmaWs carve(const Problem &pb, void *ws)
 {
     MfmaWs w;
     const size_t rows = (size_t)pb.units * pb.n, R = pb.r, D = pb.d, tb = pb.t > 1 ? pb.t - 1 : 0;
     const size_t sets = pb.per_head ? pb.heads : 1;
-    const size_t parts = rows / (size_t)(tiles ? 128 * tiles : part_tokens(pb));
+    const size_t parts = rows / (size_t)part_tokens(pb);
     size_t off = 0;
     char *base = (char *)ws;
     auto take = [&](size_t bytes) { char *p = base + off; off += align_up(bytes, 256); return p; };
@@ -2766,8 +2752,6 @@ MfmaWs carve(const Problem &pb, void *ws, int tiles)
     w.total = off;
     return w;
 }
-
-size_t carve_bytes(const Problem &pb, int tiles) { return carve(pb, nullptr, tiles).total; }
 
 psf_status launch_transpose_g(const Problem &pb, const void *G, bf16_t *Gt, hipStream_t s)
 {
@@ -2878,7 +2862,7 @@ psf_status attn_impl(const Problem &pb, const void *Q, const void *K, const void
                      bf16_t *MK_rm = nullptr, bool noncausal = false)
 {
     MfmaWs w = carve(pb, ws);
-    const int tiles = sketch_tiles_per_wg(pb);
+    const int tiles = sketch_tiles_per_wg(pb.b);
     psf_status st;
     // the state kernel's launch also runs the in-block part of the output, the denominator scan
     // and, with Gaussian sketches of degree 4, the sketch of the query rows
@@ -3285,7 +3269,7 @@ psf_status total_state_impl(const Problem &pb, int src_n, const void *K, const v
     } else {
         st = launch_transpose_g(pb, G, w.Gt, s);
         if (st != PSF_OK) return st;
-        st = launch_sketch<D, R, P>(pb, K, w.Gt, false, nullptr, w.MK8, w.Spart, sketch_tiles_per_wg(pb), s, src_n);
+        st = launch_sketch<D, R, P>(pb, K, w.Gt, false, nullptr, w.MK8, w.Spart, sketch_tiles_per_wg(pb.b), s, src_n);
         if (st != PSF_OK) return st;
     }
     return launch_state<D, R>(pb, w.MK8, (const bf16_t *)V, (size_t)src_n * D, 0, w.Zg, s);

@@ -36,3 +36,13 @@ def test_no_mask(d, p, r, counts):
     first, *others = rows_by_units(psf.psf_noncausal_attn_fwd, 512, d, p, r, 256, counts)
     for count, x in zip(counts[1:], others):
         assert torch.equal(first, x), "%d units" % count
+
+
+# blocks of whole 1024s: few and many workgroups of the sketches, whose sums over a tile of keys make the denominators
+@pytest.mark.parametrize("d,p,r", [(64, 4, 32), (64, 8, 32), (128, 4, 64), (128, 8, 32)])
+@pytest.mark.parametrize("call", [psf.psf_causal_attn_fwd, psf.psf_noncausal_attn_fwd], ids=["causal", "no_mask"])
+def test_denominators_of_long_blocks(call, d, p, r):
+    counts = (1, 20, 70, 140)
+    first, *others = rows_by_units(call, 2048, d, p, r, 1024, counts)
+    for count, x in zip(counts[1:], others):
+        assert torch.equal(first, x), "%d units" % count
