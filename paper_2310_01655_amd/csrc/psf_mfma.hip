@@ -53,6 +53,7 @@
 
 #include "psf_internal.h"
 #include "psf_lds.h"
+#include "psf_learned_slices.h"
 
 namespace psf {
 namespace {

@@ -1096,7 +1096,7 @@ MfmaBwdWs carve_bwd(const Problem &pb, void *ws)
         w.sg.DAT = (bf16_t *)take(2 * rows * R * 2);
         w.sg.ST = (float *)take(2 * 4 * rows * 4);
         w.GB1 = (float *)take(rows / 256 * 2 * 2 * D * 4);
-        const LearnedSlices ls = learned_bwd_slices(pb);
+        const LearnedSlices ls = learned_slices(pb.units, pb.n, !pb.per_head, pb.r, pb.g_len);
         w.part = (float *)take(2 * (size_t)std::max(pb.units, ls.units * ls.per_unit) * pb.g_len * 4);
     }
     w.total = off;
@@ -1266,7 +1266,7 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
             // through the networks: one side after the other, the staging buffers serve both
             const int sets = pb.per_head ? pb.heads : 1;
             const unsigned grid_rows = (unsigned)(rows / 256);
-            const LearnedSlices sl = learned_bwd_slices(pb);
+            const LearnedSlices sl = learned_slices(pb.units, pb.n, !pb.per_head, pb.r, pb.g_len);
             const int slices = sl.units * sl.per_unit, slice_rows = sl.n / sl.per_unit;
             const unsigned grid_par = (unsigned)(slices * 2 * (R / 4 / 4));
             hipLaunchKernelGGL((k_learned_bwd_prep<R>), dim3(4 * (R / 4), sets), dim3(kWg), 0, s, (const bf16_t *)G,

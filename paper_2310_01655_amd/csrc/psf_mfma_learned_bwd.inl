@@ -814,30 +814,6 @@ __global__ __launch_bounds__(kWg, 2) void k_learned_bwd_params(LbStage sg, const
     }
 }
 
-// How the rows are cut into slices for the parameter kernel.  One parameter set: the rows of all units are one run;
-// a set per head: the slices stay inside their unit.  A slice is a multiple of 256 rows and at least 512.
-// More slices fill the last round of workgroups better (512 at a time, 31 us for 256 rows in both halves together),
-// and each writes a blob that the reduction reads: the count with the smallest sum of both.  (48 units of
-// 8192 rows, r = 32: 768 slices a side, by filling alone, 967 us in the three kernels; 128 take 827.)
-struct LearnedSlices { int units, n, per_unit; };
-LearnedSlices learned_bwd_slices(const Problem &pb)
-{
-    const bool one_run = !pb.per_head && (long long)pb.units * pb.n < (1LL << 31);
-    LearnedSlices ls{one_run ? 1 : pb.units, one_run ? pb.units * pb.n : pb.n, 1};
-    const long long jobs = 2 * (pb.r / 4 / 4), tiles = ls.n / 256;
-    double best = 0.0;
-    for (int k = 1; k <= 2048 && tiles / k >= (k > 1 ? 2 : 1); ++k) {
-        if (tiles % k) continue;
-        const long long rounds = (ls.units * jobs * k + 511) / 512;
-        const double us = 31.0 * (double)(rounds * (tiles / k)) + (double)ls.units * k * (double)pb.g_len * 8 / 5e6;
-        if (best == 0.0 || us < best) {
-            best = us;
-            ls.per_unit = k;
-        }
-    }
-    return ls;
-}
-
 // dG[set][idx] = sum over the sides (query rows, key rows) and the slices of the units of the
 // set, in order.  part: [side][unit][slice of the unit][blob].
 __global__ __launch_bounds__(kWg) void k_learned_bwd_reduce(const float *__restrict__ part, float *__restrict__ dG,
