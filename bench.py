@@ -145,6 +145,11 @@ def bwd_stage_flops_mfma(cfg, learned=False):
         # matrices and the outer products of the parameter gradient (one forward's worth each)
         nets = 2 * n * 2 * 2 * (d * 8 * r + 24 * r * r)
         f["cross_block_and_sketch_gradient"] = U * (2 * cross + 8 * (n - b) * F + 4 * nets)
+    elif d == 64 and p == 4 and r == 32:
+        # the two parts of a side in one kernel: three products per pair and dm(q), four and dm(k), dV
+        f["in_block_and_dv"] = f["cross_block_and_sketch_gradient"] = 0
+        f["query_side"] = U * (pairs * 2 * 3 * d + cross + 4 * (n - b) * F + sketch)
+        f["key_side"] = U * (pairs * 2 * 4 * d + 2 * cross + 4 * (n - b) * F + sketch)
     f["total"] = sum(f.values())
     return f
 
@@ -235,7 +240,7 @@ def run_backward(args, cfg, psf, inputs, torch, q, k, v, G, idx):
                      "unit": "TFLOP/s", "frac": achieved / peak,
                      "traffic": (BWD_MEASURED_TRAFFIC_BYTES.get((args.workload, dom))
                                  if mfma and not args.learned and not args.local_sketch else None),
-                     "per_stage_tflops": {nm: fl[nm] / (acc[nm] * 1e-3) / 1e12 for nm in acc}},
+                     "per_stage_tflops": {nm: fl[nm] / (acc[nm] * 1e-3) / 1e12 for nm in acc if fl[nm]}},
     }
     if args.learned:
         out["stage_note"] = ("stage_ms from the timed call, which leaves out the parameter sums; "

@@ -175,7 +175,8 @@ psf_status psf_causal_attn_fwd_static(const psf_desc *desc, const void *Q, const
 
 /*
  * Same call, but brackets each kernel with HIP events on `hip_stream`, waits for the stream
- * and reports per-stage milliseconds: stage_ms[i], stage names via psf_stage_name(path, i).
+ * and reports per-stage milliseconds: stage_ms[i], stage names via psf_stage_name(path, i).  On the MFMA path the
+ * scan of the denominators runs in the launch of the states: "denominator_scan" is empty, its time in "block_states_scan".
  * n_stages is the capacity of stage_ms; returns the stage count in *n_written.  Creates and
  * destroys HIP events; intended for benchmarking only.
  */
@@ -230,7 +231,9 @@ psf_status psf_noncausal_attn_fwd_timed(const psf_desc *desc, const void *Q, con
  * networks' layers take fp16 activations like the forward kernel, their gradients bf16);
  * everything else runs the general fp32 kernels (== 2).  -1: invalid descriptor or unsupported.
  * The _timed variant reports per-stage milliseconds like psf_causal_attn_fwd_timed, stage
- * names via psf_stage_name(psf_bwd_kernel_path(desc), i).
+ * names via psf_stage_name(psf_bwd_kernel_path(desc), i).  The MFMA kernels report five stages, or seven (d = 64,
+ * p = 4, r = 32, Gaussian sketches): there "query_side" and "key_side" do what "in_block_and_dv" and
+ * "cross_block_and_sketch_gradient", then empty, do elsewhere.
  */
 int psf_bwd_kernel_path(const psf_desc *desc);
 size_t psf_bwd_workspace_bytes(const psf_desc *desc);

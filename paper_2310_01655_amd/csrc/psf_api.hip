@@ -541,8 +541,8 @@ const char *psf_stage_name(int path, int32_t stage)
     if (path == 2 && stage >= 0 && stage < 6) return bwd[stage];
     // (learned sketches: the last stage also holds the networks' reverse pass and the parameter sums)
     static const char *bwd_mfma[] = {"forward_again", "g_c_and_layouts", "mirror_states", "in_block_and_dv",
-                                     "cross_block_and_sketch_gradient"};
-    if (path == 3 && stage >= 0 && stage < 5) return bwd_mfma[stage];
+                                     "cross_block_and_sketch_gradient", "query_side", "key_side"};
+    if (path == 3 && stage >= 0 && stage < 7) return bwd_mfma[stage];
     static const char *general[] = {"sketch_q", "sketch_k", "block_states", "exclusive_scan",
                                     "output"};
     static const char *mfma[] = {"sketch_and_layouts", "denominator_scan", "block_states_scan",

@@ -1185,7 +1185,11 @@ psf_status attn_bwd_impl(const Problem &pb, const void *Q, const void *K, const 
     if (tm) tm->mark();
     if constexpr (D == 64 && P == 4 && R == 32) {
         if (!pb.learned) {
-            // both parts of a side in one kernel; the timed call's last two stages are the query and the key side
+            // both parts of a side in one kernel, each a stage of its own: the two that divide them otherwise are empty
+            if (tm) {
+                tm->mark();
+                tm->mark();
+            }
             const unsigned main = (unsigned)(rows / (32 * NWL));
             const DenScan den = {w.ScPart, w.Rchi, w.Rclo, pb.b / 256, pb.n / 256, (int)main};
             const int ph = pb.per_head ? 1 : 0;
