@@ -1,6 +1,6 @@
 """Kernels whose form goes by the number of units, at the numbers where it changes: the state kernel's deals (one or
-two tiles a wave, two waves a SIMD, the full deal), the sketches as one launch or two, their parts per workgroup, and the
-decode step for few and many units.  First, middle and last unit against the float64 oracle."""
+two tiles a wave, two waves a SIMD, the full deal), the sketches as one launch or two, and the decode step for few and
+many units.  First, middle and last unit against the float64 oracle."""
 import pytest
 import torch
 
@@ -14,11 +14,13 @@ pytestmark = pytest.mark.gpu
 
 
 # r = 32 deals 3 workgroups a unit, r = 64 10; d = 128 the same: at most 128 or 256 of them, twice as many, and past it;
-# 192 parts of 128 rows and up of either sketch are two launches
+# more than 384 parts (of 256 rows with b = 256) are two launches of the sketches
 @pytest.mark.parametrize("units,n,d,r,b", [
     (1, 512, 64, 32, 256), (42, 512, 64, 32, 256), (43, 512, 64, 32, 256), (85, 512, 64, 32, 256), (86, 768, 64, 32, 256),
     (129, 512, 64, 32, 256), (171, 512, 64, 32, 256), (12, 768, 64, 64, 256), (13, 512, 64, 64, 256),
     (26, 512, 64, 64, 256), (81, 512, 64, 64, 256), (25, 512, 128, 64, 256), (43, 512, 128, 32, 256), (47, 1024, 64, 32, 1024),
+    (192, 512, 64, 32, 256), (193, 512, 64, 32, 256), (192, 512, 64, 64, 256), (193, 512, 64, 64, 256),
+    (16, 6144, 64, 64, 256), (17, 6144, 64, 64, 256),       # the same with the values' role: fp16 states beside the rows
 ])
 def test_states_and_sketches_by_units(units, n, d, r, b):
     cfg = dict(batch=1, heads=units, n=n, d=d, p=4, r=r, b=b, dtype="bf16", per_head=False)
@@ -38,7 +40,8 @@ def test_states_and_sketches_by_units(units, n, d, r, b):
         assert_close(plain[0, h].float().cpu().numpy(), full, "bf16", "no mask, unit %d" % h)
 
 
-# both widths of rows and of sketches, slots at the edges of a chunk of 32 cached tokens, alone and one workgroup a unit
+# both widths of rows and of sketches, a cache of no, few and many rows, a state and none, alone and one workgroup a unit
+# (where the cache goes through the kernel's loop more than once: test_gpu_decode_cache.py)
 @pytest.mark.parametrize("batch,heads,n,n_prompt,d,r,b", [
     (1, 1, 192, 126, 128, 64, 64), (1, 2, 99, 65, 128, 32, 33), (1, 3, 140, 70, 64, 64, 70), (1, 2, 64, 31, 64, 32, 64),
     (16, 16, 36, 30, 128, 64, 12), (16, 17, 36, 33, 64, 64, 12),
