@@ -724,12 +724,9 @@ psf_status rows_launch(const Problem &pb, const F32Plan &pl, const float *MQ, co
 }  // namespace
 
 // Rows so few that even 16 of them a workgroup leave CUs idle, in a call that keeps no states: the key tiles of the
-// same rows are shared out, as few a workgroup as leave no more than kShareWorkgroups of them (one fills a CU's LDS)
-// and as many slots for their sums as the room of the state records, which such a call does not use, holds.
-// A tile of 128 keys is 3.4 us of a workgroup's chain, the launch that adds the sums 3: at least two tiles shorter.
-// us a call: 1 unit of 1024 tokens, fp32 storage, r = 16 32.5 -> 22.8, r = 64 37.1 -> 27.0; no mask, r = 16 31.0 -> 23.2; 2 units,
-// r = 32 32.8 -> 23.5.  (Room for one tile fewer a workgroup would take the first to 18.)
-constexpr long long kShareWorkgroups = 288;
+// same rows are shared out (row_share); the slots for the sums take the room of the state records, which such a call
+// does not use.  us a call: 1 unit of 1024 tokens, fp32 storage, r = 16 32.5 -> 22.4, r = 64 37.9 -> 22.2; no mask, r = 16
+// 31.0 -> 23.2; 2 units, r = 32 32.6 -> 23.1.  (Room for one tile fewer a workgroup would take the first to 18.)
 int f32_row_share(const Problem &pb, const F32Plan &pl, size_t part_floats)
 {
     if (pl.states || pl.spans != 1) return 0;
@@ -741,15 +738,7 @@ int f32_row_share(const Problem &pb, const F32Plan &pl, size_t part_floats)
             return PSF_OK;
         });
     });
-    if (!sixteen) return 0;
-    const int tiles = (pb.n + 127) / 128, blocks = (pb.n + 15) / 16, causal = !pl.noncausal;
-    for (int share = 1; share + 2 <= tiles; ++share) {
-        const long long slots = row_slots_before(blocks, pb.n, share, causal);
-        const long long whole = causal ? (blocks < 8 * share ? blocks : 8 * share) : 0;
-        if (pb.units * (whole + slots) <= kShareWorkgroups && (size_t)(pb.units * slots) * kSlotFloats <= part_floats)
-            return share;
-    }
-    return 0;
+    return sixteen ? row_share(pb.units, pb.n, !pl.noncausal, pb.bf16 && pb.mcols <= 32, part_floats / kSlotFloats) : 0;
 }
 
 bool f32_supported(const Problem &pb)

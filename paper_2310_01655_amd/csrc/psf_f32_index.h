@@ -97,5 +97,25 @@ PSF_HD int row_slots_before(int block, int n, int share, int causal)    // of th
     return q < 1 ? 0 : per * ((q - 1) * (q + 2) / 2) + (block - q * per) * (q + 1);
 }
 
+// Tiles a workgroup takes where few rows' keys are shared out; 0: they are not.  As few as leave no more workgroups than run
+// at once and as many slots as there is room for.  One workgroup fills a CU's LDS: without a mask, where all walk alike, 256.
+// Under the mask the last slices are short: from three tiles on a second round of 32 costs little; workgroups of one
+// tile all last as long, and 240 of them took longer than no sharing.  A tile is 2.8 to 3.4 us of a workgroup's chain and
+// the launch that adds the sums 3, so at least two tiles shorter; 2.2 us for rows and at most 32 sketch columns in bf16 (`light`): three.
+// us a call, shared and not: causal, 6 units of 384 tokens (288 workgroups of a tile), r = 16 23.1, 18.8; 3 of 512 (240), r = 64 26.6,
+// 25.4; 2 of 1536 (288 of six) 35.7, 51.6; no mask, 3 of 768 (288 of three) 36.2, 30.9, 2 of 768 (192) 24.2, 30.5; 1 of 384, bf16, r = 32
+// (two tiles shorter) 16.2, 15.0.
+inline int row_share(int units, int n, int causal, bool light, unsigned long long room)
+{
+    const int tiles = (n + 127) / 128, blocks = (n + 15) / 16;
+    for (int share = 1; share + (light ? 3 : 2) <= tiles; ++share) {
+        const long long slots = row_slots_before(blocks, n, share, causal);
+        const long long whole = causal ? (blocks < 8 * share ? blocks : 8 * share) : 0;
+        const long long most = !causal ? 256 : 192 + 32 * (share < 3 ? share : 3);
+        if (units * (whole + slots) <= most && (unsigned long long)(units * slots) <= room) return share;
+    }
+    return 0;
+}
+
 }  // namespace psf
 #endif

@@ -112,3 +112,43 @@ int main()
 def test_slots_of_shared_rows_are_counted_through(tmp_path):
     """Where the workgroups that share a block's keys leave their sums, against counting them."""
     run_host(tmp_path, SLOTS)
+
+
+SHARES = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "psf_f32_index.h"
+using namespace psf;
+int main()
+{
+    int bad = 0;
+    for (int causal = 0; causal < 2; ++causal)
+        for (int n = 1; n <= 4200; n += n < 300 ? 1 : 37)
+            for (int units = 1; units <= 20; ++units)
+                for (unsigned long long room : {0ull, 16ull, 200ull, 100000ull})
+                    for (int light = 0; light < 2; ++light) {
+                        const int share = row_share(units, n, causal, light, room);
+                        if (!share) continue;
+                        int workgroups = 0, longest = 0, slots = 0;
+                        for (int block = 0; block < (n + 15) / 16; ++block) {
+                            const int s = row_slices(block, n, share, causal);
+                            workgroups += units * s;
+                            slots += s > 1 ? units * s : 0;
+                            longest = s > 1 ? share : longest;
+                        }
+                        // one a CU, but for the short ones under a mask; two tiles shorter and more; sums where there is room
+                        const int most = !causal ? 256 : share == 1 ? 224 : share == 2 ? 256 : 288;
+                        const bool ok = workgroups <= most && longest + (light ? 3 : 2) <= (n + 127) / 128 &&
+                                        (unsigned long long)slots <= room;
+                        if (!ok && bad++ < 4)
+                            printf("causal %d n %d units %d: %d tiles, %d workgroups, %d slots\n", causal, n, units, share,
+                                   workgroups, slots);
+                    }
+    return bad != 0;
+}
+"""
+
+
+def test_shared_rows_fill_the_chip_once(tmp_path):
+    """More workgroups than CUs wait for each other: a call then takes longer than with its keys not shared out."""
+    run_host(tmp_path, SHARES)
