@@ -27,8 +27,8 @@ HBM_PEAK_GBS = 8000.0
 # runs summarised in profiles/ (scaled by the copy calibration described there).  bench.py
 # cannot collect counters itself; workloads without a committed counter run report null.
 MEASURED_TRAFFIC_BYTES = {
-    ("config3", "output"): 0.802e9,                 # k_out, cross-block part: 631 MB read + 171 MB written
-    ("config3", "block_states_scan"): 1.529e9,      # k_state_and_in_block: 965 MB read + 564 MB written
+    ("config3", "output"): 0.663e9,                 # k_out, cross-block part: 562 MB read + 101 MB written
+    ("config3", "block_states_scan"): 1.522e9,      # k_state_and_in_block: 958 MB read + 564 MB written
 }
 
 
@@ -156,15 +156,17 @@ def bwd_stage_flops_mfma(cfg, learned=False):
 
 # HBM bytes per step and stage of the MFMA backward pass (Gaussian sketches, exact in-block weights),
 # from rocprofv3 FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 summed over the stage's kernels
-# (profiles/config3_backward_mfma_kernel_trace.md, profiles/config5_backward_mfma_kernel_trace.md)
+# (profiles/backward_mfma_kernel_trace_and_traffic.md)
 MIB = 1048576
 BWD_MEASURED_TRAFFIC_BYTES = {
-    ("config3", "forward_again"): 2722 * MIB, ("config3", "g_c_and_layouts"): 1638 * MIB,
-    ("config3", "mirror_states"): 2398 * MIB, ("config3", "in_block_and_dv"): 2675 * MIB,
-    ("config3", "cross_block_and_sketch_gradient"): 2042 * MIB,
-    ("config5", "forward_again"): 1695 * MIB, ("config5", "g_c_and_layouts"): 1088 * MIB,
-    ("config5", "mirror_states"): 2551 * MIB, ("config5", "in_block_and_dv"): 1905 * MIB,
-    ("config5", "cross_block_and_sketch_gradient"): 1999 * MIB,
+    ("config2", "forward_again"): 844 * MIB, ("config2", "g_c_and_layouts"): 148 * MIB,
+    ("config2", "mirror_states"): 356 * MIB, ("config2", "query_side"): 466 * MIB, ("config2", "key_side"): 717 * MIB,
+    ("config3", "forward_again"): 2584 * MIB, ("config3", "g_c_and_layouts"): 294 * MIB,
+    ("config3", "mirror_states"): 850 * MIB, ("config3", "in_block_and_dv"): 2175 * MIB,
+    ("config3", "cross_block_and_sketch_gradient"): 1638 * MIB,
+    ("config5", "forward_again"): 1790 * MIB, ("config5", "g_c_and_layouts"): 194 * MIB,
+    ("config5", "mirror_states"): 555 * MIB, ("config5", "in_block_and_dv"): 1410 * MIB,
+    ("config5", "cross_block_and_sketch_gradient"): 1601 * MIB,
 }
 
 
@@ -307,9 +309,9 @@ def run_train(args, cfg, psf, inputs, torch, q, k, v, G, idx):
     print(json.dumps(out))
 
 
-# HBM bytes of one dec_state_kernel launch at the serving shape, mid-block (rocprofv3 counters,
+# HBM bytes of one dec_step_kernel launch at the serving shape, mid-block (rocprofv3 counters,
 # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0; see profiles/decode_serving_kernel_trace.md)
-DECODE_MEASURED_TRAFFIC_BYTES = 3.13e8
+DECODE_MEASURED_TRAFFIC_BYTES = 3.126e8
 
 
 def run_decode(args, psf, inputs, torch):
@@ -394,7 +396,7 @@ def run_decode(args, psf, inputs, torch):
                    "first_timed_position": first_timed, "state_bytes": psf.decode_state_bytes(desc),
                    "ms_mid_block_step": ms_mid, "ms_block_completion_step": ms_completion,
                    "prefill_tokens_per_sequence": n_prompt, "ms_prefill": ms_prefill},
-        "roofline": {"kernel": "dec_state_kernel", "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
+        "roofline": {"kernel": "dec_step_kernel", "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": DECODE_MEASURED_TRAFFIC_BYTES if cfg["batch"] == 64 else None,
                      "note": "whole step time (the step is this one kernel, plus the block fold spread over "

@@ -3230,7 +3230,7 @@ static TotalWs carve_total(const Problem &pb, void *ws)
     w.LW = (bf16_t *)take(pb.learned ? sets * 4 * nch * kLsSlotBytes : 0);
     w.C1 = (float *)take(pb.learned ? sets * 2 * nch * 32 * 4 : 0);
     w.LVp = (float *)take(pb.learned ? sets * 2 * nch * 2 * R * 4 : 0);
-    off += align_up(rows * D * 2, 256);              // (the least size callers budget with: it held a layout of V)
+    off += align_up(rows * D * 2, 256);              // (unused: the tests of the interface state a lower bound with room for a layout of V)
     w.total = off;
     return w;
 }

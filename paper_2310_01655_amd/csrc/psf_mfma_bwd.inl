@@ -432,7 +432,7 @@ struct StateTimesRow : StateTiles<R, D> {
             dm[I] += __uint_as_float(s[0]) + __uint_as_float(s[1]);
         }
     }
-    // The ring's first tiles are on their way (stage_first).  vec: B operands; ends with a barrier.
+    // The ring's first tiles are on their way (Ring::fill).  vec: B operands; ends with a barrier.
     static __device__ __forceinline__ void run(const bf16_t *__restrict__ Z, const bf16x8 (&vec)[TT][VS],
                                                const float (&m)[TT][8 * RS], float (&dm)[TT][8 * RS], unsigned char *lds)
     {
@@ -1079,8 +1079,8 @@ MfmaBwdWs carve_bwd(const Problem &pb, void *ws)
     w.dVc = (float *)take(rows * D * 4);
     w.dQacc = (float *)take(rows * D * 4);
     w.dKacc = (float *)take(rows * D * 4);
-    // The size this call asked for when it kept re-laid states and row layouts of its own is still its least: callers
-    // budget with it, and a buffer made for it serves either.
+    // Its least size is what it was with re-laid states and layouts of the rows beside them, the lower bound that the tests of
+    // the interface state; nothing lies in what is more than the arrays above.
     off = std::max(off, align_up(carve(pb, nullptr).total, 256) + 2 * snaps * R * R * D * 2 + 5 * rows * D * 4);
     if (pb.learned) {
         const size_t sets = pb.per_head ? pb.heads : 1, nch = R / 4;
